@@ -87,7 +87,7 @@ def _on_host(x):
     return host
 
 
-def prepare(case, seed):
+def _inputs(case, seed):
     gen = torch.Generator(device="cuda").manual_seed(seed)
     T, M, E = case["tokens"], case["hidden"], case["n_experts"]
 
@@ -102,6 +102,12 @@ def prepare(case, seed):
         scores += (-case["zipf"] * torch.log(rank)).float()
     routed = normal(case["n_local"] * 3 * case["inter"] * M, 0.02)
     shared = normal(case["n_shared"] * 3 * case["shared_inter"] * M, 0.02) if case["n_shared"] else None
+    return tokens, scores, routed, shared
+
+
+def prepare(case, seed):
+    T, M, E = case["tokens"], case["hidden"], case["n_experts"]
+    tokens, scores, routed, shared = _inputs(case, seed)
     out = torch.zeros((T, M), dtype=torch.bfloat16, device="cuda")
     io_mode = moe_ep.IO_DEVICE
     if case["pinned"]:
@@ -148,3 +154,29 @@ def tolerance(case):
     # largest difference of 0.9e-2 .. 2.7e-2 (on the shares, where few experts of a token are here, the rounded
     # activation alone gives 1.5e-2); about four times that.
     return {"rel": 1e-2, "max": 0.1}
+
+
+def exact(case, seed):
+    """The layer in float64: gate over all experts, the local ones' SwiGLU projections, the weighted sum."""
+    tokens, scores, routed, shared = _inputs(case, seed)
+    T, M, k = case["tokens"], case["hidden"], case["top_k"]
+    x = tokens.double()
+
+    def ffn(rows, weights, inter):
+        gate, up, down = weights.view(3, -1)
+        gate, up, down = gate.view(inter, M).double(), up.view(inter, M).double(), down.view(M, inter).double()
+        z = rows @ gate.t()
+        return (z * torch.sigmoid(z) * (rows @ up.t())) @ down.t()
+
+    # equal scores go to the lower expert
+    top, chosen = torch.sort(scores, dim=1, descending=True, stable=True)
+    top, chosen = torch.softmax(top[:, :k].double(), dim=1), chosen[:, :k]
+    out = torch.zeros((T, M), dtype=torch.float64, device="cuda")
+    for e, weights in enumerate(routed.view(case["n_local"], -1)):
+        row, slot = torch.nonzero(chosen == e, as_tuple=True)
+        if row.numel():
+            out.index_add_(0, row, top[row, slot, None] * ffn(x[row], weights, case["inter"]))
+    if case["n_shared"]:
+        for weights in shared.view(case["n_shared"], -1):
+            out += ffn(x, weights, case["shared_inter"])
+    return out.cpu() if case["pinned"] else out
