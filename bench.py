@@ -36,6 +36,8 @@ def kernel_name(ctx, stage):
         return None
     swiglu = "true" if "gate_up" in stage else "false"
     ragged = "true" if stage.startswith("routed") else "false"
+    if (sh["rows"], sh["cols"], sh["waves_m"], sh["waves_n"]) == (64, 128, 1, 4):   # few rows per expert
+        return f"narrow_gemm_kernel<{swiglu}, {'true' if sh['tile_order'] else 'false'}"
     # last argument: what the epilogue writes (MOE_EP_EXPERT_OUT, the routed down projection only)
     epi = {"f": 1, "s": 2}.get(os.environ.get("MOE_EP_EXPERT_OUT", " ")[0], 0) if stage == "routed_down_gemm" else 0
     # and whether the weights are read from a tile-order copy (moe_ep_prepare_weights)

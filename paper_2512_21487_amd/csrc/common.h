@@ -26,4 +26,11 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
+// g * sigmoid(g) from the hardware's exp2 and reciprocal (about 1 ulp each: far below the bf16
+// rounding of the result); exp2 saturates to +inf / 0 at the ends, which give -0 and g
+__device__ __forceinline__ float silu_f(float g)
+{
+    return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(g * -1.4426950408889634f));
+}
+
 }  // namespace moe_ep

@@ -100,13 +100,6 @@ struct GemmCfg {
     }
 };
 
-// g * sigmoid(g) from the hardware's exp2 and reciprocal (about 1 ulp each: far below the bf16
-// rounding of the result); exp2 saturates to +inf / 0 at the ends, which give -0 and g
-__device__ __forceinline__ float silu_f(float g)
-{
-    return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(g * -1.4426950408889634f));
-}
-
 // s_waitcnt vmcnt(n) lgkmcnt(0): all but the newest n vector-memory loads have landed and every LDS
 // read has returned (gfx9 encoding: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] << 14)
 #define MOE_EP_WAIT_VMCNT_LGKM0(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | 0x0070)
@@ -369,7 +362,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, uint4* lds, const 
                     n = t.n0 + jw;
                 }
                 n = min(n, a.N - 1);
-                goff[i] = packed ? (uint32_t)(jw * BK + c * 8) * 2u
+                // tile order is the order the slots have in LDS: 1 KB runs, lane by lane
+                goff[i] = packed ? (uint32_t)((j - BM / RPR) * 64 + lane) * 16u
                                  : (base + (uint32_t)n * (uint32_t)a.ldw + c * 8) * 2u;
             }
         }
@@ -391,6 +385,15 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, uint4* lds, const 
                                                  : BN / 2 + wn * (Cfg::WTN / 2) + (nb - NB16 / 2) * 16);
         return BM + wn * Cfg::WTN + nb * 16;
     };
+    // the same for weights in tile order: 16-byte chunk of the ring slot's weight part that holds row block nb's
+    // first chunk.  Blocks of 16 rows lie one behind the other (SwiGLU: gate and up in turn), each as
+    // [8 chunks of k][16 rows], so that a fragment read is 256 contiguous bytes per 16 lanes
+    auto w_packed_base = [&](int nb) -> int {
+        constexpr int BL = MI == 16 ? 1 : 2, N_ = MI == 16 ? NB16 : NB;   // 16-row blocks of a fragment, fragments
+        const int f = SWIGLU ? wn * (N_ / 2) + (nb < N_ / 2 ? nb : nb - N_ / 2) : wn * N_ + nb;
+        const int b = f * BL + (MI == 16 ? 0 : fr_row >> 4);
+        return BM * CPR + (SWIGLU ? 2 * b + (nb < N_ / 2 ? 0 : 1) : b) * 128 + (fr_row & 15);
+    };
     f32x4_t acc16[MI == 16 ? MB16 : 1][MI == 16 ? NB16 : 1];
     bf16x8_t xf16[2][MI == 16 ? MB16 : 1], wf16[2][MI == 16 ? NB16 : 1];
     // one LDS fragment read of a 16-row block from ring slot base sT_, step kk_ of 32: f < MB16 an activation
@@ -400,6 +403,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, uint4* lds, const 
         const int csw_ = ((kk_) * 4 + fr_kh) ^ fr_sw;                                             \
         if ((f_) < MB16) xf16[set_][(f_) < MB16 ? (f_) : 0] = __builtin_bit_cast(bf16x8_t,        \
             (sT_)[(wm * Cfg::WTM + (f_) * 16 + fr_row) * CPR + csw_]);                            \
+        else if (packed) wf16[set_][(f_) >= MB16 ? (f_) - MB16 : 0] = __builtin_bit_cast(bf16x8_t, \
+            (sT_)[w_packed_base((f_) >= MB16 ? (f_) - MB16 : 0) + ((kk_) * 4 + fr_kh) * 16]);     \
         else wf16[set_][(f_) >= MB16 ? (f_) - MB16 : 0] = __builtin_bit_cast(bf16x8_t,            \
             (sT_)[(w_row_base16((f_) >= MB16 ? (f_) - MB16 : 0) + fr_row) * CPR + csw_]);         \
     }
@@ -410,6 +415,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, uint4* lds, const 
         const int csw_ = ((kk_) * 2 + fr_kh) ^ fr_sw;                                             \
         if ((f_) < MB) xf[set_][(f_) < MB ? (f_) : 0] = __builtin_bit_cast(bf16x8_t,              \
             (sT_)[(wm * Cfg::WTM + (f_) * 32 + fr_row) * CPR + csw_]);                            \
+        else if (packed) wf[set_][(f_) >= MB ? (f_) - MB : 0] = __builtin_bit_cast(bf16x8_t,      \
+            (sT_)[w_packed_base((f_) >= MB ? (f_) - MB : 0) + ((kk_) * 2 + fr_kh) * 16]);         \
         else wf[set_][(f_) >= MB ? (f_) - MB : 0] = __builtin_bit_cast(bf16x8_t,                  \
             (sT_)[(w_row_base((f_) >= MB ? (f_) - MB : 0) + fr_row) * CPR + csw_]);               \
     }
@@ -934,22 +941,23 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(GemmArgs a, bool swig
 {
     const int bn_out = swiglu ? kPackRows / 2 : kPackRows;
     const int NT = (a.N + bn_out - 1) / bn_out, KT = a.K / kPackK;
+    // a thread reads the chunks of a row in order (whole lines) and writes them where the layout has them:
+    // a wavefront covers whole lines on both sides
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < chunks; i += (size_t)gridDim.x * blockDim.x) {
         const int c = (int)(i % 8);                       // 16-byte chunk of the 128-byte row
-        size_t r = i / 8;
-        const int jw = (int)(r % kPackRows); r /= kPackRows;
+        const int row = (int)(i / 8 % 16);                // row of a block of 16
+        size_t r = i / 128;
+        const int blk = (int)(r % (kPackRows / 16)); r /= kPackRows / 16;
         const int ks = (int)(r % KT); r /= KT;
         const int nt = (int)(r % NT);
         const int g = (int)(r / NT);
-        int n = nt * bn_out + jw;
-        long long base = 0;
-        if (swiglu && jw >= kPackRows / 2) { n = nt * bn_out + jw - kPackRows / 2; base = a.w_up_offset; }
-        n = min(n, a.N - 1);
+        const int n = min(nt * bn_out + (swiglu ? blk / 2 : blk) * 16 + row, a.N - 1);
+        const long long base = swiglu && (blk & 1) ? a.w_up_offset : 0;
         const int k = ks * kPackK + c * 8;
         const int seg = k / a.kseg_len;
         const uint16_t* src = a.W + (size_t)g * a.w_group_stride + base + (size_t)n * a.ldw +
                               (size_t)seg * a.w_kseg_stride + (k - seg * a.kseg_len);
-        dst[i] = *reinterpret_cast<const uint4*>(src);
+        dst[i - i % 128 + c * 16 + row] = *reinterpret_cast<const uint4*>(src);
     }
 }
 

@@ -70,9 +70,12 @@ struct GemmArgs {
     const uint16_t* Wp;
 };
 // Weights in tile order: for every group, column tile and K step of kPackK, the kPackRows x kPackK
-// block the GEMM's weight tile holds at that step (SwiGLU: kPackRows / 2 rows of W_gate, then the
-// matching rows of W_up; rows past N repeat row N - 1), contiguous (32 KB), blocks in (group, column
-// tile, K step) order.  a.W etc. describe the source as for a launch; a.Wp is ignored.
+// block the GEMM's weight tile holds at that step, contiguous (32 KB), blocks in (group, column tile, K step)
+// order.  A block is 16 row blocks of 16 rows (SwiGLU: of W_gate and of W_up in turn, 8 of each; rows past N
+// repeat row N - 1), a row block is [8 chunks of 8 k][16 rows]: the order in which the lanes of a wavefront
+// hold the operand of a 16 x 16 x 32 matrix instruction, so that 1 KB of it is one load instruction without
+// gaps, and in LDS a fragment read without bank conflicts.  a.W etc. describe the source as for a launch;
+// a.Wp is ignored.
 constexpr int kPackRows = 256, kPackK = 64;
 size_t packed_weight_elems(const GemmArgs& a, bool swiglu);
 hipError_t launch_pack_weights(const GemmArgs& a, bool swiglu, uint16_t* dst, int grid, hipStream_t s);
@@ -81,6 +84,14 @@ hipError_t launch_pack_weights(const GemmArgs& a, bool swiglu, uint16_t* dst, in
 // `offset`; the bound only sizes the grid); ignored in dense mode
 hipError_t launch_grouped_gemm(const GemmArgs& a, bool swiglu, int variant, int n_cu,
                                long long max_rows, hipStream_t s);
+// The same projections where few token rows meet every expert (narrow_gemm.hip): the routed groups
+// `routed` (ragged) and, when `shared` is not NULL, the shared experts (dense) in one launch, bit for bit
+// what launch_grouped_gemm writes.  expected_rows: rows per routed group the grid is sized for (any
+// routing is served); no other epilogue than epi == 0.
+hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bool swiglu, double expected_rows,
+                              long long max_rows, hipStream_t s);
+constexpr int kNarrowRows = 64;   // tallest row tile
+constexpr int kNarrowDepth = 4;   // K steps of 64 in flight per wavefront
 hipError_t grouped_gemm_init();   // raises the dynamic-LDS limit of every instantiation once
 // the shape a launch of `variant` really runs (after the fall-backs for a short K or many groups):
 // shape[] = tallest tile rows, weight rows per tile, K step, ring slots, wavefronts in m, in n,

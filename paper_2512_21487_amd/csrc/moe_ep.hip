@@ -24,6 +24,17 @@ namespace {
 
 enum Stage { ST_ROUTER = 0, ST_PARTITION, ST_GEMM1, ST_GEMM2, ST_SGEMM1, ST_SGEMM2, ST_COMBINE, ST_TOTAL, ST_COPY_IN, ST_COPY_OUT, ST_ATTN, ST_COUNT };
 
+// Where the narrow kernels (narrow_gemm.hip) take over.  Forwards in us, tiled -> narrow, prepared weights:
+// Qwen3-235B-A22B-shaped share, 16 / 32 / 44 / 50 / 64 rows per expert: 143 -> 130, 146 -> 134, 152 -> 139, 151 -> 149,
+// 157 -> 183; Qwen3-30B-A3B-shaped layer, 31 / 44 / 50 rows: 270 -> 249, 274 -> 257, 277 -> 273.  Beyond 48 rows on average more
+// and more experts need a second row tile, whose weights come from L2 again.
+constexpr double kNarrowMeanRows = 48.0;
+// The shared experts go along up to this many rows: alone, 256-row tiles of a few hundred rows leave most compute
+// units idle (DeepSeek-V2-Lite-shaped layer, 256 / 500 tokens: 298 -> 229, 321 -> 267 us; DeepSeek-V2-shaped share, 500 / 800 / 1200:
+// 332 -> 266, 335 -> 323, 345 -> 376).
+constexpr int kNarrowSharedRows = 768;
+constexpr int kNarrowVariant = -2;   // in last_variants, beside the tile variants of grouped_gemm.hip
+
 struct ProfSpan { hipEvent_t a, b; int stage; int forward; };
 
 }  // namespace
@@ -39,6 +50,8 @@ struct moe_ep_ctx {
     // v_mfma_f32_32x32x16_bf16); a shape named through a knob is taken as named
     bool mfma16 = true;
     bool shared_variant_named = false;
+    // chunks whose routed experts get at most this many rows on average run the narrow kernels; 0 = never
+    double narrow_rows = kNarrowMeanRows;
     bool fused_gather = true;  // the gate/up projection gathers the token rows itself (no grouped copy)
     int y_mode = 0;            // expert outputs: 0 bf16, 1 fp32, 2 bf16 scaled by the routing weight (expert_out_mode)
     // pinned-host mode, moe_ep_forward: the aggregation writes its rows straight into the caller's host
@@ -84,6 +97,7 @@ struct moe_ep_ctx {
     int last_T = -1, last_k = 0, last_r = 0, last_r1 = 1;
     bool last_prepared_routed = false, last_prepared_shared = false;  // it read tile-order copies of the weights
     struct ChunkVariants { int up, down; };
+    bool last_shared_narrow = false;
     std::vector<ChunkVariants> last_variants;  // per chunk of the last forward: tile variants of the routed projections
     // stage profiling
     int prof_depth = 0, prof_recorded = 0;
@@ -179,6 +193,7 @@ void read_knobs(moe_ep_ctx* ctx)
     if (const char* v = getenv("MOE_EP_DOWN_VARIANT")) ctx->down_variant = atoi(v);
     if (const char* v = getenv("MOE_EP_UP_UNITS")) ctx->up_units = atoi(v);
     if (const char* v = getenv("MOE_EP_DOWN_UNITS")) ctx->down_units = atoi(v);
+    if (const char* v = getenv("MOE_EP_NARROW_ROWS")) ctx->narrow_rows = atof(v);
     // workgroups of a copy kernel: ~128 KB in flight fills the host link; more only queues up in the
     // memory fabric in front of the compute kernels
     if (const char* v = getenv("MOE_EP_LINK_GRID")) ctx->link_grid = atoi(v) > 0 ? atoi(v) : 64;
@@ -193,6 +208,9 @@ void read_knobs(moe_ep_ctx* ctx)
     }
     ctx->fused_gather = fused_gather_enabled();
     ctx->y_mode = expert_out_mode();
+    // a tile shape, instruction or form of the expert outputs asked for by name belongs to the tiled kernels
+    if (ctx->gemm_variant >= 0 || ctx->up_variant >= 0 || ctx->down_variant >= 0 || ctx->shared_variant_named || !ctx->mfma16 ||
+        ctx->up_units || ctx->down_units || ctx->y_mode != 0) ctx->narrow_rows = 0.0;
     if (const char* v = getenv("MOE_EP_FUSED_OUT")) ctx->fused_out = atoi(v) != 0;
     // MOE_EP_CHECK_POINTERS=0 skips the per-forward pointer queries (a few microseconds of host time)
     if (const char* v = getenv("MOE_EP_CHECK_POINTERS")) ctx->check_spans = atoi(v) != 0;
@@ -668,23 +686,25 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
     ctx->last_prepared_shared = prep_s != nullptr;
 
     // shared experts of token range [t0, t0+Tn) -> output rows [t0, t0+Tn); the aggregation adds to them
-    auto run_shared = [&](int t0, int Tn, hipStream_t st) -> int {
-        if (Tn <= 0) return MOE_EP_OK;
-        GemmArgs g1{};
+    auto shared_args = [&](int t0, int Tn, GemmArgs& g1, GemmArgs& g2) {
         shared_up_w(g1);
         g1.Wp = prep_s ? prep_s->up : nullptr;
         g1.A = tok_dev + (size_t)t0 * M; g1.C = ctx->hs + (size_t)t0 * Ns * Hs;
         g1.offset = nullptr; g1.dense_rows = Tn;
         g1.lda = M; g1.ldc = Ns * Hs; g1.c_group_col_stride = Hs;
-        int sp = prof_begin(ctx, prof, ST_SGEMM1, st);
-        HIP_TRY(ctx, launch_grouped_gemm(g1, true, ctx->shared_variant, n_cu, 0, st));
-        prof_end(ctx, sp, st);
-        GemmArgs g2{};
         shared_down_w(g2);
         g2.Wp = prep_s ? prep_s->down : nullptr;
         g2.A = ctx->hs + (size_t)t0 * Ns * Hs; g2.C = out_dev + (size_t)t0 * M;
         g2.offset = nullptr; g2.dense_rows = Tn;
         g2.lda = Ns * Hs; g2.ldc = M; g2.c_group_col_stride = 0;
+    };
+    auto run_shared = [&](int t0, int Tn, hipStream_t st) -> int {
+        if (Tn <= 0) return MOE_EP_OK;
+        GemmArgs g1{}, g2{};
+        shared_args(t0, Tn, g1, g2);
+        int sp = prof_begin(ctx, prof, ST_SGEMM1, st);
+        HIP_TRY(ctx, launch_grouped_gemm(g1, true, ctx->shared_variant, n_cu, 0, st));
+        prof_end(ctx, sp, st);
         sp = prof_begin(ctx, prof, ST_SGEMM2, st);
         HIP_TRY(ctx, launch_grouped_gemm(g2, false, ctx->shared_variant, n_cu, 0, st));
         prof_end(ctx, sp, st);
@@ -762,7 +782,20 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
             if (rc != MOE_EP_OK) return rc;
         }
     }
-    if (!dep && Ns > 0 && order == MOE_EP_ORDER_SHARED_FIRST) {
+    // Few rows per routed expert: the narrow kernels, bound by the weight stream alone.  They take the shared
+    // experts along in the same launches -- every token's with the first chunk where these come first --
+    // unless their stages are being timed, which takes launches of their own.
+    const auto use_narrow = [&](int Tn) {
+        return ctx->narrow_rows > 0.0 && Tn > 0 && ctx->fused_gather && (unsigned long long)Tn * M * 2 < (1ull << 32) &&
+               (double)Tn * k / E <= ctx->narrow_rows;
+    };
+    const bool shared_first = !dep && Ns > 0 && order == MOE_EP_ORDER_SHARED_FIRST;
+    const bool shared_beside = !dep && Ns > 0 && (prep_r != nullptr) == (prep_s != nullptr) && !(prof && (ctx->prof_mask & ((1u << ST_SGEMM1) | (1u << ST_SGEMM2))));
+    int c0_t0, c0_Tn;
+    chunk_range(T, r_1, r_2, 0, &c0_t0, &c0_Tn);
+    const bool first_takes_all = shared_first && shared_beside && use_narrow(c0_Tn) && T <= kNarrowSharedRows;
+    ctx->last_shared_narrow = false;
+    if (shared_first && !first_takes_all) {
         if (pinned) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[r - 1], 0));
         int rc = run_shared(0, T, s_comp);
         if (rc != MOE_EP_OK) return rc;
@@ -784,6 +817,8 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         int v_down = ctx->gemm_variant >= 0 ? ctx->gemm_variant : picked(routed_variant(Tn, k, E, El, (M + 255) / 256, H, n_cu));
         if (ctx->up_variant >= 0) v_up = ctx->up_variant;
         if (ctx->down_variant >= 0) v_down = ctx->down_variant;
+        const bool narrow = use_narrow(Tn);
+        if (narrow) v_up = v_down = kNarrowVariant;
         if (cidx < (int)ctx->last_variants.size()) ctx->last_variants[cidx] = {v_up, v_down};
         int32_t* idx = ctx->idx + (size_t)t0 * k;
         float* w = ctx->w + (size_t)t0 * k;
@@ -803,7 +838,9 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
             HIP_TRY(ctx, launch_gather_rows(tok_dev + (size_t)t0 * M, perm, offset + El, k, M, ctx->xp, bw_grid, s_comp));
         }
         prof_end(ctx, sp, s_comp);
-        if (pinned) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[cidx], 0));   // the token rows
+        const bool takes_all = first_takes_all && cidx == 0;
+        // the token rows (with every shared expert's row: of all chunks)
+        if (pinned) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[takes_all ? r - 1 : cidx], 0));
         if (Tn == 0) {
             if (pinned && !fused_out) HIP_TRY(ctx, hipEventRecord(ctx->ev_comp[cidx], s_comp));
             continue;
@@ -820,8 +857,16 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         if (fused) {  // the projection reads the token rows through the row -> assignment map
             g1.A = tok_dev + (size_t)t0 * M; g1.a_row_map = perm; g1.a_row_div = k; g1.a_src_rows = Tn;
         }
+        const bool interleaved = !dep && Ns > 0 && order == MOE_EP_ORDER_INTERLEAVED;
+        const bool along = takes_all || (narrow && interleaved && shared_beside && Tn <= kNarrowSharedRows);
+        GemmArgs s1{}, s2{};
+        if (along) {
+            shared_args(takes_all ? 0 : t0, takes_all ? T : Tn, s1, s2);
+            ctx->last_shared_narrow = true;
+        }
         sp = prof_begin(ctx, prof, ST_GEMM1, s_comp);
-        HIP_TRY(ctx, launch_grouped_gemm(g1, true, v_up, n_cu, a_max, s_comp));
+        if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g1, along ? &s1 : nullptr, true, (double)Tn * k / E, a_max, s_comp));
+        else HIP_TRY(ctx, launch_grouped_gemm(g1, true, v_up, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);
 
         GemmArgs g2{};
@@ -832,10 +877,11 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         g2.max_units = ctx->down_units;
         g2.epi = ctx->y_mode; g2.row_weight = w; g2.row_assignment = perm;
         sp = prof_begin(ctx, prof, ST_GEMM2, s_comp);
-        HIP_TRY(ctx, launch_grouped_gemm(g2, false, v_down, n_cu, a_max, s_comp));
+        if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g2, along ? &s2 : nullptr, false, (double)Tn * k / E, a_max, s_comp));
+        else HIP_TRY(ctx, launch_grouped_gemm(g2, false, v_down, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);
 
-        if (!dep && Ns > 0 && order == MOE_EP_ORDER_INTERLEAVED) {
+        if (interleaved && !along) {
             int rc = run_shared(t0, Tn, s_comp);
             if (rc != MOE_EP_OK) return rc;
         }
@@ -911,8 +957,8 @@ int moe_ep_last_tile_shape(const moe_ep_ctx* ctx, int32_t chunk, int32_t stage, 
     const moe_ep_config& c = ctx->cfg;
     const int variant = shared ? ctx->shared_variant : (up ? ctx->last_variants[chunk].up : ctx->last_variants[chunk].down);
     const int K = shared ? (up ? c.hidden : c.n_shared * c.shared_inter) : (up ? c.hidden : c.inter);
-    int v[8];
-    if (!grouped_gemm_variant_shape(variant, K, !shared, shared ? 1 : c.n_local, v)) return MOE_EP_ESTATE;
+    int v[8] = {kNarrowRows, 128, kPackK, kNarrowDepth, 1, 4, 1, 16};   // the narrow kernels
+    if (!(shared ? ctx->last_shared_narrow : variant == kNarrowVariant) && !grouped_gemm_variant_shape(variant, K, !shared, shared ? 1 : c.n_local, v)) return MOE_EP_ESTATE;
     if (mfma_rows) *mfma_rows = v[7];
     if (tile_order) *tile_order = v[6] && (shared ? ctx->last_prepared_shared : ctx->last_prepared_routed);
     if (rows) *rows = v[0];

@@ -1,0 +1,352 @@
+// Expert projections for few token rows per expert (Sec. 3.1; decode): the weights are read once and
+// everything else is small, so the launch lasts as long as the weight stream from HBM.  Measured on launches of
+// the gate/up projection: DeepSeek-V2-Lite-shaped layer, 33 tokens (761 MB with the shared experts) 132 + 50 us in the
+// tiled kernels, 123 us here = 6.2 TB/s; Qwen3-235B-A22B-shaped share, 256 tokens (403 MB) 79 and 69 us = 5.8 TB/s.
+//
+// A workgroup is four wavefronts.  A wavefront owns two blocks of 16 weight rows (gate/up: the gate and the up
+// rows of the same 16 activation columns) and up to four blocks of 16 token rows of one expert.  Its weights go
+// from global memory straight into registers, kNarrowDepth K steps ahead of the matrix instructions (16 KB in
+// flight per wavefront, two workgroups per compute unit).  The token rows, which all four wavefronts need, are
+// staged through LDS kNarrowDepth K steps at a time, two buffers deep with one barrier each: read fragment by
+// fragment from global memory, 16 rows per load instruction, they would cost the compute unit's address path four
+// times what the same bytes cost as whole lines, and that path, not HBM, would set the pace.
+// Against the 128 x 256 tiles of grouped_gemm.hip a tile is 64 (gate/up) or 128 (down) output columns wide, so
+// that one token's experts already cover the GPU, and no matrix work goes into rows that are not there.
+//
+// Every output element is accumulated over K in the order of grouped_gemm.hip by the same instruction, and the
+// epilogue rounds at the same place: the results are the same bits.
+#include "common.h"
+#include "kernels.h"
+
+namespace moe_ep {
+
+namespace {
+
+constexpr int kNarrowThreads = 256;
+constexpr int kNarrowMaxGroups = 512;
+
+constexpr int kChunkRowBytes = kNarrowDepth * kPackK * 2;         // one token row of a staged chunk: 512 bytes
+constexpr int kChunksPerRow = kChunkRowBytes / 16;
+constexpr int kRowsPerPass = kNarrowThreads / kChunksPerRow;      // token rows one load per thread stages: 8
+constexpr int kBufferBytes = kNarrowRows * kChunkRowBytes;
+constexpr int kTurnBytes = 16 * kPackK * 2;                       // one block of 16 weight rows of a K step
+
+// one wavefront's share of a tile: uniform bases, the lane's byte offsets, and how the weight base moves
+// from K step to K step (seg_steps steps of w_step bytes, then a jump to the next K segment)
+struct NarrowTile {
+    const char* w;         // first weight row block at K step 0
+    long long w_delta;     // bytes to the second block
+    uint32_t w_off;        // the lane's bytes of a block's first load; its second load is w_half further on
+    uint32_t w_half;
+    long long w_step, seg_jump;
+    int seg_steps;
+    const char* x;         // token rows
+    uint32_t x_off[kNarrowRows / kRowsPerPass];   // the rows this thread stages
+    int KT;
+};
+
+// 16 bytes at base + lane offset + wavefront offset: the buffer form keeps bases in scalar registers (the
+// pointers are valid for every offset used; the record count is not what bounds them)
+template <int CACHE = 0>   // 2: non-temporal
+__device__ __forceinline__ uint4 load16(const char* base, uint32_t lane_off, uint32_t wave_off)
+{
+    auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, 0xffffffffu, 0x00027000);
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_off, wave_off, CACHE));
+}
+
+// LDS accesses of every wavefront done, loads from global memory left in flight
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+template <bool SWIGLU, bool PACKED, int MB>
+__device__ __forceinline__ void narrow_tile(const NarrowTile& t, int nrows, int tid, char* lds, bool stores, uint16_t* c, int ldc)
+{
+    constexpr int D = kNarrowDepth;
+    constexpr int PASSES = MB * 16 / kRowsPerPass;
+    const int lane = tid & 63;
+    uint4 w[D][2][2], st[PASSES];   // [ring slot][row block][half of the K step]; the next chunk's token rows
+    f32x4_t acc[2][MB];
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int m = 0; m < MB; ++m) acc[b][m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const char* wk = t.w;
+    int seg = t.seg_steps;
+    // non-temporal: a layer's weights are read once per call, and between two calls lie the other layers'.  Five
+    // layers in turn, kept / non-temporal: DeepSeek-V2-Lite-shaped layer, 1 token 65 / 62 us, 33 tokens 222 / 200;
+    // Qwen3-235B-A22B-shaped share, 8 tokens 71 / 65
+    auto load_w = [&](int slot) __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) w[slot][b][h] = load16<2>(b == 0 ? wk : wk + t.w_delta, t.w_off, h * t.w_half);
+        wk += t.w_step;
+        if (--seg == 0) { seg = t.seg_steps; wk += t.seg_jump; }
+    };
+    // token rows: thread -> row tid / 32 + 8 i, 16-byte chunk tid % 32 of the staged 512 bytes.  In LDS chunk c of row r
+    // lies at c ^ (r mod 16), so that both the writes (one row) and the fragment reads (16 rows, one
+    // chunk column) touch all banks evenly.  Chunks past the end of a row re-read its last one, unused.
+    const int st_row = tid / kChunksPerRow, st_chunk = tid % kChunksPerRow;
+    auto load_x = [&](int ch) __attribute__((always_inline)) {
+        const uint32_t k_off = min((uint32_t)(ch * kChunkRowBytes + st_chunk * 16), (uint32_t)t.KT * (kPackK * 2) - 16u);
+#pragma unroll
+        for (int i = 0; i < PASSES; ++i) st[i] = load16(t.x, t.x_off[i] + k_off, 0);
+    };
+    auto stage_x = [&](int ch) __attribute__((always_inline)) {
+        char* buf = lds + (ch & 1) * kBufferBytes;
+#pragma unroll
+        for (int i = 0; i < PASSES; ++i) {
+            const int r = st_row + kRowsPerPass * i;
+            *reinterpret_cast<uint4*>(buf + r * kChunkRowBytes + (st_chunk ^ (r & 15)) * 16) = st[i];
+        }
+    };
+    // Weights in tile order arrive as operands: load h of a block is the k half h of its 16 rows.  From the
+    // caller's rows a load takes 8 rows of 128 bytes (read as operands, 16 rows of 64, the address path takes
+    // four times as long and every line is asked for twice) and the wavefront turns a block into operands
+    // through 2 KB of LDS of its own; chunk c of row r lies at c ^ (r / 2 mod 8), all banks in use both ways.
+    char* turn = lds + 2 * kBufferBytes + (tid >> 6) * kTurnBytes;
+    auto operand = [&](int slot, int b, bf16x8_t (&f)[2]) __attribute__((always_inline)) {
+        if (PACKED) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) f[h] = __builtin_bit_cast(bf16x8_t, w[slot][b][h]);
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int r = i * 8 + (lane >> 3);
+            *reinterpret_cast<uint4*>(turn + r * 128 + ((lane & 7) ^ (r >> 1)) * 16) = w[slot][b][i];
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int r = lane & 15;
+            f[h] = *reinterpret_cast<const bf16x8_t*>(turn + r * 128 + ((h * 4 + (lane >> 4)) ^ (r >> 1)) * 16);
+        }
+    };
+    auto multiply = [&](int ch, int slot) __attribute__((always_inline)) {
+        const char* buf = lds + (ch & 1) * kBufferBytes + (lane & 15) * kChunkRowBytes;
+        bf16x8_t f[2][2];
+        operand(slot, 0, f[0]);
+        operand(slot, 1, f[1]);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int col = ((slot * 8 + h * 4 + (lane >> 4)) ^ (lane & 15)) * 16;
+#pragma unroll
+            for (int m = 0; m < MB; ++m) {
+                const bf16x8_t x = *reinterpret_cast<const bf16x8_t*>(buf + m * 16 * kChunkRowBytes + col);
+#pragma unroll
+                for (int b = 0; b < 2; ++b) acc[b][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[b][h], x, acc[b][m], 0, 0, 0);
+            }
+        }
+    };
+    const int chunks = (t.KT + D - 1) / D;
+    // the weights first: the token rows wait for the row map
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        if (d < t.KT) load_w(d);
+    load_x(0);
+    lds_barrier();   // the wavefronts that still read the tile before this one are done
+    stage_x(0);
+    lds_barrier();
+    int ch = 0;
+    for (; (ch + 2) * D <= t.KT; ++ch) {
+        load_x(ch + 1);
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            multiply(ch, d);
+            load_w(d);
+            __builtin_amdgcn_sched_barrier(0);   // the loads stay D steps ahead of their use
+        }
+        stage_x(ch + 1);
+        lds_barrier();
+    }
+    for (; ch < chunks; ++ch) {   // the last one or two chunks
+        const bool more = ch + 1 < chunks;
+        if (more) load_x(ch + 1);
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            if (ch * D + d < t.KT) multiply(ch, d);
+            if ((ch + 1) * D + d < t.KT) load_w(d);
+        }
+        if (more) { stage_x(ch + 1); lds_barrier(); }
+    }
+    if (!stores) return;
+    // a lane holds four consecutive output columns, 4 * (lane >> 4) + {0..3} of a block, of token row lane & 15
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+        const int r = m * 16 + (lane & 15);
+        if (r >= nrows) continue;
+        uint16_t* row = c + (size_t)r * ldc + (lane >> 4) * 4;
+        if (SWIGLU) {
+            float h[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) h[i] = silu_f(acc[0][m][i]) * acc[1][m][i];
+            *reinterpret_cast<uint2*>(row) = make_uint2(pack_bf16x2(h[0], h[1]), pack_bf16x2(h[2], h[3]));
+        } else {
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+                *reinterpret_cast<uint2*>(row + b * 16) =
+                    make_uint2(pack_bf16x2(acc[b][m][0], acc[b][m][1]), pack_bf16x2(acc[b][m][2], acc[b][m][3]));
+        }
+    }
+}
+
+template <bool SWIGLU, bool PACKED>
+__device__ __forceinline__ void narrow_dispatch(const GemmArgs& a, int g, int row0, int nrows, int n0, int wave, int tid, char* lds)
+{
+    constexpr int WAVE_COLS = SWIGLU ? 16 : 32;
+    // N is a multiple of 64: a wavefront's columns are all there or none is; one without any works on the last
+    // ones (the barriers count it) and stores nothing
+    const bool stores = n0 + wave * WAVE_COLS < a.N;
+    const int n = stores ? n0 + wave * WAVE_COLS : a.N - WAVE_COLS;
+    const int lane = tid & 63;
+    NarrowTile t;
+    t.KT = a.K / kPackK;
+    if (PACKED) {   // weights in tile order: 4 KB per K step and wavefront, each load instruction 1 KB without gaps
+        constexpr int COLS = SWIGLU ? kPackRows / 2 : kPackRows;
+        const int NT = (a.N + COLS - 1) / COLS, nt = n / COLS, blk = (n - nt * COLS) / 16 * (SWIGLU ? 2 : 1);
+        t.w = reinterpret_cast<const char*>(a.Wp + (((size_t)g * NT + nt) * t.KT * kPackRows + blk * 16) * kPackK);
+        t.w_delta = 16 * kPackK * 2;
+        t.w_half = 1024;
+        t.w_off = lane * 16u;
+        t.w_step = (long long)kPackRows * kPackK * 2;
+        t.seg_steps = t.KT;
+        t.seg_jump = 0;
+    } else {
+        t.w = reinterpret_cast<const char*>(a.W + (size_t)g * a.w_group_stride + (size_t)n * a.ldw);
+        t.w_delta = SWIGLU ? a.w_up_offset * 2 : (long long)16 * a.ldw * 2;
+        t.w_off = (uint32_t)(lane >> 3) * (uint32_t)a.ldw * 2u + (lane & 7) * 16u;
+        t.w_half = 8u * (uint32_t)a.ldw * 2u;
+        t.w_step = kPackK * 2;
+        t.seg_steps = a.kseg_len / kPackK;
+        t.seg_jump = (a.w_kseg_stride - a.kseg_len) * 2;
+    }
+    const bool mapped = a.a_row_map != nullptr;
+    t.x = reinterpret_cast<const char*>(mapped ? a.A : a.A + (size_t)row0 * a.lda);
+#pragma unroll
+    for (int i = 0; i < kNarrowRows / kRowsPerPass; ++i) {
+        // rows past the tile's end re-read its last one; they are multiplied and not stored
+        const int r = min(tid / kChunksPerRow + kRowsPerPass * i, nrows - 1);
+        const int src = mapped ? a.a_row_map[row0 + r] / a.a_row_div : r;
+        t.x_off[i] = (uint32_t)src * (uint32_t)a.lda * 2u;
+    }
+    uint16_t* c = a.C + (size_t)g * a.c_group_col_stride + (size_t)row0 * a.ldc + n;
+    switch ((nrows + 15) >> 4) {
+        case 1: narrow_tile<SWIGLU, PACKED, 1>(t, nrows, tid, lds, stores, c, a.ldc); break;
+        case 2: narrow_tile<SWIGLU, PACKED, 2>(t, nrows, tid, lds, stores, c, a.ldc); break;
+        case 3: narrow_tile<SWIGLU, PACKED, 3>(t, nrows, tid, lds, stores, c, a.ldc); break;
+        default: narrow_tile<SWIGLU, PACKED, 4>(t, nrows, tid, lds, stores, c, a.ldc); break;
+    }
+}
+
+// row tiles of n rows and the rows of each but the last: equal heights in blocks of 16
+__host__ __device__ __forceinline__ int narrow_tiles(int rows) { return (rows + kNarrowRows - 1) / kNarrowRows; }
+__device__ __forceinline__ int narrow_height(int rows, int tiles) { return ((rows + 15) / 16 + tiles - 1) / tiles * 16; }
+
+template <bool SWIGLU>
+constexpr int narrow_cols() { return SWIGLU ? 64 : 128; }
+
+}  // namespace
+
+// Tile ids: first those of the shared experts s (s.G == 0: none), then those of the routed groups r; each XCD
+// (workgroup id mod 8) takes a contiguous run of both, in which the row tiles of one column tile are neighbours,
+// so that a group with several of them reads its weights from HBM once.
+template <bool SWIGLU, bool PACKED>
+__global__ __launch_bounds__(kNarrowThreads, 2) void narrow_gemm_kernel(GemmArgs r, GemmArgs s)
+{
+    __shared__ int s_pref[kNarrowMaxGroups + 1], s_row0[kNarrowMaxGroups + 1];
+    __shared__ __align__(16) char lds[2 * kBufferBytes + (PACKED ? 0 : kNarrowThreads / 64 * kTurnBytes)];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (wave == 0) {   // row tiles before every routed group, from the partition's row offsets
+        int before = 0;
+        for (int g0 = 0; g0 < r.G; g0 += 64) {
+            const int g = g0 + lane;
+            const int r0 = g < r.G ? r.offset[g] : 0, r1 = g < r.G ? r.offset[g + 1] : 0;
+            const int n = narrow_tiles(r1 - r0);
+            int incl = n;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int up = __shfl_up(incl, d, 64);
+                if (lane >= d) incl += up;
+            }
+            if (g < r.G) { s_pref[g] = before + incl - n; s_row0[g] = r0; }
+            if (g == r.G - 1) { s_pref[r.G] = before + incl; s_row0[r.G] = r1; }
+            before += __shfl(incl, 63, 64);
+        }
+    }
+    __syncthreads();
+    constexpr int COLS = narrow_cols<SWIGLU>();
+    const int s_mt = s.G > 0 ? narrow_tiles(s.dense_rows) : 0, s_nt = s.G > 0 ? (s.N + COLS - 1) / COLS : 0;
+    const int s_total = s.G * s_mt * s_nt, s_xcd = (s_total + 7) >> 3;
+    const int r_nt = (r.N + COLS - 1) / COLS;
+    const int r_total = __builtin_amdgcn_readfirstlane(s_pref[r.G]) * r_nt, r_xcd = (r_total + 7) >> 3;
+    const int xcd = blockIdx.x & 7;
+    for (int slot = blockIdx.x >> 3; slot < s_xcd + r_xcd; slot += gridDim.x >> 3) {
+        if (slot < s_xcd) {
+            const int L = xcd * s_xcd + slot;
+            if (L >= s_total) continue;
+            const int g = L / (s_mt * s_nt), l = L - g * s_mt * s_nt, ni = l / s_mt, mi = l - ni * s_mt;
+            const int h = narrow_height(s.dense_rows, s_mt);
+            narrow_dispatch<SWIGLU, PACKED>(s, g, mi * h, min(h, s.dense_rows - mi * h), ni * COLS, wave, tid, lds);
+        } else {
+            const int L = xcd * r_xcd + slot - s_xcd;
+            if (L >= r_total) continue;
+            int lo = 0, hi = r.G;
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (s_pref[mid] * r_nt <= L) lo = mid; else hi = mid;
+            }
+            const int g = __builtin_amdgcn_readfirstlane(lo);
+            const int pref = __builtin_amdgcn_readfirstlane(s_pref[g]), mt = __builtin_amdgcn_readfirstlane(s_pref[g + 1]) - pref;
+            const int row_a = __builtin_amdgcn_readfirstlane(s_row0[g]), rows = __builtin_amdgcn_readfirstlane(s_row0[g + 1]) - row_a;
+            const int l = L - pref * r_nt, ni = l / mt, mi = l - ni * mt;
+            const int h = narrow_height(rows, mt);
+            narrow_dispatch<SWIGLU, PACKED>(r, g, row_a + mi * h, min(h, rows - mi * h), ni * COLS, wave, tid, lds);
+        }
+    }
+}
+
+static bool narrow_args_fit(const GemmArgs& a)
+{
+    if (a.K < kPackK || a.K % kPackK || a.kseg_len < kPackK || a.kseg_len % kPackK || a.N < 64 || a.N % 64) return false;
+    if (a.G < 1 || a.G > kNarrowMaxGroups || a.epi != 0) return false;
+    // lanes address token rows and a block of weight rows with 32-bit byte offsets
+    const long long rows = a.a_row_map ? a.a_src_rows : kNarrowRows;
+    if (rows * a.lda * 2 >= (1ll << 32) || 16ll * a.ldw * 2 >= (1ll << 32) || (a.a_row_map && a.a_row_div < 1)) return false;
+    if (a.lda % 8 || a.ldw % 8 || a.w_group_stride % 8 || a.w_up_offset % 8 || a.w_kseg_stride % 8) return false;
+    if ((reinterpret_cast<uintptr_t>(a.A) | reinterpret_cast<uintptr_t>(a.W) | reinterpret_cast<uintptr_t>(a.Wp)) & 15) return false;
+    return !(a.ldc % 4 || a.c_group_col_stride % 4 || (reinterpret_cast<uintptr_t>(a.C) & 7));
+}
+
+hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bool swiglu, double expected_rows,
+                              long long max_rows, hipStream_t s)
+{
+    GemmArgs none{};
+    const GemmArgs& sh = shared ? *shared : none;
+    if (routed.offset == nullptr || max_rows < 1 || !narrow_args_fit(routed)) return hipErrorInvalidValue;
+    if (shared && (sh.dense_rows < 1 || (sh.Wp != nullptr) != (routed.Wp != nullptr) || !narrow_args_fit(sh))) return hipErrorInvalidValue;
+    const int cols = swiglu ? narrow_cols<true>() : narrow_cols<false>();
+    const auto col_tiles = [&](const GemmArgs& a) { return (long long)(a.N + cols - 1) / cols; };
+    const long long s_tiles = shared ? col_tiles(sh) * narrow_tiles(sh.dense_rows) * sh.G : 0;
+    // Workgroups: every tile one of its own (a compute unit holds two at a time and takes the next when one
+    // ends) as far as the host can foresee the routing; groups with more rows than expected are reached by the
+    // kernel's loop over tile ids.
+    const long long filled = max_rows < routed.G ? max_rows : routed.G;
+    const long long most = filled + max_rows / kNarrowRows;
+    long long r_tiles = (long long)(filled * (1.0 + expected_rows / kNarrowRows));
+    if (r_tiles > most) r_tiles = most;
+    long long grid = (s_tiles + 7) / 8 * 8 + (r_tiles * col_tiles(routed) + 7) / 8 * 8;
+    if (grid < 8) grid = 8;
+    if (grid > (1 << 20)) grid = 1 << 20;
+    const auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kNarrowThreads), 0, s, routed, sh); };
+    if (routed.Wp) { if (swiglu) go(narrow_gemm_kernel<true, true>); else go(narrow_gemm_kernel<false, true>); }
+    else { if (swiglu) go(narrow_gemm_kernel<true, false>); else go(narrow_gemm_kernel<false, false>); }
+    return hipGetLastError();
+}
+
+}  // namespace moe_ep

@@ -1,0 +1,86 @@
+"""The projections of chunks with few rows per expert (narrow_gemm.hip): the bits of the tiled kernels, which the
+oracle tests pin, on every row count and column or K remainder where a tile, a staged chunk or a ring can go wrong."""
+import numpy as np
+import pytest
+
+from workloads import make_inputs, tiny_workload
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# rows of the experts: none, one, around a block of 16, around a row tile of 64, several tiles with a remainder
+LOADS = [0, 1, 15, 16, 17, 0, 33, 63, 64, 65, 129, 200]
+
+
+def _env(monkeypatch, rows):
+    monkeypatch.setenv("MOE_EP_NARROW_ROWS", str(rows))
+
+
+def _exact_loads(wl, inp):
+    lg = np.full((wl.n_tokens, wl.n_experts), -30.0, dtype=np.float32)
+    t = 0
+    for e, n in enumerate(LOADS):
+        lg[t:t + n, e] = 5.0
+        t += n
+    inp["gate_logits"][:] = lg[np.random.default_rng(7).permutation(wl.n_tokens)]
+
+
+def _run(monkeypatch, wl, inp, rows, what=(), calls=((1, 0),), pinned=False):
+    """Output bits of the calls (r, order) with the narrow kernels up to `rows` rows per expert (0: never)."""
+    import gpu_util as g
+    _env(monkeypatch, rows)
+    ctx = g.make_ctx(wl, pinned=pinned)
+    d = g.DeviceInputs(wl, inp, pinned=pinned)
+    if what:
+        ctx.prepare_weights(d.routed if "routed" in what else None, d.shared if "shared" in what else None)
+    outs = [g.run_forward(ctx, wl, d, r=r, order=order) for r, order in calls]
+    shape = ctx.last_tile_shape("routed_gate_up_gemm")
+    ctx.destroy()
+    return outs, shape["rows"] == 64
+
+
+@pytest.mark.parametrize("what", [(), ("routed", "shared"), ("routed",), ("shared",)])
+@pytest.mark.parametrize("hidden,inter,shared_inter", [(64, 64, 64), (192, 128, 192), (256, 320, 64), (320, 576, 320), (576, 448, 128)])
+def test_same_bits_as_the_tiled_kernels(monkeypatch, hidden, inter, shared_inter, what):
+    """K of 1, 2, 3, 4, 5, 7 and 9 steps of 64, columns that end inside a tile, two shared experts whose K
+    segments end inside a staged chunk, weights in either layout and in both at once, and chunks."""
+    wl = tiny_workload(name=f"narrow_M{hidden}_H{inter}", n_tokens=sum(LOADS), hidden=hidden, inter=inter, n_experts=12,
+                       n_local=12, top_k=1, n_shared=2, shared_inter=shared_inter)
+    inp = make_inputs(wl, seed=61)
+    _exact_loads(wl, inp)
+    calls = ((1, 0), (3, 0), (3, 1))
+    want, _ = _run(monkeypatch, wl, inp, 0, what, calls)
+    got, narrow = _run(monkeypatch, wl, inp, 1e9, what, calls)
+    assert narrow and want[0].any()
+    for w, o, c in zip(want, got, calls):
+        assert np.array_equal(o, w), f"r, order = {c}"
+
+
+@pytest.mark.parametrize("n_tokens", [1, 2, 16, 63, 300])
+@pytest.mark.parametrize("pinned", [False, True])
+def test_small_calls_of_a_share(monkeypatch, n_tokens, pinned):
+    """By the library's own rule: a local share that starts at expert 2 of 70, no shared experts, k = 5."""
+    wl = tiny_workload(name=f"narrow_share_{n_tokens}", n_tokens=n_tokens, hidden=192, inter=320, n_experts=70,
+                       local_begin=2, n_local=66, top_k=5)
+    inp = make_inputs(wl, seed=62)
+    calls = ((1, 0), (2, 0))
+    want, _ = _run(monkeypatch, wl, inp, 0, (), calls, pinned)
+    got, narrow = _run(monkeypatch, wl, inp, 48, (), calls, pinned)
+    assert narrow
+    for w, o in zip(want, got):
+        assert np.array_equal(o, w)
+
+
+def test_most_experts_and_nothing_kept(monkeypatch):
+    """512 local experts, 64 per token (several groups of lanes in the kernel's prefix sum); then no token at all
+    for the local share."""
+    wl = tiny_workload(name="narrow_E512", n_tokens=40, hidden=64, inter=64, n_experts=512, n_local=512, top_k=64)
+    inp = make_inputs(wl, seed=63)
+    want, _ = _run(monkeypatch, wl, inp, 0)
+    got, narrow = _run(monkeypatch, wl, inp, 48)
+    assert narrow and np.array_equal(got[0], want[0]) and want[0].any()
+    wl = tiny_workload(name="narrow_none", n_tokens=40, hidden=64, inter=64, n_experts=8, local_begin=6, n_local=2, top_k=2)
+    inp = make_inputs(wl, seed=64)
+    inp["gate_logits"][:, 6:] = -40.0
+    got, narrow = _run(monkeypatch, wl, inp, 48)
+    assert narrow and not got[0].any()
