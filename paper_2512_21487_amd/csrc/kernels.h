@@ -12,6 +12,10 @@ constexpr int kTokPerBlock = 64;
 hipError_t launch_router(const float* logits, int Tn, int E, int k, int e0, int El, int32_t* idx,
                          float* w, unsigned long long* blk_mask, hipStream_t s);
 
+// gate and partition of at most kTokPerBlock tokens in one launch; outputs as launch_router and launch_dispatch
+hipError_t launch_route_and_partition(const float* logits, int Tn, int E, int k, int e0, int El, int32_t* idx, float* w,
+                                      int32_t* count, int32_t* offset, int32_t* pos, int32_t* perm, hipStream_t s);
+
 // ---- partition by expert (Sec. 2.1; Sec. 3.1 "The MoE Part")
 // count [El], offset [El + 1], pos [Tn * k] (row of an assignment or -1), perm [rows] (row -> assignment)
 hipError_t launch_dispatch(const int32_t* idx, const unsigned long long* blk_mask, int Tn, int k, int e0, int El,

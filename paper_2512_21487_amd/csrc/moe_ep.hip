@@ -826,13 +826,15 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         int32_t* perm = ctx->perm + (size_t)t0 * k;
 
         int sp = prof_begin(ctx, prof, ST_ROUTER, s_comp);
-        HIP_TRY(ctx, launch_router(log_dev + (size_t)t0 * E, Tn, E, k, e0, El, idx, w, ctx->blk_mask, s_comp));
+        const bool one_block = Tn > 0 && Tn <= kTokPerBlock;   // one workgroup's tokens: partitioned in the same launch
+        if (one_block) HIP_TRY(ctx, launch_route_and_partition(log_dev + (size_t)t0 * E, Tn, E, k, e0, El, idx, w, count, offset, pos, perm, s_comp));
+        else HIP_TRY(ctx, launch_router(log_dev + (size_t)t0 * E, Tn, E, k, e0, El, idx, w, ctx->blk_mask, s_comp));
         prof_end(ctx, sp, s_comp);
 
         // the fused gather addresses a chunk's token rows with 32-bit byte offsets
         const bool fused = ctx->fused_gather && (unsigned long long)Tn * M * 2 < (1ull << 32);
         sp = prof_begin(ctx, prof, ST_PARTITION, s_comp);
-        HIP_TRY(ctx, launch_dispatch(idx, ctx->blk_mask, Tn, k, e0, El, count, offset, pos, perm, s_comp));
+        if (!one_block) HIP_TRY(ctx, launch_dispatch(idx, ctx->blk_mask, Tn, k, e0, El, count, offset, pos, perm, s_comp));
         if (Tn > 0 && !fused) {   // the grouped copy reads the token rows
             if (pinned) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[cidx], 0));
             HIP_TRY(ctx, launch_gather_rows(tok_dev + (size_t)t0 * M, perm, offset + El, k, M, ctx->xp, bw_grid, s_comp));

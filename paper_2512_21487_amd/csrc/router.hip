@@ -1,103 +1,134 @@
 // Gate: per token, the top-k of E routing scores and their renormalised softmax weights
 // (Sec. 2.1).  A token is owned by one 16-lane row of a wavefront, so a wavefront advances four
-// tokens at once: lane l of the row holds scores l, l+16, ... in registers, and each of the k
-// selection rounds is a lane-local scan plus a four-step arg-max over the row done with DPP
-// lane exchanges (quad swaps and row mirrors: register moves, no LDS traffic).
-// The same workgroup (64 tokens) also records, per local expert, a 64-bit mask of the
+// tokens at once: lane l of the row holds scores l, l+16, ... in registers as integers of the same order, and
+// each of the k selection rounds is a lane-local maximum, a four-step maximum over the row done with DPP
+// lane exchanges (quad swaps and row mirrors: register moves, no LDS traffic), and the same for the lowest expert
+// that has it.  The rounds are what the kernel lasts for, and the wavefronts of a SIMD take turns at them: a
+// workgroup is 16 tokens, one wavefront per SIMD (64 tokens and 16 wavefronts: 256 tokens, 128 scores, k = 8 6.7 us
+// instead of 4.7, 8192 tokens 12.4 instead of 10.5, launch included).
+// The workgroup also records, per local expert, 16 bits of the 64-bit mask (one per expert and 64 tokens) of the
 // tokens that selected it; the partition kernels derive counts and stable ranks from it,
-// so no atomically allocated slot ever decides an order.
-#include "common.h"
-#include "kernels.h"
+// so no atomically allocated slot ever decides an order.  A call of at most 64 tokens is one workgroup of 64, which
+// partitions right away out of LDS (route_and_partition): one launch less.
+#include "partition.h"
 
 namespace moe_ep {
 
-constexpr int kRouterThreads = 1024;  // 16 wavefronts x 4 rows = the 64 tokens of a workgroup
+constexpr int kRouterTokens = 16;   // of a workgroup: 16 lanes each
 
 // the value lane (lane ^ pattern) of the same 16-lane row holds; ctrl is a DPP control:
 // 0xB1 / 0x4E swap neighbours / pairs inside a quad, 0x141 / 0x140 mirror a half row / a row
 template <int CTRL>
 __device__ __forceinline__ int row_exchange(int x) { return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xF, 0xF, false); }
 
-// larger score first, equal scores keep the lower expert index
-__device__ __forceinline__ void keep_better(float& bv, int& bi, float ov, int oi)
-{
-    if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-}
-
 template <int CTRL>
-__device__ __forceinline__ void row_argmax_step(float& bv, int& bi)
+__device__ __forceinline__ uint32_t row_max_step(uint32_t x) { return max(x, (uint32_t)row_exchange<CTRL>((int)x)); }
+template <int CTRL>
+__device__ __forceinline__ int row_min_step(int x) { return min(x, row_exchange<CTRL>(x)); }
+
+// scores as unsigned integers of the same order, equal for equal scores (-0 == +0); 0 is below every score
+__device__ __forceinline__ uint32_t order_key(float v)
 {
-    const float ov = __builtin_bit_cast(float, row_exchange<CTRL>(__builtin_bit_cast(int, bv)));
-    const int oi = row_exchange<CTRL>(bi);
-    keep_better(bv, bi, ov, oi);
+    const uint32_t u = __float_as_uint(v + 0.0f);
+    return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+}
+__device__ __forceinline__ float key_score(uint32_t key)
+{
+    return __uint_as_float(key ^ ((key & 0x80000000u) ? 0x80000000u : 0xffffffffu));
 }
 
-template <int EPL>  // scores per lane: E <= 16 * EPL
-__global__ __launch_bounds__(kRouterThreads) void router_topk_kernel(
+template <int EPL, bool PARTITION>  // scores per lane: E <= 16 * EPL; PARTITION: one workgroup holds every token
+__global__ __launch_bounds__((PARTITION ? kTokPerBlock : kRouterTokens) * 16) void router_topk_kernel(
     const float* __restrict__ logits, int Tn, int E, int k, int e0, int El,
-    int32_t* __restrict__ idx, float* __restrict__ w, unsigned long long* __restrict__ blk_mask)
+    int32_t* __restrict__ idx, float* __restrict__ w, unsigned long long* __restrict__ blk_mask, PartitionOut part)
 {
+    constexpr int TOKENS = PARTITION ? kTokPerBlock : kRouterTokens, THREADS = TOKENS * 16;
     extern __shared__ unsigned long long smask[];                  // [El] token masks of the local experts
-    int* s_idx = reinterpret_cast<int*>(smask + El);               // [64][k] selected experts
-    float* s_ex = reinterpret_cast<float*>(s_idx + kTokPerBlock * k);  // [64][k] exp(score - best score)
+    int* s_idx = reinterpret_cast<int*>(smask + El);               // [TOKENS][k] selected experts
+    float* s_ex = reinterpret_cast<float*>(s_idx + TOKENS * k);    // [TOKENS][k] score, then exp(score - best score)
+    int* s_total = reinterpret_cast<int*>(s_ex + TOKENS * k);      // [El] rows, [El] first row (PARTITION)
+    int* s_base = s_total + El;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int sub = lane & 15, tl = wave * 4 + (lane >> 4);        // lane inside the row; token inside the block
-    for (int i = tid; i < El; i += kRouterThreads) smask[i] = 0ull;
+    for (int i = tid; i < El; i += THREADS) smask[i] = 0ull;
     __syncthreads();
 
-    const int t = blockIdx.x * kTokPerBlock + tl;
+    const int t = blockIdx.x * TOKENS + tl;
     const bool live = t < Tn;
-    const float* row = logits + (size_t)min(t, Tn - 1) * E;
-    float v[EPL];
-    unsigned taken = 0;  // bit i: score i of this lane is out of range or already selected
+    if (wave * 4 + blockIdx.x * TOKENS < Tn) {   // the wavefront has a token
+        const float* row = logits + (size_t)min(t, Tn - 1) * E;
+        uint32_t key[EPL];   // 0: out of range or already selected
 #pragma unroll
-    for (int i = 0; i < EPL; ++i) {
-        const int e = sub + 16 * i;
-        if (e < E) v[i] = row[e]; else { v[i] = 0.f; taken |= 1u << i; }
-    }
-    float v0 = 0.f, sum = 0.f;
-    for (int s = 0; s < k; ++s) {
-        float bv = -INFINITY;
-        int bi = INT_MAX;
-#pragma unroll
-        for (int i = 0; i < EPL; ++i)  // ascending index inside a lane: a strict > keeps the lower one
-            if (!((taken >> i) & 1u) && (bi == INT_MAX || v[i] > bv)) { bv = v[i]; bi = sub + 16 * i; }
-        row_argmax_step<0xB1>(bv, bi);
-        row_argmax_step<0x4E>(bv, bi);
-        row_argmax_step<0x141>(bv, bi);
-        row_argmax_step<0x140>(bv, bi);   // every lane of the row now holds the round's winner
-        if ((bi & 15) == sub) taken |= 1u << (bi >> 4);
-        if (s == 0) v0 = bv;
-        // softmax restricted to the selection = full softmax renormalised over it
-        const float ex = expf(bv - v0);
-        sum += ex;
-        if (sub == 0 && live) {
-            s_idx[tl * k + s] = bi;
-            s_ex[tl * k + s] = ex;
-            const int el = bi - e0;
-            if (el >= 0 && el < El) atomicOr(&smask[el], 1ull << tl);
+        for (int i = 0; i < EPL; ++i) {
+            const int e = sub + 16 * i;
+            key[i] = e < E ? order_key(row[e]) : 0u;
         }
+        for (int s = 0; s < k; ++s) {
+            uint32_t best = key[0];
+#pragma unroll
+            for (int i = 1; i < EPL; ++i) best = max(best, key[i]);
+            best = row_max_step<0xB1>(best);
+            best = row_max_step<0x4E>(best);
+            best = row_max_step<0x141>(best);
+            best = row_max_step<0x140>(best);   // every lane of the row now holds the round's winner
+            int bi = INT_MAX;                   // equal scores: the lowest expert
+#pragma unroll
+            for (int i = EPL - 1; i >= 0; --i) bi = key[i] == best ? sub + 16 * i : bi;
+            bi = row_min_step<0xB1>(bi);
+            bi = row_min_step<0x4E>(bi);
+            bi = row_min_step<0x141>(bi);
+            bi = row_min_step<0x140>(bi);
+#pragma unroll
+            for (int i = 0; i < EPL; ++i) key[i] = bi == sub + 16 * i ? 0u : key[i];
+            if (sub == 0) {
+                s_idx[tl * k + s] = bi;
+                s_ex[tl * k + s] = key_score(best);
+            }
+        }
+        // Everything that need not follow round by round, a lane per slot.  Softmax restricted to the selection
+        // = full softmax renormalised over it; the sum runs in slot order in every lane.
+        const float v0 = s_ex[tl * k];
+        for (int s = sub; s < k; s += 16) {
+            s_ex[tl * k + s] = expf(s_ex[tl * k + s] - v0);
+            const int el = s_idx[tl * k + s] - e0;
+            if (live && el >= 0 && el < El) atomicOr(&smask[el], 1ull << tl);
+        }
+        float sum = 0.f;
+        for (int s = 0; s < k; ++s) sum += s_ex[tl * k + s];
+        if (live)
+            for (int s = sub; s < k; s += 16) {
+                idx[(size_t)t * k + s] = s_idx[tl * k + s];
+                w[(size_t)t * k + s] = s_ex[tl * k + s] / sum;
+            }
     }
     __syncthreads();
-    if (live)
-        for (int s = sub; s < k; s += 16) {
-            idx[(size_t)t * k + s] = s_idx[tl * k + s];
-            w[(size_t)t * k + s] = s_ex[tl * k + s] / sum;
-        }
-    unsigned long long* dst = blk_mask + (size_t)blockIdx.x * El;
-    for (int i = tid; i < El; i += kRouterThreads) dst[i] = smask[i];
+    if (PARTITION) {
+        for (int e = tid; e < El; e += THREADS) { s_total[e] = __popcll(smask[e]); s_base[e] = 0; }
+        __syncthreads();
+        if (wave == 0) scan_experts(lane, El, s_total, s_base, part.count, part.offset);
+        __syncthreads();
+        for (int a = tid; a < Tn * k; a += THREADS) place_assignment(a, a / k, s_idx[a] - e0, El, smask, s_base, part.pos, part.perm);
+    } else {
+        // this workgroup's quarter of the 64-token masks
+        constexpr int PARTS = kTokPerBlock / kRouterTokens;
+        uint16_t* dst = reinterpret_cast<uint16_t*>(blk_mask) + (size_t)(blockIdx.x / PARTS) * El * PARTS + blockIdx.x % PARTS;
+        for (int i = tid; i < El; i += THREADS) dst[(size_t)i * PARTS] = (uint16_t)smask[i];
+    }
 }
 
-hipError_t launch_router(const float* logits, int Tn, int E, int k, int e0, int El, int32_t* idx,
-                         float* w, unsigned long long* blk_mask, hipStream_t s)
+template <bool PARTITION>
+static hipError_t launch(const float* logits, int Tn, int E, int k, int e0, int El, int32_t* idx, float* w,
+                         unsigned long long* blk_mask, const PartitionOut& part, hipStream_t s)
 {
-    if (Tn <= 0) return hipSuccess;
     if (E < 1 || E > 512 || k < 1 || k > 64) return hipErrorInvalidValue;
-    const int nblk = (Tn + kTokPerBlock - 1) / kTokPerBlock;
-    const size_t lds = El * sizeof(unsigned long long) + (size_t)kTokPerBlock * k * 8;
+    constexpr int TOKENS = PARTITION ? kTokPerBlock : kRouterTokens;
+    static_assert(kTokPerBlock == 4 * kRouterTokens && kRouterTokens == 16, "a workgroup's mask is a 16-bit quarter");
+    // whole masks: the last 64 tokens' workgroups without a token write zeros
+    const int nblk = (Tn + kTokPerBlock - 1) / kTokPerBlock * (kTokPerBlock / TOKENS);
+    const size_t lds = El * sizeof(unsigned long long) + (size_t)TOKENS * k * 8 + (PARTITION ? (size_t)El * 8 : 0);
 #define MOE_EP_ROUTER(EPL)                                                                          \
-    hipLaunchKernelGGL(router_topk_kernel<EPL>, dim3(nblk), dim3(kRouterThreads), lds, s, logits, Tn, E, k, e0, \
-                       El, idx, w, blk_mask)
+    hipLaunchKernelGGL((router_topk_kernel<EPL, PARTITION>), dim3(nblk), dim3(TOKENS * 16), lds, s, logits, Tn, E, k, e0, \
+                       El, idx, w, blk_mask, part)
     if (E <= 16) MOE_EP_ROUTER(1);
     else if (E <= 32) MOE_EP_ROUTER(2);
     else if (E <= 64) MOE_EP_ROUTER(4);
@@ -107,6 +138,20 @@ hipError_t launch_router(const float* logits, int Tn, int E, int k, int e0, int 
     else MOE_EP_ROUTER(32);
 #undef MOE_EP_ROUTER
     return hipGetLastError();
+}
+
+hipError_t launch_router(const float* logits, int Tn, int E, int k, int e0, int El, int32_t* idx,
+                         float* w, unsigned long long* blk_mask, hipStream_t s)
+{
+    if (Tn <= 0) return hipSuccess;
+    return launch<false>(logits, Tn, E, k, e0, El, idx, w, blk_mask, PartitionOut{}, s);
+}
+
+hipError_t launch_route_and_partition(const float* logits, int Tn, int E, int k, int e0, int El, int32_t* idx, float* w,
+                                      int32_t* count, int32_t* offset, int32_t* pos, int32_t* perm, hipStream_t s)
+{
+    if (Tn < 1 || Tn > kTokPerBlock) return hipErrorInvalidValue;
+    return launch<true>(logits, Tn, E, k, e0, El, idx, w, nullptr, PartitionOut{count, offset, pos, perm}, s);
 }
 
 }  // namespace moe_ep
