@@ -52,6 +52,9 @@ struct moe_ep_ctx {
     bool shared_variant_named = false;
     // chunks whose routed experts get at most this many rows on average run the narrow kernels; 0 = never
     double narrow_rows = kNarrowMeanRows;
+    bool by_rule = true;     // no tile shape, instruction or form of the expert outputs was asked for by name
+    int merge = -1;          // shared and routed experts in one launch: -1 by the cost of both (plan_chunk), 0 never, 1 always
+    int last_shared_up = -1, last_shared_down = -1;   // tile variants of the last forward's shared experts
     bool fused_gather = true;  // the gate/up projection gathers the token rows itself (no grouped copy)
     int y_mode = 0;            // expert outputs: 0 bf16, 1 fp32, 2 bf16 scaled by the routing weight (expert_out_mode)
     // pinned-host mode, moe_ep_forward: the aggregation writes its rows straight into the caller's host
@@ -97,7 +100,6 @@ struct moe_ep_ctx {
     int last_T = -1, last_k = 0, last_r = 0, last_r1 = 1;
     bool last_prepared_routed = false, last_prepared_shared = false;  // it read tile-order copies of the weights
     struct ChunkVariants { int up, down; };
-    bool last_shared_narrow = false;
     std::vector<ChunkVariants> last_variants;  // per chunk of the last forward: tile variants of the routed projections
     // stage profiling
     int prof_depth = 0, prof_recorded = 0;
@@ -193,6 +195,7 @@ void read_knobs(moe_ep_ctx* ctx)
     if (const char* v = getenv("MOE_EP_DOWN_VARIANT")) ctx->down_variant = atoi(v);
     if (const char* v = getenv("MOE_EP_UP_UNITS")) ctx->up_units = atoi(v);
     if (const char* v = getenv("MOE_EP_DOWN_UNITS")) ctx->down_units = atoi(v);
+    if (const char* v = getenv("MOE_EP_MERGE")) ctx->merge = atoi(v) != 0;
     if (const char* v = getenv("MOE_EP_NARROW_ROWS")) ctx->narrow_rows = atof(v);
     // workgroups of a copy kernel: ~128 KB in flight fills the host link; more only queues up in the
     // memory fabric in front of the compute kernels
@@ -208,9 +211,8 @@ void read_knobs(moe_ep_ctx* ctx)
     }
     ctx->fused_gather = fused_gather_enabled();
     ctx->y_mode = expert_out_mode();
-    // a tile shape, instruction or form of the expert outputs asked for by name belongs to the tiled kernels
-    if (ctx->gemm_variant >= 0 || ctx->up_variant >= 0 || ctx->down_variant >= 0 || ctx->shared_variant_named || !ctx->mfma16 ||
-        ctx->up_units || ctx->down_units || ctx->y_mode != 0) ctx->narrow_rows = 0.0;
+    ctx->by_rule = ctx->gemm_variant < 0 && ctx->up_variant < 0 && ctx->down_variant < 0 && !ctx->shared_variant_named &&
+                   ctx->mfma16 && !ctx->up_units && !ctx->down_units && ctx->y_mode == 0;
     if (const char* v = getenv("MOE_EP_FUSED_OUT")) ctx->fused_out = atoi(v) != 0;
     // MOE_EP_CHECK_POINTERS=0 skips the per-forward pointer queries (a few microseconds of host time)
     if (const char* v = getenv("MOE_EP_CHECK_POINTERS")) ctx->check_spans = atoi(v) != 0;
@@ -290,23 +292,28 @@ constexpr RoutedShape kRoutedShapes[] = {
     {13, 32, 7, 1.744, 1.709, false},   // 224 x 256, 1 x 4, two slots
     {14, 32, 8, 1.794, 1.764, false},   // 256 x 256, 1 x 4, two slots
 };
-const RoutedShape* routed_shape(int Tn, int k, int E, int El, int col_tiles, int K, int n_cu)
+// Expected row tiles of one expert.  E[tiles] = sum over j >= 0 of P(rows > j * tile_rows): a group of n rows gets
+// ceil(ceil(n / unit_rows) / max_units) tiles, i.e. one more tile each time n passes a
+// multiple of unit_rows * max_units; 1 for every multiple more than 6 sd below the mean,
+// 0 beyond 6 sd above it, the normal tail in between
+double expected_row_tiles(int Tn, int k, int E, const RoutedShape& sh)
 {
     const double mean = (double)Tn * k / E, sd = sqrt(mean > 1.0 ? mean : 1.0);
+    const double bm = (double)sh.unit_rows * sh.max_units;
+    const double lo = (mean - 6.0 * sd) / bm;
+    const long long j0 = lo > 0.0 ? (long long)lo : 0;
+    double tiles = (double)j0;
+    for (long long j = j0; j * bm < mean + 6.0 * sd; ++j) tiles += 0.5 * erfc((j * bm - mean) / (sd * 1.4142135623730951));
+    return tiles;
+}
+double tile_rel(const RoutedShape& sh, int K) { return K >= 2048 ? sh.rel_long_k : sh.rel_short_k; }
+const RoutedShape* routed_shape(int Tn, int k, int E, int El, int col_tiles, int K, int n_cu)
+{
     const RoutedShape* best = &kRoutedShapes[0];
     double best_cost = 0.0;
     for (const RoutedShape& sh : kRoutedShapes) {
         if (!sh.automatic) continue;
-        // E[tiles] = sum over j >= 0 of P(rows > j * tile_rows): a group of n rows gets
-        // ceil(ceil(n / unit_rows) / max_units) tiles, i.e. one more tile each time n passes a
-        // multiple of unit_rows * max_units; 1 for every multiple more than 6 sd below the mean,
-        // 0 beyond 6 sd above it, the normal tail in between
-        const double bm = (double)sh.unit_rows * sh.max_units;
-        const double lo = (mean - 6.0 * sd) / bm;
-        const long long j0 = lo > 0.0 ? (long long)lo : 0;
-        double tiles = (double)j0;
-        for (long long j = j0; j * bm < mean + 6.0 * sd; ++j) tiles += 0.5 * erfc((j * bm - mean) / (sd * 1.4142135623730951));
-        const double cost = ceil(tiles * El * col_tiles / n_cu - 0.02) * (K >= 2048 ? sh.rel_long_k : sh.rel_short_k);
+        const double cost = ceil(expected_row_tiles(Tn, k, E, sh) * El * col_tiles / n_cu - 0.02) * tile_rel(sh, K);
         if (&sh == &kRoutedShapes[0] || cost < best_cost) { best = &sh; best_cost = cost; }
     }
     return best;
@@ -314,6 +321,33 @@ const RoutedShape* routed_shape(int Tn, int k, int E, int El, int col_tiles, int
 int routed_variant(int Tn, int k, int E, int El, int col_tiles, int K, int n_cu)
 {
     return routed_shape(Tn, k, E, El, col_tiles, K, n_cu)->variant;
+}
+
+// What a launch of the tiled kernels is expected to take, in us: its rounds of tiles, or its weights from HBM.  A
+// 128 x 256 tile takes 15.4 ns per unit of K (DeepSeek-V2-Lite- and DeepSeek-V2-shaped launches of several rounds: 31.6 us with
+// K = 2048, 79 with 5120); launches bound by their weights read 5 TB/s; a launch more costs 4 us.
+constexpr int kCostKnownK = 512;   // shorter reductions are mostly epilogue and launch
+double launch_us(double tiles, double rel, int K, double weight_bytes, int n_cu)
+{
+    const double mfma = ceil(tiles / n_cu - 0.02) * rel * K * 15.4e-3, hbm = weight_bytes / 5.0e6;
+    return 4.0 + (mfma > hbm ? mfma : hbm);
+}
+
+// Tile variant (32 x 32 x 16 form) of a dense launch over `groups` groups of `rows` rows: 256-row tiles cost 10 % less per
+// row than 128-row ones, but leave compute units idle where their number is small
+int dense_variant(int rows, int groups, int col_tiles, int K, int n_cu, double* us)
+{
+    const struct { int variant, rows; double rel; } shapes[] = {
+        {2, 256, K >= 2048 ? 1.79 : 1.76},
+        {11, 160, tile_rel(kRoutedShapes[1], K)},
+        {1, 128, tile_rel(kRoutedShapes[0], K)},
+    };
+    int best = 2;
+    for (const auto& sh : shapes) {
+        const double t = launch_us((double)((rows + sh.rows - 1) / sh.rows) * groups * col_tiles, sh.rel, K, 0.0, n_cu);
+        if (sh.variant == 2 || t < *us) { best = sh.variant; *us = t; }
+    }
+    return best;
 }
 
 hipEvent_t prof_event(moe_ep_ctx* ctx)
@@ -698,15 +732,24 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         g2.offset = nullptr; g2.dense_rows = Tn;
         g2.lda = Ns * Hs; g2.ldc = M; g2.c_group_col_stride = 0;
     };
+    // a shape the library picks itself is taken in its 16 x 16 x 32 form, one named through a knob as named
+    const auto picked = [&](int v) { return ctx->mfma16 ? grouped_gemm_variant_mfma16(v) : v; };
     auto run_shared = [&](int t0, int Tn, hipStream_t st) -> int {
         if (Tn <= 0) return MOE_EP_OK;
+        int v_up = ctx->shared_variant, v_down = v_up;
+        if (!ctx->shared_variant_named) {
+            double us;
+            v_up = picked(dense_variant(Tn, Ns, (Hs + 127) / 128, M, n_cu, &us));
+            v_down = picked(dense_variant(Tn, 1, (M + 255) / 256, Ns * Hs, n_cu, &us));
+        }
+        ctx->last_shared_up = v_up; ctx->last_shared_down = v_down;
         GemmArgs g1{}, g2{};
         shared_args(t0, Tn, g1, g2);
         int sp = prof_begin(ctx, prof, ST_SGEMM1, st);
-        HIP_TRY(ctx, launch_grouped_gemm(g1, true, ctx->shared_variant, n_cu, 0, st));
+        HIP_TRY(ctx, launch_grouped_gemm(g1, true, v_up, n_cu, 0, st));
         prof_end(ctx, sp, st);
         sp = prof_begin(ctx, prof, ST_SGEMM2, st);
-        HIP_TRY(ctx, launch_grouped_gemm(g2, false, ctx->shared_variant, n_cu, 0, st));
+        HIP_TRY(ctx, launch_grouped_gemm(g2, false, v_down, n_cu, 0, st));
         prof_end(ctx, sp, st);
         return MOE_EP_OK;
     };
@@ -782,19 +825,60 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
             if (rc != MOE_EP_OK) return rc;
         }
     }
-    // Few rows per routed expert: the narrow kernels, bound by the weight stream alone.  They take the shared
-    // experts along in the same launches -- every token's with the first chunk where these come first --
-    // unless their stages are being timed, which takes launches of their own.
-    const auto use_narrow = [&](int Tn) {
-        return ctx->narrow_rows > 0.0 && Tn > 0 && ctx->fused_gather && (unsigned long long)Tn * M * 2 < (1ull << 32) &&
-               (double)Tn * k / E <= ctx->narrow_rows;
+    // How a chunk of Tn tokens runs, and whether `rows` rows of the shared experts run in the same launches (rows = 0:
+    // there are none, or they may not).
+    struct Plan { bool narrow, along; int up, down; };
+    const int ct_up = (H + 127) / 128, ct_down = (M + 255) / 256, ct_s = (Hs + 127) / 128;
+    const auto plan_chunk = [&](int Tn, int rows) -> Plan {
+        Plan p{false, false, -1, -1};
+        if (Tn <= 0) return p;
+        const bool fits = ctx->by_rule && ctx->fused_gather && (unsigned long long)Tn * M * 2 < (1ull << 32);
+        // few rows per routed expert: the narrow kernels, bound by the weight stream alone
+        if (fits && (double)Tn * k / E <= ctx->narrow_rows) return Plan{true, rows > 0 && rows <= kNarrowSharedRows, kNarrowVariant, kNarrowVariant};
+        // tile shapes of the two routed projections: N = H in tiles of 128 activation columns, N = M in
+        // tiles of 256 columns
+        p.up = ctx->gemm_variant >= 0 ? ctx->gemm_variant : picked(routed_variant(Tn, k, E, El, ct_up, M, n_cu));
+        p.down = ctx->gemm_variant >= 0 ? ctx->gemm_variant : picked(routed_variant(Tn, k, E, El, ct_down, H, n_cu));
+        if (ctx->up_variant >= 0) p.up = ctx->up_variant;
+        if (ctx->down_variant >= 0) p.down = ctx->down_variant;
+        // shared and routed experts in one launch per projection, or in one each: by what both should take, where
+        // launch_us has been held against measurements
+        const bool known = M >= kCostKnownK && H >= kCostKnownK && Hs >= kCostKnownK;
+        if (rows <= 0 || !fits || !(ctx->merge == 1 || (ctx->merge != 0 && known))) return p;
+        const double touched = El * (1.0 - pow(1.0 - (double)k / E, Tn)), w_up = 4.0 * M * H * touched, w_down = w_up / 2;
+        const int Ks = Ns * Hs, worth = (Ks + H / 2) / H > 1 ? (Ks + H / 2) / H : 1;
+        double apart = 0.0, up_one = 1e300, down_one = 1e300, us;
+        dense_variant(rows, Ns, ct_s, M, n_cu, &us); apart += us;
+        dense_variant(rows, 1, ct_down, Ks, n_cu, &us); apart += us;
+        double up_apart = 1e300, down_apart = 1e300;
+        int v_up = -1, v_down = -1;
+        for (const RoutedShape& sh : kRoutedShapes) {
+            if (!sh.automatic) continue;
+            const double routed = expected_row_tiles(Tn, k, E, sh) * El;
+            const int bm = sh.unit_rows * sh.max_units, dense = (rows + bm - 1) / bm;
+            us = launch_us(routed * ct_up, tile_rel(sh, M), M, w_up, n_cu);
+            if (us < up_apart) up_apart = us;
+            us = launch_us(routed * ct_down, tile_rel(sh, H), H, w_down, n_cu);
+            if (us < down_apart) down_apart = us;
+            const int v = picked(sh.variant);
+            int shape[8];
+            const auto is_built = [&](int K) { return grouped_gemm_variant_shape(v, K, true, El, shape) && shape[7] == 16 && shape[0] == bm; };
+            if (!is_built(M < H ? (M < Ks ? M : Ks) : (H < Ks ? H : Ks))) continue;
+            us = launch_us(routed * ct_up + (double)dense * Ns * ct_s, tile_rel(sh, M), M, w_up + 4.0 * M * Hs * Ns, n_cu);
+            if (us < up_one) { up_one = us; v_up = v; }
+            us = launch_us(routed * ct_down + (double)dense * ct_down * worth, tile_rel(sh, H), H, w_down + 2.0 * M * Hs * Ns, n_cu);
+            if (us < down_one) { down_one = us; v_down = v; }
+        }
+        if (v_up >= 0 && v_down >= 0 && (ctx->merge == 1 || up_one + down_one < apart + up_apart + down_apart)) return Plan{false, true, v_up, v_down};
+        return p;
     };
+    // The shared experts may run beside routed ones -- every token's with the first chunk where they come first -- unless
+    // their stages are being timed, which takes launches of their own, or only one side's weights are in tile order.
     const bool shared_first = !dep && Ns > 0 && order == MOE_EP_ORDER_SHARED_FIRST;
     const bool shared_beside = !dep && Ns > 0 && (prep_r != nullptr) == (prep_s != nullptr) && !(prof && (ctx->prof_mask & ((1u << ST_SGEMM1) | (1u << ST_SGEMM2))));
     int c0_t0, c0_Tn;
     chunk_range(T, r_1, r_2, 0, &c0_t0, &c0_Tn);
-    const bool first_takes_all = shared_first && shared_beside && use_narrow(c0_Tn) && T <= kNarrowSharedRows;
-    ctx->last_shared_narrow = false;
+    const bool first_takes_all = shared_first && shared_beside && plan_chunk(c0_Tn, T).along;
     if (shared_first && !first_takes_all) {
         if (pinned) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[r - 1], 0));
         int rc = run_shared(0, T, s_comp);
@@ -809,16 +893,11 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         // gate and partition need the chunk's gate scores only, which travel first
         if (pinned) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_scores[cidx], 0));
         else if (dep && cidx % r_2 == 0) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_attn[cidx / r_2], 0));
-        // tile shapes of the two routed projections: N = H in tiles of 128 activation columns, N = M in
-        // tiles of 256 columns
-        // a shape the library picks itself is taken in its 16 x 16 x 32 form, one named through a knob as named
-        const auto picked = [&](int v) { return ctx->mfma16 ? grouped_gemm_variant_mfma16(v) : v; };
-        int v_up = ctx->gemm_variant >= 0 ? ctx->gemm_variant : picked(routed_variant(Tn, k, E, El, (H + 127) / 128, M, n_cu));
-        int v_down = ctx->gemm_variant >= 0 ? ctx->gemm_variant : picked(routed_variant(Tn, k, E, El, (M + 255) / 256, H, n_cu));
-        if (ctx->up_variant >= 0) v_up = ctx->up_variant;
-        if (ctx->down_variant >= 0) v_down = ctx->down_variant;
-        const bool narrow = use_narrow(Tn);
-        if (narrow) v_up = v_down = kNarrowVariant;
+        const bool takes_all = first_takes_all && cidx == 0;
+        const bool interleaved = !dep && Ns > 0 && order == MOE_EP_ORDER_INTERLEAVED;
+        const Plan plan = plan_chunk(Tn, takes_all ? T : interleaved && shared_beside ? Tn : 0);
+        const bool narrow = plan.narrow, along = plan.along;
+        const int v_up = plan.up, v_down = plan.down;
         if (cidx < (int)ctx->last_variants.size()) ctx->last_variants[cidx] = {v_up, v_down};
         int32_t* idx = ctx->idx + (size_t)t0 * k;
         float* w = ctx->w + (size_t)t0 * k;
@@ -840,7 +919,6 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
             HIP_TRY(ctx, launch_gather_rows(tok_dev + (size_t)t0 * M, perm, offset + El, k, M, ctx->xp, bw_grid, s_comp));
         }
         prof_end(ctx, sp, s_comp);
-        const bool takes_all = first_takes_all && cidx == 0;
         // the token rows (with every shared expert's row: of all chunks)
         if (pinned) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[takes_all ? r - 1 : cidx], 0));
         if (Tn == 0) {
@@ -859,15 +937,14 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         if (fused) {  // the projection reads the token rows through the row -> assignment map
             g1.A = tok_dev + (size_t)t0 * M; g1.a_row_map = perm; g1.a_row_div = k; g1.a_src_rows = Tn;
         }
-        const bool interleaved = !dep && Ns > 0 && order == MOE_EP_ORDER_INTERLEAVED;
-        const bool along = takes_all || (narrow && interleaved && shared_beside && Tn <= kNarrowSharedRows);
         GemmArgs s1{}, s2{};
         if (along) {
             shared_args(takes_all ? 0 : t0, takes_all ? T : Tn, s1, s2);
-            ctx->last_shared_narrow = true;
+            ctx->last_shared_up = v_up; ctx->last_shared_down = v_down;
         }
         sp = prof_begin(ctx, prof, ST_GEMM1, s_comp);
         if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g1, along ? &s1 : nullptr, true, (double)Tn * k / E, a_max, s_comp));
+        else if (along) HIP_TRY(ctx, launch_merged_gemm(g1, s1, true, v_up, n_cu, s_comp));
         else HIP_TRY(ctx, launch_grouped_gemm(g1, true, v_up, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);
 
@@ -880,6 +957,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         g2.epi = ctx->y_mode; g2.row_weight = w; g2.row_assignment = perm;
         sp = prof_begin(ctx, prof, ST_GEMM2, s_comp);
         if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g2, along ? &s2 : nullptr, false, (double)Tn * k / E, a_max, s_comp));
+        else if (along) HIP_TRY(ctx, launch_merged_gemm(g2, s2, false, v_down, n_cu, s_comp));
         else HIP_TRY(ctx, launch_grouped_gemm(g2, false, v_down, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);
 
@@ -957,10 +1035,10 @@ int moe_ep_last_tile_shape(const moe_ep_ctx* ctx, int32_t chunk, int32_t stage, 
     if (shared && ctx->cfg.n_shared == 0) return MOE_EP_ESTATE;
     if (!shared && (chunk < 0 || chunk >= ctx->last_r || chunk >= (int)ctx->last_variants.size())) return MOE_EP_EINVAL;
     const moe_ep_config& c = ctx->cfg;
-    const int variant = shared ? ctx->shared_variant : (up ? ctx->last_variants[chunk].up : ctx->last_variants[chunk].down);
+    const int variant = shared ? (up ? ctx->last_shared_up : ctx->last_shared_down) : (up ? ctx->last_variants[chunk].up : ctx->last_variants[chunk].down);
     const int K = shared ? (up ? c.hidden : c.n_shared * c.shared_inter) : (up ? c.hidden : c.inter);
     int v[8] = {kNarrowRows, 128, kPackK, kNarrowDepth, 1, 4, 1, 16};   // the narrow kernels
-    if (!(shared ? ctx->last_shared_narrow : variant == kNarrowVariant) && !grouped_gemm_variant_shape(variant, K, !shared, shared ? 1 : c.n_local, v)) return MOE_EP_ESTATE;
+    if (variant != kNarrowVariant && !grouped_gemm_variant_shape(variant, K, !shared, shared ? 1 : c.n_local, v)) return MOE_EP_ESTATE;
     if (mfma_rows) *mfma_rows = v[7];
     if (tile_order) *tile_order = v[6] && (shared ? ctx->last_prepared_shared : ctx->last_prepared_routed);
     if (rows) *rows = v[0];
