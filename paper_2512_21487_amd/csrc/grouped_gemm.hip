@@ -189,11 +189,12 @@ static int lds_cap(int bytes) { return bytes < kLdsPerWorkgroup ? bytes : kLdsPe
 // 0 bf16 results; 1 fp32 results (the experts' outputs are then not rounded before the aggregation);
 // 2 bf16 results already multiplied by the routing weight of the row's assignment (Sec. 2.1: the
 // aggregation then only adds)
+// ONCE: the weights are read non-temporally.
 // MERGED: the tiles of the dense groups `d` (the shared experts) beside those of the ragged ones, in one list
 // (decode_tile below); a tile's group is then a.G + the dense group, and what differs between the two -- operands,
 // leading dimensions, K -- is picked per tile.
 template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool SWIGLU, bool RAGGED, int EPI = 0, bool PACKED = false, int MI = 32,
-          bool MERGED = false>
+          bool MERGED = false, bool ONCE = false>
 __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d, uint4* lds, const int* s_pref, const int* s_row0,
                                            const int* s_rowend, int* s_tile, int max_units)
 {
@@ -472,10 +473,12 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
         const size_t wk_ = packed ? (size_t)(ks_) * (BN * BK)                                     \
                                   : (size_t)seg_ * kseg_stride + (k_ - seg_ * kseg_len);          \
         uint4* dst_ = lds + (stage_) * Cfg::STAGE_CHUNKS + wave * 64 + NW * 64 * (i_);            \
-        __builtin_amdgcn_global_load_lds(                                                         \
-            reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(                         \
-                (i_) < XRPW ? Xi + k_ : Wi + wk_) + goff[i_]),                                    \
-            dst_, 16, 0, 0);                                                                      \
+        if ((i_) < XRPW)                                                                          \
+            __builtin_amdgcn_global_load_lds(                                                     \
+                reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(Xi + k_) + goff[i_]), dst_, 16, 0, 0);     \
+        else                                                                                      \
+            __builtin_amdgcn_global_load_lds(                                                     \
+                reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(Wi + wk_) + goff[i_]), dst_, 16, 0, ONCE ? 2 : 0); \
     }
 #define SB() __builtin_amdgcn_sched_barrier(0)
     // The hand-over of a ring slot to the MFMAs: this wavefront's loads into it have landed (all
@@ -821,6 +824,19 @@ __global__ __launch_bounds__(WGM* WGN * 64) void grouped_gemm_kernel(GemmArgs a)
     const LdsTables t = lds_tables(lds, Cfg::LDS_BYTES, a.G);
     const int max_units = (a.max_units > 0 && a.max_units < Cfg::MB) ? a.max_units : Cfg::MB;
     if (RAGGED) fill_tables(a, t, 32 * WGM, max_units);
+    // Where nearly every group is one row tile, nothing reads a group's weights a second time, and they are loaded
+    // without a place in the caches; with more tiles per group sharing them through L2 that is slower.  The routing
+    // decides, which only the device knows.  Qwen3-235B-A22B-shaped share, 800 / 1024 / 1500 tokens 146 -> 132, 147 -> 134, 154 -> 137 us,
+    // Qwen3-30B-A3B-shaped layer, 1500 tokens 275 -> 260 (skewed, 1200 tokens: 264 -> 280, so it is not done there).
+    if constexpr (RAGGED && EPI == 0 && MI == 16 && BM <= 160) {
+        int groups = 0;
+        for (int g = 0; g < a.G; g += 64) {
+            const int i = g + (threadIdx.x & 63);
+            groups += __builtin_popcountll(__ballot(i < a.G && t.rowend[i] > t.row0[i]));
+        }
+        if (__builtin_amdgcn_readfirstlane(t.pref[a.G]) * 8 <= groups * 9)
+            return gemm_tiles<BM, BN, BK, STAGES, WGM, WGN, SWIGLU, RAGGED, EPI, PACKED, MI, false, true>(a, a, lds, t.pref, t.row0, t.rowend, t.tile, max_units);
+    }
     gemm_tiles<BM, BN, BK, STAGES, WGM, WGN, SWIGLU, RAGGED, EPI, PACKED, MI>(a, a, lds, t.pref, t.row0, t.rowend, t.tile, max_units);
 }
 

@@ -24,11 +24,12 @@ namespace {
 
 enum Stage { ST_ROUTER = 0, ST_PARTITION, ST_GEMM1, ST_GEMM2, ST_SGEMM1, ST_SGEMM2, ST_COMBINE, ST_TOTAL, ST_COPY_IN, ST_COPY_OUT, ST_ATTN, ST_COUNT };
 
-// Where the narrow kernels (narrow_gemm.hip) take over.  Forwards in us, tiled -> narrow, prepared weights:
-// Qwen3-235B-A22B-shaped share, 16 / 32 / 44 / 50 / 64 rows per expert: 143 -> 130, 146 -> 134, 152 -> 139, 151 -> 149,
-// 157 -> 183; Qwen3-30B-A3B-shaped layer, 31 / 44 / 50 rows: 270 -> 249, 274 -> 257, 277 -> 273.  Beyond 48 rows on average more
-// and more experts need a second row tile, whose weights come from L2 again.
-constexpr double kNarrowMeanRows = 48.0;
+// Where the narrow kernels (narrow_gemm.hip) take over, in rows per routed expert.  Forwards in us, tiled / narrow, five
+// layers in turn: DeepSeek-V2-Lite-shaped layer, 3 rows 325 / 199, 24 rows 352 / 229 (before the tiled launches took shared experts
+// along); DeepSeek-V2-shaped share, 11 / 19 rows 241 / 228, 262 / 252; Qwen3-235B-A22B-shaped share, 16 rows 122 / 119.  From 24
+// to 48 rows the two are within 3 % under balanced load, but the narrow row tile of 64 loses up to 10 % where the load is
+// skewed (Qwen3-30B-A3B-shaped layer, Zipf 1.1, 600 tokens: 206 / 228).
+constexpr double kNarrowMeanRows = 24.0;
 // The shared experts go along up to this many rows: alone, 256-row tiles of a few hundred rows leave most compute
 // units idle (DeepSeek-V2-Lite-shaped layer, 256 / 500 tokens: 298 -> 229, 321 -> 267 us; DeepSeek-V2-shaped share, 500 / 800 / 1200:
 // 332 -> 266, 335 -> 323, 345 -> 376).

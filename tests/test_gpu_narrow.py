@@ -65,7 +65,7 @@ def test_small_calls_of_a_share(monkeypatch, n_tokens, pinned):
     inp = make_inputs(wl, seed=62)
     calls = ((1, 0), (2, 0))
     want, _ = _run(monkeypatch, wl, inp, 0, (), calls, pinned)
-    got, narrow = _run(monkeypatch, wl, inp, 48, (), calls, pinned)
+    got, narrow = _run(monkeypatch, wl, inp, 24, (), calls, pinned)
     assert narrow
     for w, o in zip(want, got):
         assert np.array_equal(o, w)
@@ -77,10 +77,10 @@ def test_most_experts_and_nothing_kept(monkeypatch):
     wl = tiny_workload(name="narrow_E512", n_tokens=40, hidden=64, inter=64, n_experts=512, n_local=512, top_k=64)
     inp = make_inputs(wl, seed=63)
     want, _ = _run(monkeypatch, wl, inp, 0)
-    got, narrow = _run(monkeypatch, wl, inp, 48)
+    got, narrow = _run(monkeypatch, wl, inp, 24)
     assert narrow and np.array_equal(got[0], want[0]) and want[0].any()
     wl = tiny_workload(name="narrow_none", n_tokens=40, hidden=64, inter=64, n_experts=8, local_begin=6, n_local=2, top_k=2)
     inp = make_inputs(wl, seed=64)
     inp["gate_logits"][:, 6:] = -40.0
-    got, narrow = _run(monkeypatch, wl, inp, 48)
+    got, narrow = _run(monkeypatch, wl, inp, 24)
     assert narrow and not got[0].any()
