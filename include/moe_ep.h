@@ -147,11 +147,10 @@ int moe_ep_forward(moe_ep_ctx *ctx, const void *tokens, const float *gate_logits
  * of an expert are the same in every call, only the tokens change).  moe_ep_prepare_weights makes, in
  * device memory the context owns, a copy of the weights at routed_w and / or shared_w (either may be
  * NULL; layouts as for moe_ep_forward) in the order the projections' weight tiles read them: for every
- * expert, block of 256 output rows (gate/up: 128 rows of W_gate and the same 128 of W_up) and 64
- * reduction steps, one contiguous 32 KB block.  From then on every forward of this context that is
- * handed the same pointer reads the copy instead (the same kernels with another address pattern: the
- * same bits; 2-5 % less time on the prefill shapes, 19 % on the gate/up weight stream of the decode
- * shapes).  A pointer that has not been prepared is read where it is, as before.
+ * expert, block of 256 output rows (gate/up: 128 rows of W_gate and the same 128 of W_up, 16 rows of each
+ * in turn) and 64 reduction steps, one contiguous 32 KB block in the order in which a wavefront's lanes hold
+ * it.  From then on every forward of this context that is handed the same pointer reads the copy instead
+ * (the same kernels with another address pattern: the same bits; 2-6 % less time).  A pointer that has not been prepared is read where it is, as before.
  *
  *   stream   the copy kernels are enqueued here and the call returns; a forward that uses the copy must
  *            be ordered after them (same stream, or an event).
@@ -364,7 +363,8 @@ int32_t moe_ep_routed_tile_rows(const moe_ep_config *cfg, int32_t n_tokens, int3
  * wavefronts along rows and along columns --, whether it read the weights from a tile-order copy
  * (moe_ep_prepare_weights; 1 or 0), and the rows of the block its matrix instruction multiplies (16:
  * v_mfma_f32_16x16x32_bf16, 32: v_mfma_f32_32x32x16_bf16), so that a measurement can name the kernel it
- * timed.  Any pointer may be NULL.  MOE_EP_ESTATE before any forward or for a stage the layer does not have.
+ * timed.  Chunks with few rows per expert run kernels that hold their weights in registers: 64 rows, 128
+ * columns, 1 x 4 wavefronts, and the K steps in flight in place of ring slots.  Any pointer may be NULL.  MOE_EP_ESTATE before any forward or for a stage the layer does not have.
  */
 int moe_ep_last_tile_shape(const moe_ep_ctx *ctx, int32_t chunk, int32_t stage, int32_t *rows,
                            int32_t *cols, int32_t *k_step, int32_t *ring_slots, int32_t *waves_m,
