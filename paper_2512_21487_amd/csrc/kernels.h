@@ -95,9 +95,9 @@ hipError_t launch_merged_gemm(const GemmArgs& routed, const GemmArgs& shared, bo
 // The same projections where few token rows meet every expert (narrow_gemm.hip): the routed groups
 // `routed` (ragged) and, when `shared` is not NULL, the shared experts (dense) in one launch, bit for bit
 // what launch_grouped_gemm writes.  expected_rows: rows per routed group the grid is sized for (any
-// routing is served); no other epilogue than epi == 0.
-hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bool swiglu, double expected_rows,
-                              long long max_rows, hipStream_t s);
+// routing is served); max_tokens: the most rows one routed group can have; no other epilogue than epi == 0.
+hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bool swiglu, int n_cu, double expected_rows,
+                              int max_tokens, long long max_rows, hipStream_t s);
 constexpr int kNarrowRows = 64;   // tallest row tile
 constexpr int kNarrowDepth = 4;   // K steps of 64 in flight per wavefront
 hipError_t grouped_gemm_init();   // raises the dynamic-LDS limit of every instantiation once

@@ -944,7 +944,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
             ctx->last_shared_up = v_up; ctx->last_shared_down = v_down;
         }
         sp = prof_begin(ctx, prof, ST_GEMM1, s_comp);
-        if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g1, along ? &s1 : nullptr, true, (double)Tn * k / E, a_max, s_comp));
+        if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g1, along ? &s1 : nullptr, true, n_cu, (double)Tn * k / E, Tn, a_max, s_comp));
         else if (along) HIP_TRY(ctx, launch_merged_gemm(g1, s1, true, v_up, n_cu, s_comp));
         else HIP_TRY(ctx, launch_grouped_gemm(g1, true, v_up, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);
@@ -957,7 +957,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         g2.max_units = ctx->down_units;
         g2.epi = ctx->y_mode; g2.row_weight = w; g2.row_assignment = perm;
         sp = prof_begin(ctx, prof, ST_GEMM2, s_comp);
-        if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g2, along ? &s2 : nullptr, false, (double)Tn * k / E, a_max, s_comp));
+        if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g2, along ? &s2 : nullptr, false, n_cu, (double)Tn * k / E, Tn, a_max, s_comp));
         else if (along) HIP_TRY(ctx, launch_merged_gemm(g2, s2, false, v_down, n_cu, s_comp));
         else HIP_TRY(ctx, launch_grouped_gemm(g2, false, v_down, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);

@@ -15,6 +15,8 @@
 //
 // Every output element is accumulated over K in the order of grouped_gemm.hip by the same instruction, and the
 // epilogue rounds at the same place: the results are the same bits.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -22,17 +24,28 @@ namespace moe_ep {
 
 namespace {
 
-constexpr int kNarrowThreads = 256;
 constexpr int kNarrowMaxGroups = 512;
 
-constexpr int kChunkRowBytes = kNarrowDepth * kPackK * 2;         // one token row of a staged chunk: 512 bytes
-constexpr int kChunksPerRow = kChunkRowBytes / 16;
-constexpr int kRowsPerPass = kNarrowThreads / kChunksPerRow;      // token rows one load per thread stages: 8
-constexpr int kBufferBytes = kNarrowRows * kChunkRowBytes;
+// D K steps of weights in flight, row tiles of at most ROWS rows, WAVES wavefronts per workgroup
+template <int D_, int ROWS_, int WAVES_>
+struct NarrowCfg {
+    static constexpr int D = D_, ROWS = ROWS_, WAVES = WAVES_, THREADS = WAVES * 64;
+    static constexpr int ROW_BYTES = D * kPackK * 2;             // one token row of a staged chunk (D K steps)
+    static constexpr int ROW_CHUNKS = ROW_BYTES / 16;
+    static constexpr int PASS_ROWS = THREADS / ROW_CHUNKS; // token rows one load per thread stages
+    static constexpr int BUFFER_BYTES = ROWS * ROW_BYTES;
+    static_assert(THREADS % ROW_CHUNKS == 0 && 16 % PASS_ROWS == 0, "a block of 16 rows is whole passes");
+};
+using NarrowStream = NarrowCfg<kNarrowDepth, kNarrowRows, 4>;
+// A compute unit draws about 46 GB/s, whatever is in flight (twice the K steps: no change).  Where a launch of 128-column
+// tiles leaves compute units without one, half as wide tiles halve what the busiest one has to draw: down projection
+// of one token of the DeepSeek-V2-Lite-shaped layer, 112 workgroups, the shared experts' 720 KB each, forward 47 -> 43 us.
+using NarrowFew = NarrowCfg<kNarrowDepth, 16, 2>;
 constexpr int kTurnBytes = 16 * kPackK * 2;                       // one block of 16 weight rows of a K step
 
 // one wavefront's share of a tile: uniform bases, the lane's byte offsets, and how the weight base moves
 // from K step to K step (seg_steps steps of w_step bytes, then a jump to the next K segment)
+template <class Cfg>
 struct NarrowTile {
     const char* w;         // first weight row block at K step 0
     long long w_delta;     // bytes to the second block
@@ -41,7 +54,7 @@ struct NarrowTile {
     long long w_step, seg_jump;
     int seg_steps;
     const char* x;         // token rows
-    uint32_t x_off[kNarrowRows / kRowsPerPass];   // the rows this thread stages
+    uint32_t x_off[Cfg::ROWS / Cfg::PASS_ROWS];   // the rows this thread stages
     int KT;
 };
 
@@ -63,11 +76,11 @@ __device__ __forceinline__ void lds_barrier()
     asm volatile("" ::: "memory");
 }
 
-template <bool SWIGLU, bool PACKED, int MB>
-__device__ __forceinline__ void narrow_tile(const NarrowTile& t, int nrows, int tid, char* lds, bool stores, uint16_t* c, int ldc)
+template <class Cfg, bool SWIGLU, bool PACKED, int MB>
+__device__ __forceinline__ void narrow_tile(const NarrowTile<Cfg>& t, int nrows, int tid, char* lds, bool stores, uint16_t* c, int ldc)
 {
-    constexpr int D = kNarrowDepth;
-    constexpr int PASSES = MB * 16 / kRowsPerPass;
+    constexpr int D = Cfg::D;
+    constexpr int PASSES = MB * 16 / Cfg::PASS_ROWS;
     const int lane = tid & 63;
     uint4 w[D][2][2], st[PASSES];   // [ring slot][row block][half of the K step]; the next chunk's token rows
     f32x4_t acc[2][MB];
@@ -91,25 +104,25 @@ __device__ __forceinline__ void narrow_tile(const NarrowTile& t, int nrows, int 
     // token rows: thread -> row tid / 32 + 8 i, 16-byte chunk tid % 32 of the staged 512 bytes.  In LDS chunk c of row r
     // lies at c ^ (r mod 16), so that both the writes (one row) and the fragment reads (16 rows, one
     // chunk column) touch all banks evenly.  Chunks past the end of a row re-read its last one, unused.
-    const int st_row = tid / kChunksPerRow, st_chunk = tid % kChunksPerRow;
+    const int st_row = tid / Cfg::ROW_CHUNKS, st_chunk = tid % Cfg::ROW_CHUNKS;
     auto load_x = [&](int ch) __attribute__((always_inline)) {
-        const uint32_t k_off = min((uint32_t)(ch * kChunkRowBytes + st_chunk * 16), (uint32_t)t.KT * (kPackK * 2) - 16u);
+        const uint32_t k_off = min((uint32_t)(ch * Cfg::ROW_BYTES + st_chunk * 16), (uint32_t)t.KT * (kPackK * 2) - 16u);
 #pragma unroll
         for (int i = 0; i < PASSES; ++i) st[i] = load16(t.x, t.x_off[i] + k_off, 0);
     };
     auto stage_x = [&](int ch) __attribute__((always_inline)) {
-        char* buf = lds + (ch & 1) * kBufferBytes;
+        char* buf = lds + (ch & 1) * Cfg::BUFFER_BYTES;
 #pragma unroll
         for (int i = 0; i < PASSES; ++i) {
-            const int r = st_row + kRowsPerPass * i;
-            *reinterpret_cast<uint4*>(buf + r * kChunkRowBytes + (st_chunk ^ (r & 15)) * 16) = st[i];
+            const int r = st_row + Cfg::PASS_ROWS * i;
+            *reinterpret_cast<uint4*>(buf + r * Cfg::ROW_BYTES + (st_chunk ^ (r & 15)) * 16) = st[i];
         }
     };
     // Weights in tile order arrive as operands: load h of a block is the k half h of its 16 rows.  From the
     // caller's rows a load takes 8 rows of 128 bytes (read as operands, 16 rows of 64, the address path takes
     // four times as long and every line is asked for twice) and the wavefront turns a block into operands
     // through 2 KB of LDS of its own; chunk c of row r lies at c ^ (r / 2 mod 8), all banks in use both ways.
-    char* turn = lds + 2 * kBufferBytes + (tid >> 6) * kTurnBytes;
+    char* turn = lds + 2 * Cfg::BUFFER_BYTES + (tid >> 6) * kTurnBytes;
     auto operand = [&](int slot, int b, bf16x8_t (&f)[2]) __attribute__((always_inline)) {
         if (PACKED) {
 #pragma unroll
@@ -128,7 +141,7 @@ __device__ __forceinline__ void narrow_tile(const NarrowTile& t, int nrows, int 
         }
     };
     auto multiply = [&](int ch, int slot) __attribute__((always_inline)) {
-        const char* buf = lds + (ch & 1) * kBufferBytes + (lane & 15) * kChunkRowBytes;
+        const char* buf = lds + (ch & 1) * Cfg::BUFFER_BYTES + (lane & 15) * Cfg::ROW_BYTES;
         bf16x8_t f[2][2];
         operand(slot, 0, f[0]);
         operand(slot, 1, f[1]);
@@ -137,7 +150,7 @@ __device__ __forceinline__ void narrow_tile(const NarrowTile& t, int nrows, int 
             const int col = ((slot * 8 + h * 4 + (lane >> 4)) ^ (lane & 15)) * 16;
 #pragma unroll
             for (int m = 0; m < MB; ++m) {
-                const bf16x8_t x = *reinterpret_cast<const bf16x8_t*>(buf + m * 16 * kChunkRowBytes + col);
+                const bf16x8_t x = *reinterpret_cast<const bf16x8_t*>(buf + m * 16 * Cfg::ROW_BYTES + col);
 #pragma unroll
                 for (int b = 0; b < 2; ++b) acc[b][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[b][h], x, acc[b][m], 0, 0, 0);
             }
@@ -195,7 +208,7 @@ __device__ __forceinline__ void narrow_tile(const NarrowTile& t, int nrows, int 
     }
 }
 
-template <bool SWIGLU, bool PACKED>
+template <class Cfg, bool SWIGLU, bool PACKED>
 __device__ __forceinline__ void narrow_dispatch(const GemmArgs& a, int g, int row0, int nrows, int n0, int wave, int tid, char* lds)
 {
     constexpr int WAVE_COLS = SWIGLU ? 16 : 32;
@@ -204,7 +217,7 @@ __device__ __forceinline__ void narrow_dispatch(const GemmArgs& a, int g, int ro
     const bool stores = n0 + wave * WAVE_COLS < a.N;
     const int n = stores ? n0 + wave * WAVE_COLS : a.N - WAVE_COLS;
     const int lane = tid & 63;
-    NarrowTile t;
+    NarrowTile<Cfg> t;
     t.KT = a.K / kPackK;
     if (PACKED) {   // weights in tile order: 4 KB per K step and wavefront, each load instruction 1 KB without gaps
         constexpr int COLS = SWIGLU ? kPackRows / 2 : kPackRows;
@@ -228,38 +241,43 @@ __device__ __forceinline__ void narrow_dispatch(const GemmArgs& a, int g, int ro
     const bool mapped = a.a_row_map != nullptr;
     t.x = reinterpret_cast<const char*>(mapped ? a.A : a.A + (size_t)row0 * a.lda);
 #pragma unroll
-    for (int i = 0; i < kNarrowRows / kRowsPerPass; ++i) {
+    for (int i = 0; i < Cfg::ROWS / Cfg::PASS_ROWS; ++i) {
         // rows past the tile's end re-read its last one; they are multiplied and not stored
-        const int r = min(tid / kChunksPerRow + kRowsPerPass * i, nrows - 1);
+        const int r = min(tid / Cfg::ROW_CHUNKS + Cfg::PASS_ROWS * i, nrows - 1);
         const int src = mapped ? a.a_row_map[row0 + r] / a.a_row_div : r;
         t.x_off[i] = (uint32_t)src * (uint32_t)a.lda * 2u;
     }
     uint16_t* c = a.C + (size_t)g * a.c_group_col_stride + (size_t)row0 * a.ldc + n;
-    switch ((nrows + 15) >> 4) {
-        case 1: narrow_tile<SWIGLU, PACKED, 1>(t, nrows, tid, lds, stores, c, a.ldc); break;
-        case 2: narrow_tile<SWIGLU, PACKED, 2>(t, nrows, tid, lds, stores, c, a.ldc); break;
-        case 3: narrow_tile<SWIGLU, PACKED, 3>(t, nrows, tid, lds, stores, c, a.ldc); break;
-        default: narrow_tile<SWIGLU, PACKED, 4>(t, nrows, tid, lds, stores, c, a.ldc); break;
+    if constexpr (Cfg::ROWS == 16) {
+        narrow_tile<Cfg, SWIGLU, PACKED, 1>(t, nrows, tid, lds, stores, c, a.ldc);
+    } else {
+        static_assert(Cfg::ROWS == 16 || Cfg::ROWS == 64, "row blocks of a tile");
+        switch ((nrows + 15) >> 4) {
+            case 1: narrow_tile<Cfg, SWIGLU, PACKED, 1>(t, nrows, tid, lds, stores, c, a.ldc); break;
+            case 2: narrow_tile<Cfg, SWIGLU, PACKED, 2>(t, nrows, tid, lds, stores, c, a.ldc); break;
+            case 3: narrow_tile<Cfg, SWIGLU, PACKED, 3>(t, nrows, tid, lds, stores, c, a.ldc); break;
+            default: narrow_tile<Cfg, SWIGLU, PACKED, 4>(t, nrows, tid, lds, stores, c, a.ldc); break;
+        }
     }
 }
 
 // row tiles of n rows and the rows of each but the last: equal heights in blocks of 16
-__host__ __device__ __forceinline__ int narrow_tiles(int rows) { return (rows + kNarrowRows - 1) / kNarrowRows; }
+__host__ __device__ __forceinline__ int narrow_tiles(int rows, int tallest) { return (rows + tallest - 1) / tallest; }
 __device__ __forceinline__ int narrow_height(int rows, int tiles) { return ((rows + 15) / 16 + tiles - 1) / tiles * 16; }
 
-template <bool SWIGLU>
-constexpr int narrow_cols() { return SWIGLU ? 64 : 128; }
+template <class Cfg, bool SWIGLU>
+constexpr int narrow_cols() { return Cfg::WAVES * (SWIGLU ? 16 : 32); }
 
 }  // namespace
 
 // Tile ids: first those of the shared experts s (s.G == 0: none), then those of the routed groups r; each XCD
 // (workgroup id mod 8) takes a contiguous run of both, in which the row tiles of one column tile are neighbours,
 // so that a group with several of them reads its weights from HBM once.
-template <bool SWIGLU, bool PACKED>
-__global__ __launch_bounds__(kNarrowThreads, 2) void narrow_gemm_kernel(GemmArgs r, GemmArgs s)
+template <class Cfg, bool SWIGLU, bool PACKED>
+__global__ __launch_bounds__(Cfg::THREADS, 2) void narrow_gemm_kernel(GemmArgs r, GemmArgs s)
 {
     __shared__ int s_pref[kNarrowMaxGroups + 1], s_row0[kNarrowMaxGroups + 1];
-    __shared__ __align__(16) char lds[2 * kBufferBytes + (PACKED ? 0 : kNarrowThreads / 64 * kTurnBytes)];
+    __shared__ __align__(16) char lds[2 * Cfg::BUFFER_BYTES + (PACKED ? 0 : Cfg::WAVES * kTurnBytes)];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (wave == 0) {   // row tiles before every routed group, from the partition's row offsets
@@ -267,7 +285,7 @@ __global__ __launch_bounds__(kNarrowThreads, 2) void narrow_gemm_kernel(GemmArgs
         for (int g0 = 0; g0 < r.G; g0 += 64) {
             const int g = g0 + lane;
             const int r0 = g < r.G ? r.offset[g] : 0, r1 = g < r.G ? r.offset[g + 1] : 0;
-            const int n = narrow_tiles(r1 - r0);
+            const int n = narrow_tiles(r1 - r0, Cfg::ROWS);
             int incl = n;
 #pragma unroll
             for (int d = 1; d < 64; d <<= 1) {
@@ -280,8 +298,8 @@ __global__ __launch_bounds__(kNarrowThreads, 2) void narrow_gemm_kernel(GemmArgs
         }
     }
     __syncthreads();
-    constexpr int COLS = narrow_cols<SWIGLU>();
-    const int s_mt = s.G > 0 ? narrow_tiles(s.dense_rows) : 0, s_nt = s.G > 0 ? (s.N + COLS - 1) / COLS : 0;
+    constexpr int COLS = narrow_cols<Cfg, SWIGLU>();
+    const int s_mt = s.G > 0 ? narrow_tiles(s.dense_rows, Cfg::ROWS) : 0, s_nt = s.G > 0 ? (s.N + COLS - 1) / COLS : 0;
     const int s_total = s.G * s_mt * s_nt, s_xcd = (s_total + 7) >> 3;
     const int r_nt = (r.N + COLS - 1) / COLS;
     const int r_total = __builtin_amdgcn_readfirstlane(s_pref[r.G]) * r_nt, r_xcd = (r_total + 7) >> 3;
@@ -292,7 +310,7 @@ __global__ __launch_bounds__(kNarrowThreads, 2) void narrow_gemm_kernel(GemmArgs
             if (L >= s_total) continue;
             const int g = L / (s_mt * s_nt), l = L - g * s_mt * s_nt, ni = l / s_mt, mi = l - ni * s_mt;
             const int h = narrow_height(s.dense_rows, s_mt);
-            narrow_dispatch<SWIGLU, PACKED>(s, g, mi * h, min(h, s.dense_rows - mi * h), ni * COLS, wave, tid, lds);
+            narrow_dispatch<Cfg, SWIGLU, PACKED>(s, g, mi * h, min(h, s.dense_rows - mi * h), ni * COLS, wave, tid, lds);
         } else {
             const int L = xcd * r_xcd + slot - s_xcd;
             if (L >= r_total) continue;
@@ -306,7 +324,7 @@ __global__ __launch_bounds__(kNarrowThreads, 2) void narrow_gemm_kernel(GemmArgs
             const int row_a = __builtin_amdgcn_readfirstlane(s_row0[g]), rows = __builtin_amdgcn_readfirstlane(s_row0[g + 1]) - row_a;
             const int l = L - pref * r_nt, ni = l / mt, mi = l - ni * mt;
             const int h = narrow_height(rows, mt);
-            narrow_dispatch<SWIGLU, PACKED>(r, g, row_a + mi * h, min(h, rows - mi * h), ni * COLS, wave, tid, lds);
+            narrow_dispatch<Cfg, SWIGLU, PACKED>(r, g, row_a + mi * h, min(h, rows - mi * h), ni * COLS, wave, tid, lds);
         }
     }
 }
@@ -323,29 +341,40 @@ static bool narrow_args_fit(const GemmArgs& a)
     return !(a.ldc % 4 || a.c_group_col_stride % 4 || (reinterpret_cast<uintptr_t>(a.C) & 7));
 }
 
-hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bool swiglu, double expected_rows,
-                              long long max_rows, hipStream_t s)
+hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bool swiglu, int n_cu, double expected_rows,
+                              int max_tokens, long long max_rows, hipStream_t s)
 {
     GemmArgs none{};
     const GemmArgs& sh = shared ? *shared : none;
     if (routed.offset == nullptr || max_rows < 1 || !narrow_args_fit(routed)) return hipErrorInvalidValue;
     if (shared && (sh.dense_rows < 1 || (sh.Wp != nullptr) != (routed.Wp != nullptr) || !narrow_args_fit(sh))) return hipErrorInvalidValue;
-    const int cols = swiglu ? narrow_cols<true>() : narrow_cols<false>();
-    const auto col_tiles = [&](const GemmArgs& a) { return (long long)(a.N + cols - 1) / cols; };
-    const long long s_tiles = shared ? col_tiles(sh) * narrow_tiles(sh.dense_rows) * sh.G : 0;
     // Workgroups: every tile one of its own (a compute unit holds two at a time and takes the next when one
     // ends) as far as the host can foresee the routing; groups with more rows than expected are reached by the
     // kernel's loop over tile ids.
     const long long filled = max_rows < routed.G ? max_rows : routed.G;
-    const long long most = filled + max_rows / kNarrowRows;
-    long long r_tiles = (long long)(filled * (1.0 + expected_rows / kNarrowRows));
-    if (r_tiles > most) r_tiles = most;
-    long long grid = (s_tiles + 7) / 8 * 8 + (r_tiles * col_tiles(routed) + 7) / 8 * 8;
-    if (grid < 8) grid = 8;
-    if (grid > (1 << 20)) grid = 1 << 20;
-    const auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kNarrowThreads), 0, s, routed, sh); };
-    if (routed.Wp) { if (swiglu) go(narrow_gemm_kernel<true, true>); else go(narrow_gemm_kernel<false, true>); }
-    else { if (swiglu) go(narrow_gemm_kernel<true, false>); else go(narrow_gemm_kernel<false, false>); }
+    const auto grid_for = [&](int tallest, int cols, long long groups) {
+        const auto col_tiles = [&](const GemmArgs& a) { return (long long)(a.N + cols - 1) / cols; };
+        const long long s_tiles = shared ? col_tiles(sh) * narrow_tiles(sh.dense_rows, tallest) * sh.G : 0;
+        const long long most = groups + max_rows / tallest;
+        long long r_tiles = (long long)(groups * (1.0 + expected_rows / tallest));
+        if (r_tiles > most) r_tiles = most;
+        const long long grid = (s_tiles + 7) / 8 * 8 + (r_tiles * col_tiles(routed) + 7) / 8 * 8;
+        return grid < 8 ? 8 : grid > (1 << 20) ? 1 << 20 : grid;
+    };
+    const auto go = [&](auto kernel, long long grid, int threads) { hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(threads), 0, s, routed, sh); };
+    const auto with = [&](auto cfg, auto sw) {
+        using Cfg = decltype(cfg);
+        constexpr bool SW = decltype(sw)::value;
+        const long long grid = grid_for(Cfg::ROWS, narrow_cols<Cfg, SW>(), filled);
+        if (routed.Wp) go(narrow_gemm_kernel<Cfg, SW, true>, grid, Cfg::THREADS);
+        else go(narrow_gemm_kernel<Cfg, SW, false>, grid, Cfg::THREADS);
+    };
+    // no group has more than max_tokens rows: one row tile each; of a share, about `kept` rows stay here
+    const long long kept = (long long)(expected_rows * routed.G + 0.999);
+    const bool one_block = max_tokens <= NarrowFew::ROWS && (!shared || sh.dense_rows <= NarrowFew::ROWS);
+    if (swiglu) with(NarrowStream{}, std::true_type{});
+    else if (one_block && grid_for(kNarrowRows, narrow_cols<NarrowStream, false>(), kept < filled ? kept : filled) <= n_cu) with(NarrowFew{}, std::false_type{});
+    else with(NarrowStream{}, std::false_type{});
     return hipGetLastError();
 }
 

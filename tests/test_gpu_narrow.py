@@ -57,15 +57,17 @@ def test_same_bits_as_the_tiled_kernels(monkeypatch, hidden, inter, shared_inter
 
 
 @pytest.mark.parametrize("n_tokens", [1, 2, 16, 63, 300])
+@pytest.mark.parametrize("n_shared,what", [(0, ()), (0, ("routed",)), (2, ()), (2, ("routed", "shared"))])
 @pytest.mark.parametrize("pinned", [False, True])
-def test_small_calls_of_a_share(monkeypatch, n_tokens, pinned):
-    """By the library's own rule: a local share that starts at expert 2 of 70, no shared experts, k = 5."""
+def test_small_calls_of_a_share(monkeypatch, n_tokens, pinned, n_shared, what):
+    """By the library's own rule: a local share that starts at expert 2 of 70, k = 5, without and with shared experts
+    (up to 16 tokens the down projection's tiles are half as wide)."""
     wl = tiny_workload(name=f"narrow_share_{n_tokens}", n_tokens=n_tokens, hidden=192, inter=320, n_experts=70,
-                       local_begin=2, n_local=66, top_k=5)
+                       local_begin=2, n_local=66, top_k=5, n_shared=n_shared, shared_inter=192 if n_shared else 0)
     inp = make_inputs(wl, seed=62)
     calls = ((1, 0), (2, 0))
-    want, _ = _run(monkeypatch, wl, inp, 0, (), calls, pinned)
-    got, narrow = _run(monkeypatch, wl, inp, 24, (), calls, pinned)
+    want, _ = _run(monkeypatch, wl, inp, 0, what, calls, pinned)
+    got, narrow = _run(monkeypatch, wl, inp, 24, what, calls, pinned)
     assert narrow
     for w, o in zip(want, got):
         assert np.array_equal(o, w)
