@@ -26,11 +26,12 @@ __device__ __forceinline__ uint32_t row_max_step(uint32_t x) { return max(x, (ui
 template <int CTRL>
 __device__ __forceinline__ int row_min_step(int x) { return min(x, row_exchange<CTRL>(x)); }
 
-// scores as unsigned integers of the same order, equal for equal scores (-0 == +0); 0 is below every score
+// scores as unsigned integers of the same order, equal for equal scores (-0 == +0); 0 is below every score, also below
+// the NaN whose bits are all ones, which would map to it (padding rows: an expert would be selected twice)
 __device__ __forceinline__ uint32_t order_key(float v)
 {
     const uint32_t u = __float_as_uint(v + 0.0f);
-    return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+    return max(u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u), 1u);
 }
 __device__ __forceinline__ float key_score(uint32_t key)
 {

@@ -59,3 +59,29 @@ def test_aggregation_of_every_slot_count(hidden, top_k, n_local, n_shared):
         out = bf16_bits_to_f32(g.run_forward(ctx, wl, g.DeviceInputs(wl, inp, pinned=pinned)))
         ctx.destroy()
         assert rel_err_rows(out, ref["out"]) <= 2e-2   # the bound of every full-path comparison (test_gpu_parity)
+
+
+@pytest.mark.parametrize("n_tokens", [5, 100])   # one launch with the partition, and one in front of it
+@pytest.mark.parametrize("n_experts,top_k", [(128, 8), (20, 7)])
+def test_scores_that_are_not_numbers_select_no_expert_twice(n_tokens, n_experts, top_k):
+    """Padding rows of 0xff bytes (every score a NaN) and rows in which only a few scores are numbers: a token's experts
+    are different ones, so that the partition's rows and maps belong together; the other tokens are not touched."""
+    import gpu_util as g
+    wl = tiny_workload(name="nan", n_tokens=n_tokens, hidden=64, inter=64, n_experts=n_experts, n_local=n_experts, top_k=top_k)
+    inp = make_inputs(wl, seed=83)
+    lg = inp["gate_logits"]
+    clean = np.argsort(-lg.astype(np.float64), axis=1, kind="stable")[:, :top_k]
+    bits = lg.view(np.uint32)
+    bits[0::4] = 0xffffffff
+    bits[1::4, 3:] = 0xffffffff
+    ctx = g.make_ctx(wl)
+    g.run_forward(ctx, wl, g.DeviceInputs(wl, inp))
+    got = ctx.get_routing(0)
+    ctx.destroy()
+    idx = got["idx"]
+    assert idx.min() >= 0 and idx.max() < n_experts
+    assert all(len(set(row)) == top_k for row in idx.tolist())
+    part = oracle.dispatch(idx, 0, n_experts)
+    for key in ("count", "offset", "perm", "pos"):
+        assert np.array_equal(got[key], part[key]), key
+    assert np.array_equal(idx[2::4], clean[2::4]) and np.array_equal(idx[3::4], clean[3::4])
