@@ -26,6 +26,15 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
+// Between an LDS access of one lane and that of another lane of the same wavefront to the same place: a wavefront's LDS
+// accesses run in program order, so nothing has to be waited for, but the compiler must keep that order.
+__device__ __forceinline__ void wavefront_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // g * sigmoid(g) from the hardware's exp2 and reciprocal (about 1 ulp each: far below the bf16
 // rounding of the result); exp2 saturates to +inf / 0 at the ends, which give -0 and g
 __device__ __forceinline__ float silu_f(float g)

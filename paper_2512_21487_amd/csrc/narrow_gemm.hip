@@ -129,11 +129,13 @@ __device__ __forceinline__ void narrow_tile(const NarrowTile<Cfg>& t, int nrows,
             for (int h = 0; h < 2; ++h) f[h] = __builtin_bit_cast(bf16x8_t, w[slot][b][h]);
             return;
         }
+        wavefront_lds_order();   // the block before this one has been read
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int r = i * 8 + (lane >> 3);
             *reinterpret_cast<uint4*>(turn + r * 128 + ((lane & 7) ^ (r >> 1)) * 16) = w[slot][b][i];
         }
+        wavefront_lds_order();
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int r = lane & 15;

@@ -88,12 +88,15 @@ __global__ __launch_bounds__((PARTITION ? kTokPerBlock : kRouterTokens) * 16) vo
         }
         // Everything that need not follow round by round, a lane per slot.  Softmax restricted to the selection
         // = full softmax renormalised over it; the sum runs in slot order in every lane.
+        wavefront_lds_order();
         const float v0 = s_ex[tl * k];
+        wavefront_lds_order();
         for (int s = sub; s < k; s += 16) {
             s_ex[tl * k + s] = expf(s_ex[tl * k + s] - v0);
             const int el = s_idx[tl * k + s] - e0;
             if (live && el >= 0 && el < El) atomicOr(&smask[el], 1ull << tl);
         }
+        wavefront_lds_order();
         float sum = 0.f;
         for (int s = 0; s < k; ++s) sum += s_ex[tl * k + s];
         if (live)
