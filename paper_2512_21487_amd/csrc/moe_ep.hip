@@ -24,16 +24,34 @@ namespace {
 
 enum Stage { ST_ROUTER = 0, ST_PARTITION, ST_GEMM1, ST_GEMM2, ST_SGEMM1, ST_SGEMM2, ST_COMBINE, ST_TOTAL, ST_COPY_IN, ST_COPY_OUT, ST_ATTN, ST_COUNT };
 
-// Where the narrow kernels (narrow_gemm.hip) take over, in rows per routed expert.  Forwards in us, tiled / narrow, five
-// layers in turn: DeepSeek-V2-Lite-shaped layer, 3 rows 325 / 199, 24 rows 352 / 229 (before the tiled launches took shared experts
-// along); DeepSeek-V2-shaped share, 11 / 19 rows 241 / 228, 262 / 252; Qwen3-235B-A22B-shaped share, 16 rows 122 / 119.  From 24
-// to 48 rows the two are within 3 % under balanced load, but the narrow row tile of 64 loses up to 10 % where the load is
-// skewed (Qwen3-30B-A3B-shaped layer, Zipf 1.1, 600 tokens: 206 / 228).
+// Where the narrow kernels (narrow_gemm.hip) take over, in rows per routed expert.  Forwards in us under balanced load,
+// three layers in turn, tiled (shared experts in the same launch where plan_chunk puts them) / narrow: DeepSeek-V2-Lite-shaped
+// layer, 3 / 12 / 24 / 48 rows 204 / 183, 234 / 199, 237 / 214, 253 / 243; DeepSeek-V2-shaped share, 11 / 19 / 24 / 28 rows
+// 253 / 221, 266 / 246, 272 / 257, 278 / 287; Qwen3-235B-A22B-shaped share, 8 / 16 / 32 rows 126 / 117, 128 / 120, 122 / 128;
+// Qwen3-30B-A3B-shaped layer, 24 rows 218 / 218, and with its load skewed (Zipf 1.1) 24 / 38 rows 180 / 173, 201 / 208.
 constexpr double kNarrowMeanRows = 24.0;
-// The shared experts go along up to this many rows: alone, 256-row tiles of a few hundred rows leave most compute
-// units idle (DeepSeek-V2-Lite-shaped layer, 256 / 500 tokens: 298 -> 229, 321 -> 267 us; DeepSeek-V2-shaped share, 500 / 800 / 1200:
-// 332 -> 266, 335 -> 323, 345 -> 376).
+// The shared experts go along up to this many rows; beyond, launches of their own with tall tiles.  Apart / along, the routed
+// experts in narrow tiles both times: DeepSeek-V2-Lite-shaped layer, 256 / 512 tokens 251 / 212, 269 / 229 us; DeepSeek-V2-shaped share,
+// 300 / 640 / 800 / 1200 tokens 278 / 220, 289 / 254, 282 / 292, 300 / 336.
 constexpr int kNarrowSharedRows = 768;
+// The host knows the mean of a chunk's load only.  Every row tile of 64 streams its expert's weights again; where the
+// tokens all choose the same experts this costs more than balanced load gains.  The narrow kernels run where even then
+// no expert has more than kNarrowGroupTiles row tiles, and all of them no more than kNarrowLoadTiles times as many as
+// balanced load, one per expert.  Tiled / narrow, Qwen3-235B-A22B-shaped share: 128 tokens balanced 122 / 115, all on 8 of its
+// experts 108 / 105; 256 tokens balanced 120 / 117 (weights in the caller's layout 141 / 126), with two and four times the
+// share's rows 129 / 125 and 131 / 163, all on 8 experts 117 / 165; 384 tokens, over the line, 128 / 123 (146 / 132), 131 / 133, 129 / 181,
+// 179 / 237; one expert per token and all on the same, 384 / 1536 tokens 76 / 59, 84 / 116.  Qwen3-30B-A3B-shaped layer, 384 tokens
+// balanced 222 / 215 (249 / 225), all on eight experts 67 / 80 (68 / 90).  512 experts of 2048 x 512, 256 / 1536 tokens on eight
+// experts 66 / 131, 123 / 275.
+// Where the shared experts go along, balanced load gains more and the mean alone decides: DeepSeek-V2-shaped share, 256 / 400 /
+// 600 tokens 238 / 208, 246 / 229, 259 / 251, with four times the share's rows 400 / 640 tokens 267 / 268, 293 / 344; the launches
+// apart that the tiled kernels had to make of these before they took shared experts along were slower under every load (403, 411).
+constexpr int kNarrowGroupTiles = 6, kNarrowLoadTiles = 2;
+bool narrow_under_any_load(int Tn, int k, int El)
+{
+    const int tiles = (Tn + kNarrowRows - 1) / kNarrowRows;
+    return tiles <= kNarrowGroupTiles && (k < El ? k : El) * tiles <= kNarrowLoadTiles * El;
+}
 constexpr int kNarrowVariant = -2;   // in last_variants, beside the tile variants of grouped_gemm.hip
 
 struct ProfSpan { hipEvent_t a, b; int stage; int forward; };
@@ -53,6 +71,7 @@ struct moe_ep_ctx {
     bool shared_variant_named = false;
     // chunks whose routed experts get at most this many rows on average run the narrow kernels; 0 = never
     double narrow_rows = kNarrowMeanRows;
+    bool narrow_named = false;   // the number came from the environment: it alone decides
     bool by_rule = true;     // no tile shape, instruction or form of the expert outputs was asked for by name
     int merge = -1;          // shared and routed experts in one launch: -1 by the cost of both (plan_chunk), 0 never, 1 always
     int last_shared_up = -1, last_shared_down = -1;   // tile variants of the last forward's shared experts
@@ -197,7 +216,7 @@ void read_knobs(moe_ep_ctx* ctx)
     if (const char* v = getenv("MOE_EP_UP_UNITS")) ctx->up_units = atoi(v);
     if (const char* v = getenv("MOE_EP_DOWN_UNITS")) ctx->down_units = atoi(v);
     if (const char* v = getenv("MOE_EP_MERGE")) ctx->merge = atoi(v) != 0;
-    if (const char* v = getenv("MOE_EP_NARROW_ROWS")) ctx->narrow_rows = atof(v);
+    if (const char* v = getenv("MOE_EP_NARROW_ROWS")) { ctx->narrow_rows = atof(v); ctx->narrow_named = true; }
     // workgroups of a copy kernel: ~128 KB in flight fills the host link; more only queues up in the
     // memory fabric in front of the compute kernels
     if (const char* v = getenv("MOE_EP_LINK_GRID")) ctx->link_grid = atoi(v) > 0 ? atoi(v) : 64;
@@ -829,13 +848,17 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
     // How a chunk of Tn tokens runs, and whether `rows` rows of the shared experts run in the same launches (rows = 0:
     // there are none, or they may not).
     struct Plan { bool narrow, along; int up, down; };
+    // timing the shared experts' stages takes launches of their own
+    const bool shared_timed = prof && (ctx->prof_mask & ((1u << ST_SGEMM1) | (1u << ST_SGEMM2)));
     const int ct_up = (H + 127) / 128, ct_down = (M + 255) / 256, ct_s = (Hs + 127) / 128;
     const auto plan_chunk = [&](int Tn, int rows) -> Plan {
         Plan p{false, false, -1, -1};
         if (Tn <= 0) return p;
         const bool fits = ctx->by_rule && ctx->fused_gather && (unsigned long long)Tn * M * 2 < (1ull << 32);
         // few rows per routed expert: the narrow kernels, bound by the weight stream alone
-        if (fits && (double)Tn * k / E <= ctx->narrow_rows) return Plan{true, rows > 0 && rows <= kNarrowSharedRows, kNarrowVariant, kNarrowVariant};
+        const bool beside = rows > 0 && rows <= kNarrowSharedRows;
+        if (fits && (double)Tn * k / E <= ctx->narrow_rows && (beside || ctx->narrow_named || narrow_under_any_load(Tn, k, El)))
+            return Plan{true, beside && !shared_timed, kNarrowVariant, kNarrowVariant};
         // tile shapes of the two routed projections: N = H in tiles of 128 activation columns, N = M in
         // tiles of 256 columns
         p.up = ctx->gemm_variant >= 0 ? ctx->gemm_variant : picked(routed_variant(Tn, k, E, El, ct_up, M, n_cu));
@@ -845,7 +868,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         // shared and routed experts in one launch per projection, or in one each: by what both should take, where
         // launch_us has been held against measurements
         const bool known = M >= kCostKnownK && H >= kCostKnownK && Hs >= kCostKnownK;
-        if (rows <= 0 || !fits || !(ctx->merge == 1 || (ctx->merge != 0 && known))) return p;
+        if (rows <= 0 || shared_timed || !fits || !(ctx->merge == 1 || (ctx->merge != 0 && known))) return p;
         const double touched = El * (1.0 - pow(1.0 - (double)k / E, Tn)), w_up = 4.0 * M * H * touched, w_down = w_up / 2;
         const int Ks = Ns * Hs, worth = (Ks + H / 2) / H > 1 ? (Ks + H / 2) / H : 1;
         double apart = 0.0, up_one = 1e300, down_one = 1e300, us;
@@ -874,12 +897,13 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         return p;
     };
     // The shared experts may run beside routed ones -- every token's with the first chunk where they come first -- unless
-    // their stages are being timed, which takes launches of their own, or only one side's weights are in tile order.
+    // only one side's weights are in tile order.
     const bool shared_first = !dep && Ns > 0 && order == MOE_EP_ORDER_SHARED_FIRST;
-    const bool shared_beside = !dep && Ns > 0 && (prep_r != nullptr) == (prep_s != nullptr) && !(prof && (ctx->prof_mask & ((1u << ST_SGEMM1) | (1u << ST_SGEMM2))));
+    const bool shared_beside = !dep && Ns > 0 && (prep_r != nullptr) == (prep_s != nullptr);
+    const auto rows_beside = [&](int cidx, int Tn) { return !shared_beside ? 0 : !shared_first ? Tn : cidx == 0 ? T : 0; };
     int c0_t0, c0_Tn;
     chunk_range(T, r_1, r_2, 0, &c0_t0, &c0_Tn);
-    const bool first_takes_all = shared_first && shared_beside && plan_chunk(c0_Tn, T).along;
+    const bool first_takes_all = shared_first && plan_chunk(c0_Tn, rows_beside(0, c0_Tn)).along;
     if (shared_first && !first_takes_all) {
         if (pinned) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[r - 1], 0));
         int rc = run_shared(0, T, s_comp);
@@ -896,7 +920,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         else if (dep && cidx % r_2 == 0) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_attn[cidx / r_2], 0));
         const bool takes_all = first_takes_all && cidx == 0;
         const bool interleaved = !dep && Ns > 0 && order == MOE_EP_ORDER_INTERLEAVED;
-        const Plan plan = plan_chunk(Tn, takes_all ? T : interleaved && shared_beside ? Tn : 0);
+        const Plan plan = plan_chunk(Tn, rows_beside(cidx, Tn));
         const bool narrow = plan.narrow, along = plan.along;
         const int v_up = plan.up, v_down = plan.down;
         if (cidx < (int)ctx->last_variants.size()) ctx->last_variants[cidx] = {v_up, v_down};

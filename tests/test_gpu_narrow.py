@@ -135,3 +135,13 @@ def test_row_tiles_of_one_group_share_its_weights(monkeypatch, n_tokens):
                                        n_experts=160, n_local=20, top_k=6, n_tokens=n_tokens, hot=6, n_shared=2)
     assert torch.equal(outs[0], outs[1])
     assert narrow < 1.5 * tiled, f"{narrow:.0f} us against {tiled:.0f}"
+
+
+@pytest.mark.parametrize("n_tokens,top_k,hot", [(384, 8, 8), (384, 8, 16), (1536, 1, 1)])
+def test_a_load_far_from_balanced_runs_tall_tiles(monkeypatch, n_tokens, top_k, hot):
+    """At most 24 rows per expert on average, but all of them on few: 6 to 24 row tiles would stream each expert's
+    weights.  By the mean alone the narrow kernels ran, 1.45, 1.8 and 1.55 times as long as the tiled ones."""
+    (tiled, rule), outs = _skewed_us(monkeypatch, [{"MOE_EP_NARROW_ROWS": "0"}, {}], hidden=4096, inter=1536, n_experts=128,
+                                     n_local=16, top_k=top_k, n_tokens=n_tokens, hot=hot)
+    assert torch.equal(outs[0], outs[1])
+    assert rule < 1.2 * tiled, f"{rule:.0f} us against {tiled:.0f}"
