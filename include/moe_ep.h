@@ -364,7 +364,10 @@ int32_t moe_ep_routed_tile_rows(const moe_ep_config *cfg, int32_t n_tokens, int3
  * (moe_ep_prepare_weights; 1 or 0), and the rows of the block its matrix instruction multiplies (16:
  * v_mfma_f32_16x16x32_bf16, 32: v_mfma_f32_32x32x16_bf16), so that a measurement can name the kernel it
  * timed.  Chunks with few rows per expert run kernels that hold their weights in registers: 64 rows, 128
- * columns, 1 x 4 wavefronts, and the K steps in flight in place of ring slots.  Any pointer may be NULL.  MOE_EP_ESTATE before any forward or for a stage the layer does not have.
+ * weight rows, 1 x 4 wavefronts (a down projection of at most 16 tokens that leaves compute units idle so: 16 rows,
+ * 64 weight rows, 1 x 2 wavefronts), and the K steps in flight in place of ring slots.  For a chunk without a token, and
+ * for the shared experts before their first launch, the shape that would be launched.  Any pointer may be NULL.
+ * MOE_EP_ESTATE before any forward or for a stage the layer does not have.
  */
 int moe_ep_last_tile_shape(const moe_ep_ctx *ctx, int32_t chunk, int32_t stage, int32_t *rows,
                            int32_t *cols, int32_t *k_step, int32_t *ring_slots, int32_t *waves_m,

@@ -96,10 +96,13 @@ hipError_t launch_merged_gemm(const GemmArgs& routed, const GemmArgs& shared, bo
 // `routed` (ragged) and, when `shared` is not NULL, the shared experts (dense) in one launch, bit for bit
 // what launch_grouped_gemm writes.  expected_rows: rows per routed group the grid is sized for (any
 // routing is served); max_tokens: the most rows one routed group can have; no other epilogue than epi == 0.
+// few: set to whether the launch's tiles were those for a few tokens.
 hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bool swiglu, int n_cu, double expected_rows,
-                              int max_tokens, long long max_rows, hipStream_t s);
-constexpr int kNarrowRows = 64;   // tallest row tile
-constexpr int kNarrowDepth = 4;   // K steps of 64 in flight per wavefront
+                              int max_tokens, long long max_rows, hipStream_t s, bool* few);
+constexpr int kNarrowRows = 64, kNarrowWaves = 4;         // tallest row tile, wavefronts
+constexpr int kNarrowFewRows = 16, kNarrowFewWaves = 2;   // the same of the tiles for a few tokens
+constexpr int kNarrowWaveRows = 32;                       // weight rows of a wavefront
+constexpr int kNarrowDepth = 4;                           // K steps of 64 in flight per wavefront
 hipError_t grouped_gemm_init();   // raises the dynamic-LDS limit of every instantiation once
 // the shape a launch of `variant` really runs (after the fall-backs for a short K or many groups):
 // shape[] = tallest tile rows, weight rows per tile, K step, ring slots, wavefronts in m, in n,

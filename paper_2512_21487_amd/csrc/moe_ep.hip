@@ -52,7 +52,8 @@ bool narrow_under_any_load(int Tn, int k, int El)
     const int tiles = (Tn + kNarrowRows - 1) / kNarrowRows;
     return tiles <= kNarrowGroupTiles && (k < El ? k : El) * tiles <= kNarrowLoadTiles * El;
 }
-constexpr int kNarrowVariant = -2;   // in last_variants, beside the tile variants of grouped_gemm.hip
+// in last_variants, beside the tile variants of grouped_gemm.hip; the second: tiles for a few tokens
+constexpr int kNarrowVariant = -2, kNarrowFewVariant = -3;
 
 struct ProfSpan { hipEvent_t a, b; int stage; int forward; };
 
@@ -74,7 +75,7 @@ struct moe_ep_ctx {
     bool narrow_named = false;   // the number came from the environment: it alone decides
     bool by_rule = true;     // no tile shape, instruction or form of the expert outputs was asked for by name
     int merge = -1;          // shared and routed experts in one launch: -1 by the cost of both (plan_chunk), 0 never, 1 always
-    int last_shared_up = -1, last_shared_down = -1;   // tile variants of the last forward's shared experts
+    int last_shared_up = -1, last_shared_down = -1;   // tile variants of the shared experts' last launches; before any, shared_variant
     bool fused_gather = true;  // the gate/up projection gathers the token rows itself (no grouped copy)
     int y_mode = 0;            // expert outputs: 0 bf16, 1 fp32, 2 bf16 scaled by the routing weight (expert_out_mode)
     // pinned-host mode, moe_ep_forward: the aggregation writes its rows straight into the caller's host
@@ -229,6 +230,7 @@ void read_knobs(moe_ep_ctx* ctx)
         ctx->memcpy_in = v[0] == '1' || v[0] == 'i';
         ctx->memcpy_out = v[0] == '1' || v[0] == 'o';
     }
+    ctx->last_shared_up = ctx->last_shared_down = ctx->shared_variant;
     ctx->fused_gather = fused_gather_enabled();
     ctx->y_mode = expert_out_mode();
     ctx->by_rule = ctx->gemm_variant < 0 && ctx->up_variant < 0 && ctx->down_variant < 0 && !ctx->shared_variant_named &&
@@ -853,11 +855,10 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
     const int ct_up = (H + 127) / 128, ct_down = (M + 255) / 256, ct_s = (Hs + 127) / 128;
     const auto plan_chunk = [&](int Tn, int rows) -> Plan {
         Plan p{false, false, -1, -1};
-        if (Tn <= 0) return p;
         const bool fits = ctx->by_rule && ctx->fused_gather && (unsigned long long)Tn * M * 2 < (1ull << 32);
         // few rows per routed expert: the narrow kernels, bound by the weight stream alone
         const bool beside = rows > 0 && rows <= kNarrowSharedRows;
-        if (fits && (double)Tn * k / E <= ctx->narrow_rows && (beside || ctx->narrow_named || narrow_under_any_load(Tn, k, El)))
+        if (fits && Tn > 0 && (double)Tn * k / E <= ctx->narrow_rows && (beside || ctx->narrow_named || narrow_under_any_load(Tn, k, El)))
             return Plan{true, beside && !shared_timed, kNarrowVariant, kNarrowVariant};
         // tile shapes of the two routed projections: N = H in tiles of 128 activation columns, N = M in
         // tiles of 256 columns
@@ -868,7 +869,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         // shared and routed experts in one launch per projection, or in one each: by what both should take, where
         // launch_us has been held against measurements
         const bool known = M >= kCostKnownK && H >= kCostKnownK && Hs >= kCostKnownK;
-        if (rows <= 0 || shared_timed || !fits || !(ctx->merge == 1 || (ctx->merge != 0 && known))) return p;
+        if (Tn <= 0 || rows <= 0 || shared_timed || !fits || !(ctx->merge == 1 || (ctx->merge != 0 && known))) return p;
         const double touched = El * (1.0 - pow(1.0 - (double)k / E, Tn)), w_up = 4.0 * M * H * touched, w_down = w_up / 2;
         const int Ks = Ns * Hs, worth = (Ks + H / 2) / H > 1 ? (Ks + H / 2) / H : 1;
         double apart = 0.0, up_one = 1e300, down_one = 1e300, us;
@@ -967,8 +968,9 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
             shared_args(takes_all ? 0 : t0, takes_all ? T : Tn, s1, s2);
             ctx->last_shared_up = v_up; ctx->last_shared_down = v_down;
         }
+        bool few = false;   // of the launch that follows
         sp = prof_begin(ctx, prof, ST_GEMM1, s_comp);
-        if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g1, along ? &s1 : nullptr, true, n_cu, (double)Tn * k / E, Tn, a_max, s_comp));
+        if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g1, along ? &s1 : nullptr, true, n_cu, (double)Tn * k / E, Tn, a_max, s_comp, &few));
         else if (along) HIP_TRY(ctx, launch_merged_gemm(g1, s1, true, v_up, n_cu, s_comp));
         else HIP_TRY(ctx, launch_grouped_gemm(g1, true, v_up, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);
@@ -981,10 +983,14 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         g2.max_units = ctx->down_units;
         g2.epi = ctx->y_mode; g2.row_weight = w; g2.row_assignment = perm;
         sp = prof_begin(ctx, prof, ST_GEMM2, s_comp);
-        if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g2, along ? &s2 : nullptr, false, n_cu, (double)Tn * k / E, Tn, a_max, s_comp));
+        if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g2, along ? &s2 : nullptr, false, n_cu, (double)Tn * k / E, Tn, a_max, s_comp, &few));
         else if (along) HIP_TRY(ctx, launch_merged_gemm(g2, s2, false, v_down, n_cu, s_comp));
         else HIP_TRY(ctx, launch_grouped_gemm(g2, false, v_down, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);
+        if (few) {   // the gate/up projection has no such tiles
+            if (cidx < (int)ctx->last_variants.size()) ctx->last_variants[cidx].down = kNarrowFewVariant;
+            if (along) ctx->last_shared_down = kNarrowFewVariant;
+        }
 
         if (interleaved && !along) {
             int rc = run_shared(t0, Tn, s_comp);
@@ -1062,8 +1068,10 @@ int moe_ep_last_tile_shape(const moe_ep_ctx* ctx, int32_t chunk, int32_t stage, 
     const moe_ep_config& c = ctx->cfg;
     const int variant = shared ? (up ? ctx->last_shared_up : ctx->last_shared_down) : (up ? ctx->last_variants[chunk].up : ctx->last_variants[chunk].down);
     const int K = shared ? (up ? c.hidden : c.n_shared * c.shared_inter) : (up ? c.hidden : c.inter);
-    int v[8] = {kNarrowRows, 128, kPackK, kNarrowDepth, 1, 4, 1, 16};   // the narrow kernels
-    if (variant != kNarrowVariant && !grouped_gemm_variant_shape(variant, K, !shared, shared ? 1 : c.n_local, v)) return MOE_EP_ESTATE;
+    const bool few = variant == kNarrowFewVariant;
+    const int waves = few ? kNarrowFewWaves : kNarrowWaves;
+    int v[8] = {few ? kNarrowFewRows : kNarrowRows, waves * kNarrowWaveRows, kPackK, kNarrowDepth, 1, waves, 1, 16};   // the narrow kernels
+    if (variant != kNarrowVariant && !few && !grouped_gemm_variant_shape(variant, K, !shared, shared ? 1 : c.n_local, v)) return MOE_EP_ESTATE;
     if (mfma_rows) *mfma_rows = v[7];
     if (tile_order) *tile_order = v[6] && (shared ? ctx->last_prepared_shared : ctx->last_prepared_routed);
     if (rows) *rows = v[0];

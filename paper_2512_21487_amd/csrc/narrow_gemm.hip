@@ -36,11 +36,11 @@ struct NarrowCfg {
     static constexpr int BUFFER_BYTES = ROWS * ROW_BYTES;
     static_assert(THREADS % ROW_CHUNKS == 0 && 16 % PASS_ROWS == 0, "a block of 16 rows is whole passes");
 };
-using NarrowStream = NarrowCfg<kNarrowDepth, kNarrowRows, 4>;
+using NarrowStream = NarrowCfg<kNarrowDepth, kNarrowRows, kNarrowWaves>;
 // A compute unit draws about 46 GB/s, whatever is in flight (twice the K steps: no change).  Where a launch of 128-column
 // tiles leaves compute units without one, half as wide tiles halve what the busiest one has to draw: down projection
 // of one token of the DeepSeek-V2-Lite-shaped layer, 112 workgroups, the shared experts' 720 KB each, forward 47 -> 43 us.
-using NarrowFew = NarrowCfg<kNarrowDepth, 16, 2>;
+using NarrowFew = NarrowCfg<kNarrowDepth, kNarrowFewRows, kNarrowFewWaves>;
 constexpr int kTurnBytes = 16 * kPackK * 2;                       // one block of 16 weight rows of a K step
 
 // one wavefront's share of a tile: uniform bases, the lane's byte offsets, and how the weight base moves
@@ -352,7 +352,7 @@ static bool narrow_args_fit(const GemmArgs& a)
 }
 
 hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bool swiglu, int n_cu, double expected_rows,
-                              int max_tokens, long long max_rows, hipStream_t s)
+                              int max_tokens, long long max_rows, hipStream_t s, bool* few)
 {
     GemmArgs none{};
     const GemmArgs& sh = shared ? *shared : none;
@@ -382,8 +382,9 @@ hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bo
     // no group has more than max_tokens rows: one row tile each; of a share, about `kept` rows stay here
     const long long kept = (long long)(expected_rows * routed.G + 0.999);
     const bool one_block = max_tokens <= NarrowFew::ROWS && (!shared || sh.dense_rows <= NarrowFew::ROWS);
+    *few = !swiglu && one_block && grid_for(kNarrowRows, narrow_cols<NarrowStream, false>(), kept < filled ? kept : filled) <= n_cu;
     if (swiglu) with(NarrowStream{}, std::true_type{});
-    else if (one_block && grid_for(kNarrowRows, narrow_cols<NarrowStream, false>(), kept < filled ? kept : filled) <= n_cu) with(NarrowFew{}, std::false_type{});
+    else if (*few) with(NarrowFew{}, std::false_type{});
     else with(NarrowStream{}, std::false_type{});
     return hipGetLastError();
 }

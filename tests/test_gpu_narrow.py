@@ -145,3 +145,24 @@ def test_a_load_far_from_balanced_runs_tall_tiles(monkeypatch, n_tokens, top_k, 
                                      n_local=16, top_k=top_k, n_tokens=n_tokens, hot=hot)
     assert torch.equal(outs[0], outs[1])
     assert rule < 1.2 * tiled, f"{rule:.0f} us against {tiled:.0f}"
+
+
+def test_the_tile_shape_that_ran_is_reported():
+    """moe_ep_last_tile_shape: the tiles of a few tokens' down projection, the 64-row tiles, and the shapes of a call
+    without tokens and of a chunk without a token."""
+    import gpu_util as g
+    wl = tiny_workload(name="narrow_shape", n_tokens=17, hidden=192, inter=320, n_experts=70, n_local=70, top_k=5,
+                       n_shared=1, shared_inter=192)
+    ctx = g.make_ctx(wl)
+    d = g.DeviceInputs(wl, make_inputs(wl, seed=65))
+    tile = lambda stage, chunk=0: tuple(ctx.last_tile_shape(stage, chunk)[n] for n in ("rows", "cols", "k_step", "ring_slots", "waves_m", "waves_n"))
+    g.run_forward(ctx, wl, d, n_tokens=0)
+    assert ctx.last_tile_shape("shared_gate_up_gemm") and ctx.last_tile_shape("shared_down_gemm")
+    for n_tokens, down in ((1, (16, 64, 64, 4, 1, 2)), (16, (16, 64, 64, 4, 1, 2)), (17, (64, 128, 64, 4, 1, 4))):
+        g.run_forward(ctx, wl, d, n_tokens=n_tokens)
+        assert tile("routed_gate_up_gemm") == tile("shared_gate_up_gemm") == (64, 128, 64, 4, 1, 4)
+        assert tile("routed_down_gemm") == tile("shared_down_gemm") == down
+    g.run_forward(ctx, wl, d, r=4, n_tokens=2)   # two of the four chunks are empty
+    for chunk in range(4):
+        assert ctx.last_tile_shape("routed_gate_up_gemm", chunk) and ctx.last_tile_shape("routed_down_gemm", chunk)
+    ctx.destroy()
