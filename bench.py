@@ -28,6 +28,11 @@ STAGE_LABEL = {"routed_gate_up_gemm": "routed gate/up projection", "routed_down_
                "shared_down_gemm": "shared-expert down projection"}
 
 
+# What the events inside the timed region bracket: whole forwards.  A forward whose shared-expert stages are timed
+# gives them launches of their own, which an untimed one may not, so per-stage times come from further passes.
+TIMED_REGION_STAGES = ["forward"]
+
+
 def kernel_name(ctx, stage):
     """The kernel the last forward launched for a projection, as rocprofv3 names its template
     arguments (read from the library: moe_ep_last_tile_shape), or None."""
@@ -36,13 +41,17 @@ def kernel_name(ctx, stage):
         return None
     swiglu = "true" if "gate_up" in stage else "false"
     ragged = "true" if stage.startswith("routed") else "false"
-    if (sh["rows"], sh["cols"], sh["waves_m"], sh["waves_n"]) == (64, 128, 1, 4):   # few rows per expert
-        return f"narrow_gemm_kernel<{swiglu}, {'true' if sh['tile_order'] else 'false'}"
+    tile_order = "true" if sh["tile_order"] else "false"
+    if (sh["rows"], sh["cols"], sh["waves_m"], sh["waves_n"]) in ((64, 128, 1, 4), (16, 64, 1, 2)):   # few rows per expert
+        return f"narrow_gemm_kernel<NarrowCfg<{sh['ring_slots']}, {sh['rows']}, {sh['waves_n']}>, {swiglu}, {tile_order}>"
+    if ctx.last_shared_beside():
+        return (f"grouped_gemm_merged_kernel<{sh['rows']}, {sh['cols']}, {sh['k_step']}, {sh['ring_slots']}, "
+                f"{sh['waves_m']}, {sh['waves_n']}, {swiglu}, {tile_order}, {sh['mfma_rows']}>")
     # last argument: what the epilogue writes (MOE_EP_EXPERT_OUT, the routed down projection only)
     epi = {"f": 1, "s": 2}.get(os.environ.get("MOE_EP_EXPERT_OUT", " ")[0], 0) if stage == "routed_down_gemm" else 0
     # and whether the weights are read from a tile-order copy (moe_ep_prepare_weights)
     return (f"grouped_gemm_kernel<{sh['rows']}, {sh['cols']}, {sh['k_step']}, {sh['ring_slots']}, "
-            f"{sh['waves_m']}, {sh['waves_n']}, {swiglu}, {ragged}, {epi}, {'true' if sh['tile_order'] else 'false'}, "
+            f"{sh['waves_m']}, {sh['waves_n']}, {swiglu}, {ragged}, {epi}, {tile_order}, "
             f"{sh['mfma_rows']}>")
 
 
@@ -321,16 +330,13 @@ def main() -> int:
     for _ in range(args.warmup):
         step()
     torch.cuda.synchronize()
-    # Timed region: HIP events (on the stream the kernel runs on) bracket only the dominant kernel,
-    # the routed gate/up projection, whose duration the roofline object needs; events between all
-    # stages would cost 2 % of a dsv2_eg forward and 20 % of a 256-token one.
     # The kernel with the largest share of the forward: the shared experts' gate/up projection when
     # the workload has shared experts (42 % of a dsv2_eg forward), else the routed one.  The routed
     # gate/up projection is timed too: it carries the metric's "grouped GEMM % of peak".
     dominant = "shared_gate_up_gemm" if wl.n_shared > 0 else "routed_gate_up_gemm"
     timed_stages = sorted({dominant, "routed_gate_up_gemm", "routed_down_gemm"})
     if not args.no_stage_timing:
-        ctx.set_profiling_stages(timed_stages + ["forward"])   # + one event pair around every forward
+        ctx.set_profiling_stages(TIMED_REGION_STAGES)
         ctx.set_profiling(min(args.steps, 256))   # the library keeps events of at most 256 forwards
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -339,23 +345,36 @@ def main() -> int:
     t_enq = time.perf_counter() - t0       # host time spent enqueueing (the calls do not block)
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
+    # did the shared experts run in the routed experts' launches?
+    beside = wl.n_shared > 0 and all(ctx.last_shared_beside(c) for c in range(ctx.last_chunks() if args.order == 1 else 1))
+    joint = None   # those launches' times
+
+    def timed_pass(names):
+        ctx.set_profiling_stages(names)
+        ctx.set_profiling(min(args.steps, 256))   # the library keeps events of at most 256 forwards
+        for _ in range(args.steps):
+            step()
+        return ctx.get_stage_ms()
+
     if args.no_stage_timing:
         stages = {n: 0.0 for n in pkg.STAGES}
     else:
         # device time of each of the K forwards (Sec. 5.2 reports the timed trials of a point by one figure)
         per_forward_ms = [e - b for n, _, b, e in ctx.get_timeline() if n == "forward"]
-        in_region = ctx.get_stage_ms()
-        # Second pass, outside the timed region: the same forwards with events around every stage
-        # (the per-stage breakdown; its "forward" is a little longer than ms_per_step for that reason).
-        ctx.set_profiling_stages(None)
-        ctx.set_profiling(min(args.steps, 256))   # the library keeps events of at most 256 forwards
-        for _ in range(args.steps):
-            step()
-        stages = ctx.get_stage_ms()
+        ctx.get_stage_ms()
+        # Outside the timed region, the same forwards again.  If the shared experts ran beside the routed ones: once with
+        # events around those launches.  Then with events around the dominant kernel and the routed projections only (events
+        # between all stages cost 2 % of a dsv2_eg forward and 20 % of a 256-token one; the shared experts in launches of
+        # their own), and with events around every stage.
+        if beside:
+            joint = timed_pass(["routed_gate_up_gemm", "routed_down_gemm"])
+            joint_kernels = {n: kernel_name(ctx, n) for n in ("routed_gate_up_gemm", "routed_down_gemm")}
+        few_events = timed_pass(timed_stages)
+        stages = timed_pass(None)
         ctx.set_profiling(0)
-        second_pass = {n: stages[n] for n in timed_stages}
+        all_events = {n: stages[n] for n in timed_stages}
         for n in timed_stages:
-            stages[n] = in_region[n]
+            stages[n] = few_events[n]
 
     routing = [ctx.get_routing(c) for c in range(args.r)]
     kept = sum(int(rt["offset"][-1]) for rt in routing)
@@ -420,6 +439,13 @@ def main() -> int:
         if line_ is not None and st in names:
             line_["kernel"] = names[st]
 
+    if joint:   # routed and shared experts of a projection together
+        up, down = "routed_gate_up_gemm", "routed_down_gemm"
+        w_bytes = r * wl.n_local * 2.0 * H * M + Ns * 2.0 * Hs * M   # of one weight matrix per expert
+        both = {up: gemm_line(4.0 * M * (kept * H + T * Ns * Hs), 2 * w_bytes + 2.0 * (kept * (M + H) + T * (M + Ns * Hs)), joint[up]),
+                down: gemm_line(2.0 * M * (kept * H + T * Ns * Hs), w_bytes + 2.0 * (kept * (M + H) + T * (M + Ns * Hs)), joint[down])}
+        joint = {n: dict(l, kernel=joint_kernels[n]) for n, l in both.items() if l}
+
     line = {
         "metric": "expert-layer tokens/sec at 1 GPU; grouped-GEMM % of bf16 MFMA peak",
         "value": value, "unit": "tokens/s", "n_gpus": 1, "steps": args.steps,
@@ -434,11 +460,14 @@ def main() -> int:
         "grouped_gemm_pct_of_bf16_mfma_peak": routed_pct,
         "roofline": roof,
         "kernels": kernels,
+        "joint_launches": joint,
         "stage_ms": stages,
-        "stage_ms_note": (", ".join(timed_stages) + ": HIP events inside the timed region; other stages: a "
-                          "second pass of the same forwards with events around every stage"
+        "stage_ms_note": (", ".join(timed_stages) + ": HIP events around these stages in a second pass of the same "
+                          "forwards; other stages: a third pass with events around every stage"
                           + ("" if args.no_stage_timing else
-                             " (there: " + ", ".join(f"{n} {second_pass[n]:.4f}" for n in timed_stages) + " ms)")),
+                             " (there: " + ", ".join(f"{n} {all_events[n]:.4f}" for n in timed_stages) + " ms)")
+                          + ("; shared experts in launches of their own, in the timed region they ran in the routed "
+                             "experts' (joint_launches)" if beside else "")),
         "host_enqueue_ms_per_step": t_enq / args.steps * 1e3,
     }
     if not args.no_stage_timing and per_forward_ms:
@@ -452,12 +481,13 @@ def main() -> int:
         # takes t_in = t_out = t_a2e; here the inbound copy also carries the gate scores.
         r = args.r
         t_in, t_out = stages["copy_in"] / r, stages["copy_out"] / r
-        t_e = sum(stages[n] for n in ("router", "partition", "routed_gate_up_gemm", "routed_down_gemm",
-                                      "shared_gate_up_gemm", "shared_down_gemm", "aggregation")) / r
+        t_e = sum(stages[n] for n in COMPUTE_STAGES) / r
+        if joint:
+            t_e = (sum(stages[n] for n in ("router", "partition", "aggregation")) + sum(l["ms_per_step"] for l in joint.values())) / r
         line["pipeline"] = {
             "t_in_ms_per_chunk": t_in, "t_e_ms_per_chunk": t_e, "t_out_ms_per_chunk": t_out,
             "closed_form_ms": t_in + t_e + t_out + (r - 1) * max(t_in, t_e, t_out),
-            "measured_ms": stages["forward"],
+            "measured_ms": float(np.median(per_forward_ms)) if joint else stages["forward"],
             "bytes_in_per_chunk": (T // r) * (2 * M + 4 * wl.n_experts), "bytes_out_per_chunk": (T // r) * 2 * M,
         }
     if pinned and args.fit_pipeline:

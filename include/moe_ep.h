@@ -218,7 +218,10 @@ int moe_ep_get_routing(moe_ep_ctx *ctx, int32_t chunk, int32_t *idx, float *w, i
 /*
  * Per-stage device time, in milliseconds, measured with HIP events on the streams the stages
  * run on (the task times t_e, t_s, t_a2e that Sec. 4.1 fits its linear models to).  moe_ep_set_profiling(ctx, depth) makes the next `depth` forwards (0..256; 0 = off)
- * record an event before and after every stage; this serialises nothing.
+ * record an event before and after every stage.  The events serialise nothing.  Without them the shared experts
+ * may run in the routed experts' launches (moe_ep_last_shared_beside); a forward that times stage 4 or 5 gives them
+ * launches of their own, since stages that share a launch have no times of their own: the same bits, and possibly a
+ * longer forward than the same call untimed (moe_ep_set_profiling_stages leaves the two out).
  * moe_ep_get_stage_ms synchronises, returns the per-forward AVERAGE over the forwards recorded
  * since the last call, and opens a new window of `depth` forwards:
  *   ms[0] gate  ms[1] partition (permute + row gather)  ms[2] routed gate/up GEMM
@@ -232,7 +235,8 @@ int moe_ep_get_routing(moe_ep_ctx *ctx, int32_t chunk, int32_t *idx, float *w, i
 int moe_ep_set_profiling(moe_ep_ctx *ctx, int32_t depth);
 /* Restricts the events to the stages whose bit (1 << index into ms[]) is set in `mask`; the default
  * is every stage.  Events between all stages cost a few percent of a forward (more for small
- * calls); timing only one stage leaves the rest of the forward undisturbed. */
+ * calls).  Without the bits of stages 4 and 5 a forward makes the launches it makes untimed; where the shared experts
+ * run in the routed experts' launches, ms[2] and ms[3] are then the times of both together. */
 int moe_ep_set_profiling_stages(moe_ep_ctx *ctx, uint32_t mask);
 int moe_ep_get_stage_ms(moe_ep_ctx *ctx, float *ms, int32_t n);
 /*
@@ -372,6 +376,13 @@ int32_t moe_ep_routed_tile_rows(const moe_ep_config *cfg, int32_t n_tokens, int3
 int moe_ep_last_tile_shape(const moe_ep_ctx *ctx, int32_t chunk, int32_t stage, int32_t *rows,
                            int32_t *cols, int32_t *k_step, int32_t *ring_slots, int32_t *waves_m,
                            int32_t *waves_n, int32_t *tile_order, int32_t *mfma_rows);
+
+/*
+ * 1 if the last forward ran the shared experts in the launches of this chunk's routed experts (one launch per
+ * projection for both: of the chunk's tokens, or with MOE_EP_ORDER_SHARED_FIRST of all tokens in chunk 0's), else 0.
+ * MOE_EP_ESTATE before any forward, MOE_EP_EINVAL for a chunk it did not have.
+ */
+int moe_ep_last_shared_beside(const moe_ep_ctx *ctx, int32_t chunk);
 
 int moe_ep_forward_dep(moe_ep_ctx *ctx, const void *tokens, const float *gate_logits,
                        const void *routed_w, const void *shared_w, int32_t top_k, int32_t r_1,

@@ -130,6 +130,8 @@ def load_library() -> ctypes.CDLL:
     lib.moe_ep_last_tile_shape.argtypes = [vp, i32, i32] + [ctypes.POINTER(i32)] * 8
     lib.moe_ep_get_routing.restype = ctypes.c_int
     lib.moe_ep_get_routing.argtypes = [vp, i32, vp, vp, vp, vp, vp, vp]
+    lib.moe_ep_last_shared_beside.restype = ctypes.c_int
+    lib.moe_ep_last_shared_beside.argtypes = [vp, i32]
     lib.moe_ep_set_profiling.restype = ctypes.c_int
     lib.moe_ep_set_profiling.argtypes = [vp, i32]
     lib.moe_ep_set_profiling_stages.restype = ctypes.c_int
@@ -482,6 +484,13 @@ class MoeEp:
             raise MoeEpError(rc, "moe_ep_last_tile_shape: bad arguments")
         return dict(zip(("rows", "cols", "k_step", "ring_slots", "waves_m", "waves_n", "tile_order", "mfma_rows"),
                         (x.value for x in v)))
+
+    def last_shared_beside(self, chunk: int = 0) -> bool:
+        """Whether the last forward ran the shared experts in the launches of this chunk's routed experts."""
+        rc = self._lib.moe_ep_last_shared_beside(self._ctx, chunk)
+        if rc < 0:
+            raise MoeEpError(rc, "moe_ep_last_shared_beside: no forward, or no such chunk")
+        return rc == 1
 
     # -- timing model ---------------------------------------------------------------------
     def set_pipeline_model(self, model: Optional[PipelineModel]) -> None:

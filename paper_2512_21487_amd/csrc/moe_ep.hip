@@ -120,7 +120,7 @@ struct moe_ep_ctx {
     // last forward (for moe_ep_get_routing): tokens, top_k, chunks = micro-batches x chunks of each
     int last_T = -1, last_k = 0, last_r = 0, last_r1 = 1;
     bool last_prepared_routed = false, last_prepared_shared = false;  // it read tile-order copies of the weights
-    struct ChunkVariants { int up, down; };
+    struct ChunkVariants { int up, down; bool beside; };   // beside: the shared experts ran in the same launches
     std::vector<ChunkVariants> last_variants;  // per chunk of the last forward: tile variants of the routed projections
     // stage profiling
     int prof_depth = 0, prof_recorded = 0;
@@ -495,7 +495,7 @@ int moe_ep_create(const moe_ep_config* cfg, moe_ep_ctx** out_ctx)
     char* slab = nullptr;
     if (hipMalloc(reinterpret_cast<void**>(&slab), L.total) != hipSuccess) { delete ctx; return MOE_EP_ENOMEM; }
     bind_workspaces(ctx, slab, L);  // L.tokens == 0: d_tokens is the slab base, freed in destroy
-    ctx->last_variants.assign((size_t)cfg->max_chunks, {-1, -1});
+    ctx->last_variants.assign((size_t)cfg->max_chunks, {-1, -1, false});
 
     // the chunk events order GPU work against GPU work only, so they skip the system-scope cache
     // write-back a default event record implies (it stalled the other streams' kernels)
@@ -924,7 +924,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         const Plan plan = plan_chunk(Tn, rows_beside(cidx, Tn));
         const bool narrow = plan.narrow, along = plan.along;
         const int v_up = plan.up, v_down = plan.down;
-        if (cidx < (int)ctx->last_variants.size()) ctx->last_variants[cidx] = {v_up, v_down};
+        if (cidx < (int)ctx->last_variants.size()) ctx->last_variants[cidx] = {v_up, v_down, along};
         int32_t* idx = ctx->idx + (size_t)t0 * k;
         float* w = ctx->w + (size_t)t0 * k;
         int32_t* pos = ctx->pos + (size_t)t0 * k;
@@ -1081,6 +1081,14 @@ int moe_ep_last_tile_shape(const moe_ep_ctx* ctx, int32_t chunk, int32_t stage, 
     if (waves_m) *waves_m = v[4];
     if (waves_n) *waves_n = v[5];
     return MOE_EP_OK;
+}
+
+int moe_ep_last_shared_beside(const moe_ep_ctx* ctx, int32_t chunk)
+{
+    if (!ctx) return MOE_EP_EINVAL;
+    if (ctx->last_T < 0) return MOE_EP_ESTATE;
+    if (chunk < 0 || chunk >= ctx->last_r || chunk >= (int)ctx->last_variants.size()) return MOE_EP_EINVAL;
+    return ctx->last_T > 0 && ctx->last_variants[chunk].beside;
 }
 
 int moe_ep_forward(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits,

@@ -54,3 +54,29 @@ def test_share_without_any_row(monkeypatch):
     want = _run(monkeypatch, wl, inp, 0, True, ((1, 0),))
     got = _run(monkeypatch, wl, inp, 1, True, ((1, 0),))
     assert want[0].any() and np.array_equal(got[0], want[0])
+
+
+@pytest.mark.parametrize("narrow_rows", ["0", "1e9"])   # the tiled launches, the narrow ones
+def test_timing_a_forward(monkeypatch, narrow_rows):
+    """What bench.py times inside its timed region is the launches an untimed forward makes; timing the shared experts'
+    stages takes them apart, timing the routed ones alone does not.  The bits are the same."""
+    import bench
+    import gpu_util as g
+    monkeypatch.setenv("MOE_EP_NARROW_ROWS", narrow_rows)
+    monkeypatch.setenv("MOE_EP_MERGE", "1")
+    wl = tiny_workload(name="timing", n_tokens=300, hidden=256, inter=192, n_experts=8, n_local=8, top_k=2, n_shared=1, shared_inter=256)
+    ctx = g.make_ctx(wl)
+    d = g.DeviceInputs(wl, make_inputs(wl, seed=93))
+    want = g.run_forward(ctx, wl, d)
+    assert ctx.last_shared_beside() and want.any()
+    for names, beside in ((bench.TIMED_REGION_STAGES, True), (["routed_gate_up_gemm", "routed_down_gemm"], True),
+                          (["shared_down_gemm"], False), (None, False)):
+        ctx.set_profiling_stages(names)
+        ctx.set_profiling(1)
+        assert np.array_equal(g.run_forward(ctx, wl, d), want)
+        assert ctx.last_shared_beside() == beside, names
+        ms = ctx.get_stage_ms()
+        assert all(ms[n] > 0.0 for n in names or ("routed_gate_up_gemm", "shared_gate_up_gemm", "shared_down_gemm", "forward"))
+        ctx.set_profiling(0)
+    assert np.array_equal(g.run_forward(ctx, wl, d), want) and ctx.last_shared_beside()
+    ctx.destroy()
