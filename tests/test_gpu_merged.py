@@ -17,7 +17,11 @@ def _run(monkeypatch, wl, inp, merge, prepared, calls, pinned=False):
     d = g.DeviceInputs(wl, inp, pinned=pinned)
     if prepared:
         ctx.prepare_weights(d.routed, d.shared)
-    outs = [g.run_forward(ctx, wl, d, r=r, order=order) for r, order in calls]
+    outs = []
+    for r, order in calls:
+        outs.append(g.run_forward(ctx, wl, d, r=r, order=order))
+        assert ctx.last_shared_beside() == bool(merge), "the launches under test"
+        assert ctx.last_tile_shape("routed_gate_up_gemm")["rows"] >= 128   # not the narrow kernels
     ctx.destroy()
     return outs
 

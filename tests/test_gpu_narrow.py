@@ -34,9 +34,10 @@ def _run(monkeypatch, wl, inp, rows, what=(), calls=((1, 0),), pinned=False):
     if what:
         ctx.prepare_weights(d.routed if "routed" in what else None, d.shared if "shared" in what else None)
     outs = [g.run_forward(ctx, wl, d, r=r, order=order) for r, order in calls]
-    shape = ctx.last_tile_shape("routed_gate_up_gemm")
+    narrow = ctx.last_tile_shape("routed_gate_up_gemm")["rows"] == 64
+    assert not (narrow and rows == 0), "the tiled kernels are the reference"
     ctx.destroy()
-    return outs, shape["rows"] == 64
+    return outs, narrow
 
 
 @pytest.mark.parametrize("what", [(), ("routed", "shared"), ("routed",), ("shared",)])
@@ -71,6 +72,36 @@ def test_small_calls_of_a_share(monkeypatch, n_tokens, pinned, n_shared, what):
     assert narrow
     for w, o in zip(want, got):
         assert np.array_equal(o, w)
+
+
+@pytest.mark.parametrize("what", [(), ("routed", "shared")])
+@pytest.mark.parametrize("n_tokens,hidden,inter,shared_inter", [
+    (1, 192, 64, 64),        # K steps of 64 in the down projection, routed and shared: 1 and 2
+    (15, 320, 128, 320),     # 2 and 10: segments of 5, two and a half staged chunks of 4
+    (16, 192, 512, 704),     # 8 (the first turn of the steady loop) and 22: segments of 11
+    (17, 192, 512, 704),     # the same out of 64-row tiles
+    (16, 448, 576, 192),     # 9: the loop and one step; columns that end inside a tile
+    (2, 2048, 1088, 576),    # 17, and more column tiles
+    (16, 192, 1408, 1408),   # 22 and 44
+])
+def test_down_projection_of_a_few_tokens(monkeypatch, n_tokens, hidden, inter, shared_inter, what):
+    """The 16-row tiles with two wavefronts, from fewer K steps than are staged at once to many turns of the loop over
+    both row buffers, shared experts' segments that end inside a staged chunk, weights in either layout."""
+    import gpu_util as g
+    wl = tiny_workload(name="narrow_few", n_tokens=n_tokens, hidden=hidden, inter=inter, n_experts=12, local_begin=1, n_local=11,
+                       top_k=3, n_shared=2, shared_inter=shared_inter)
+    inp = make_inputs(wl, seed=66)
+    want, _ = _run(monkeypatch, wl, inp, 0, what)
+    monkeypatch.delenv("MOE_EP_NARROW_ROWS")
+    ctx = g.make_ctx(wl)   # by the library's own rule
+    d = g.DeviceInputs(wl, inp)
+    if what:
+        ctx.prepare_weights(d.routed, d.shared)
+    got = g.run_forward(ctx, wl, d)
+    few = ctx.last_tile_shape("routed_down_gemm")["rows"] == 16
+    assert ctx.last_shared_beside() and few == (n_tokens <= 16)
+    ctx.destroy()
+    assert want[0].any() and np.array_equal(got, want[0])
 
 
 def test_most_experts_and_nothing_kept(monkeypatch):
