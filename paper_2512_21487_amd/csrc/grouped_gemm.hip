@@ -125,10 +125,10 @@ __device__ __forceinline__ LdsTables lds_tables(uint4* lds, int ring_bytes, int 
 // tall, a unit being one 32-row accumulator block for each of the workgroup's WGM rows of wavefronts
 // (unit_rows = 32 * WGM); a group of n rows has u = ceil(n / unit_rows) units and gets
 // ceil(u / max_units) tiles whose heights differ by at most one unit: 616 rows in units of 32 with
-// at most 8 per tile are tiles of 7, 7 and 6 units, not 256 + 256 + 104 rows.  A wavefront skips the
-// MFMAs of the blocks a tile does not have, so a group costs ceil(n / unit_rows) units of matrix
-// work whatever max_units is; max_units (a launch argument, at most the MB the kernel was
-// compiled for) only trades tile count against operand bytes per flop.
+// at most 8 per tile are tiles of 7, 7 and 6 units, not 256 + 256 + 104 rows.  The cut decides which rows a
+// tile loads and stores; the K loop multiplies all MB blocks the kernel was compiled for, also those a tile
+// does not have, so a group costs its tile count times MB units of matrix work.  max_units (a launch argument, at
+// most MB) lowers the tiles further: more of them, no less work in each.
 struct TileCut { int tiles, base, rem; };   // tiles of base units, the first rem of them one more
 __host__ __device__ __forceinline__ TileCut cut_group(int rows, int unit_rows, int max_units)
 {

@@ -1,7 +1,7 @@
 // Expert projections for few token rows per expert (Sec. 3.1; decode): the weights are read once and
 // everything else is small, so the launch lasts as long as the weight stream from HBM.  Measured on launches of
-// the gate/up projection: DeepSeek-V2-Lite-shaped layer, 33 tokens (761 MB with the shared experts) 132 + 50 us in the
-// tiled kernels, 123 us here = 6.2 TB/s; Qwen3-235B-A22B-shaped share, 256 tokens (403 MB) 79 and 69 us = 5.8 TB/s.
+// the gate/up projection: DeepSeek-V2-Lite-shaped layer, 33 tokens (733 MB with the shared experts) 132 + 50 us in the
+// tiled kernels, 118 us here = 6.2 TB/s; Qwen3-235B-A22B-shaped share, 256 tokens (403 MB) 79 and 68 us = 5.9 TB/s.
 //
 // A workgroup is four wavefronts.  A wavefront owns two blocks of 16 weight rows (gate/up: the gate and the up
 // rows of the same 16 activation columns) and up to four blocks of 16 token rows of one expert.  Its weights go
@@ -101,7 +101,8 @@ __device__ __forceinline__ void narrow_tile(const NarrowTile<Cfg>& t, int nrows,
         wk += t.w_step;
         if (--seg == 0) { seg = t.seg_steps; wk += t.seg_jump; }
     };
-    // token rows: thread -> row tid / 32 + 8 i, 16-byte chunk tid % 32 of the staged 512 bytes.  In LDS chunk c of row r
+    // token rows: thread -> row tid / ROW_CHUNKS + PASS_ROWS * i (passes of 8 rows with four wavefronts, of 4 with two),
+    // 16-byte chunk tid % ROW_CHUNKS of the row's staged ROW_BYTES (32 chunks, 512 bytes).  In LDS chunk c of row r
     // lies at c ^ (r mod 16), so that both the writes (one row) and the fragment reads (16 rows, one
     // chunk column) touch all banks evenly.  Chunks past the end of a row re-read its last one, unused.
     const int st_row = tid / Cfg::ROW_CHUNKS, st_chunk = tid % Cfg::ROW_CHUNKS;
