@@ -44,9 +44,8 @@ def kernel_name(ctx, stage):
     tile_order = "true" if sh["tile_order"] else "false"
     if (sh["rows"], sh["cols"], sh["waves_m"], sh["waves_n"]) in ((64, 128, 1, 4), (16, 64, 1, 2)):   # few rows per expert
         return f"narrow_gemm_kernel<NarrowCfg<{sh['ring_slots']}, {sh['rows']}, {sh['waves_n']}>, {swiglu}, {tile_order}>"
-    if ctx.last_shared_beside():
-        return (f"grouped_gemm_merged_kernel<{sh['rows']}, {sh['cols']}, {sh['k_step']}, {sh['ring_slots']}, "
-                f"{sh['waves_m']}, {sh['waves_n']}, {swiglu}, {tile_order}, {sh['mfma_rows']}>")
+    if (sh["rows"], sh["cols"], sh["waves_m"], sh["waves_n"]) == (192, 256, 2, 4):   # loading wavefronts beside the multiplying ones
+        return f"loader_gemm_kernel<{swiglu}, {tile_order}>"
     # last argument: what the epilogue writes (MOE_EP_EXPERT_OUT, the routed down projection only)
     epi = {"f": 1, "s": 2}.get(os.environ.get("MOE_EP_EXPERT_OUT", " ")[0], 0) if stage == "routed_down_gemm" else 0
     # and whether the weights are read from a tile-order copy (moe_ep_prepare_weights)

@@ -350,14 +350,13 @@ int moe_ep_chunk_range(int32_t n_tokens, int32_t r_1, int32_t r_2, int32_t chunk
 
 /*
  * Host only: the tallest row tile (128 or 160 rows; 224- and 256-row shapes exist but are
- * never chosen) the library's tiled launches give a routed projection
+ * never chosen) that a tiled launch without loading wavefronts -- an instruction or a form of the expert outputs was asked
+ * for by name (MOE_EP_MFMA, MOE_EP_EXPERT_OUT), but no shape -- gives a routed projection
  * (Sec. 3.1, Eq. moe_detail) of a chunk of n_tokens tokens -- down == 0: gate/up projection, else
  * the down projection -- on a GPU of n_cu compute units.  An expert of the balanced load of Sec. 3.1
  * gets n_tokens * top_k / E rows; its row tiles are cut to equal heights below the tallest; the
  * choice compares expected rounds of tiles times the measured time of a tile of each shape.  It
- * changes no result bit.  It is the answer for routed experts in a launch of their own: chunks with few rows per expert
- * run other kernels, and where the shared experts go along the choice is made for both (moe_ep_last_tile_shape
- * tells what a forward launched).  MOE_EP_EINVAL (negative) on bad arguments.
+ * changes no result bit.  By default chunks run other kernels (moe_ep_last_tile_shape tells what a forward launched).  MOE_EP_EINVAL (negative) on bad arguments.
  */
 int32_t moe_ep_routed_tile_rows(const moe_ep_config *cfg, int32_t n_tokens, int32_t top_k, int32_t down,
                                 int32_t n_cu);
@@ -370,7 +369,8 @@ int32_t moe_ep_routed_tile_rows(const moe_ep_config *cfg, int32_t n_tokens, int3
  * wavefronts along rows and along columns --, whether it read the weights from a tile-order copy
  * (moe_ep_prepare_weights; 1 or 0), and the rows of the block its matrix instruction multiplies (16:
  * v_mfma_f32_16x16x32_bf16, 32: v_mfma_f32_32x32x16_bf16), so that a measurement can name the kernel it
- * timed.  Chunks with few rows per expert run kernels that hold their weights in registers: 64 rows, 128
+ * timed.  By default a chunk runs kernels with loading wavefronts: 192 rows, 256 weight rows, 3 ring slots, 2 x 4
+ * (multiplying) wavefronts.  Chunks with few rows per expert run kernels that hold their weights in registers: 64 rows, 128
  * weight rows, 1 x 4 wavefronts (a down projection of at most 16 tokens that leaves compute units idle so: 16 rows,
  * 64 weight rows, 1 x 2 wavefronts), and the K steps in flight in place of ring slots.  For a chunk without a token, and
  * for the shared experts before their first launch, the shape that would be launched.  Any pointer may be NULL.

@@ -12,7 +12,7 @@ INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libmoe_ep.so")
 OBJDIR = os.path.join(HERE, "_build")
 
-SOURCES = ["router.hip", "dispatch.hip", "combine.hip", "transfer.hip", "grouped_gemm.hip", "narrow_gemm.hip", "schedule.hip", "dep_schedule.hip", "moe_ep.hip"]
+SOURCES = ["router.hip", "dispatch.hip", "combine.hip", "transfer.hip", "grouped_gemm.hip", "narrow_gemm.hip", "loader_gemm.hip", "schedule.hip", "dep_schedule.hip", "moe_ep.hip"]
 # the benchmark's measurement aid: a library of its own, not linked into the layer's
 PROBE_SOURCE = "probe.hip"
 PROBE_LIB = os.path.join(HERE, "libmoe_ep_probe.so")

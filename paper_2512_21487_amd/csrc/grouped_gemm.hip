@@ -189,16 +189,10 @@ static int lds_cap(int bytes) { return bytes < kLdsPerWorkgroup ? bytes : kLdsPe
 // 0 bf16 results; 1 fp32 results (the experts' outputs are then not rounded before the aggregation);
 // 2 bf16 results already multiplied by the routing weight of the row's assignment (Sec. 2.1: the
 // aggregation then only adds)
-// ONCE: the weights are read non-temporally.
-// MERGED: the tiles of the dense groups `d` (the shared experts) beside those of the ragged ones, in one list
-// (decode_tile below); a tile's group is then a.G + the dense group, and what differs between the two -- operands,
-// leading dimensions, K -- is picked per tile.
-template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool SWIGLU, bool RAGGED, int EPI = 0, bool PACKED = false, int MI = 32,
-          bool MERGED = false, bool ONCE = false>
-__device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d, uint4* lds, const int* s_pref, const int* s_row0,
+template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool SWIGLU, bool RAGGED, int EPI = 0, bool PACKED = false, int MI = 32>
+__device__ __forceinline__ void gemm_tiles(const GemmArgs& a, uint4* lds, const int* s_pref, const int* s_row0,
                                            const int* s_rowend, int* s_tile, int max_units)
 {
-    static_assert(!MERGED || (RAGGED && EPI == 0), "the shared experts run beside ragged groups");
     using Cfg = GemmCfg<BM, BN, BK, STAGES, WGM, WGN, SWIGLU>;
     constexpr int MB = Cfg::MB, NB = Cfg::NB, RPW = Cfg::RPW, XRPW = Cfg::XRPW, NW = Cfg::NW;
     constexpr int THREADS = Cfg::THREADS, BN_OUT = Cfg::BN_OUT, CPR = Cfg::CPR, RP = Cfg::RP;
@@ -221,22 +215,17 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
         mt_total = mt_per * a.G;
     }
     const int total = mt_total * NT;
-    // the dense groups' tiles, and how many ragged ones a tile of them is worth (its K may be longer)
-    const int d_nt = MERGED ? (d.N + BN_OUT - 1) / BN_OUT : 0;
-    const int d_mt = MERGED ? cut_group(d.dense_rows, 32 * WGM, max_units).tiles : 0;
-    const int d_total = MERGED ? d.G * d_mt * d_nt : 0, d_worth = MERGED ? max(1, (d.K + a.K / 2) / a.K) : 1;
-    const int worth = total + d_total * d_worth;
     // A launch lasts as many tiles as its busiest workgroup works through: rounds = ceil(total /
     // workgroups).  Only as many workgroups as it takes to finish in that many rounds stay: the
     // others would run one tile less and then wait (984 tiles on 256 compute units are 4 rounds on 248
     // as well; no measurable change in time, less work for the power budget).  The count is a multiple
     // of 8 so that every XCD (workgroup id mod 8) keeps the same number of workgroups.
-    const int rounds = (worth + (int)gridDim.x - 1) / (int)gridDim.x;
-    const int active = rounds > 0 ? min((int)gridDim.x, (((worth + rounds - 1) / rounds) + 7) & ~7) : 0;
+    const int rounds = (total + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int active = rounds > 0 ? min((int)gridDim.x, (((total + rounds - 1) / rounds) + 7) & ~7) : 0;
     const int per_xcd = active >> 3;
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     if (slot >= per_xcd) return;   // the whole workgroup leaves, before any barrier of the tile pass
-    const int KT_a = a.K / BK, KT_d = MERGED ? d.K / BK : 0;
+    const int KT = a.K / BK;
     // fragment geometry of this lane: row inside a 32-row block, swizzle term, k half
     // (16 x 16 blocks: row inside a 16-row block, swizzle term, which 8 of a step's 32 k values)
     const int fr_row = MI == 16 ? lane & 15 : lane & 31, fr_sw = (fr_row / RP) % CPR, fr_kh = MI == 16 ? lane >> 4 : lane >> 5;
@@ -250,10 +239,6 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
     // the rows of a tile are dealt to the WGM rows of wavefronts hb * 32 at a time
     struct Tile { int g, row0, nrows, n0, hb; };
     const bool a_mapped = RAGGED && a.a_row_map != nullptr;   // token rows gathered by the tile loads
-    const auto is_dense = [&](const Tile& t) { return MERGED && t.g >= a.G; };
-    int KT_issue = KT_a;                                      // of the tile being fetched
-    int kseg_len = a.kseg_len;
-    long long kseg_stride = a.w_kseg_stride;
     // weights in tile order (kernels.h): a K step's weight tile is one contiguous block
     constexpr bool packed = PACKED;
     static_assert(!PACKED || (BN == kPackRows && BK == kPackK), "the tile-order copy is laid out for one weight tile shape");
@@ -266,33 +251,15 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
 
     // tile number it of this workgroup -> coordinates; false past the last tile
     auto decode_tile = [&](int it, int& g, int& row0, int& nrows, int& n0, int& hb) -> bool {
-        int L = (it * 8 + xcd) * per_xcd + slot;
-        bool dense = false;
-        if (MERGED) {
-            // The dense tiles come first, one workgroup after the other; a workgroup that has one more than the
-            // others takes d_worth ragged tiles fewer.
-            const int w = xcd * per_xcd + slot, full = d_total / active, rem = d_total - full * active;
-            const int mine = full + (w < rem ? 1 : 0);
-            dense = it < mine;
-            if (!dense) {
-                const int v = it - mine + (w < rem ? d_worth : 0);   // in ragged tiles after the rounds of dense ones
-                L = v < d_worth ? v * (active - rem) + w - rem : d_worth * (active - rem) + (v - d_worth) * active + w;
-            }
-        }
-        if (L >= (dense ? d_total : total)) return false;
+        const int L = (it * 8 + xcd) * per_xcd + slot;
+        if (L >= total) return false;
         // tile id -> (group, row tile, column tile): inside a group the row tiles are taken in bands
         // of kBand; inside a band the row tile runs fastest, then the column tile.  A run of 32
         // consecutive ids (one XCD's share) then covers about kBand row panels x 32/kBand
         // weight panels instead of 32 x 1, which is what that XCD's L2 has to fetch.
         constexpr int kBand = 8;
-        int mi, ni, mt_g, l, nt = NT;
-        if (dense) {
-            const int per_g = MERGED ? d_mt * d_nt : 1;
-            g = L / per_g;
-            mt_g = d_mt;
-            nt = d_nt;
-            l = L - g * per_g;
-        } else if (RAGGED) {
+        int mi, ni, mt_g, l;
+        if (RAGGED) {
             int lo = 0, hi = a.G;
             while (hi - lo > 1) {
                 const int mid = (lo + hi) >> 1;
@@ -308,19 +275,18 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
             l = L - g * per_g;
         }
         {
-            const int band = l / (kBand * nt);
+            const int band = l / (kBand * NT);
             const int band_h = min(kBand, mt_g - band * kBand);
-            const int lb = l - band * kBand * nt;
+            const int lb = l - band * kBand * NT;
             ni = lb / band_h;
             mi = band * kBand + (lb - ni * band_h);
         }
         if (RAGGED) {
-            const int g_row0 = dense ? 0 : s_row0[g], g_end = dense ? d.dense_rows : s_rowend[g];
+            const int g_row0 = s_row0[g], g_end = s_rowend[g];
             const TileCut c = cut_group(g_end - g_row0, 32 * WGM, max_units);
             hb = c.base + (mi < c.rem ? 1 : 0);
             row0 = g_row0 + (mi * c.base + min(mi, c.rem)) * (32 * WGM);
             nrows = min(hb * 32 * WGM, g_end - row0);
-            if (dense) g += a.G;
         } else {
             hb = MB;
             row0 = mi * BM;
@@ -355,19 +321,10 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
         t.nrows = __builtin_amdgcn_readfirstlane(nrows);
         t.n0 = __builtin_amdgcn_readfirstlane(n0);
         t.hb = __builtin_amdgcn_readfirstlane(hb);
-        const bool dense = is_dense(t), mapped = a_mapped && !dense;
-        const int wg = dense ? t.g - a.G : t.g, lda = dense ? d.lda : a.lda, ldw = dense ? d.ldw : a.ldw;
-        const int N_t = dense ? d.N : a.N;
-        const long long w_up_offset = dense ? d.w_up_offset : a.w_up_offset;
-        if (MERGED) {
-            KT_issue = dense ? KT_d : KT_a;
-            kseg_len = dense ? d.kseg_len : a.kseg_len;
-            kseg_stride = dense ? d.w_kseg_stride : a.w_kseg_stride;
-        }
-        if (packed) Wi = (dense ? d.Wp : a.Wp) + ((size_t)wg * (dense ? d_nt : NT) + t.n0 / BN_OUT) * ((size_t)KT_issue * BN * BK);
-        else Wi = (dense ? d.W : a.W) + (size_t)wg * (dense ? d.w_group_stride : a.w_group_stride);
-        Xi = dense ? d.A : a.A;
-        if (!mapped) Xi += (size_t)t.row0 * lda;
+        if (packed) Wi = a.Wp + ((size_t)t.g * NT + t.n0 / BN_OUT) * ((size_t)KT * BN * BK);
+        else Wi = a.W + (size_t)t.g * a.w_group_stride;
+        Xi = a.A;
+        if (!a_mapped) Xi += (size_t)t.row0 * a.lda;
         // activation regions first: the tile row each lane fetches, and with gathered token rows the
         // row map's entries for all of them in one go (the loads are independent; one wait for the lot
         // instead of one memory round trip per region in the middle of a K loop)
@@ -383,7 +340,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
             if (RAGGED && within >= t.hb * 32) rr = t.nrows - 1;
             src_row[i] = min(rr, t.nrows - 1);
         }
-        if (mapped) {
+        if (a_mapped) {
 #pragma unroll
             for (int i = 0; i < XRPW; ++i) src_row[i] = a.a_row_map[t.row0 + src_row[i]];
             asm volatile("" ::: "memory");   // all of them are in flight before the first is used
@@ -396,20 +353,20 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
             const int r = j * RPR + ld_row;              // row in the stacked [activations; weights] tile
             const int c = ld_p ^ ((r / RP) % CPR);       // logical chunk stored at physical slot ld_p
             if (i < XRPW) {
-                goff[i] = ((uint32_t)src_row[i < XRPW ? i : 0] * (uint32_t)lda + c * 8) * 2u;
+                goff[i] = ((uint32_t)src_row[i < XRPW ? i : 0] * (uint32_t)a.lda + c * 8) * 2u;
             } else {
                 const int jw = r - BM;                   // row of the weight tile
                 int n;
                 uint32_t base = 0;
                 if (SWIGLU) {
-                    if (jw < BN / 2) n = t.n0 + jw; else { n = t.n0 + jw - BN / 2; base = (uint32_t)w_up_offset; }
+                    if (jw < BN / 2) n = t.n0 + jw; else { n = t.n0 + jw - BN / 2; base = (uint32_t)a.w_up_offset; }
                 } else {
                     n = t.n0 + jw;
                 }
-                n = min(n, N_t - 1);
+                n = min(n, a.N - 1);
                 // tile order is the order the slots have in LDS: 1 KB runs, lane by lane
                 goff[i] = packed ? (uint32_t)((j - BM / RPR) * 64 + lane) * 16u
-                                 : (base + (uint32_t)n * (uint32_t)ldw + c * 8) * 2u;
+                                 : (base + (uint32_t)n * (uint32_t)a.ldw + c * 8) * 2u;
             }
         }
         return true;
@@ -469,16 +426,16 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
 #define MOE_EP_ISSUE1(ks_, stage_, i_)                                                            \
     {                                                                                             \
         const int k_ = (ks_) * BK;                                                                \
-        const int seg_ = k_ / kseg_len;                                                           \
+        const int seg_ = k_ / a.kseg_len;                                                         \
         const size_t wk_ = packed ? (size_t)(ks_) * (BN * BK)                                     \
-                                  : (size_t)seg_ * kseg_stride + (k_ - seg_ * kseg_len);          \
+                                  : (size_t)seg_ * a.w_kseg_stride + (k_ - seg_ * a.kseg_len);         \
         uint4* dst_ = lds + (stage_) * Cfg::STAGE_CHUNKS + wave * 64 + NW * 64 * (i_);            \
         if ((i_) < XRPW)                                                                          \
             __builtin_amdgcn_global_load_lds(                                                     \
                 reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(Xi + k_) + goff[i_]), dst_, 16, 0, 0);     \
         else                                                                                      \
             __builtin_amdgcn_global_load_lds(                                                     \
-                reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(Wi + wk_) + goff[i_]), dst_, 16, 0, ONCE ? 2 : 0); \
+                reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(Wi + wk_) + goff[i_]), dst_, 16, 0, 0); \
     }
 #define SB() __builtin_amdgcn_sched_barrier(0)
     // The hand-over of a ring slot to the MFMAs: this wavefront's loads into it have landed (all
@@ -512,7 +469,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
         const int st_prev = stage == 0 ? STAGES - 1 : stage - 1;                                  \
         _Pragma("unroll") for (int i = 0; i < KKW; ++i) {                                         \
             if (i == KKW - 1) {                                                                   \
-                if (ki == KT_issue) {                                                                \
+                if (ki == KT) {                                                                \
                     if (!issue_end) {                                                             \
                         has_nxt = setup_tile(it_issue + 1, nxt);                                  \
                         if (has_nxt) ++it_issue; else issue_end = true;                           \
@@ -559,7 +516,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
             _Pragma("unroll") for (int q = 0; q < MB16 * NB16; ++q) {                             \
                 const int m_ = j * MB16 * NB16 + q;                                               \
                 if (m_ == HO16) {                                                                 \
-                    if (ki == KT_issue) {                                                            \
+                    if (ki == KT) {                                                            \
                         if (!issue_end) {                                                         \
                             has_nxt = setup_tile(it_issue + 1, nxt);                              \
                             if (has_nxt) ++it_issue; else issue_end = true;                       \
@@ -634,10 +591,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
         SB();
     }
     for (;;) {
-        const bool dense = is_dense(cur);
-        const int KT_cur = dense ? KT_d : KT_a, ldc = dense ? d.ldc : a.ldc, N_cur = dense ? d.N : a.N;
         // column 0 of the group's output rows
-        uint16_t* const C_cur = (dense ? d.C : a.C) + (size_t)(dense ? cur.g - a.G : cur.g) * (dense ? d.c_group_col_stride : a.c_group_col_stride);
+        uint16_t* const C_cur = a.C + (size_t)cur.g * a.c_group_col_stride;
         // one loop shape for every K step: the last one of a tile hands the next tile's first K
         // step over and reads its first fragments, which wait in registers through the epilogue
         if constexpr (MI == 32) {
@@ -647,7 +602,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
                 for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) acc[mb][nb][r] = 0.f;
-            for (int kt = 0; kt < KT_cur; ++kt) MOE_EP_STEP(true)
+            for (int kt = 0; kt < KT; ++kt) MOE_EP_STEP(true)
         } else {
 #pragma unroll
             for (int mb = 0; mb < MB16; ++mb)
@@ -660,7 +615,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
             SB();
             asm volatile("s_nop 7");
             SB();
-            for (int kt = 0; kt < KT_cur; ++kt) MOE_EP_STEP16(true)
+            for (int kt = 0; kt < KT; ++kt) MOE_EP_STEP16(true)
             SB();
             asm volatile("s_nop 15");
             asm volatile("s_nop 15");
@@ -698,16 +653,16 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
                     if (m >= cur.nrows) continue;  // the same for the lanes of an exchange (they share lane & 15)
                     if (EPI == 1) {
                         float* frow = reinterpret_cast<float*>(a.C) + (size_t)cur.g * a.c_group_col_stride +
-                                      (size_t)(cur.row0 + m) * ldc + cur.n0 + wn * Cfg::WTN + g4 * 4;
+                                      (size_t)(cur.row0 + m) * a.ldc + cur.n0 + wn * Cfg::WTN + g4 * 4;
 #pragma unroll
                         for (int nb = 0; nb < NB16; ++nb) {
-                            if (GUARD_N && cur.n0 + wn * Cfg::WTN + g4 * 4 + nb * 16 >= N_cur) continue;
+                            if (GUARD_N && cur.n0 + wn * Cfg::WTN + g4 * 4 + nb * 16 >= a.N) continue;
                             *reinterpret_cast<f32x4_t*>(frow + nb * 16) = acc16[mb][nb];
                         }
                         continue;
                     }
                     const float rw = EPI == 2 ? a.row_weight[a.row_assignment[cur.row0 + m]] : 1.0f;
-                    uint16_t* crow = Cg + (size_t)(cur.row0 + m) * ldc;
+                    uint16_t* crow = Cg + (size_t)(cur.row0 + m) * a.ldc;
 #pragma unroll
                     for (int nb = 0; nb < (SWIGLU ? NB16 / 2 : NB16); nb += 2) {
                         uint32_t pk[2][2];  // [block nb, nb + 1][column pair]
@@ -726,14 +681,14 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
                         const auto s1 = __builtin_amdgcn_permlane16_swap(pk[0][1], pk[1][1], false, false);
                         // rows of lanes 0 / 2 now hold columns 0..7 / 8..15 of block nb, rows 1 / 3 those of block nb + 1
                         const int col = (nb + (g4 & 1)) * 16 + (g4 >> 1) * 8;
-                        if (GUARD_N && n_wave + col >= N_cur) continue;
+                        if (GUARD_N && n_wave + col >= a.N) continue;
                         uint4 o;
                         o.x = s0[0]; o.y = s1[0]; o.z = s0[1]; o.w = s1[1];
                         *reinterpret_cast<uint4*>(crow + col) = o;
                     }
                 }
             };
-            if (cur.n0 + Cfg::BN_OUT <= N_cur) store_tile16(std::false_type{});
+            if (cur.n0 + Cfg::BN_OUT <= a.N) store_tile16(std::false_type{});
             else store_tile16(std::true_type{});
         } else {
             const int n_lane = cur.n0 + wn * (SWIGLU ? Cfg::WTN / 2 : Cfg::WTN) + fr_kh * 8;
@@ -751,12 +706,12 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
                     if (EPI == 1) {
                         // fp32 results: a lane's register quad is 4 consecutive columns = one 16-byte store
                         float* frow = reinterpret_cast<float*>(a.C) + (size_t)cur.g * a.c_group_col_stride +
-                                      (size_t)(cur.row0 + m) * ldc + cur.n0 + wn * Cfg::WTN + fr_kh * 4;
+                                      (size_t)(cur.row0 + m) * a.ldc + cur.n0 + wn * Cfg::WTN + fr_kh * 4;
 #pragma unroll
                         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
                             for (int q = 0; q < 4; ++q) {
-                                if (GUARD_N && cur.n0 + wn * Cfg::WTN + fr_kh * 4 + nb * 32 + q * 8 >= N_cur) continue;
+                                if (GUARD_N && cur.n0 + wn * Cfg::WTN + fr_kh * 4 + nb * 32 + q * 8 >= a.N) continue;
                                 f32x4_t o = {acc[mb][nb][q * 4], acc[mb][nb][q * 4 + 1], acc[mb][nb][q * 4 + 2], acc[mb][nb][q * 4 + 3]};
                                 *reinterpret_cast<f32x4_t*>(frow + nb * 32 + q * 8) = o;
                             }
@@ -764,7 +719,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
                     }
                     // EPI == 2: the routing weight of the assignment this grouped row belongs to
                     const float rw = EPI == 2 ? a.row_weight[a.row_assignment[cur.row0 + m]] : 1.0f;
-                    uint16_t* crow = Cg + (size_t)(cur.row0 + m) * ldc;
+                    uint16_t* crow = Cg + (size_t)(cur.row0 + m) * a.ldc;
 #pragma unroll
                     for (int nb = 0; nb < (SWIGLU ? NB / 2 : NB); ++nb) {
                         // the block stays in its accumulator registers until here: without the
@@ -787,7 +742,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
                             // lanes 32..63 of quad q  <->  lanes 0..31 of quad q+1
                             const auto s0 = __builtin_amdgcn_permlane32_swap(pk[0][0], pk[1][0], false, false);
                             const auto s1 = __builtin_amdgcn_permlane32_swap(pk[0][1], pk[1][1], false, false);
-                            if (GUARD_N && n_lane + nb * 32 + q * 8 >= N_cur) continue;
+                            if (GUARD_N && n_lane + nb * 32 + q * 8 >= a.N) continue;
                             uint4 o;
                             o.x = s0[0]; o.y = s1[0]; o.z = s0[1]; o.w = s1[1];
                             *reinterpret_cast<uint4*>(crow + nb * 32 + q * 8) = o;
@@ -795,7 +750,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, const GemmArgs& d,
                     }
                 }
             };
-            if (cur.n0 + Cfg::BN_OUT <= N_cur) store_tile(std::false_type{});
+            if (cur.n0 + Cfg::BN_OUT <= a.N) store_tile(std::false_type{});
             else store_tile(std::true_type{});
         }
         if (!has_nxt) break;
@@ -824,36 +779,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void grouped_gemm_kernel(GemmArgs a)
     const LdsTables t = lds_tables(lds, Cfg::LDS_BYTES, a.G);
     const int max_units = (a.max_units > 0 && a.max_units < Cfg::MB) ? a.max_units : Cfg::MB;
     if (RAGGED) fill_tables(a, t, 32 * WGM, max_units);
-    // Where nearly every group is one row tile, nothing reads a group's weights a second time, and they are loaded
-    // without a place in the caches; with more tiles per group sharing them through L2 that is slower.  The routing
-    // decides, which only the device knows.  Qwen3-235B-A22B-shaped share, 800 / 1024 / 1500 tokens 146 -> 132, 147 -> 134, 154 -> 137 us,
-    // Qwen3-30B-A3B-shaped layer, 1500 tokens 275 -> 260 (skewed, 1200 tokens: 264 -> 280, so it is not done there).
-    if constexpr (RAGGED && EPI == 0 && MI == 16 && BM <= 160) {
-        int groups = 0;
-        for (int g = 0; g < a.G; g += 64) {
-            const int i = g + (threadIdx.x & 63);
-            groups += __builtin_popcountll(__ballot(i < a.G && t.rowend[i] > t.row0[i]));
-        }
-        if (__builtin_amdgcn_readfirstlane(t.pref[a.G]) * 8 <= groups * 9)
-            return gemm_tiles<BM, BN, BK, STAGES, WGM, WGN, SWIGLU, RAGGED, EPI, PACKED, MI, false, true>(a, a, lds, t.pref, t.row0, t.rowend, t.tile, max_units);
-    }
-    gemm_tiles<BM, BN, BK, STAGES, WGM, WGN, SWIGLU, RAGGED, EPI, PACKED, MI>(a, a, lds, t.pref, t.row0, t.rowend, t.tile, max_units);
-}
-
-// Routed experts and shared experts in one launch: the shared experts' tiles fill what the routed ones leave of the
-// last round, and the other way round; where the routed weights stream from HBM, the shared experts' matrix work runs
-// meanwhile.  Forwards, launches of their own (with the best tile of each) / together: DeepSeek-V2-Lite-shaped layer, 600 / 1531 /
-// 4096 tokens 290 / 258, 364 / 309, 615 / 598 us; DeepSeek-V2-shaped share, 1700 / 5003 / 9000 tokens 379 / 339, 673 / 660, 1049 / 1012;
-// 16384 tokens 1648 / 1695, where the dense launch fills its rounds of 256-row tiles by itself (plan_chunk in moe_ep.hip
-// then keeps them apart).
-template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool SWIGLU, bool PACKED, int MI>
-__global__ __launch_bounds__(WGM* WGN * 64) void grouped_gemm_merged_kernel(GemmArgs a, GemmArgs d)
-{
-    extern __shared__ uint4 lds[];
-    using Cfg = GemmCfg<BM, BN, BK, STAGES, WGM, WGN, SWIGLU>;
-    const LdsTables t = lds_tables(lds, Cfg::LDS_BYTES, a.G);
-    fill_tables(a, t, 32 * WGM, Cfg::MB);
-    gemm_tiles<BM, BN, BK, STAGES, WGM, WGN, SWIGLU, true, 0, PACKED, MI, true>(a, d, lds, t.pref, t.row0, t.rowend, t.tile, Cfg::MB);
+    gemm_tiles<BM, BN, BK, STAGES, WGM, WGN, SWIGLU, RAGGED, EPI, PACKED, MI>(a, lds, t.pref, t.row0, t.rowend, t.tile, max_units);
 }
 
 // what every kernel here assumes of its arguments beyond the shapes the caller has checked
@@ -961,61 +887,9 @@ static hipError_t launch_cfg(const GemmArgs& a, bool swiglu, int n_cu, long long
     X(22, 256, 256, 64, 2, 2, 2, 9, true, 16) \
     X(31, 160, 256, 64, 3, 1, 4, 12, true, 16)
 
-// the variants a launch of routed and shared experts together is built for
-#define MOE_EP_MERGED_VARIANTS(X)  \
-    X(21, 128, 256, 64, 3, 2, 2)   \
-    X(31, 160, 256, 64, 3, 1, 4)
-
-template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool SWIGLU, bool PACKED>
-static hipError_t launch_merged(const GemmArgs& a, const GemmArgs& d, int n_cu, hipStream_t s)
-{
-    using Cfg = GemmCfg<BM, BN, BK, STAGES, WGM, WGN, SWIGLU>;
-    const int lds_bytes = Cfg::LDS_BYTES + lds_table_bytes(true, a.G);
-    if (lds_bytes > kLdsPerWorkgroup || a.K < STAGES * BK || d.K < STAGES * BK) return hipErrorInvalidValue;
-    if (!args_fit(a, SWIGLU, true, BM) || !args_fit(d, SWIGLU, false, BM)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((grouped_gemm_merged_kernel<BM, BN, BK, STAGES, WGM, WGN, SWIGLU, PACKED, 16>), dim3((n_cu + 7) / 8 * 8),
-                       dim3(Cfg::THREADS), lds_bytes, s, a, d);
-    return hipGetLastError();
-}
-
-hipError_t launch_merged_gemm(const GemmArgs& a, const GemmArgs& d, bool swiglu, int variant, int n_cu, hipStream_t s)
-{
-    if (a.K < 64 || a.K % 64 || d.K < 64 || d.K % 64 || !a.offset || a.epi != 0 || a.max_units != 0 || d.offset || d.dense_rows < 1 ||
-        (a.Wp != nullptr) != (d.Wp != nullptr)) return hipErrorInvalidValue;
-    switch (variant) {
-#define X(id, BM, BN, BK, ST, WGM, WGN)                                                               \
-        case id:                                                                                      \
-            if (a.Wp) return swiglu ? launch_merged<BM, BN, BK, ST, WGM, WGN, true, true>(a, d, n_cu, s)     \
-                                    : launch_merged<BM, BN, BK, ST, WGM, WGN, false, true>(a, d, n_cu, s);   \
-            return swiglu ? launch_merged<BM, BN, BK, ST, WGM, WGN, true, false>(a, d, n_cu, s)       \
-                          : launch_merged<BM, BN, BK, ST, WGM, WGN, false, false>(a, d, n_cu, s);
-        MOE_EP_MERGED_VARIANTS(X)
-#undef X
-        default: return hipErrorInvalidValue;
-    }
-}
-
-template <int BM, int BN, int BK, int STAGES, int WGM, int WGN>
-static hipError_t raise_merged()
-{
-    hipError_t e;
-#define R(SW, PK)                                                                                       \
-    if ((e = hipFuncSetAttribute(                                                                       \
-             reinterpret_cast<const void*>(&grouped_gemm_merged_kernel<BM, BN, BK, STAGES, WGM, WGN, SW, PK, 16>), \
-             hipFuncAttributeMaxDynamicSharedMemorySize,                                                \
-             lds_cap(GemmCfg<BM, BN, BK, STAGES, WGM, WGN, SW>::LDS_BYTES + lds_table_bytes(true, kMaxGroups)))) != hipSuccess) return e;
-    R(true, true) R(true, false) R(false, true) R(false, false)
-#undef R
-    return hipSuccess;
-}
-
 hipError_t grouped_gemm_init()
 {
     hipError_t e;
-#define X(id, BM, BN, BK, ST, WGM, WGN)                                                                 \
-    if ((e = raise_merged<BM, BN, BK, ST, WGM, WGN>()) != hipSuccess) return e;
-    MOE_EP_MERGED_VARIANTS(X)
-#undef X
 #define X(id, BM, BN, BK, ST, WGM, WGN, FB, PK, MI)                                      \
     if ((e = raise_all<BM, BN, BK, ST, WGM, WGN, false, MI>()) != hipSuccess) return e;  \
     if constexpr (PK) if ((e = raise_all<BM, BN, BK, ST, WGM, WGN, PK, MI>()) != hipSuccess) return e;

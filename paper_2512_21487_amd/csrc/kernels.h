@@ -88,10 +88,6 @@ hipError_t launch_pack_weights(const GemmArgs& a, bool swiglu, uint16_t* dst, in
 // `offset`; the bound only sizes the grid); ignored in dense mode
 hipError_t launch_grouped_gemm(const GemmArgs& a, bool swiglu, int variant, int n_cu,
                                long long max_rows, hipStream_t s);
-// Ragged groups `routed` and dense groups `shared` in one launch, out of the tiles of `variant` (21 or 31); no other
-// epilogue than epi == 0, no max_units, both or neither with weights in tile order.  hipErrorInvalidValue for a K
-// below 192, or more groups than the variant's LDS holds.
-hipError_t launch_merged_gemm(const GemmArgs& routed, const GemmArgs& shared, bool swiglu, int variant, int n_cu, hipStream_t s);
 // The same projections where few token rows meet every expert (narrow_gemm.hip): the routed groups
 // `routed` (ragged) and, when `shared` is not NULL, the shared experts (dense) in one launch, bit for bit
 // what launch_grouped_gemm writes.  expected_rows: rows per routed group the grid is sized for (any
@@ -103,6 +99,12 @@ constexpr int kNarrowRows = 64, kNarrowWaves = 4;         // tallest row tile, w
 constexpr int kNarrowFewRows = 16, kNarrowFewWaves = 2;   // the same of the tiles for a few tokens
 constexpr int kNarrowWaveRows = 32;                       // weight rows of a wavefront
 constexpr int kNarrowDepth = 4;                           // K steps of 64 in flight per wavefront
+// Tiled projections of prefill with loading wavefronts (loader_gemm.hip): the routed groups `routed` (ragged) and, when
+// `shared` is not NULL, the shared experts (dense) in one launch; no other epilogue than epi == 0, no max_units, both
+// or neither with weights in tile order.
+hipError_t launch_loader_gemm(const GemmArgs& routed, const GemmArgs* shared, bool swiglu, int n_cu, hipStream_t s);
+constexpr int kLoaderRows = 192;                          // tallest row tile
+hipError_t loader_gemm_init();    // raises the dynamic-LDS limit of its kernels once
 hipError_t grouped_gemm_init();   // raises the dynamic-LDS limit of every instantiation once
 // the shape a launch of `variant` really runs (after the fall-backs for a short K or many groups):
 // shape[] = tallest tile rows, weight rows per tile, K step, ring slots, wavefronts in m, in n,

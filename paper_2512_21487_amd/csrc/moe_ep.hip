@@ -54,6 +54,12 @@ bool narrow_under_any_load(int Tn, int k, int El)
 }
 // in last_variants, beside the tile variants of grouped_gemm.hip; the second: tiles for a few tokens
 constexpr int kNarrowVariant = -2, kNarrowFewVariant = -3;
+// The tiled launches of the kernels with loading wavefronts (loader_gemm.hip), as a variant.  Shared experts run beside the
+// routed ones up to kAlongRows rows -- apart (256-row tiles of their own) / along, us: DeepSeek-V2-shaped share, 1600 / 5000 /
+// 10000 / 12000 tokens 349 / 289, 691 / 622, 1146 / 1120, 1330 / 1287, 16384 tokens 1709 / 1711 and on another box 1688 / 1705;
+// DeepSeek-V2-Lite-shaped layer, 1531 / 2700 / 4096 tokens 351 / 304, 462 / 428, 592 / 568 -- and where every reduction has at
+// least kAlongK steps: shorter launches are mostly start-up and epilogue, and were not compared.
+constexpr int kLoaderVariant = -4, kAlongRows = 14336, kAlongK = 512;
 
 struct ProfSpan { hipEvent_t a, b; int stage; int forward; };
 
@@ -74,7 +80,7 @@ struct moe_ep_ctx {
     double narrow_rows = kNarrowMeanRows;
     bool narrow_named = false;   // the number came from the environment: it alone decides
     bool by_rule = true;     // no tile shape, instruction or form of the expert outputs was asked for by name
-    int merge = -1;          // shared and routed experts in one launch: -1 by the cost of both (plan_chunk), 0 never, 1 always
+    int merge = -1;          // shared and routed experts in one tiled launch: -1 by rule (plan_chunk), 0 never, 1 always
     int last_shared_up = -1, last_shared_down = -1;   // tile variants of the shared experts' last launches; before any, shared_variant
     bool fused_gather = true;  // the gate/up projection gathers the token rows itself (no grouped copy)
     int y_mode = 0;            // expert outputs: 0 bf16, 1 fp32, 2 bf16 scaled by the routing weight (expert_out_mode)
@@ -345,19 +351,9 @@ int routed_variant(int Tn, int k, int E, int El, int col_tiles, int K, int n_cu)
     return routed_shape(Tn, k, E, El, col_tiles, K, n_cu)->variant;
 }
 
-// What a launch of the tiled kernels is expected to take, in us: its rounds of tiles, or its weights from HBM.  A
-// 128 x 256 tile takes 15.4 ns per unit of K (DeepSeek-V2-Lite- and DeepSeek-V2-shaped launches of several rounds: 31.6 us with
-// K = 2048, 79 with 5120); launches bound by their weights read 5 TB/s; a launch more costs 4 us.
-constexpr int kCostKnownK = 512;   // shorter reductions are mostly epilogue and launch
-double launch_us(double tiles, double rel, int K, double weight_bytes, int n_cu)
-{
-    const double mfma = ceil(tiles / n_cu - 0.02) * rel * K * 15.4e-3, hbm = weight_bytes / 5.0e6;
-    return 4.0 + (mfma > hbm ? mfma : hbm);
-}
-
 // Tile variant (32 x 32 x 16 form) of a dense launch over `groups` groups of `rows` rows: 256-row tiles cost 10 % less per
 // row than 128-row ones, but leave compute units idle where their number is small
-int dense_variant(int rows, int groups, int col_tiles, int K, int n_cu, double* us)
+int dense_variant(int rows, int groups, int col_tiles, int K, int n_cu)
 {
     const struct { int variant, rows; double rel; } shapes[] = {
         {2, 256, K >= 2048 ? 1.79 : 1.76},
@@ -365,9 +361,10 @@ int dense_variant(int rows, int groups, int col_tiles, int K, int n_cu, double* 
         {1, 128, tile_rel(kRoutedShapes[0], K)},
     };
     int best = 2;
+    double cost = 0.0;
     for (const auto& sh : shapes) {
-        const double t = launch_us((double)((rows + sh.rows - 1) / sh.rows) * groups * col_tiles, sh.rel, K, 0.0, n_cu);
-        if (sh.variant == 2 || t < *us) { best = sh.variant; *us = t; }
+        const double t = ceil((double)((rows + sh.rows - 1) / sh.rows) * groups * col_tiles / n_cu - 0.02) * sh.rel;
+        if (sh.variant == 2 || t < cost) { best = sh.variant; cost = t; }
     }
     return best;
 }
@@ -489,7 +486,7 @@ int moe_ep_create(const moe_ep_config* cfg, moe_ep_ctx** out_ctx)
     if (hipGetDeviceProperties(&prop, cfg->device) != hipSuccess) { delete ctx; return MOE_EP_EHIP; }
     ctx->n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     read_knobs(ctx);
-    if (grouped_gemm_init() != hipSuccess) { delete ctx; return MOE_EP_EHIP; }
+    if (grouped_gemm_init() != hipSuccess || loader_gemm_init() != hipSuccess) { delete ctx; return MOE_EP_EHIP; }
 
     const WsLayout L = ws_layout(*cfg);
     char* slab = nullptr;
@@ -760,9 +757,8 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         if (Tn <= 0) return MOE_EP_OK;
         int v_up = ctx->shared_variant, v_down = v_up;
         if (!ctx->shared_variant_named) {
-            double us;
-            v_up = picked(dense_variant(Tn, Ns, (Hs + 127) / 128, M, n_cu, &us));
-            v_down = picked(dense_variant(Tn, 1, (M + 255) / 256, Ns * Hs, n_cu, &us));
+            v_up = picked(dense_variant(Tn, Ns, (Hs + 127) / 128, M, n_cu));
+            v_down = picked(dense_variant(Tn, 1, (M + 255) / 256, Ns * Hs, n_cu));
         }
         ctx->last_shared_up = v_up; ctx->last_shared_down = v_down;
         GemmArgs g1{}, g2{};
@@ -849,52 +845,27 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
     }
     // How a chunk of Tn tokens runs, and whether `rows` rows of the shared experts run in the same launches (rows = 0:
     // there are none, or they may not).
-    struct Plan { bool narrow, along; int up, down; };
+    struct Plan { bool narrow, loader, along; int up, down; };
     // timing the shared experts' stages takes launches of their own
     const bool shared_timed = prof && (ctx->prof_mask & ((1u << ST_SGEMM1) | (1u << ST_SGEMM2)));
-    const int ct_up = (H + 127) / 128, ct_down = (M + 255) / 256, ct_s = (Hs + 127) / 128;
+    const int ct_up = (H + 127) / 128, ct_down = (M + 255) / 256;
     const auto plan_chunk = [&](int Tn, int rows) -> Plan {
-        Plan p{false, false, -1, -1};
+        Plan p{false, false, false, -1, -1};
         const bool fits = ctx->by_rule && ctx->fused_gather && (unsigned long long)Tn * M * 2 < (1ull << 32);
         // few rows per routed expert: the narrow kernels, bound by the weight stream alone
         const bool beside = rows > 0 && rows <= kNarrowSharedRows;
         if (fits && Tn > 0 && (double)Tn * k / E <= ctx->narrow_rows && (beside || ctx->narrow_named || narrow_under_any_load(Tn, k, El)))
-            return Plan{true, beside && !shared_timed, kNarrowVariant, kNarrowVariant};
-        // tile shapes of the two routed projections: N = H in tiles of 128 activation columns, N = M in
-        // tiles of 256 columns
+            return Plan{true, false, beside && !shared_timed, kNarrowVariant, kNarrowVariant};
+        if (ctx->by_rule && Tn > 0) {
+            const bool pays = rows <= kAlongRows && M >= kAlongK && H >= kAlongK && Hs >= kAlongK;
+            return Plan{false, true, rows > 0 && !shared_timed && (ctx->merge == 1 || (ctx->merge != 0 && pays)), kLoaderVariant, kLoaderVariant};
+        }
+        // a shape, an instruction or a form of the expert outputs was asked for by name: grouped_gemm.hip.  Tile shapes of
+        // the two routed projections: N = H in tiles of 128 activation columns, N = M in tiles of 256 columns
         p.up = ctx->gemm_variant >= 0 ? ctx->gemm_variant : picked(routed_variant(Tn, k, E, El, ct_up, M, n_cu));
         p.down = ctx->gemm_variant >= 0 ? ctx->gemm_variant : picked(routed_variant(Tn, k, E, El, ct_down, H, n_cu));
         if (ctx->up_variant >= 0) p.up = ctx->up_variant;
         if (ctx->down_variant >= 0) p.down = ctx->down_variant;
-        // shared and routed experts in one launch per projection, or in one each: by what both should take, where
-        // launch_us has been held against measurements
-        const bool known = M >= kCostKnownK && H >= kCostKnownK && Hs >= kCostKnownK;
-        if (Tn <= 0 || rows <= 0 || shared_timed || !fits || !(ctx->merge == 1 || (ctx->merge != 0 && known))) return p;
-        const double touched = El * (1.0 - pow(1.0 - (double)k / E, Tn)), w_up = 4.0 * M * H * touched, w_down = w_up / 2;
-        const int Ks = Ns * Hs, worth = (Ks + H / 2) / H > 1 ? (Ks + H / 2) / H : 1;
-        double apart = 0.0, up_one = 1e300, down_one = 1e300, us;
-        dense_variant(rows, Ns, ct_s, M, n_cu, &us); apart += us;
-        dense_variant(rows, 1, ct_down, Ks, n_cu, &us); apart += us;
-        double up_apart = 1e300, down_apart = 1e300;
-        int v_up = -1, v_down = -1;
-        for (const RoutedShape& sh : kRoutedShapes) {
-            if (!sh.automatic) continue;
-            const double routed = expected_row_tiles(Tn, k, E, sh) * El;
-            const int bm = sh.unit_rows * sh.max_units, dense = (rows + bm - 1) / bm;
-            us = launch_us(routed * ct_up, tile_rel(sh, M), M, w_up, n_cu);
-            if (us < up_apart) up_apart = us;
-            us = launch_us(routed * ct_down, tile_rel(sh, H), H, w_down, n_cu);
-            if (us < down_apart) down_apart = us;
-            const int v = picked(sh.variant);
-            int shape[8];
-            const auto is_built = [&](int K) { return grouped_gemm_variant_shape(v, K, true, El, shape) && shape[7] == 16 && shape[0] == bm; };
-            if (!is_built(M < H ? (M < Ks ? M : Ks) : (H < Ks ? H : Ks))) continue;
-            us = launch_us(routed * ct_up + (double)dense * Ns * ct_s, tile_rel(sh, M), M, w_up + 4.0 * M * Hs * Ns, n_cu);
-            if (us < up_one) { up_one = us; v_up = v; }
-            us = launch_us(routed * ct_down + (double)dense * ct_down * worth, tile_rel(sh, H), H, w_down + 2.0 * M * Hs * Ns, n_cu);
-            if (us < down_one) { down_one = us; v_down = v; }
-        }
-        if (v_up >= 0 && v_down >= 0 && (ctx->merge == 1 || up_one + down_one < apart + up_apart + down_apart)) return Plan{false, true, v_up, v_down};
         return p;
     };
     // The shared experts may run beside routed ones -- every token's with the first chunk where they come first -- unless
@@ -922,7 +893,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         const bool takes_all = first_takes_all && cidx == 0;
         const bool interleaved = !dep && Ns > 0 && order == MOE_EP_ORDER_INTERLEAVED;
         const Plan plan = plan_chunk(Tn, rows_beside(cidx, Tn));
-        const bool narrow = plan.narrow, along = plan.along;
+        const bool narrow = plan.narrow, loader = plan.loader, along = plan.along;
         const int v_up = plan.up, v_down = plan.down;
         if (cidx < (int)ctx->last_variants.size()) ctx->last_variants[cidx] = {v_up, v_down, along};
         int32_t* idx = ctx->idx + (size_t)t0 * k;
@@ -971,7 +942,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         bool few = false;   // of the launch that follows
         sp = prof_begin(ctx, prof, ST_GEMM1, s_comp);
         if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g1, along ? &s1 : nullptr, true, n_cu, (double)Tn * k / E, Tn, a_max, s_comp, &few));
-        else if (along) HIP_TRY(ctx, launch_merged_gemm(g1, s1, true, v_up, n_cu, s_comp));
+        else if (loader) HIP_TRY(ctx, launch_loader_gemm(g1, along ? &s1 : nullptr, true, n_cu, s_comp));
         else HIP_TRY(ctx, launch_grouped_gemm(g1, true, v_up, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);
 
@@ -984,7 +955,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         g2.epi = ctx->y_mode; g2.row_weight = w; g2.row_assignment = perm;
         sp = prof_begin(ctx, prof, ST_GEMM2, s_comp);
         if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g2, along ? &s2 : nullptr, false, n_cu, (double)Tn * k / E, Tn, a_max, s_comp, &few));
-        else if (along) HIP_TRY(ctx, launch_merged_gemm(g2, s2, false, v_down, n_cu, s_comp));
+        else if (loader) HIP_TRY(ctx, launch_loader_gemm(g2, along ? &s2 : nullptr, false, n_cu, s_comp));
         else HIP_TRY(ctx, launch_grouped_gemm(g2, false, v_down, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);
         if (few) {   // the gate/up projection has no such tiles
@@ -1071,7 +1042,8 @@ int moe_ep_last_tile_shape(const moe_ep_ctx* ctx, int32_t chunk, int32_t stage, 
     const bool few = variant == kNarrowFewVariant;
     const int waves = few ? kNarrowFewWaves : kNarrowWaves;
     int v[8] = {few ? kNarrowFewRows : kNarrowRows, waves * kNarrowWaveRows, kPackK, kNarrowDepth, 1, waves, 1, 16};   // the narrow kernels
-    if (variant != kNarrowVariant && !few && !grouped_gemm_variant_shape(variant, K, !shared, shared ? 1 : c.n_local, v)) return MOE_EP_ESTATE;
+    if (variant == kLoaderVariant) { v[0] = kLoaderRows; v[1] = kPackRows; v[3] = 3; v[4] = 2; v[5] = 4; }
+    else if (variant != kNarrowVariant && !few && !grouped_gemm_variant_shape(variant, K, !shared, shared ? 1 : c.n_local, v)) return MOE_EP_ESTATE;
     if (mfma_rows) *mfma_rows = v[7];
     if (tile_order) *tile_order = v[6] && (shared ? ctx->last_prepared_shared : ctx->last_prepared_routed);
     if (rows) *rows = v[0];
@@ -1301,7 +1273,7 @@ extern "C" int moe_ep_forward_noalloc(const moe_ep_config* cfg, const void* toke
             }
             hipDeviceProp_t prop;
             if (hipGetDeviceProperties(&prop, cfg->device) != hipSuccess) { set_why(why, "hipGetDeviceProperties failed"); return MOE_EP_EHIP; }
-            if (grouped_gemm_init() != hipSuccess) { set_why(why, "raising the kernels' LDS limit failed"); return MOE_EP_EHIP; }
+            if (grouped_gemm_init() != hipSuccess || loader_gemm_init() != hipSuccess) { set_why(why, "raising the kernels' LDS limit failed"); return MOE_EP_EHIP; }
             slot.base = static_cast<char*>(p);
             ctx->n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
             read_knobs(ctx);
