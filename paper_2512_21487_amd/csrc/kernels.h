@@ -32,8 +32,9 @@ hipError_t launch_gather_rows(const void* tokens, const int32_t* perm, const int
 hipError_t launch_combine(const void* y, const int32_t* pos, const float* w, int Tn, int k, int M,
                           bool accumulate, int y_mode, const void* out_src, void* out, int grid, hipStream_t s);
 
-// ---- chunk transfers over the host link (pinned-host mode); bytes must be a multiple of 4
-hipError_t launch_copy(void* dst, const void* src, size_t bytes, int grid, hipStream_t s, int threads = 256, int unroll = 4);
+// ---- chunk transfers over the host link (pinned-host mode); bytes must be a multiple of 4; lds: bytes of LDS every
+// workgroup keeps other kernels' workgroups out with
+hipError_t launch_copy(void* dst, const void* src, size_t bytes, int grid, hipStream_t s, int threads = 256, int unroll = 4, int lds = 0);
 // a one-wavefront kernel that lasts about `microseconds` (at most 1 s): stand-in for a task that
 // runs on other hardware
 hipError_t launch_busy(double microseconds, hipStream_t s);

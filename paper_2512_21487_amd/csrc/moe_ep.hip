@@ -61,6 +61,16 @@ constexpr int kNarrowVariant = -2, kNarrowFewVariant = -3;
 // least kAlongK steps: shorter launches are mostly start-up and epilogue, and were not compared.
 constexpr int kLoaderVariant = -4, kAlongRows = 14336, kAlongK = 512;
 
+// Chunks that arrive while others are multiplied (moe_ep_forward): kLinkUnits copy workgroups of four wavefronts (128 KB over the link, as
+// 64 of one), and a projection's launch that runs beside them leaves them as many compute units.  They ask for LDS they do not
+// use, more than a workgroup of loader_gemm.hip leaves: on one compute unit the projection's loads would queue behind
+// reads that take microseconds, and the launch lasts as long as its slowest workgroup.  Qwen3-235B-A22B-shaped share, 4096 tokens
+// in two chunks: gate/up beside the second chunk's transfer 155 -> 84 us, gate 28 -> 9, forward 1362 -> 1334; four chunks 1494 ->
+// 1379, 2000 tokens in two 805 -> 740.  (Not in moe_ep_forward_dep, whose other launches fill every compute unit.)  The same
+// forwards with a chunk's outbound rows on a stream of their own beside the next chunk's projections, in one to eight pieces, on
+// 2 to 128 workgroups: 1320 - 1400 us and more, the two directions slow each other and the projections down.
+constexpr int kLinkUnits = 16, kLinkLds = 24 * 1024;
+
 struct ProfSpan { hipEvent_t a, b; int stage; int forward; };
 
 }  // namespace
@@ -98,6 +108,7 @@ struct moe_ep_ctx {
     // lasts as long as its slowest tile): 4096 decode tokens in 2 chunks 1.53 -> 1.44 ms
     int link_grid = 64;
     int link_threads = 64, link_unroll = 2;
+    bool link_named = false;   // one of these came from the environment
     bool memcpy_in = false, memcpy_out = false;  // host-link copies through the runtime instead of kernels
     bool check_spans = true;   // every forward asks the runtime what its pointer arguments point at
     // Weights in tile order (moe_ep_prepare_weights): copies of the gate/up and of the down weights laid
@@ -229,6 +240,7 @@ void read_knobs(moe_ep_ctx* ctx)
     if (const char* v = getenv("MOE_EP_LINK_GRID")) ctx->link_grid = atoi(v) > 0 ? atoi(v) : 64;
     if (const char* v = getenv("MOE_EP_LINK_THREADS")) ctx->link_threads = (atoi(v) >= 64 && atoi(v) <= 256 && atoi(v) % 64 == 0) ? atoi(v) : 64;
     if (const char* v = getenv("MOE_EP_LINK_UNROLL")) ctx->link_unroll = atoi(v) >= 1 ? atoi(v) : 2;
+    ctx->link_named = getenv("MOE_EP_LINK_GRID") || getenv("MOE_EP_LINK_THREADS") || getenv("MOE_EP_LINK_UNROLL");
     // MOE_EP_LINK_MEMCPY = 1 | in | out: the runtime's asynchronous copies (DMA engines) instead of copy
     // kernels in both / one direction, kept for comparison: inbound they overlap cleanly with compute,
     // but each call costs the host thread 0.2-0.3 ms on this system
@@ -710,9 +722,11 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         }
     }
     ctx->last_T = T; ctx->last_k = k; ctx->last_r = r; ctx->last_r1 = r_1;
+    const bool units_apart = pinned && !dep && r > 1 && !ctx->link_named;
     auto link_copy = [&](void* dst, const void* src, size_t bytes, int grid, hipStream_t st) -> hipError_t {
         if (st == s_in ? ctx->memcpy_in : ctx->memcpy_out)
             return bytes ? hipMemcpyAsync(dst, src, bytes, hipMemcpyDefault, st) : hipSuccess;
+        if (units_apart) return launch_copy(dst, src, bytes, kLinkUnits, st, 256, 2, kLinkLds);
         return launch_copy(dst, src, bytes, grid, st, ctx->link_threads, ctx->link_unroll);
     };
     const int link_grid = ctx->link_grid;
@@ -924,6 +938,8 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         }
 
         const long long a_max = (long long)Tn * k;  // the most rows the routing can keep
+        // the next chunk is on the link (shared experts that come first have waited for every chunk)
+        const int cus = units_apart && !shared_first && cidx + 1 < r ? n_cu - kLinkUnits : n_cu;
 
         GemmArgs g1{};
         routed_up_w(g1);
@@ -942,7 +958,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         bool few = false;   // of the launch that follows
         sp = prof_begin(ctx, prof, ST_GEMM1, s_comp);
         if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g1, along ? &s1 : nullptr, true, n_cu, (double)Tn * k / E, Tn, a_max, s_comp, &few));
-        else if (loader) HIP_TRY(ctx, launch_loader_gemm(g1, along ? &s1 : nullptr, true, n_cu, s_comp));
+        else if (loader) HIP_TRY(ctx, launch_loader_gemm(g1, along ? &s1 : nullptr, true, cus, s_comp));
         else HIP_TRY(ctx, launch_grouped_gemm(g1, true, v_up, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);
 
@@ -955,7 +971,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         g2.epi = ctx->y_mode; g2.row_weight = w; g2.row_assignment = perm;
         sp = prof_begin(ctx, prof, ST_GEMM2, s_comp);
         if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g2, along ? &s2 : nullptr, false, n_cu, (double)Tn * k / E, Tn, a_max, s_comp, &few));
-        else if (loader) HIP_TRY(ctx, launch_loader_gemm(g2, along ? &s2 : nullptr, false, n_cu, s_comp));
+        else if (loader) HIP_TRY(ctx, launch_loader_gemm(g2, along ? &s2 : nullptr, false, cus, s_comp));
         else HIP_TRY(ctx, launch_grouped_gemm(g2, false, v_down, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);
         if (few) {   // the gate/up projection has no such tiles

@@ -27,7 +27,7 @@ __global__ __launch_bounds__(256) void copy_kernel(const V* __restrict__ src, V*
 }
 
 // grid workgroups of `threads` lanes, `unroll` loads in flight per lane (1, 2 or 4)
-hipError_t launch_copy(void* dst, const void* src, size_t bytes, int grid, hipStream_t s, int threads, int unroll)
+hipError_t launch_copy(void* dst, const void* src, size_t bytes, int grid, hipStream_t s, int threads, int unroll, int lds)
 {
     if (bytes == 0) return hipSuccess;
     if (threads < 64 || threads > 256 || threads % 64) return hipErrorInvalidValue;
@@ -35,11 +35,11 @@ hipError_t launch_copy(void* dst, const void* src, size_t bytes, int grid, hipSt
     if (a16) {
         auto* sp = static_cast<const uint4*>(src);
         auto* dp = static_cast<uint4*>(dst);
-        if (unroll >= 4) hipLaunchKernelGGL((copy_kernel<uint4, 4>), dim3(grid), dim3(threads), 0, s, sp, dp, bytes / 16);
-        else if (unroll >= 2) hipLaunchKernelGGL((copy_kernel<uint4, 2>), dim3(grid), dim3(threads), 0, s, sp, dp, bytes / 16);
-        else hipLaunchKernelGGL((copy_kernel<uint4, 1>), dim3(grid), dim3(threads), 0, s, sp, dp, bytes / 16);
+        if (unroll >= 4) hipLaunchKernelGGL((copy_kernel<uint4, 4>), dim3(grid), dim3(threads), lds, s, sp, dp, bytes / 16);
+        else if (unroll >= 2) hipLaunchKernelGGL((copy_kernel<uint4, 2>), dim3(grid), dim3(threads), lds, s, sp, dp, bytes / 16);
+        else hipLaunchKernelGGL((copy_kernel<uint4, 1>), dim3(grid), dim3(threads), lds, s, sp, dp, bytes / 16);
     } else {  // 4-byte granularity (gate scores of a chunk need not start on a 16-byte boundary)
-        hipLaunchKernelGGL((copy_kernel<uint32_t, 4>), dim3(grid), dim3(threads), 0, s, static_cast<const uint32_t*>(src),
+        hipLaunchKernelGGL((copy_kernel<uint32_t, 4>), dim3(grid), dim3(threads), lds, s, static_cast<const uint32_t*>(src),
                            static_cast<uint32_t*>(dst), bytes / 4);
     }
     return hipGetLastError();
