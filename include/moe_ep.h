@@ -371,8 +371,9 @@ int32_t moe_ep_routed_tile_rows(const moe_ep_config *cfg, int32_t n_tokens, int3
  * v_mfma_f32_16x16x32_bf16, 32: v_mfma_f32_32x32x16_bf16), so that a measurement can name the kernel it
  * timed.  By default a chunk runs kernels with loading wavefronts: 192 rows, 256 weight rows, 3 ring slots, 2 x 4
  * (multiplying) wavefronts.  Chunks with few rows per expert run kernels that hold their weights in registers: 64 rows, 128
- * weight rows, 1 x 4 wavefronts (a down projection of at most 16 tokens that leaves compute units idle so: 16 rows,
- * 64 weight rows, 1 x 2 wavefronts), and the K steps in flight in place of ring slots.  For a chunk without a token, and
+ * weight rows, 1 x 4 wavefronts (up to 32 tokens, where that spreads the weights better over the compute units: 16 rows, 32
+ * weight rows, 1 x 1; 16 rows, 64 weight rows, 1 x 2; 32 rows, 64 weight rows, 1 x 2), and the K steps in flight in place
+ * of ring slots.  For a chunk without a token, and
  * for the shared experts before their first launch, the shape that would be launched.  Any pointer may be NULL.
  * MOE_EP_ESTATE before any forward or for a stage the layer does not have.
  */

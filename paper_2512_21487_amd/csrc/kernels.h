@@ -93,11 +93,15 @@ hipError_t launch_grouped_gemm(const GemmArgs& a, bool swiglu, int variant, int 
 // `routed` (ragged) and, when `shared` is not NULL, the shared experts (dense) in one launch, bit for bit
 // what launch_grouped_gemm writes.  expected_rows: rows per routed group the grid is sized for (any
 // routing is served); max_tokens: the most rows one routed group can have; no other epilogue than epi == 0.
-// few: set to whether the launch's tiles were those for a few tokens.
+// kind: the tiles launched: kNarrowTiles[*kind].
 hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bool swiglu, int n_cu, double expected_rows,
-                              int max_tokens, long long max_rows, hipStream_t s, bool* few);
+                              int max_tokens, long long max_rows, hipStream_t s, int* kind);
 constexpr int kNarrowRows = 64, kNarrowWaves = 4;         // tallest row tile, wavefronts
-constexpr int kNarrowFewRows = 16, kNarrowFewWaves = 2;   // the same of the tiles for a few tokens
+constexpr int kNarrowFewRows = 16, kNarrowFewWaves = 2;   // the same of the tiles for a few tokens; also of one wavefront
+constexpr int kNarrowPairRows = 32;                       // and of two wavefronts for some more
+struct NarrowTiles { int rows, waves; };
+constexpr NarrowTiles kNarrowTiles[4] = {{kNarrowRows, kNarrowWaves}, {kNarrowFewRows, kNarrowFewWaves}, {kNarrowFewRows, 1}, {kNarrowPairRows, kNarrowFewWaves}};
+constexpr int kNarrowFineK = 1024;                        // shortest reduction the last two are for
 constexpr int kNarrowWaveRows = 32;                       // weight rows of a wavefront
 constexpr int kNarrowDepth = 4;                           // K steps of 64 in flight per wavefront
 // Tiled projections of prefill with loading wavefronts (loader_gemm.hip): the routed groups `routed` (ragged) and, when

@@ -52,14 +52,14 @@ bool narrow_under_any_load(int Tn, int k, int El)
     const int tiles = (Tn + kNarrowRows - 1) / kNarrowRows;
     return tiles <= kNarrowGroupTiles && (k < El ? k : El) * tiles <= kNarrowLoadTiles * El;
 }
-// in last_variants, beside the tile variants of grouped_gemm.hip; the second: tiles for a few tokens
-constexpr int kNarrowVariant = -2, kNarrowFewVariant = -3;
+// in last_variants, beside the tile variants of grouped_gemm.hip: kNarrowVariant - i stands for kNarrowTiles[i]
+constexpr int kNarrowVariant = -2;
 // The tiled launches of the kernels with loading wavefronts (loader_gemm.hip), as a variant.  Shared experts run beside the
 // routed ones up to kAlongRows rows -- apart (256-row tiles of their own) / along, us: DeepSeek-V2-shaped share, 1600 / 5000 /
 // 10000 / 12000 tokens 349 / 289, 691 / 622, 1146 / 1120, 1330 / 1287, 16384 tokens 1709 / 1711 and on another box 1688 / 1705;
 // DeepSeek-V2-Lite-shaped layer, 1531 / 2700 / 4096 tokens 351 / 304, 462 / 428, 592 / 568 -- and where every reduction has at
 // least kAlongK steps: shorter launches are mostly start-up and epilogue, and were not compared.
-constexpr int kLoaderVariant = -4, kAlongRows = 14336, kAlongK = 512;
+constexpr int kLoaderVariant = -9, kAlongRows = 14336, kAlongK = 512;
 
 // Chunks that arrive while others are multiplied (moe_ep_forward): kLinkUnits copy workgroups of four wavefronts (128 KB over the link, as
 // 64 of one), and a projection's launch that runs beside them leaves them as many compute units.  They ask for LDS they do not
@@ -955,9 +955,9 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
             shared_args(takes_all ? 0 : t0, takes_all ? T : Tn, s1, s2);
             ctx->last_shared_up = v_up; ctx->last_shared_down = v_down;
         }
-        bool few = false;   // of the launch that follows
+        int kind_up = 0, kind_down = 0;   // of the narrow launches that follow
         sp = prof_begin(ctx, prof, ST_GEMM1, s_comp);
-        if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g1, along ? &s1 : nullptr, true, n_cu, (double)Tn * k / E, Tn, a_max, s_comp, &few));
+        if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g1, along ? &s1 : nullptr, true, n_cu, (double)Tn * k / E, Tn, a_max, s_comp, &kind_up));
         else if (loader) HIP_TRY(ctx, launch_loader_gemm(g1, along ? &s1 : nullptr, true, cus, s_comp));
         else HIP_TRY(ctx, launch_grouped_gemm(g1, true, v_up, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);
@@ -970,13 +970,14 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         g2.max_units = ctx->down_units;
         g2.epi = ctx->y_mode; g2.row_weight = w; g2.row_assignment = perm;
         sp = prof_begin(ctx, prof, ST_GEMM2, s_comp);
-        if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g2, along ? &s2 : nullptr, false, n_cu, (double)Tn * k / E, Tn, a_max, s_comp, &few));
+        if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g2, along ? &s2 : nullptr, false, n_cu, (double)Tn * k / E, Tn, a_max, s_comp, &kind_down));
         else if (loader) HIP_TRY(ctx, launch_loader_gemm(g2, along ? &s2 : nullptr, false, cus, s_comp));
         else HIP_TRY(ctx, launch_grouped_gemm(g2, false, v_down, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);
-        if (few) {   // the gate/up projection has no such tiles
-            if (cidx < (int)ctx->last_variants.size()) ctx->last_variants[cidx].down = kNarrowFewVariant;
-            if (along) ctx->last_shared_down = kNarrowFewVariant;
+        if (narrow) {
+            const int u = kNarrowVariant - kind_up, v = kNarrowVariant - kind_down;
+            if (cidx < (int)ctx->last_variants.size()) { ctx->last_variants[cidx].up = u; ctx->last_variants[cidx].down = v; }
+            if (along) { ctx->last_shared_up = u; ctx->last_shared_down = v; }
         }
 
         if (interleaved && !along) {
@@ -1055,11 +1056,11 @@ int moe_ep_last_tile_shape(const moe_ep_ctx* ctx, int32_t chunk, int32_t stage, 
     const moe_ep_config& c = ctx->cfg;
     const int variant = shared ? (up ? ctx->last_shared_up : ctx->last_shared_down) : (up ? ctx->last_variants[chunk].up : ctx->last_variants[chunk].down);
     const int K = shared ? (up ? c.hidden : c.n_shared * c.shared_inter) : (up ? c.hidden : c.inter);
-    const bool few = variant == kNarrowFewVariant;
-    const int waves = few ? kNarrowFewWaves : kNarrowWaves;
-    int v[8] = {few ? kNarrowFewRows : kNarrowRows, waves * kNarrowWaveRows, kPackK, kNarrowDepth, 1, waves, 1, 16};   // the narrow kernels
+    const bool narrow = variant <= kNarrowVariant && variant > kLoaderVariant;
+    const NarrowTiles nt = kNarrowTiles[narrow ? kNarrowVariant - variant : 0];
+    int v[8] = {nt.rows, nt.waves * kNarrowWaveRows, kPackK, kNarrowDepth, 1, nt.waves, 1, 16};
     if (variant == kLoaderVariant) { v[0] = kLoaderRows; v[1] = kPackRows; v[3] = 3; v[4] = 2; v[5] = 4; }
-    else if (variant != kNarrowVariant && !few && !grouped_gemm_variant_shape(variant, K, !shared, shared ? 1 : c.n_local, v)) return MOE_EP_ESTATE;
+    else if (!narrow && !grouped_gemm_variant_shape(variant, K, !shared, shared ? 1 : c.n_local, v)) return MOE_EP_ESTATE;
     if (mfma_rows) *mfma_rows = v[7];
     if (tile_order) *tile_order = v[6] && (shared ? ctx->last_prepared_shared : ctx->last_prepared_routed);
     if (rows) *rows = v[0];

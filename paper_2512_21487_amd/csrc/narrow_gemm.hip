@@ -15,6 +15,7 @@
 //
 // Every output element is accumulated over K in the order of grouped_gemm.hip by the same instruction, and the
 // epilogue rounds at the same place: the results are the same bits.
+#include <cmath>
 #include <type_traits>
 
 #include "common.h"
@@ -41,6 +42,10 @@ using NarrowStream = NarrowCfg<kNarrowDepth, kNarrowRows, kNarrowWaves>;
 // tiles leaves compute units without one, half as wide tiles halve what the busiest one has to draw: down projection
 // of one token of the DeepSeek-V2-Lite-shaped layer, 112 workgroups, the shared experts' 720 KB each, forward 47 -> 43 us.
 using NarrowFew = NarrowCfg<kNarrowDepth, kNarrowFewRows, kNarrowFewWaves>;
+// Small tiles in single wavefronts or pairs of them spread a few experts' weights evenly over the compute units, whatever the
+// number of tiles is: the choice is launch_narrow_gemm's.
+using NarrowFine = NarrowCfg<kNarrowDepth, kNarrowFewRows, 1>;
+using NarrowPair = NarrowCfg<kNarrowDepth, kNarrowPairRows, kNarrowFewWaves>;
 constexpr int kTurnBytes = 16 * kPackK * 2;                       // one block of 16 weight rows of a K step
 
 // one wavefront's share of a tile: uniform bases, the lane's byte offsets, and how the weight base moves
@@ -109,12 +114,14 @@ __device__ __forceinline__ void narrow_tile(const NarrowTile<Cfg>& t, int nrows,
     auto load_x = [&](int ch) __attribute__((always_inline)) {
         const uint32_t k_off = min((uint32_t)(ch * Cfg::ROW_BYTES + st_chunk * 16), (uint32_t)t.KT * (kPackK * 2) - 16u);
 #pragma unroll
-        for (int i = 0; i < PASSES; ++i) st[i] = load16(t.x, t.x_off[i] + k_off, 0);
+        for (int i = 0; i < PASSES; ++i)
+            if (Cfg::PASS_ROWS > 1 || i < nrows) st[i] = load16(t.x, t.x_off[i] + k_off, 0);   // a row a load: none for rows that are not there
     };
     auto stage_x = [&](int ch) __attribute__((always_inline)) {
         char* buf = lds + (ch & 1) * Cfg::BUFFER_BYTES;
 #pragma unroll
         for (int i = 0; i < PASSES; ++i) {
+            if (Cfg::PASS_ROWS == 1 && i >= nrows) continue;
             const int r = st_row + Cfg::PASS_ROWS * i;
             *reinterpret_cast<uint4*>(buf + r * Cfg::ROW_BYTES + (st_chunk ^ (r & 15)) * 16) = st[i];
         }
@@ -253,8 +260,11 @@ __device__ __forceinline__ void narrow_dispatch(const GemmArgs& a, int g, int ro
     uint16_t* c = a.C + (size_t)g * a.c_group_col_stride + (size_t)row0 * a.ldc + n;
     if constexpr (Cfg::ROWS == 16) {
         narrow_tile<Cfg, SWIGLU, PACKED, 1>(t, nrows, tid, lds, stores, c, a.ldc);
+    } else if constexpr (Cfg::ROWS == 32) {   // launched where no group has more rows
+        if (nrows <= 16) narrow_tile<Cfg, SWIGLU, PACKED, 1>(t, nrows, tid, lds, stores, c, a.ldc);
+        else narrow_tile<Cfg, SWIGLU, PACKED, 2>(t, nrows, tid, lds, stores, c, a.ldc);
     } else {
-        static_assert(Cfg::ROWS == 16 || Cfg::ROWS == 64, "row blocks of a tile");
+        static_assert(Cfg::ROWS == 64, "row blocks of a tile");
         // The row tiles of a group that has several, 48 or 64 rows each, read the same weights at about the same time
         // through one L2, so these stay in the caches.  All tokens on the same experts, non-temporal / cached:
         // DeepSeek-V2-shaped share, 200 / 400 tokens 246 / 188, 368 / 279 us, Qwen3-235B-A22B-shaped share, 384 tokens 263 / 237.
@@ -353,7 +363,7 @@ static bool narrow_args_fit(const GemmArgs& a)
 }
 
 hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bool swiglu, int n_cu, double expected_rows,
-                              int max_tokens, long long max_rows, hipStream_t s, bool* few)
+                              int max_tokens, long long max_rows, hipStream_t s, int* kind)
 {
     GemmArgs none{};
     const GemmArgs& sh = shared ? *shared : none;
@@ -383,10 +393,34 @@ hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bo
     // no group has more than max_tokens rows: one row tile each; of a share, about `kept` rows stay here
     const long long kept = (long long)(expected_rows * routed.G + 0.999);
     const bool one_block = max_tokens <= NarrowFew::ROWS && (!shared || sh.dense_rows <= NarrowFew::ROWS);
-    *few = !swiglu && one_block && grid_for(kNarrowRows, narrow_cols<NarrowStream, false>(), kept < filled ? kept : filled) <= n_cu;
-    if (swiglu) with(NarrowStream{}, std::true_type{});
-    else if (*few) with(NarrowFew{}, std::false_type{});
-    else with(NarrowStream{}, std::false_type{});
+    const bool two_blocks = max_tokens <= NarrowPair::ROWS && (!shared || sh.dense_rows <= NarrowPair::ROWS);
+    *kind = !swiglu && one_block && grid_for(kNarrowRows, narrow_cols<NarrowStream, false>(), kept < filled ? kept : filled) <= n_cu ? 1 : 0;
+    if (two_blocks && routed.K >= kNarrowFineK && (!shared || sh.K >= kNarrowFineK)) {
+        // What the busiest compute unit draws (columns times K) out of tiles of w wavefronts spread evenly, the experts
+        // expected to have a row each.  Smaller tiles where that is less; with a short K the launch is start-up.  Forwards, us,
+        // tiles of four (down: two) wavefronts / one: DeepSeek-V2-Lite-shaped layer, 1 / 2 / 4 / 8 tokens 42.6 / 40.2, 62.1 / 57.0, 88.3 /
+        // 82.1, 127 / 120; DeepSeek-V2-shaped share, 1 / 4 / 16 tokens 58.0 / 49.2, 65.5 / 60.3, 130 / 111; Qwen3-235B-A22B-shaped share, 1 / 2
+        // tokens 25.2 / 21.6, 31.8 / 26.8; with 8 K steps in flight instead of 4 44.4, 61.6, 90.7, 134; 52.5, 62.2, 118; 23.2, 30.0.
+        // Four / two wavefronts, 32 rows: DeepSeek-V2-shaped share, 20 / 33 tokens 135 / 120, 145 / 135, Qwen3-235B-A22B-shaped share, 24 / 32
+        // tokens 103 / 95, 104 / 100 (all on eight experts, 20 tokens: 69 / 72).  Beyond 32 tokens an expert can have a second
+        // tile: balanced loads of 33 to 64 tokens still gain 1 - 4 %, all tokens on eight experts lose 25 %.
+        const double worth = shared ? (double)sh.K / routed.K : 0.0, touched = routed.G * (1.0 - std::exp(-expected_rows));
+        const auto busiest = [&](int w) {
+            const int cols = w * (swiglu ? 16 : 32);
+            const double tiles = (double)((routed.N + cols - 1) / cols) * touched + (shared ? worth * ((sh.N + cols - 1) / cols) * sh.G : 0.0);
+            return w * std::fmax(std::ceil(tiles / n_cu), worth);
+        };
+        const double now = busiest(*kind ? kNarrowFewWaves : kNarrowWaves);
+        if (one_block) { if (busiest(1) < now) *kind = 2; }
+        else if (busiest(kNarrowFewWaves) < now) *kind = 3;
+    }
+    const auto pick = [&](auto sw) {
+        if (*kind == 3) with(NarrowPair{}, sw);
+        else if (*kind == 2) with(NarrowFine{}, sw);
+        else if (*kind == 1) with(NarrowFew{}, sw);
+        else with(NarrowStream{}, sw);
+    };
+    if (swiglu) pick(std::true_type{}); else pick(std::false_type{});
     return hipGetLastError();
 }
 
