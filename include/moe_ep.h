@@ -55,7 +55,8 @@ typedef enum {
                                  out, standing in for the A2E / E2A transfers (Sec. 2.2; Eq.
                                  a2e_detail): inbound as a copy on a stream of the context
                                  (a chunk's gate scores first: gate and partition run while its
-                                 token rows are still on the link),
+                                 token rows are still on the link; the first chunk of
+                                 moe_ep_forward beside the gate, on the caller's stream),
                                  outbound as the aggregation's own stores into the host buffer
                                  (moe_ep_forward; the environment variable MOE_EP_FUSED_OUT=0
                                  makes it a copy on a second stream) or as such a copy

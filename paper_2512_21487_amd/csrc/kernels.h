@@ -8,13 +8,16 @@ namespace moe_ep {
 // tokens per router / permute workgroup: one bit each in a 64-bit mask per expert
 constexpr int kTokPerBlock = 64;
 
+// Token rows that a launch of the gate brings in beside its own work (16-byte aligned; first: set by the launcher)
+struct RowCopy { void* dst; const void* src; size_t bytes; int first; };
+
 // ---- gate: softmax + top-k (Sec. 2.1) and per-workgroup expert bit masks for the partition
 hipError_t launch_router(const float* logits, int Tn, int E, int k, int e0, int El, int32_t* idx,
-                         float* w, unsigned long long* blk_mask, hipStream_t s);
+                         float* w, unsigned long long* blk_mask, hipStream_t s, const RowCopy* copy = nullptr);
 
 // gate and partition of at most kTokPerBlock tokens in one launch; outputs as launch_router and launch_dispatch
 hipError_t launch_route_and_partition(const float* logits, int Tn, int E, int k, int e0, int El, int32_t* idx, float* w,
-                                      int32_t* count, int32_t* offset, int32_t* pos, int32_t* perm, hipStream_t s);
+                                      int32_t* count, int32_t* offset, int32_t* pos, int32_t* perm, hipStream_t s, const RowCopy* copy = nullptr);
 
 // ---- partition by expert (Sec. 2.1; Sec. 3.1 "The MoE Part")
 // count [El], offset [El + 1], pos [Tn * k] (row of an assignment or -1), perm [rows] (row -> assignment)

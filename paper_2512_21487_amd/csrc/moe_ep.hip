@@ -721,6 +721,12 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
             if (&x == &sp[2]) h_out = static_cast<char*>(const_cast<void*>(dev));
         }
     }
+    // One chunk: the gate's launch reads the scores where the caller has them and brings the token rows in, on the caller's
+    // stream.  Several chunks' inbound transfers have a stream of their own, as has one that is timed.
+    const bool in_place = pinned && !dep && r == 1 && !ctx->memcpy_in && !(reinterpret_cast<uintptr_t>(h_tokens) & 15) &&
+                          !(prof && (ctx->prof_mask & (1u << ST_COPY_IN)));
+    const bool inbound = pinned && !in_place;
+    if (in_place) log_dev = reinterpret_cast<const float*>(h_logits);
     ctx->last_T = T; ctx->last_k = k; ctx->last_r = r; ctx->last_r1 = r_1;
     const bool units_apart = pinned && !dep && r > 1 && !ctx->link_named;
     auto link_copy = [&](void* dst, const void* src, size_t bytes, int grid, hipStream_t st) -> hipError_t {
@@ -732,10 +738,10 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
     const int link_grid = ctx->link_grid;
     const int span_total = prof_begin(ctx, prof, ST_TOTAL, user);
     hipStream_t s_ag = dep ? ctx->s_ag : user;  // attention stand-ins and, in dep mode, the shared experts
-    if (pinned || dep) HIP_TRY(ctx, hipEventRecord(ctx->ev_start, user));
-    if (pinned) {
+    if (inbound || dep) HIP_TRY(ctx, hipEventRecord(ctx->ev_start, user));
+    if (inbound) {
         HIP_TRY(ctx, hipStreamWaitEvent(s_in, ctx->ev_start, 0));
-        HIP_TRY(ctx, hipStreamWaitEvent(s_out, ctx->ev_start, 0));
+        if (!fused_out) HIP_TRY(ctx, hipStreamWaitEvent(s_out, ctx->ev_start, 0));
     }
     if (dep) HIP_TRY(ctx, hipStreamWaitEvent(s_ag, ctx->ev_start, 0));
     const int bw_grid = n_cu * 8;  // bandwidth kernels: 8 workgroups of 4 wavefronts per CU
@@ -850,7 +856,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
                 const int rc = shared_of_micro_batch(i);
                 if (rc != MOE_EP_OK) return rc;
             }
-    } else if (pinned) {
+    } else if (inbound) {
         // all chunks are queued at once on their own stream
         for (int cidx = 0; cidx < r; ++cidx) {
             const int rc = enqueue_inbound(cidx);
@@ -890,8 +896,27 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
     int c0_t0, c0_Tn;
     chunk_range(T, r_1, r_2, 0, &c0_t0, &c0_Tn);
     const bool first_takes_all = shared_first && plan_chunk(c0_Tn, rows_beside(0, c0_Tn)).along;
+    const auto gate = [&](int cidx) -> int {
+        int t0, Tn;
+        chunk_range(T, r_1, r_2, cidx, &t0, &Tn);
+        int32_t* idx = ctx->idx + (size_t)t0 * k;
+        float* w = ctx->w + (size_t)t0 * k;
+        // gate and partition need the chunk's gate scores only, which travel first
+        if (inbound) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_scores[cidx], 0));
+        else if (dep && cidx % r_2 == 0) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_attn[cidx / r_2], 0));
+        const RowCopy rows{ctx->d_tokens, h_tokens, (size_t)T * M * 2, 0};
+        const int sp = prof_begin(ctx, prof, ST_ROUTER, s_comp);
+        if (Tn > 0 && Tn <= kTokPerBlock)   // one workgroup's tokens: partitioned in the same launch
+            HIP_TRY(ctx, launch_route_and_partition(log_dev + (size_t)t0 * E, Tn, E, k, e0, El, idx, w, ctx->count + (size_t)cidx * El,
+                                                    ctx->offset + (size_t)cidx * (El + 1), ctx->pos + (size_t)t0 * k, ctx->perm + (size_t)t0 * k,
+                                                    s_comp, in_place ? &rows : nullptr));
+        else HIP_TRY(ctx, launch_router(log_dev + (size_t)t0 * E, Tn, E, k, e0, El, idx, w, ctx->blk_mask, s_comp, in_place ? &rows : nullptr));
+        prof_end(ctx, sp, s_comp);
+        return MOE_EP_OK;
+    };
+    if (in_place) { const int rc = gate(0); if (rc != MOE_EP_OK) return rc; }
     if (shared_first && !first_takes_all) {
-        if (pinned) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[r - 1], 0));
+        if (inbound) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[r - 1], 0));
         int rc = run_shared(0, T, s_comp);
         if (rc != MOE_EP_OK) return rc;
     }
@@ -901,9 +926,6 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         chunk_range(T, r_1, r_2, cidx, &t0, &Tn);
         int32_t* count = ctx->count + (size_t)cidx * El;
         int32_t* offset = ctx->offset + (size_t)cidx * (El + 1);
-        // gate and partition need the chunk's gate scores only, which travel first
-        if (pinned) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_scores[cidx], 0));
-        else if (dep && cidx % r_2 == 0) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_attn[cidx / r_2], 0));
         const bool takes_all = first_takes_all && cidx == 0;
         const bool interleaved = !dep && Ns > 0 && order == MOE_EP_ORDER_INTERLEAVED;
         const Plan plan = plan_chunk(Tn, rows_beside(cidx, Tn));
@@ -915,23 +937,20 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         int32_t* pos = ctx->pos + (size_t)t0 * k;
         int32_t* perm = ctx->perm + (size_t)t0 * k;
 
-        int sp = prof_begin(ctx, prof, ST_ROUTER, s_comp);
-        const bool one_block = Tn > 0 && Tn <= kTokPerBlock;   // one workgroup's tokens: partitioned in the same launch
-        if (one_block) HIP_TRY(ctx, launch_route_and_partition(log_dev + (size_t)t0 * E, Tn, E, k, e0, El, idx, w, count, offset, pos, perm, s_comp));
-        else HIP_TRY(ctx, launch_router(log_dev + (size_t)t0 * E, Tn, E, k, e0, El, idx, w, ctx->blk_mask, s_comp));
-        prof_end(ctx, sp, s_comp);
+        if (!in_place) { const int rc = gate(cidx); if (rc != MOE_EP_OK) return rc; }
+        const bool one_block = Tn > 0 && Tn <= kTokPerBlock;
 
         // the fused gather addresses a chunk's token rows with 32-bit byte offsets
         const bool fused = ctx->fused_gather && (unsigned long long)Tn * M * 2 < (1ull << 32);
-        sp = prof_begin(ctx, prof, ST_PARTITION, s_comp);
+        int sp = prof_begin(ctx, prof, ST_PARTITION, s_comp);
         if (!one_block) HIP_TRY(ctx, launch_dispatch(idx, ctx->blk_mask, Tn, k, e0, El, count, offset, pos, perm, s_comp));
         if (Tn > 0 && !fused) {   // the grouped copy reads the token rows
-            if (pinned) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[cidx], 0));
+            if (inbound) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[cidx], 0));
             HIP_TRY(ctx, launch_gather_rows(tok_dev + (size_t)t0 * M, perm, offset + El, k, M, ctx->xp, bw_grid, s_comp));
         }
         prof_end(ctx, sp, s_comp);
         // the token rows (with every shared expert's row: of all chunks)
-        if (pinned) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[takes_all ? r - 1 : cidx], 0));
+        if (inbound) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[takes_all ? r - 1 : cidx], 0));
         if (Tn == 0) {
             if (pinned && !fused_out) HIP_TRY(ctx, hipEventRecord(ctx->ev_comp[cidx], s_comp));
             continue;

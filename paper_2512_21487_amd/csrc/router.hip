@@ -10,11 +10,16 @@
 // tokens that selected it; the partition kernels derive counts and stable ranks from it,
 // so no atomically allocated slot ever decides an order.  A call of at most 64 tokens is one workgroup of 64, which
 // partitions right away out of LDS (route_and_partition): one launch less.
+// Where a call's token rows have to cross the host link first, more workgroups of the same launch fetch them (RowCopy):
+// scores and rows are read in place, and the call stays on one stream.  Qwen3-235B-A22B-shaped share, pinned host I/O, copies on a stream of
+// their own, scores first / now: 1 / 64 / 256 / 1024 tokens 63 / 34, 155 / 135,
+// 210 / 191, 447 / 430 us (256 KB over the link instead of 128: 34, 138, 193, 431).
 #include "partition.h"
 
 namespace moe_ep {
 
 constexpr int kRouterTokens = 16;   // of a workgroup: 16 lanes each
+constexpr int kLinkBytes = 128 * 1024;   // in flight over the host link while rows come in
 
 // the value lane (lane ^ pattern) of the same 16-lane row holds; ctrl is a DPP control:
 // 0xB1 / 0x4E swap neighbours / pairs inside a quad, 0x141 / 0x140 mirror a half row / a row
@@ -41,9 +46,16 @@ __device__ __forceinline__ float key_score(uint32_t key)
 template <int EPL, bool PARTITION>  // scores per lane: E <= 16 * EPL; PARTITION: one workgroup holds every token
 __global__ __launch_bounds__((PARTITION ? kTokPerBlock : kRouterTokens) * 16) void router_topk_kernel(
     const float* __restrict__ logits, int Tn, int E, int k, int e0, int El,
-    int32_t* __restrict__ idx, float* __restrict__ w, unsigned long long* __restrict__ blk_mask, PartitionOut part)
+    int32_t* __restrict__ idx, float* __restrict__ w, unsigned long long* __restrict__ blk_mask, PartitionOut part, RowCopy copy)
 {
     constexpr int TOKENS = PARTITION ? kTokPerBlock : kRouterTokens, THREADS = TOKENS * 16;
+    if ((int)blockIdx.x >= copy.first) {   // a workgroup that brings token rows in
+        const uint4* src = static_cast<const uint4*>(copy.src);
+        uint4* dst = static_cast<uint4*>(copy.dst);
+        const size_t n = copy.bytes / 16, step = (size_t)(gridDim.x - copy.first) * THREADS;
+        for (size_t i = (size_t)(blockIdx.x - copy.first) * THREADS + threadIdx.x; i < n; i += step) dst[i] = src[i];
+        return;
+    }
     extern __shared__ unsigned long long smask[];                  // [El] token masks of the local experts
     int* s_idx = reinterpret_cast<int*>(smask + El);               // [TOKENS][k] selected experts
     float* s_ex = reinterpret_cast<float*>(s_idx + TOKENS * k);    // [TOKENS][k] score, then exp(score - best score)
@@ -122,17 +134,27 @@ __global__ __launch_bounds__((PARTITION ? kTokPerBlock : kRouterTokens) * 16) vo
 
 template <bool PARTITION>
 static hipError_t launch(const float* logits, int Tn, int E, int k, int e0, int El, int32_t* idx, float* w,
-                         unsigned long long* blk_mask, const PartitionOut& part, hipStream_t s)
+                         unsigned long long* blk_mask, const PartitionOut& part, const RowCopy* copy, hipStream_t s)
 {
     if (E < 1 || E > 512 || k < 1 || k > 64) return hipErrorInvalidValue;
     constexpr int TOKENS = PARTITION ? kTokPerBlock : kRouterTokens;
     static_assert(kTokPerBlock == 4 * kRouterTokens && kRouterTokens == 16, "a workgroup's mask is a 16-bit quarter");
     // whole masks: the last 64 tokens' workgroups without a token write zeros
     const int nblk = (Tn + kTokPerBlock - 1) / kTokPerBlock * (kTokPerBlock / TOKENS);
+    RowCopy rows{nullptr, nullptr, 0, nblk};
+    int grid = nblk;
+    if (copy && copy->bytes > 0) {
+        if ((reinterpret_cast<uintptr_t>(copy->src) | reinterpret_cast<uintptr_t>(copy->dst) | copy->bytes) & 15) return hipErrorInvalidValue;
+        rows = *copy;
+        rows.first = nblk;
+        const size_t most = (copy->bytes / 16 + TOKENS * 16 - 1) / (TOKENS * 16);
+        constexpr int wgs = kLinkBytes / (TOKENS * 16 * 16);
+        grid += (int)(most < (size_t)wgs ? most : (size_t)wgs);
+    }
     const size_t lds = El * sizeof(unsigned long long) + (size_t)TOKENS * k * 8 + (PARTITION ? (size_t)El * 8 : 0);
 #define MOE_EP_ROUTER(EPL)                                                                          \
-    hipLaunchKernelGGL((router_topk_kernel<EPL, PARTITION>), dim3(nblk), dim3(TOKENS * 16), lds, s, logits, Tn, E, k, e0, \
-                       El, idx, w, blk_mask, part)
+    hipLaunchKernelGGL((router_topk_kernel<EPL, PARTITION>), dim3(grid), dim3(TOKENS * 16), lds, s, logits, Tn, E, k, e0, \
+                       El, idx, w, blk_mask, part, rows)
     if (E <= 16) MOE_EP_ROUTER(1);
     else if (E <= 32) MOE_EP_ROUTER(2);
     else if (E <= 64) MOE_EP_ROUTER(4);
@@ -145,17 +167,17 @@ static hipError_t launch(const float* logits, int Tn, int E, int k, int e0, int 
 }
 
 hipError_t launch_router(const float* logits, int Tn, int E, int k, int e0, int El, int32_t* idx,
-                         float* w, unsigned long long* blk_mask, hipStream_t s)
+                         float* w, unsigned long long* blk_mask, hipStream_t s, const RowCopy* copy)
 {
     if (Tn <= 0) return hipSuccess;
-    return launch<false>(logits, Tn, E, k, e0, El, idx, w, blk_mask, PartitionOut{}, s);
+    return launch<false>(logits, Tn, E, k, e0, El, idx, w, blk_mask, PartitionOut{}, copy, s);
 }
 
 hipError_t launch_route_and_partition(const float* logits, int Tn, int E, int k, int e0, int El, int32_t* idx, float* w,
-                                      int32_t* count, int32_t* offset, int32_t* pos, int32_t* perm, hipStream_t s)
+                                      int32_t* count, int32_t* offset, int32_t* pos, int32_t* perm, hipStream_t s, const RowCopy* copy)
 {
     if (Tn < 1 || Tn > kTokPerBlock) return hipErrorInvalidValue;
-    return launch<true>(logits, Tn, E, k, e0, El, idx, w, nullptr, PartitionOut{count, offset, pos, perm}, s);
+    return launch<true>(logits, Tn, E, k, e0, El, idx, w, nullptr, PartitionOut{count, offset, pos, perm}, copy, s);
 }
 
 }  // namespace moe_ep
