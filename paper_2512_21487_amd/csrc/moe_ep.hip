@@ -721,12 +721,14 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
             if (&x == &sp[2]) h_out = static_cast<char*>(const_cast<void*>(dev));
         }
     }
-    // One chunk: the gate's launch reads the scores where the caller has them and brings the token rows in, on the caller's
-    // stream.  Several chunks' inbound transfers have a stream of their own, as has one that is timed.
-    const bool in_place = pinned && !dep && r == 1 && !ctx->memcpy_in && !(reinterpret_cast<uintptr_t>(h_tokens) & 15) &&
+    // The first chunk: the gate's launch reads the scores where the caller has them and brings the token rows in, on the
+    // caller's stream.  The others come in on a stream of their own, as does the first one where that is timed.  Qwen3-235B-A22B-shaped
+    // share in 2 chunks, its first one on the copies' stream / here: 500 / 1024 / 2000 / 4096 tokens 373 / 362, 512 / 502, 750 / 732,
+    // 1343 / 1343 us (there the next chunk's rows are the longer wait); in 4 chunks 300 / 4096 tokens 565 / 545, 1379 / 1368.
+    const bool in_place = pinned && !dep && !ctx->memcpy_in && !(reinterpret_cast<uintptr_t>(h_tokens) & 15) &&
                           !(prof && (ctx->prof_mask & (1u << ST_COPY_IN)));
-    const bool inbound = pinned && !in_place;
-    if (in_place) log_dev = reinterpret_cast<const float*>(h_logits);
+    const auto comes_in = [&](int cidx) { return pinned && !(in_place && cidx == 0); };
+    const bool inbound = comes_in(r - 1);
     ctx->last_T = T; ctx->last_k = k; ctx->last_r = r; ctx->last_r1 = r_1;
     const bool units_apart = pinned && !dep && r > 1 && !ctx->link_named;
     auto link_copy = [&](void* dst, const void* src, size_t bytes, int grid, hipStream_t st) -> hipError_t {
@@ -740,7 +742,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
     hipStream_t s_ag = dep ? ctx->s_ag : user;  // attention stand-ins and, in dep mode, the shared experts
     if (inbound || dep) HIP_TRY(ctx, hipEventRecord(ctx->ev_start, user));
     if (inbound) {
-        HIP_TRY(ctx, hipStreamWaitEvent(s_in, ctx->ev_start, 0));
+        if (!in_place) HIP_TRY(ctx, hipStreamWaitEvent(s_in, ctx->ev_start, 0));
         if (!fused_out) HIP_TRY(ctx, hipStreamWaitEvent(s_out, ctx->ev_start, 0));
     }
     if (dep) HIP_TRY(ctx, hipStreamWaitEvent(s_ag, ctx->ev_start, 0));
@@ -856,7 +858,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
                 const int rc = shared_of_micro_batch(i);
                 if (rc != MOE_EP_OK) return rc;
             }
-    } else if (inbound) {
+    } else if (inbound && !in_place) {
         // all chunks are queued at once on their own stream
         for (int cidx = 0; cidx < r; ++cidx) {
             const int rc = enqueue_inbound(cidx);
@@ -902,19 +904,29 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         int32_t* idx = ctx->idx + (size_t)t0 * k;
         float* w = ctx->w + (size_t)t0 * k;
         // gate and partition need the chunk's gate scores only, which travel first
-        if (inbound) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_scores[cidx], 0));
+        const bool here = in_place && cidx == 0;
+        if (comes_in(cidx)) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_scores[cidx], 0));
         else if (dep && cidx % r_2 == 0) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_attn[cidx / r_2], 0));
-        const RowCopy rows{ctx->d_tokens, h_tokens, (size_t)T * M * 2, 0};
+        const float* scores = here ? reinterpret_cast<const float*>(h_logits) : log_dev + (size_t)t0 * E;
+        const RowCopy rows{ctx->d_tokens, h_tokens, (size_t)Tn * M * 2, 0};
         const int sp = prof_begin(ctx, prof, ST_ROUTER, s_comp);
         if (Tn > 0 && Tn <= kTokPerBlock)   // one workgroup's tokens: partitioned in the same launch
-            HIP_TRY(ctx, launch_route_and_partition(log_dev + (size_t)t0 * E, Tn, E, k, e0, El, idx, w, ctx->count + (size_t)cidx * El,
+            HIP_TRY(ctx, launch_route_and_partition(scores, Tn, E, k, e0, El, idx, w, ctx->count + (size_t)cidx * El,
                                                     ctx->offset + (size_t)cidx * (El + 1), ctx->pos + (size_t)t0 * k, ctx->perm + (size_t)t0 * k,
-                                                    s_comp, in_place ? &rows : nullptr));
-        else HIP_TRY(ctx, launch_router(log_dev + (size_t)t0 * E, Tn, E, k, e0, El, idx, w, ctx->blk_mask, s_comp, in_place ? &rows : nullptr));
+                                                    s_comp, here ? &rows : nullptr));
+        else HIP_TRY(ctx, launch_router(scores, Tn, E, k, e0, El, idx, w, ctx->blk_mask, s_comp, here ? &rows : nullptr));
         prof_end(ctx, sp, s_comp);
         return MOE_EP_OK;
     };
-    if (in_place) { const int rc = gate(0); if (rc != MOE_EP_OK) return rc; }
+    if (in_place) {
+        int rc = gate(0);
+        if (rc == MOE_EP_OK && inbound) {   // one chunk on the link at a time
+            HIP_TRY(ctx, hipEventRecord(ctx->ev_in[0], s_comp));
+            HIP_TRY(ctx, hipStreamWaitEvent(s_in, ctx->ev_in[0], 0));
+        }
+        for (int cidx = 1; rc == MOE_EP_OK && cidx < r; ++cidx) rc = enqueue_inbound(cidx);
+        if (rc != MOE_EP_OK) return rc;
+    }
     if (shared_first && !first_takes_all) {
         if (inbound) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[r - 1], 0));
         int rc = run_shared(0, T, s_comp);
@@ -937,7 +949,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         int32_t* pos = ctx->pos + (size_t)t0 * k;
         int32_t* perm = ctx->perm + (size_t)t0 * k;
 
-        if (!in_place) { const int rc = gate(cidx); if (rc != MOE_EP_OK) return rc; }
+        if (!(in_place && cidx == 0)) { const int rc = gate(cidx); if (rc != MOE_EP_OK) return rc; }
         const bool one_block = Tn > 0 && Tn <= kTokPerBlock;
 
         // the fused gather addresses a chunk's token rows with 32-bit byte offsets
@@ -945,12 +957,12 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         int sp = prof_begin(ctx, prof, ST_PARTITION, s_comp);
         if (!one_block) HIP_TRY(ctx, launch_dispatch(idx, ctx->blk_mask, Tn, k, e0, El, count, offset, pos, perm, s_comp));
         if (Tn > 0 && !fused) {   // the grouped copy reads the token rows
-            if (inbound) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[cidx], 0));
+            if (comes_in(cidx)) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[cidx], 0));
             HIP_TRY(ctx, launch_gather_rows(tok_dev + (size_t)t0 * M, perm, offset + El, k, M, ctx->xp, bw_grid, s_comp));
         }
         prof_end(ctx, sp, s_comp);
         // the token rows (with every shared expert's row: of all chunks)
-        if (inbound) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[takes_all ? r - 1 : cidx], 0));
+        if (comes_in(takes_all ? r - 1 : cidx)) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[takes_all ? r - 1 : cidx], 0));
         if (Tn == 0) {
             if (pinned && !fused_out) HIP_TRY(ctx, hipEventRecord(ctx->ev_comp[cidx], s_comp));
             continue;

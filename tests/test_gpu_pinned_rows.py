@@ -1,4 +1,4 @@
-"""One chunk of pinned host rows: the gate's launch brings them in (router.hip), or, where they do not start on 16 bytes, a copy
+"""The first chunk of pinned host rows: the gate's launch brings them in (router.hip), or, where they do not start on 16 bytes, a copy
 does; the bits are those of rows that are on the GPU already."""
 import numpy as np
 import pytest
