@@ -44,6 +44,8 @@ def kernel_name(ctx, stage):
     tile_order = "true" if sh["tile_order"] else "false"
     if (sh["rows"], sh["cols"], sh["waves_m"], sh["waves_n"]) in ((64, 128, 1, 4), (16, 64, 1, 2), (16, 32, 1, 1), (32, 64, 1, 2)):   # few rows per expert
         return f"narrow_gemm_kernel<NarrowCfg<{sh['ring_slots']}, {sh['rows']}, {sh['waves_n']}>, {swiglu}, {tile_order}>"
+    if (sh["rows"], sh["waves_n"]) == (16, 8):   # the launch that aggregates as well
+        return f"narrow_sum_kernel<{tile_order}, {sh['cols']}>"
     if (sh["rows"], sh["cols"], sh["waves_m"], sh["waves_n"]) == (192, 256, 2, 4):   # loading wavefronts beside the multiplying ones
         return f"loader_gemm_kernel<{swiglu}, {tile_order}>"
     # last argument: what the epilogue writes (MOE_EP_EXPERT_OUT, the routed down projection only)

@@ -223,7 +223,8 @@ int moe_ep_get_routing(moe_ep_ctx *ctx, int32_t chunk, int32_t *idx, float *w, i
  * record an event before and after every stage.  The events serialise nothing.  Without them the shared experts
  * may run in the routed experts' launches (moe_ep_last_shared_beside); a forward that times stage 4 or 5 gives them
  * launches of their own, since stages that share a launch have no times of their own: the same bits, and possibly a
- * longer forward than the same call untimed (moe_ep_set_profiling_stages leaves the two out).
+ * longer forward than the same call untimed (moe_ep_set_profiling_stages leaves the two out).  The same holds for stages 3 and 6
+ * of up to 16 tokens.
  * moe_ep_get_stage_ms synchronises, returns the per-forward AVERAGE over the forwards recorded
  * since the last call, and opens a new window of `depth` forwards:
  *   ms[0] gate  ms[1] partition (permute + row gather)  ms[2] routed gate/up GEMM
@@ -374,7 +375,7 @@ int32_t moe_ep_routed_tile_rows(const moe_ep_config *cfg, int32_t n_tokens, int3
  * (multiplying) wavefronts.  Chunks with few rows per expert run kernels that hold their weights in registers: 64 rows, 128
  * weight rows, 1 x 4 wavefronts (up to 32 tokens, where that spreads the weights better over the compute units: 16 rows, 32
  * weight rows, 1 x 1; 16 rows, 64 weight rows, 1 x 2; 32 rows, 64 weight rows, 1 x 2), and the K steps in flight in place
- * of ring slots.  For a chunk without a token, and
+ * of ring slots; a down projection that aggregates in the same launch (up to 16 tokens): 16 rows, 8 or 16 weight rows, 1 x 8.  For a chunk without a token, and
  * for the shared experts before their first launch, the shape that would be launched.  Any pointer may be NULL.
  * MOE_EP_ESTATE before any forward or for a stage the layer does not have.
  */

@@ -107,6 +107,26 @@ constexpr NarrowTiles kNarrowTiles[4] = {{kNarrowRows, kNarrowWaves}, {kNarrowFe
 constexpr int kNarrowFineK = 1024;                        // shortest reduction the last two are for
 constexpr int kNarrowWaveRows = 32;                       // weight rows of a wavefront
 constexpr int kNarrowDepth = 4;                           // K steps of 64 in flight per wavefront
+// Down projection and weighted aggregation of at most kSumRows tokens in one launch (narrow_gemm.hip), bit for bit what
+// launch_narrow_gemm and launch_combine write: `routed` and `shared` as for the first (shared: the same Tn tokens), pos and w as
+// for the second, rows of routed.N elements at out; shared_alone: a token without a routed expert gets the shared ones' bits as they are.
+hipError_t launch_narrow_sum(const GemmArgs& routed, const GemmArgs* shared, const int32_t* pos, const float* w, int Tn, int k,
+                             bool shared_alone, void* out, int n_cu, hipStream_t s);
+constexpr int kSumRows = 16, kSumWaves = 8;
+constexpr int sum_loads(bool packed) { return packed ? 24 : 20; }   // of 1 KB in flight per wavefront (128 registers)
+constexpr int kSumKind = sizeof(kNarrowTiles) / sizeof(kNarrowTiles[0]);   // beside the tile kinds of launch_narrow_gemm
+// Output columns of a workgroup: 8 where 16 would leave compute units without one.  Forwards, us, separate launches / 16 / 8
+// columns: DeepSeek-V2-Lite-shaped layer (2048 columns), 1 / 4 / 16 tokens 40.7 / 36.4 / 36.2, 82.8 / 82.2 / 78.1, 155.9 / 166.5 / 154.5;
+// Qwen3-30B-A3B-shaped layer (2048), 1 / 16 tokens 33.1 / 30.7 / 29.9, 146.7 / 149.4 / 141.3; Qwen3-235B-A22B-shaped share (4096), 4 / 16
+// tokens 49.9 / 45.8 / 46.5, 81.5 / 78.2 / 79.7.
+inline int narrow_sum_cols(int N, int n_cu) { return N / 16 < n_cu ? 8 : 16; }
+// Whether it is the faster one: where a compute unit has one workgroup up to kSumRows tokens; where some have two, which all read the
+// token rows, up to kSumWideRows.  Separate launches / one, DeepSeek-V2-shaped share (5120 columns): 1 / 4 / 6 / 8 / 16 tokens 49.4 /
+// 45.2, 59.4 / 57.1, 67.6 / 66.5, 76.6 / 76.9, 110.9 / 113.7 us, all of 16 tokens on eight experts 94 / 104 (Qwen3-235B-A22B-shaped
+// share 65 / 64, with row-major weights 77 / 79).
+// Reductions of less than kSumK were not compared.
+constexpr int kSumWideRows = 4, kSumK = 512;
+inline bool narrow_sum_pays(int Tn, int N, int K, int n_cu) { return K >= kSumK && Tn <= (N / 16 <= n_cu ? kSumRows : kSumWideRows); }
 // Tiled projections of prefill with loading wavefronts (loader_gemm.hip): the routed groups `routed` (ragged) and, when
 // `shared` is not NULL, the shared experts (dense) in one launch; no other epilogue than epi == 0, no max_units, both
 // or neither with weights in tile order.

@@ -52,7 +52,7 @@ bool narrow_under_any_load(int Tn, int k, int El)
     const int tiles = (Tn + kNarrowRows - 1) / kNarrowRows;
     return tiles <= kNarrowGroupTiles && (k < El ? k : El) * tiles <= kNarrowLoadTiles * El;
 }
-// in last_variants, beside the tile variants of grouped_gemm.hip: kNarrowVariant - i stands for kNarrowTiles[i]
+// in last_variants, beside the tile variants of grouped_gemm.hip: kNarrowVariant - i stands for kNarrowTiles[i], or for launch_narrow_sum
 constexpr int kNarrowVariant = -2;
 // The tiled launches of the kernels with loading wavefronts (loader_gemm.hip), as a variant.  Shared experts run beside the
 // routed ones up to kAlongRows rows -- apart (256-row tiles of their own) / along, us: DeepSeek-V2-shaped share, 1600 / 5000 /
@@ -1000,8 +1000,16 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         g2.dense_rows = 0; g2.lda = H; g2.ldc = M; g2.c_group_col_stride = 0;
         g2.max_units = ctx->down_units;
         g2.epi = ctx->y_mode; g2.row_weight = w; g2.row_assignment = perm;
+        // fused outbound transfer: the aggregation reads the shared experts' rows from the device
+        // staging buffer and writes every row of the chunk into the caller's pinned buffer
+        uint16_t* out_rows = out_dev + (size_t)t0 * M;
+        uint16_t* sum_rows = fused_out ? reinterpret_cast<uint16_t*>(h_out) + (size_t)t0 * M : out_rows;
+        // a few tokens: the down projection's launch aggregates, unless one of the two is timed or the shared experts' rows are elsewhere
+        const bool sums = narrow && narrow_sum_pays(Tn, M, along && Ns * Hs < H ? Ns * Hs : H, n_cu) && !dep && (along ? s2.dense_rows == Tn : Ns == 0) &&
+                          !(prof && (ctx->prof_mask & ((1u << ST_GEMM2) | (1u << ST_COMBINE))));
         sp = prof_begin(ctx, prof, ST_GEMM2, s_comp);
-        if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g2, along ? &s2 : nullptr, false, n_cu, (double)Tn * k / E, Tn, a_max, s_comp, &kind_down));
+        if (sums) { HIP_TRY(ctx, launch_narrow_sum(g2, along ? &s2 : nullptr, pos, w, Tn, k, !fused_out, sum_rows, n_cu, s_comp)); kind_down = kSumKind; }
+        else if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g2, along ? &s2 : nullptr, false, n_cu, (double)Tn * k / E, Tn, a_max, s_comp, &kind_down));
         else if (loader) HIP_TRY(ctx, launch_loader_gemm(g2, along ? &s2 : nullptr, false, cus, s_comp));
         else HIP_TRY(ctx, launch_grouped_gemm(g2, false, v_down, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);
@@ -1018,12 +1026,8 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         // the aggregation adds to what the micro-batch's shared experts have written (attention-group stream)
         if (dep && Ns > 0) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_shared[cidx / r_2], 0));
 
-        // fused outbound transfer: the aggregation reads the shared experts' rows from the device
-        // staging buffer and writes every row of the chunk into the caller's pinned buffer
-        uint16_t* out_rows = out_dev + (size_t)t0 * M;
         sp = prof_begin(ctx, prof, ST_COMBINE, s_comp);
-        HIP_TRY(ctx, launch_combine(ctx->y, pos, w, Tn, k, M, Ns > 0, ctx->y_mode, out_rows,
-                                    fused_out ? reinterpret_cast<uint16_t*>(h_out) + (size_t)t0 * M : out_rows, bw_grid, s_comp));
+        if (!sums) HIP_TRY(ctx, launch_combine(ctx->y, pos, w, Tn, k, M, Ns > 0, ctx->y_mode, out_rows, sum_rows, bw_grid, s_comp));
         prof_end(ctx, sp, s_comp);
 
         if (pinned && !fused_out) {
@@ -1088,8 +1092,13 @@ int moe_ep_last_tile_shape(const moe_ep_ctx* ctx, int32_t chunk, int32_t stage, 
     const int variant = shared ? (up ? ctx->last_shared_up : ctx->last_shared_down) : (up ? ctx->last_variants[chunk].up : ctx->last_variants[chunk].down);
     const int K = shared ? (up ? c.hidden : c.n_shared * c.shared_inter) : (up ? c.hidden : c.inter);
     const bool narrow = variant <= kNarrowVariant && variant > kLoaderVariant;
-    const NarrowTiles nt = kNarrowTiles[narrow ? kNarrowVariant - variant : 0];
+    const int kind = narrow ? kNarrowVariant - variant : 0;
+    const NarrowTiles nt = kind < kSumKind ? kNarrowTiles[kind] : NarrowTiles{};
     int v[8] = {nt.rows, nt.waves * kNarrowWaveRows, kPackK, kNarrowDepth, 1, nt.waves, 1, 16};
+    if (kind == kSumKind) {   // K steps in flight: of experts with up to 8 rows
+        v[0] = kSumRows; v[1] = narrow_sum_cols(c.hidden, ctx->n_cu); v[5] = kSumWaves;
+        v[3] = sum_loads(shared ? ctx->last_prepared_shared : ctx->last_prepared_routed) / (v[1] / 8 + 1);
+    }
     if (variant == kLoaderVariant) { v[0] = kLoaderRows; v[1] = kPackRows; v[3] = 3; v[4] = 2; v[5] = 4; }
     else if (!narrow && !grouped_gemm_variant_shape(variant, K, !shared, shared ? 1 : c.n_local, v)) return MOE_EP_ESTATE;
     if (mfma_rows) *mfma_rows = v[7];

@@ -81,6 +81,26 @@ __device__ __forceinline__ void lds_barrier()
     asm volatile("" ::: "memory");
 }
 
+// From the caller's rows a load takes 8 rows of 128 bytes (read as operands, 16 rows of 64, the address path takes
+// four times as long and every line is asked for twice) and the wavefront turns a block into operands
+// through 2 KB of LDS of its own; chunk c of row r lies at c ^ (r / 2 mod 8), all banks in use both ways.
+template <int LOADS>   // 1: the block has 8 rows, which stand in the operand twice
+__device__ __forceinline__ void turn_block(const uint4 (&w)[LOADS], int lane, char* turn, bf16x8_t (&f)[2])
+{
+    wavefront_lds_order();   // the block before this one has been read
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+        const int r = i * 8 + (lane >> 3);
+        *reinterpret_cast<uint4*>(turn + r * 128 + ((lane & 7) ^ (r >> 1)) * 16) = w[i];
+    }
+    wavefront_lds_order();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int r = lane & (8 * LOADS - 1);
+        f[h] = *reinterpret_cast<const bf16x8_t*>(turn + r * 128 + ((h * 4 + (lane >> 4)) ^ (r >> 1)) * 16);
+    }
+}
+
 template <class Cfg, bool SWIGLU, bool PACKED, int MB, bool ONCE = true>
 __device__ __forceinline__ void narrow_tile(const NarrowTile<Cfg>& t, int nrows, int tid, char* lds, bool stores, uint16_t* c, int ldc)
 {
@@ -126,10 +146,7 @@ __device__ __forceinline__ void narrow_tile(const NarrowTile<Cfg>& t, int nrows,
             *reinterpret_cast<uint4*>(buf + r * Cfg::ROW_BYTES + (st_chunk ^ (r & 15)) * 16) = st[i];
         }
     };
-    // Weights in tile order arrive as operands: load h of a block is the k half h of its 16 rows.  From the
-    // caller's rows a load takes 8 rows of 128 bytes (read as operands, 16 rows of 64, the address path takes
-    // four times as long and every line is asked for twice) and the wavefront turns a block into operands
-    // through 2 KB of LDS of its own; chunk c of row r lies at c ^ (r / 2 mod 8), all banks in use both ways.
+    // weights in tile order arrive as operands: load h of a block is the k half h of its 16 rows
     char* turn = lds + 2 * Cfg::BUFFER_BYTES + (tid >> 6) * kTurnBytes;
     auto operand = [&](int slot, int b, bf16x8_t (&f)[2]) __attribute__((always_inline)) {
         if (PACKED) {
@@ -137,18 +154,7 @@ __device__ __forceinline__ void narrow_tile(const NarrowTile<Cfg>& t, int nrows,
             for (int h = 0; h < 2; ++h) f[h] = __builtin_bit_cast(bf16x8_t, w[slot][b][h]);
             return;
         }
-        wavefront_lds_order();   // the block before this one has been read
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int r = i * 8 + (lane >> 3);
-            *reinterpret_cast<uint4*>(turn + r * 128 + ((lane & 7) ^ (r >> 1)) * 16) = w[slot][b][i];
-        }
-        wavefront_lds_order();
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int r = lane & 15;
-            f[h] = *reinterpret_cast<const bf16x8_t*>(turn + r * 128 + ((h * 4 + (lane >> 4)) ^ (r >> 1)) * 16);
-        }
+        turn_block(w[slot][b], lane, turn, f);
     };
     auto multiply = [&](int ch, int slot) __attribute__((always_inline)) {
         const char* buf = lds + (ch & 1) * Cfg::BUFFER_BYTES + (lane & 15) * Cfg::ROW_BYTES;
@@ -350,6 +356,156 @@ __global__ __launch_bounds__(Cfg::THREADS, 2) void narrow_gemm_kernel(GemmArgs r
     }
 }
 
+// The down projection and the weighted sum of a few tokens in one launch.  A workgroup owns 16 or 8 output columns: its wavefronts
+// share out the experts that have a row (the shared ones, a single reduction, first), leave the results in LDS, rounded as the
+// expert outputs in memory would be, and add them up in the order of combine.hip.  As two launches the second one, its gap and
+// the first one's last tiles are 8 us or more of one token's forward: the weights of every column are drawn from the start here, by
+// eight wavefronts per workgroup, and the expert outputs never leave the compute unit.  The token rows are read as operands,
+// by every workgroup again (out of L2): at 16 rows per expert as many bytes as the weights, which is where it ends (narrow_sum_pays).
+struct SumArgs { const int32_t* pos; const float* w; int Tn, k; bool shared_alone; uint16_t* out; };
+
+// 16 bytes of the lane eight further on in its row of 16 lanes
+__device__ __forceinline__ uint4 from_other_half(const uint4& v)
+{
+    const auto turn = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x128, 0xF, 0xF, false); };
+    return make_uint4(turn(v.x), turn(v.y), turn(v.z), turn(v.w));
+}
+
+// COLS columns of the tokens of one expert.  An operand of which 8 of 16 rows are there comes with one load instead of two: lanes
+// 0 .. 7 of a row of 16 lanes hold the first half of the K step, lanes 8 .. 15 the second; what the matrix instruction makes of the
+// other 8 rows is not stored.
+template <bool PACKED, int COLS, int ROWS>
+__device__ __forceinline__ void sum_item(const GemmArgs& a, int g, int row0, int nrows, int n, int lane, char* turn, uint16_t* y)
+{
+    constexpr int WL = COLS / 8, XL = ROWS / 8, D = sum_loads(PACKED) / (WL + XL);   // loads of a K step; K steps in flight
+    const int KT = a.K / kPackK, half = lane >> 3 & 1;
+    const char* wk;
+    uint32_t w_off, w_half;
+    long long w_step, seg_jump = 0;
+    int seg_steps = KT;
+    if (PACKED) {
+        const int NT = (a.N + kPackRows - 1) / kPackRows, nt = n / kPackRows, blk = (n - nt * kPackRows) / 16;
+        wk = reinterpret_cast<const char*>(a.Wp + (((size_t)g * NT + nt) * KT * kPackRows + blk * 16) * kPackK);
+        w_off = COLS == 16 ? lane * 16u : half * 1024u + (lane >> 4) * 256u + ((n & 8) + (lane & 7)) * 16u;
+        w_half = 1024;
+        w_step = (long long)kPackRows * kPackK * 2;
+    } else {
+        wk = reinterpret_cast<const char*>(a.W + (size_t)g * a.w_group_stride + (size_t)n * a.ldw);
+        w_off = (uint32_t)(lane >> 3) * (uint32_t)a.ldw * 2u + (lane & 7) * 16u;
+        w_half = 8u * (uint32_t)a.ldw * 2u;
+        w_step = kPackK * 2;
+        seg_steps = a.kseg_len / kPackK;
+        seg_jump = (a.w_kseg_stride - a.kseg_len) * 2;
+    }
+    const char* xk = reinterpret_cast<const char*>(a.A + (size_t)row0 * a.lda);
+    const uint32_t x_off = (uint32_t)min(lane & (ROWS - 1), nrows - 1) * (uint32_t)a.lda * 2u + (ROWS == 8 ? half * 64u : 0u) + (lane >> 4) * 16u;
+    uint4 w[D][WL], x[D][XL];
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    int seg = seg_steps;
+    auto load = [&](int slot) __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < WL; ++h) w[slot][h] = load16<2>(wk, w_off, h * w_half);
+#pragma unroll
+        for (int h = 0; h < XL; ++h) x[slot][h] = load16(xk, x_off, h * 64);
+        wk += w_step;
+        xk += kPackK * 2;
+        if (--seg == 0) { seg = seg_steps; wk += seg_jump; }
+    };
+    auto multiply = [&](int slot) __attribute__((always_inline)) {
+        bf16x8_t f[2];
+        if (PACKED) {
+            f[0] = __builtin_bit_cast(bf16x8_t, w[slot][0]);
+            f[1] = __builtin_bit_cast(bf16x8_t, WL == 2 ? w[slot][WL - 1] : from_other_half(w[slot][0]));
+        } else turn_block(w[slot], lane, turn, f);
+        const uint4 x1 = XL == 2 ? x[slot][XL - 1] : from_other_half(x[slot][0]);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[0], __builtin_bit_cast(bf16x8_t, x[slot][0]), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[1], __builtin_bit_cast(bf16x8_t, x1), acc, 0, 0, 0);
+    };
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        if (d < KT) load(d);
+    int kt = 0;
+    for (; kt + 2 * D <= KT; kt += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            multiply(d);
+            load(d);
+            __builtin_amdgcn_sched_barrier(0);   // the loads stay D steps ahead of their use
+        }
+    }
+    for (; kt < KT; kt += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            if (kt + d < KT) multiply(d);
+            if (kt + D + d < KT) load(d);
+        }
+    }
+    const int r = lane & 15, c = (lane >> 4) * 4;
+    if (r < nrows && c < COLS) *reinterpret_cast<uint2*>(y + r * COLS + c) = make_uint2(pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3]));
+}
+
+template <bool PACKED, int COLS>
+__global__ __launch_bounds__(kSumWaves * 64, 4) void narrow_sum_kernel(GemmArgs r, GemmArgs s, SumArgs a)
+{
+    __shared__ uint32_t s_item[kNarrowMaxGroups];   // groups with a row: group, first row, rows
+    __shared__ int s_items, s_next;
+    __shared__ __align__(16) char s_turn[PACKED ? 16 : kSumWaves * kTurnBytes];
+    extern __shared__ __align__(16) char dyn[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int slots = a.Tn * a.k, n = blockIdx.x * COLS, first = s.G > 0 ? 1 : 0;
+    uint16_t* y = reinterpret_cast<uint16_t*>(dyn);            // [slots] rows of the routed experts, [Tn] of the shared ones
+    int* s_pos = reinterpret_cast<int*>(dyn + (size_t)(slots + a.Tn) * COLS * 2);
+    float* s_w = reinterpret_cast<float*>(s_pos + slots);
+    if (wave == 0) {
+        int items = 0;
+        for (int g0 = 0; g0 < r.G; g0 += 64) {
+            const int g = g0 + lane, r0 = g < r.G ? r.offset[g] : 0, rows = g < r.G ? r.offset[g + 1] - r0 : 0;
+            const unsigned long long has = __ballot(rows > 0);
+            if (rows > 0) s_item[items + __popcll(has & ((1ull << lane) - 1ull))] = (uint32_t)g << 20 | (uint32_t)r0 << 8 | (uint32_t)rows;
+            items += __popcll(has);
+        }
+        if (lane == 0) { s_items = items; s_next = kSumWaves; }
+    } else {
+        for (int i = tid - 64; i < slots; i += kSumWaves * 64 - 64) { s_pos[i] = a.pos[i]; s_w[i] = a.w[i]; }
+    }
+    __syncthreads();
+    const int items = __builtin_amdgcn_readfirstlane(s_items) + first;
+    char* turn = s_turn + (PACKED ? 0 : wave * kTurnBytes);
+    for (int i = wave; i < items;) {
+        const uint32_t it = i < first ? (uint32_t)slots << 8 | (uint32_t)a.Tn : __builtin_amdgcn_readfirstlane(s_item[i - first]);
+        const int g = it >> 20, row = it >> 8 & 0xfff, rows = it & 0xff;
+        const GemmArgs& e = i < first ? s : r;
+        const int row0 = i < first ? 0 : row;
+        if (rows <= 8) sum_item<PACKED, COLS, 8>(e, g, row0, rows, n, lane, turn, y + (size_t)row * COLS);
+        else sum_item<PACKED, COLS, 16>(e, g, row0, rows, n, lane, turn, y + (size_t)row * COLS);
+        int next = 0;
+        if (lane == 0) next = atomicAdd(&s_next, 1);
+        i = __builtin_amdgcn_readfirstlane(next);
+    }
+    __syncthreads();
+    const uint32_t* y2 = reinterpret_cast<const uint32_t*>(y);
+    for (int i = tid; i < a.Tn * (COLS / 2); i += kSumWaves * 64) {
+        const int t = i / (COLS / 2), c = i % (COLS / 2);
+        float lo = 0.f, hi = 0.f;
+        bool kept = false;
+        for (int j = t * a.k; j < (t + 1) * a.k; ++j) {
+            const int p = s_pos[j];
+            if (p < 0) continue;
+            const uint32_t v = y2[p * (COLS / 2) + c];
+            lo = fmaf(s_w[j], bf16_lo(v), lo);
+            hi = fmaf(s_w[j], bf16_hi(v), hi);
+            kept = true;
+        }
+        uint32_t o = 0;
+        if (first) o = y2[(slots + t) * (COLS / 2) + c];
+        if (kept || !first || !a.shared_alone) {
+            if (first) { lo = fmaf(1.0f, bf16_lo(o), lo); hi = fmaf(1.0f, bf16_hi(o), hi); }
+            o = pack_bf16x2(lo, hi);
+        }
+        *reinterpret_cast<uint32_t*>(a.out + (size_t)t * r.N + n + c * 2) = o;
+    }
+}
+
 static bool narrow_args_fit(const GemmArgs& a)
 {
     if (a.K < kPackK || a.K % kPackK || a.kseg_len < kPackK || a.kseg_len % kPackK || a.N < 64 || a.N % 64) return false;
@@ -421,6 +577,25 @@ hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bo
         else with(NarrowStream{}, sw);
     };
     if (swiglu) pick(std::true_type{}); else pick(std::false_type{});
+    return hipGetLastError();
+}
+
+hipError_t launch_narrow_sum(const GemmArgs& routed, const GemmArgs* shared, const int32_t* pos, const float* w, int Tn, int k,
+                             bool shared_alone, void* out, int n_cu, hipStream_t s)
+{
+    GemmArgs none{};
+    const GemmArgs& sh = shared ? *shared : none;
+    if (Tn < 1 || Tn > kSumRows || k < 1 || k > 64 || routed.offset == nullptr || routed.a_row_map || !narrow_args_fit(routed)) return hipErrorInvalidValue;
+    if (shared && (sh.G != 1 || sh.dense_rows != Tn || sh.N != routed.N || (sh.Wp != nullptr) != (routed.Wp != nullptr) || !narrow_args_fit(sh)))
+        return hipErrorInvalidValue;
+    if (reinterpret_cast<uintptr_t>(out) & 3) return hipErrorInvalidValue;
+    const SumArgs sum{pos, w, Tn, k, shared_alone, static_cast<uint16_t*>(out)};
+    const auto go = [&](auto kernel, int cols) {
+        const size_t lds = (size_t)(Tn * k + Tn) * cols * 2 + (size_t)Tn * k * 8;
+        hipLaunchKernelGGL(kernel, dim3(routed.N / cols), dim3(kSumWaves * 64), lds, s, routed, sh, sum);
+    };
+    if (narrow_sum_cols(routed.N, n_cu) == 8) { if (routed.Wp) go(narrow_sum_kernel<true, 8>, 8); else go(narrow_sum_kernel<false, 8>, 8); }
+    else { if (routed.Wp) go(narrow_sum_kernel<true, 16>, 16); else go(narrow_sum_kernel<false, 16>, 16); }
     return hipGetLastError();
 }
 
