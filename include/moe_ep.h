@@ -224,7 +224,7 @@ int moe_ep_get_routing(moe_ep_ctx *ctx, int32_t chunk, int32_t *idx, float *w, i
  * may run in the routed experts' launches (moe_ep_last_shared_beside); a forward that times stage 4 or 5 gives them
  * launches of their own, since stages that share a launch have no times of their own: the same bits, and possibly a
  * longer forward than the same call untimed (moe_ep_set_profiling_stages leaves the two out).  The same holds for stages 3 and 6
- * of up to 16 tokens.
+ * of up to 16 tokens, and for stages 0, 1 and 2 of up to 4.
  * moe_ep_get_stage_ms synchronises, returns the per-forward AVERAGE over the forwards recorded
  * since the last call, and opens a new window of `depth` forwards:
  *   ms[0] gate  ms[1] partition (permute + row gather)  ms[2] routed gate/up GEMM

@@ -96,9 +96,17 @@ hipError_t launch_grouped_gemm(const GemmArgs& a, bool swiglu, int variant, int 
 // `routed` (ragged) and, when `shared` is not NULL, the shared experts (dense) in one launch, bit for bit
 // what launch_grouped_gemm writes.  expected_rows: rows per routed group the grid is sized for (any
 // routing is served); max_tokens: the most rows one routed group can have; no other epilogue than epi == 0.
-// kind: the tiles launched: kNarrowTiles[*kind].
+// kind: the tiles launched: kNarrowTiles[*kind].  gate (gate/up of at most kGateTokens tokens, kGateExperts experts): the launch
+// routes and partitions first, as launch_route_and_partition; routed's offset and a_row_map are then what it writes, not reads.
+struct GateArgs { const float* scores; int Tn, E, k, e0; int32_t *idx; float* w; int32_t *count, *offset, *pos, *perm; };
 hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bool swiglu, int n_cu, double expected_rows,
-                              int max_tokens, long long max_rows, hipStream_t s, int* kind);
+                              int max_tokens, long long max_rows, hipStream_t s, int* kind, const GateArgs* gate = nullptr);
+// kGateTokens is what one wavefront routes at a time.  Forwards, us, gate apart / in the launch: DeepSeek-V2-Lite-shaped layer, 1 / 2 / 4 tokens
+// 36.3 / 31.4, 51.7 / 46.7, 78.7 / 72.8; DeepSeek-V2-shaped share, 1 / 4 tokens 46.0 / 39.3, 58.3 / 52.4; Qwen3-235B-A22B-shaped share, 1 / 4
+// tokens 25.9 / 22.6, 46.4 / 41.9; Qwen3-30B-A3B-shaped layer, 1 / 4 tokens 29.5 / 25.6, 62.2 / 58.1.  With four more tokens per further
+// round, 5 / 9 / 16 tokens 89 / 87, 125 / 129, 154 / 165; 67 / 62, -, 111 / 115; 47 / 46, -, 78 / 74; 71 / 74, -, 140 / 143: every
+// workgroup that follows another one on its compute unit routes again.
+constexpr int kGateTokens = 4, kGateExperts = 256;
 constexpr int kNarrowRows = 64, kNarrowWaves = 4;         // tallest row tile, wavefronts
 constexpr int kNarrowFewRows = 16, kNarrowFewWaves = 2;   // the same of the tiles for a few tokens; also of one wavefront
 constexpr int kNarrowPairRows = 32;                       // and of two wavefronts for some more

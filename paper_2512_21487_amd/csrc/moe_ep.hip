@@ -949,7 +949,11 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         int32_t* pos = ctx->pos + (size_t)t0 * k;
         int32_t* perm = ctx->perm + (size_t)t0 * k;
 
-        if (!(in_place && cidx == 0)) { const int rc = gate(cidx); if (rc != MOE_EP_OK) return rc; }
+        // a few tokens that are on the GPU: the gate/up projection's launch routes, unless one of the two is timed
+        const bool routes = narrow && Tn > 0 && Tn <= kGateTokens && E <= kGateExperts && k <= E && !dep && !pinned && !(along && takes_all && T != Tn) &&
+                            !(prof && (ctx->prof_mask & ((1u << ST_ROUTER) | (1u << ST_PARTITION) | (1u << ST_GEMM1))));
+        const GateArgs route{log_dev + (size_t)t0 * E, Tn, E, k, e0, idx, w, count, offset, pos, perm};
+        if (!routes && !(in_place && cidx == 0)) { const int rc = gate(cidx); if (rc != MOE_EP_OK) return rc; }
         const bool one_block = Tn > 0 && Tn <= kTokPerBlock;
 
         // the fused gather addresses a chunk's token rows with 32-bit byte offsets
@@ -988,7 +992,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         }
         int kind_up = 0, kind_down = 0;   // of the narrow launches that follow
         sp = prof_begin(ctx, prof, ST_GEMM1, s_comp);
-        if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g1, along ? &s1 : nullptr, true, n_cu, (double)Tn * k / E, Tn, a_max, s_comp, &kind_up));
+        if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g1, along ? &s1 : nullptr, true, n_cu, (double)Tn * k / E, Tn, a_max, s_comp, &kind_up, routes ? &route : nullptr));
         else if (loader) HIP_TRY(ctx, launch_loader_gemm(g1, along ? &s1 : nullptr, true, cus, s_comp));
         else HIP_TRY(ctx, launch_grouped_gemm(g1, true, v_up, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);

@@ -19,6 +19,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "gate.h"
 #include "kernels.h"
 
 namespace moe_ep {
@@ -225,7 +226,8 @@ __device__ __forceinline__ void narrow_tile(const NarrowTile<Cfg>& t, int nrows,
 }
 
 template <class Cfg, bool SWIGLU, bool PACKED>
-__device__ __forceinline__ void narrow_dispatch(const GemmArgs& a, int g, int row0, int nrows, int height, int tiles, int n0, int wave, int tid, char* lds)
+__device__ __forceinline__ void narrow_dispatch(const GemmArgs& a, int g, int row0, int nrows, int height, int tiles, int n0, int wave, int tid, char* lds,
+                                                const uint8_t* tokens = nullptr)   // LDS: the token of a row of the ragged groups
 {
     constexpr int WAVE_COLS = SWIGLU ? 16 : 32;
     // N is a multiple of 64: a wavefront's columns are all there or none is; one without any works on the last
@@ -254,13 +256,13 @@ __device__ __forceinline__ void narrow_dispatch(const GemmArgs& a, int g, int ro
         t.seg_steps = a.kseg_len / kPackK;
         t.seg_jump = (a.w_kseg_stride - a.kseg_len) * 2;
     }
-    const bool mapped = a.a_row_map != nullptr;
+    const bool mapped = a.a_row_map != nullptr || tokens;
     t.x = reinterpret_cast<const char*>(mapped ? a.A : a.A + (size_t)row0 * a.lda);
 #pragma unroll
     for (int i = 0; i < Cfg::ROWS / Cfg::PASS_ROWS; ++i) {
         // rows past the tile's end re-read its last one; they are multiplied and not stored
         const int r = min(tid / Cfg::ROW_CHUNKS + Cfg::PASS_ROWS * i, nrows - 1);
-        const int src = mapped ? a.a_row_map[row0 + r] / a.a_row_div : r;
+        const int src = tokens ? tokens[row0 + r] : mapped ? a.a_row_map[row0 + r] / a.a_row_div : r;
         t.x_off[i] = (uint32_t)src * (uint32_t)a.lda * 2u;
     }
     uint16_t* c = a.C + (size_t)g * a.c_group_col_stride + (size_t)row0 * a.ldc + n;
@@ -300,14 +302,103 @@ constexpr int narrow_cols() { return Cfg::WAVES * (SWIGLU ? 16 : 32); }
 // Tile ids: first those of the shared experts s (s.G == 0: none), then those of the routed groups r; each XCD
 // (workgroup id mod 8) takes a contiguous run of both, in which the row tiles of one column tile are neighbours,
 // so that a group with several of them finds its weights in that XCD's L2 after the first.
-template <class Cfg, bool SWIGLU, bool PACKED>
-__global__ __launch_bounds__(Cfg::THREADS, 2) void narrow_gemm_kernel(GemmArgs r, GemmArgs s)
+// The gate's LDS in a launch that routes by itself: where token rows are staged later.
+struct GateLds {
+    uint32_t mask[kNarrowMaxGroups];   // tokens of a local expert, a bit each
+    int idx[kGateTokens * 64];         // expert of a slot
+    float ex[kGateTokens * 64];
+};
+
+// One wavefront: the gate and the partition of at most kGateTokens tokens, the row tiles before every group and the groups'
+// first rows; the workgroup that writes leaves them in memory for the launches behind this one.
+__device__ __forceinline__ void route_here(const GateArgs& t, int G, int lane, bool writes, GateLds& l, uint8_t* s_token, int* s_pref, int* s_row0)
+{
+    const int sub = lane & 15, tl = lane >> 4, slots = t.Tn * t.k;
+    const bool live = tl < t.Tn;
+    const float* row = t.scores + (size_t)min(tl, t.Tn - 1) * t.E;
+    for (int g = lane; g < G; g += 64) l.mask[g] = 0;
+    if (t.E <= 64) select_experts<4>(row, t.E, t.k, sub, l.idx + tl * t.k, l.ex + tl * t.k);
+    else if (t.E <= 160) select_experts<10>(row, t.E, t.k, sub, l.idx + tl * t.k, l.ex + tl * t.k);
+    else select_experts<kGateExperts / 16>(row, t.E, t.k, sub, l.idx + tl * t.k, l.ex + tl * t.k);
+    const float sum = selection_sum(t.k, sub, l.ex + tl * t.k);
+    if (live)
+        for (int s = sub; s < t.k; s += 16) {
+            const int el = l.idx[tl * t.k + s] - t.e0;
+            if (el >= 0 && el < G) atomicOr(&l.mask[el], 1u << tl);
+            if (writes) {
+                t.idx[tl * t.k + s] = l.idx[tl * t.k + s];
+                t.w[tl * t.k + s] = l.ex[tl * t.k + s] / sum;
+            }
+        }
+    wavefront_lds_order();
+    int before = 0;   // tiles, rows << 16
+    for (int g0 = 0; g0 < G; g0 += 64) {
+        const int g = g0 + lane, rows = g < G ? __popc(l.mask[g]) : 0;
+        const int n = rows << 16 | (rows > 0 ? 1 : 0);
+        int incl = n;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int up = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += up;
+        }
+        const int first = before + incl - n;
+        if (g < G) {
+            s_pref[g] = first & 0xffff; s_row0[g] = first >> 16;
+            if (writes) { t.count[g] = rows; t.offset[g] = first >> 16; }
+        }
+        before += __shfl(incl, 63, 64);
+    }
+    if (lane == 0) {
+        s_pref[G] = before & 0xffff; s_row0[G] = before >> 16;
+        if (writes) t.offset[G] = before >> 16;
+    }
+    wavefront_lds_order();
+    for (int a = lane; a < slots; a += 64) {
+        const int el = l.idx[a] - t.e0, tok = a / t.k;
+        int p = -1;
+        if (el >= 0 && el < G) {
+            p = s_row0[el] + __popc(l.mask[el] & ((1u << tok) - 1u));
+            s_token[p] = (uint8_t)tok;
+            if (writes) t.perm[p] = a;
+        }
+        if (writes) t.pos[a] = p;
+    }
+}
+
+// GATE: the launch routes by itself, every workgroup with a routed tile for its own use, about 1 us where the gate's own launch and
+// the boundary behind it are 5; shared experts' tiles do not wait for it.
+template <class Cfg, bool SWIGLU, bool PACKED, bool GATE = false>
+__global__ __launch_bounds__(Cfg::THREADS, 2) void narrow_gemm_kernel(GemmArgs r, GemmArgs s, GateArgs t)
 {
     __shared__ int s_pref[kNarrowMaxGroups + 1], s_row0[kNarrowMaxGroups + 1];
     __shared__ __align__(16) char lds[2 * Cfg::BUFFER_BYTES + (PACKED ? 0 : Cfg::WAVES * kTurnBytes)];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (wave == 0) {   // row tiles before every routed group, from the partition's row offsets
+    __shared__ uint8_t s_token[GATE ? kGateTokens * 64 : 1];   // of a grouped row
+    constexpr int COLS = narrow_cols<Cfg, SWIGLU>();
+    const int s_mt = s.G > 0 ? narrow_tiles(s.dense_rows, Cfg::ROWS) : 0, s_nt = s.G > 0 ? (s.N + COLS - 1) / COLS : 0;
+    const int s_total = s.G * s_mt * s_nt, s_xcd = (s_total + 7) >> 3;
+    const int r_nt = (r.N + COLS - 1) / COLS;
+    const int xcd = blockIdx.x & 7;
+    int slot = blockIdx.x >> 3;
+    const auto shared_tile = [&]() __attribute__((always_inline)) {
+        const int L = xcd * s_xcd + slot;
+        if (L >= s_total) return;
+        const int g = L / (s_mt * s_nt), l = L - g * s_mt * s_nt, ni = l / s_mt, mi = l - ni * s_mt;
+        const int h = narrow_height(s.dense_rows, s_mt);
+        narrow_dispatch<Cfg, SWIGLU, PACKED>(s, g, mi * h, min(h, s.dense_rows - mi * h), h, s_mt, ni * COLS, wave, tid, lds);
+    };
+    bool writes = false;
+    if constexpr (GATE) {
+        static_assert(kGateTokens <= 16, "a group is one row tile");
+        writes = blockIdx.x == min((uint32_t)s_xcd * 8u, gridDim.x - 8u);
+        const int most = s_xcd + ((t.Tn * t.k * r_nt + 7) >> 3);   // slots, whatever the gate says
+        for (; slot < s_xcd; slot += gridDim.x >> 3) shared_tile();
+        if (slot >= most && !writes) return;
+        static_assert(sizeof(GateLds) <= 2 * Cfg::BUFFER_BYTES, "fits where rows are staged");
+        __syncthreads();   // a shared tile's rows have been read
+        if (wave == 0) route_here(t, r.G, lane, writes, *reinterpret_cast<GateLds*>(lds), s_token, s_pref, s_row0);
+    } else if (wave == 0) {   // row tiles before every routed group, from the partition's row offsets
         int before = 0;
         for (int g0 = 0; g0 < r.G; g0 += 64) {
             const int g = g0 + lane;
@@ -325,19 +416,11 @@ __global__ __launch_bounds__(Cfg::THREADS, 2) void narrow_gemm_kernel(GemmArgs r
         }
     }
     __syncthreads();
-    constexpr int COLS = narrow_cols<Cfg, SWIGLU>();
-    const int s_mt = s.G > 0 ? narrow_tiles(s.dense_rows, Cfg::ROWS) : 0, s_nt = s.G > 0 ? (s.N + COLS - 1) / COLS : 0;
-    const int s_total = s.G * s_mt * s_nt, s_xcd = (s_total + 7) >> 3;
-    const int r_nt = (r.N + COLS - 1) / COLS;
+    const uint8_t* tokens = GATE ? s_token : nullptr;
     const int r_total = __builtin_amdgcn_readfirstlane(s_pref[r.G]) * r_nt, r_xcd = (r_total + 7) >> 3;
-    const int xcd = blockIdx.x & 7;
-    for (int slot = blockIdx.x >> 3; slot < s_xcd + r_xcd; slot += gridDim.x >> 3) {
-        if (slot < s_xcd) {
-            const int L = xcd * s_xcd + slot;
-            if (L >= s_total) continue;
-            const int g = L / (s_mt * s_nt), l = L - g * s_mt * s_nt, ni = l / s_mt, mi = l - ni * s_mt;
-            const int h = narrow_height(s.dense_rows, s_mt);
-            narrow_dispatch<Cfg, SWIGLU, PACKED>(s, g, mi * h, min(h, s.dense_rows - mi * h), h, s_mt, ni * COLS, wave, tid, lds);
+    for (; slot < s_xcd + r_xcd; slot += gridDim.x >> 3) {
+        if (!GATE && slot < s_xcd) {
+            shared_tile();
         } else {
             const int L = xcd * r_xcd + slot - s_xcd;
             if (L >= r_total) continue;
@@ -351,7 +434,7 @@ __global__ __launch_bounds__(Cfg::THREADS, 2) void narrow_gemm_kernel(GemmArgs r
             const int row_a = __builtin_amdgcn_readfirstlane(s_row0[g]), rows = __builtin_amdgcn_readfirstlane(s_row0[g + 1]) - row_a;
             const int l = L - pref * r_nt, ni = l / mt, mi = l - ni * mt;
             const int h = narrow_height(rows, mt);
-            narrow_dispatch<Cfg, SWIGLU, PACKED>(r, g, row_a + mi * h, min(h, rows - mi * h), h, mt, ni * COLS, wave, tid, lds);
+            narrow_dispatch<Cfg, SWIGLU, PACKED>(r, g, row_a + mi * h, min(h, rows - mi * h), h, mt, ni * COLS, wave, tid, lds, tokens);
         }
     }
 }
@@ -519,7 +602,7 @@ static bool narrow_args_fit(const GemmArgs& a)
 }
 
 hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bool swiglu, int n_cu, double expected_rows,
-                              int max_tokens, long long max_rows, hipStream_t s, int* kind)
+                              int max_tokens, long long max_rows, hipStream_t s, int* kind, const GateArgs* gate)
 {
     GemmArgs none{};
     const GemmArgs& sh = shared ? *shared : none;
@@ -538,11 +621,20 @@ hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bo
         const long long grid = (s_tiles + 7) / 8 * 8 + (r_tiles * col_tiles(routed) + 7) / 8 * 8;
         return grid < 8 ? 8 : grid > (1 << 20) ? 1 << 20 : grid;
     };
-    const auto go = [&](auto kernel, long long grid, int threads) { hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(threads), 0, s, routed, sh); };
+    if (gate && (!swiglu || gate->Tn < 1 || gate->Tn > kGateTokens || gate->E < 1 || gate->E > kGateExperts || gate->k < 1 || gate->k > 64 || gate->k > gate->E))
+        return hipErrorInvalidValue;
+    const GateArgs route = gate ? *gate : GateArgs{};
+    const auto go = [&](auto kernel, long long grid, int threads) { hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(threads), 0, s, routed, sh, route); };
     const auto with = [&](auto cfg, auto sw) {
         using Cfg = decltype(cfg);
         constexpr bool SW = decltype(sw)::value;
         const long long grid = grid_for(Cfg::ROWS, narrow_cols<Cfg, SW>(), filled);
+        if constexpr (SW && (std::is_same_v<Cfg, NarrowStream> || std::is_same_v<Cfg, NarrowFine>))   // what a gate/up projection of so few tokens takes
+            if (gate) {
+                if (routed.Wp) go(narrow_gemm_kernel<Cfg, true, true, true>, grid, Cfg::THREADS);
+                else go(narrow_gemm_kernel<Cfg, true, false, true>, grid, Cfg::THREADS);
+                return;
+            }
         if (routed.Wp) go(narrow_gemm_kernel<Cfg, SW, true>, grid, Cfg::THREADS);
         else go(narrow_gemm_kernel<Cfg, SW, false>, grid, Cfg::THREADS);
     };

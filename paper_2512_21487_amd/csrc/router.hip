@@ -9,39 +9,19 @@
 // The workgroup also records, per local expert, 16 bits of the 64-bit mask (one per expert and 64 tokens) of the
 // tokens that selected it; the partition kernels derive counts and stable ranks from it,
 // so no atomically allocated slot ever decides an order.  A call of at most 64 tokens is one workgroup of 64, which
-// partitions right away out of LDS (route_and_partition): one launch less.
+// partitions right away out of LDS (route_and_partition): one launch less; of up to four tokens the gate/up projection's launch does
+// both (narrow_gemm.hip).
 // Where a call's token rows have to cross the host link first, more workgroups of the same launch fetch them (RowCopy):
 // scores and rows are read in place, and the call stays on one stream.  Qwen3-235B-A22B-shaped share, pinned host I/O, copies on a stream of
 // their own, scores first / now: 1 / 64 / 256 / 1024 tokens 63 / 34, 155 / 135,
 // 210 / 191, 447 / 430 us (256 KB over the link instead of 128: 34, 138, 193, 431).
+#include "gate.h"
 #include "partition.h"
 
 namespace moe_ep {
 
 constexpr int kRouterTokens = 16;   // of a workgroup: 16 lanes each
 constexpr int kLinkBytes = 128 * 1024;   // in flight over the host link while rows come in
-
-// the value lane (lane ^ pattern) of the same 16-lane row holds; ctrl is a DPP control:
-// 0xB1 / 0x4E swap neighbours / pairs inside a quad, 0x141 / 0x140 mirror a half row / a row
-template <int CTRL>
-__device__ __forceinline__ int row_exchange(int x) { return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xF, 0xF, false); }
-
-template <int CTRL>
-__device__ __forceinline__ uint32_t row_max_step(uint32_t x) { return max(x, (uint32_t)row_exchange<CTRL>((int)x)); }
-template <int CTRL>
-__device__ __forceinline__ int row_min_step(int x) { return min(x, row_exchange<CTRL>(x)); }
-
-// scores as unsigned integers of the same order, equal for equal scores (-0 == +0); 0 is below every score, also below
-// the NaN whose bits are all ones, which would map to it (padding rows: an expert would be selected twice)
-__device__ __forceinline__ uint32_t order_key(float v)
-{
-    const uint32_t u = __float_as_uint(v + 0.0f);
-    return max(u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u), 1u);
-}
-__device__ __forceinline__ float key_score(uint32_t key)
-{
-    return __uint_as_float(key ^ ((key & 0x80000000u) ? 0x80000000u : 0xffffffffu));
-}
 
 template <int EPL, bool PARTITION>  // scores per lane: E <= 16 * EPL; PARTITION: one workgroup holds every token
 __global__ __launch_bounds__((PARTITION ? kTokPerBlock : kRouterTokens) * 16) void router_topk_kernel(
@@ -70,49 +50,12 @@ __global__ __launch_bounds__((PARTITION ? kTokPerBlock : kRouterTokens) * 16) vo
     const bool live = t < Tn;
     if (wave * 4 + blockIdx.x * TOKENS < Tn) {   // the wavefront has a token
         const float* row = logits + (size_t)min(t, Tn - 1) * E;
-        uint32_t key[EPL];   // 0: out of range or already selected
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) {
-            const int e = sub + 16 * i;
-            key[i] = e < E ? order_key(row[e]) : 0u;
-        }
-        for (int s = 0; s < k; ++s) {
-            uint32_t best = key[0];
-#pragma unroll
-            for (int i = 1; i < EPL; ++i) best = max(best, key[i]);
-            best = row_max_step<0xB1>(best);
-            best = row_max_step<0x4E>(best);
-            best = row_max_step<0x141>(best);
-            best = row_max_step<0x140>(best);   // every lane of the row now holds the round's winner
-            int bi = INT_MAX;                   // equal scores: the lowest expert
-#pragma unroll
-            for (int i = EPL - 1; i >= 0; --i) bi = key[i] == best ? sub + 16 * i : bi;
-            bi = row_min_step<0xB1>(bi);
-            bi = row_min_step<0x4E>(bi);
-            bi = row_min_step<0x141>(bi);
-            bi = row_min_step<0x140>(bi);
-#pragma unroll
-            for (int i = 0; i < EPL; ++i) key[i] = bi == sub + 16 * i ? 0u : key[i];
-            if (sub == 0) {
-                s_idx[tl * k + s] = bi;
-                s_ex[tl * k + s] = key_score(best);
-            }
-        }
-        // Everything that need not follow round by round, a lane per slot.  Softmax restricted to the selection
-        // = full softmax renormalised over it; the sum runs in slot order in every lane.
-        wavefront_lds_order();
-        const float v0 = s_ex[tl * k];
-        wavefront_lds_order();
-        for (int s = sub; s < k; s += 16) {
-            s_ex[tl * k + s] = expf(s_ex[tl * k + s] - v0);
-            const int el = s_idx[tl * k + s] - e0;
-            if (live && el >= 0 && el < El) atomicOr(&smask[el], 1ull << tl);
-        }
-        wavefront_lds_order();
-        float sum = 0.f;
-        for (int s = 0; s < k; ++s) sum += s_ex[tl * k + s];
+        select_experts<EPL>(row, E, k, sub, s_idx + tl * k, s_ex + tl * k);
+        const float sum = selection_sum(k, sub, s_ex + tl * k);
         if (live)
             for (int s = sub; s < k; s += 16) {
+                const int el = s_idx[tl * k + s] - e0;
+                if (el >= 0 && el < El) atomicOr(&smask[el], 1ull << tl);
                 idx[(size_t)t * k + s] = s_idx[tl * k + s];
                 w[(size_t)t * k + s] = s_ex[tl * k + s] / sum;
             }
