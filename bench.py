@@ -43,7 +43,8 @@ def kernel_name(ctx, stage):
     ragged = "true" if stage.startswith("routed") else "false"
     tile_order = "true" if sh["tile_order"] else "false"
     if (sh["rows"], sh["cols"], sh["waves_m"], sh["waves_n"]) in ((64, 128, 1, 4), (16, 64, 1, 2), (16, 32, 1, 1), (32, 64, 1, 2)):   # few rows per expert
-        return f"narrow_gemm_kernel<NarrowCfg<{sh['ring_slots']}, {sh['rows']}, {sh['waves_n']}>, {swiglu}, {tile_order}>"
+        # (a launch that is timed does not route as well: last argument)
+        return f"narrow_gemm_kernel<NarrowCfg<{sh['ring_slots']}, {sh['rows']}, {sh['waves_n']}>, {swiglu}, {tile_order}, false>"
     if (sh["rows"], sh["waves_n"]) == (16, 8):   # the launch that aggregates as well
         return f"narrow_sum_kernel<{tile_order}, {sh['cols']}>"
     if (sh["rows"], sh["cols"], sh["waves_m"], sh["waves_n"]) == (192, 256, 2, 4):   # loading wavefronts beside the multiplying ones
