@@ -25,10 +25,10 @@ namespace {
 enum Stage { ST_ROUTER = 0, ST_PARTITION, ST_GEMM1, ST_GEMM2, ST_SGEMM1, ST_SGEMM2, ST_COMBINE, ST_TOTAL, ST_COPY_IN, ST_COPY_OUT, ST_ATTN, ST_COUNT };
 
 // Where the narrow kernels (narrow_gemm.hip) take over, in rows per routed expert.  Forwards in us under balanced load,
-// three layers in turn, tiled (shared experts in the same launch where plan_chunk puts them) / narrow: DeepSeek-V2-Lite-shaped
-// layer, 3 / 12 / 24 / 48 rows 204 / 183, 234 / 199, 237 / 214, 253 / 243; DeepSeek-V2-shaped share, 11 / 19 / 24 / 28 rows
-// 253 / 221, 266 / 246, 272 / 257, 278 / 287; Qwen3-235B-A22B-shaped share, 8 / 16 / 32 rows 126 / 117, 128 / 120, 122 / 128;
-// Qwen3-30B-A3B-shaped layer, 24 rows 218 / 218, and with its load skewed (Zipf 1.1) 24 / 38 rows 180 / 173, 201 / 208.
+// three layers in turn, tiled (loader_gemm.hip, shared experts in the same launch) / narrow: DeepSeek-V2-Lite-shaped layer, 3 / 12 / 24 /
+// 48 rows 174 / 180, 210 / 198, 215 / 213, 249 / 243; DeepSeek-V2-shaped share, 11 / 19 / 24 / 28 rows 230 / 220, 256 / 247, 255 / 258,
+// 260 / 285; Qwen3-235B-A22B-shaped share, 8 / 16 / 32 rows 119 / 117, 115 / 117, 121 / 121; Qwen3-30B-A3B-shaped layer, 16 / 24 rows
+// 210 / 208, 217 / 219, and with its load skewed (Zipf 1.1) 24 rows 173 / 180.
 constexpr double kNarrowMeanRows = 24.0;
 // The shared experts go along up to this many rows; beyond, launches of their own with tall tiles.  Apart / along, the routed
 // experts in narrow tiles both times: DeepSeek-V2-Lite-shaped layer, 256 / 512 tokens 251 / 212, 269 / 229 us; DeepSeek-V2-shaped share,
