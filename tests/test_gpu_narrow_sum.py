@@ -59,3 +59,28 @@ def test_same_bits_as_separate_launches(monkeypatch, hidden, inter, n_experts, l
     for (n, r), (_, waves) in got.items():
         # in several chunks with the shared experts of all of them first, the aggregation adds to rows that are already there
         assert (waves == 8) == (-(-n // r) <= most and not (r == 2 and n_shared)), (n, r)
+
+
+@pytest.mark.parametrize("pinned", [False, True])
+@pytest.mark.parametrize("offset", [1, 2, 3, 4])
+def test_output_that_begins_anywhere(offset, pinned):
+    """`out` at `offset` elements behind a 16-byte boundary: the rows of one that begins on it, and nothing beside them."""
+    import gpu_util as g
+    import paper_2512_21487_amd as pkg
+    wl = tiny_workload(name="sum_offset", n_tokens=16, hidden=192, inter=512, n_experts=6, local_begin=1, n_local=4, top_k=2, n_shared=0,
+                       shared_inter=0)
+    inp = make_inputs(wl, seed=92)
+    d = g.DeviceInputs(wl, inp, pinned=pinned)
+    ctx = g.make_ctx(wl, pinned=pinned)
+    for n in (1, 16):
+        want = g.run_forward(ctx, wl, d, n_tokens=n)
+        assert ctx.last_tile_shape("routed_down_gemm")["waves_n"] == 8, "the launch under test"
+        flat = torch.full((n * wl.hidden + 8,), 7, dtype=torch.int16, device="cpu" if pinned else "cuda", pin_memory=pinned)
+        out = flat[offset:offset + n * wl.hidden]
+        ctx.forward(d.tokens, d.logits, d.routed, None, wl.top_k, 1, 0, n_tokens=n, out=out)
+        torch.cuda.synchronize()
+        assert (ctx.last_tile_shape("routed_down_gemm")["waves_n"] == 8) == (offset % 2 == 0)
+        assert np.array_equal(out.cpu().numpy().view(np.uint16).reshape(n, -1), want) and want.any()
+        rest = flat.cpu().numpy()
+        assert (rest[:offset] == 7).all() and (rest[offset + n * wl.hidden:] == 7).all()
+    ctx.destroy()
