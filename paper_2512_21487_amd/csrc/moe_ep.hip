@@ -878,12 +878,14 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         const bool beside = rows > 0 && rows <= kNarrowSharedRows;
         if (fits && Tn > 0 && (double)Tn * k / E <= ctx->narrow_rows && (beside || ctx->narrow_named || narrow_under_any_load(Tn, k, El)))
             return Plan{true, false, beside && !shared_timed, kNarrowVariant, kNarrowVariant};
-        if (ctx->by_rule && Tn > 0) {
-            const bool pays = rows <= kAlongRows && M >= kAlongK && H >= kAlongK && Hs >= kAlongK;
-            return Plan{false, true, rows > 0 && !shared_timed && (ctx->merge == 1 || (ctx->merge != 0 && pays)), kLoaderVariant, kLoaderVariant};
+        // loader_gemm.hip addresses the activation rows of its tallest tile with 32-bit byte offsets (token rows it gathers: `fits`)
+        const auto addressed = [](long long row) { return kLoaderRows * row * 2 < (1ll << 32); };
+        if (ctx->by_rule && Tn > 0 && addressed(H) && (fits || addressed(M))) {
+            const bool pays = rows <= kAlongRows && M >= kAlongK && H >= kAlongK && Hs >= kAlongK, reach = addressed(M) && addressed((long long)Ns * Hs);
+            return Plan{false, true, rows > 0 && !shared_timed && reach && (ctx->merge == 1 || (ctx->merge != 0 && pays)), kLoaderVariant, kLoaderVariant};
         }
-        // a shape, an instruction or a form of the expert outputs was asked for by name: grouped_gemm.hip.  Tile shapes of
-        // the two routed projections: N = H in tiles of 128 activation columns, N = M in tiles of 256 columns
+        // a shape, an instruction or a form of the expert outputs was asked for by name, or rows are too long for the above:
+        // grouped_gemm.hip.  Tile shapes of the two routed projections: N = H in tiles of 128 activation columns, N = M in tiles of 256 columns
         p.up = ctx->gemm_variant >= 0 ? ctx->gemm_variant : picked(routed_variant(Tn, k, E, El, ct_up, M, n_cu));
         p.down = ctx->gemm_variant >= 0 ? ctx->gemm_variant : picked(routed_variant(Tn, k, E, El, ct_down, H, n_cu));
         if (ctx->up_variant >= 0) p.up = ctx->up_variant;

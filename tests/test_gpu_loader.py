@@ -89,3 +89,33 @@ def test_more_tiles_than_are_decoded_ahead(monkeypatch):
         outs.append(out)
         ctx.destroy()
     assert outs[0].any() and torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+
+
+# 192 rows of 11184832 elements and more are 2^32 bytes: past what a lane of these kernels addresses in one tile
+@pytest.mark.parametrize("hidden,inter,env", [
+    (64, 11184832, {}),                                    # the down projection's rows
+    (11184832, 64, {"MOE_EP_FUSED_GATHER": "0"}),          # the grouped copy of the token rows
+])
+def test_rows_longer_than_a_tile_can_address(monkeypatch, hidden, inter, env):
+    import paper_2512_21487_amd as pkg
+    T = 32
+    gen = torch.Generator(device="cuda").manual_seed(74)
+    normal = lambda n, std: torch.empty(n, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    tokens, routed = normal(T * hidden, 1.0), normal(3 * inter * hidden, 0.02 if hidden < 1000 else 5e-4)
+    with monkeypatch.context() as m:
+        for name, value in env.items():
+            m.setenv(name, value)
+        ctx = pkg.MoeEp(hidden=hidden, inter=inter, n_experts=1, n_local=1, n_shared=0, shared_inter=0, max_tokens=T, max_top_k=1, max_chunks=1)
+    out = torch.zeros(T * hidden, dtype=torch.bfloat16, device="cuda")
+    ctx.forward(tokens, torch.zeros(T, device="cuda"), routed, None, 1, 1, 0, n_tokens=T, out=out)
+    torch.cuda.synchronize()
+    assert ctx.last_tile_shape("routed_down_gemm")["rows"] == 128
+    ctx.destroy()
+    gate, up, down = routed.view(3, -1)
+    x = tokens.view(T, hidden).float()
+    z = x @ gate.view(inter, hidden).float().t()
+    act = torch.nn.functional.silu(z) * (x @ up.view(inter, hidden).float().t())
+    want = act @ down.view(hidden, inter).float().t()
+    # bf16 rounding of the activation, of the expert's output and of the result: 2^-9 / sqrt(3) each at most, relative to the norm;
+    # sums of 1.1e7 products in 3.5e5 steps of fp32: under 2^-24 sqrt(3.5e5) = 3.5e-5
+    assert float((out.float().view(T, hidden) - want).norm() / want.norm()) < 5e-3
