@@ -623,13 +623,20 @@ hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bo
     };
     if (gate && (!swiglu || gate->Tn < 1 || gate->Tn > kGateTokens || gate->E < 1 || gate->E > kGateExperts || gate->k < 1 || gate->k > 64 || gate->k > gate->E))
         return hipErrorInvalidValue;
+    // no group has more than max_tokens rows: one row tile each
+    const bool one_block = max_tokens <= NarrowFew::ROWS && (!shared || sh.dense_rows <= NarrowFew::ROWS);
+    const bool two_blocks = max_tokens <= NarrowPair::ROWS && (!shared || sh.dense_rows <= NarrowPair::ROWS);
+    // Only the tiles a gate/up projection of one block of rows takes exist with a gate; any other launch would read the
+    // rows an earlier call has partitioned.
+    static_assert(kGateTokens <= NarrowFew::ROWS && kGateTokens <= NarrowFine::ROWS, "the gate's own tokens are one block");
+    if (gate && (!one_block || gate->Tn > max_tokens)) return hipErrorInvalidValue;
     const GateArgs route = gate ? *gate : GateArgs{};
     const auto go = [&](auto kernel, long long grid, int threads) { hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(threads), 0, s, routed, sh, route); };
     const auto with = [&](auto cfg, auto sw) {
         using Cfg = decltype(cfg);
         constexpr bool SW = decltype(sw)::value;
         const long long grid = grid_for(Cfg::ROWS, narrow_cols<Cfg, SW>(), filled);
-        if constexpr (SW && (std::is_same_v<Cfg, NarrowStream> || std::is_same_v<Cfg, NarrowFine>))   // what a gate/up projection of so few tokens takes
+        if constexpr (SW && (std::is_same_v<Cfg, NarrowStream> || std::is_same_v<Cfg, NarrowFine>))   // what a gate/up projection of one block of rows takes
             if (gate) {
                 if (routed.Wp) go(narrow_gemm_kernel<Cfg, true, true, true>, grid, Cfg::THREADS);
                 else go(narrow_gemm_kernel<Cfg, true, false, true>, grid, Cfg::THREADS);
@@ -638,10 +645,8 @@ hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bo
         if (routed.Wp) go(narrow_gemm_kernel<Cfg, SW, true>, grid, Cfg::THREADS);
         else go(narrow_gemm_kernel<Cfg, SW, false>, grid, Cfg::THREADS);
     };
-    // no group has more than max_tokens rows: one row tile each; of a share, about `kept` rows stay here
+    // of a share, about `kept` rows stay here
     const long long kept = (long long)(expected_rows * routed.G + 0.999);
-    const bool one_block = max_tokens <= NarrowFew::ROWS && (!shared || sh.dense_rows <= NarrowFew::ROWS);
-    const bool two_blocks = max_tokens <= NarrowPair::ROWS && (!shared || sh.dense_rows <= NarrowPair::ROWS);
     *kind = !swiglu && one_block && grid_for(kNarrowRows, narrow_cols<NarrowStream, false>(), kept < filled ? kept : filled) <= n_cu ? 1 : 0;
     if (two_blocks && routed.K >= kNarrowFineK && (!shared || sh.K >= kNarrowFineK)) {
         // What the busiest compute unit draws (columns times K) out of tiles of w wavefronts spread evenly, the experts
