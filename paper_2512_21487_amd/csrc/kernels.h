@@ -38,6 +38,10 @@ hipError_t launch_combine(const void* y, const int32_t* pos, const float* w, int
 // ---- chunk transfers over the host link (pinned-host mode); bytes must be a multiple of 4; lds: bytes of LDS every
 // workgroup keeps other kernels' workgroups out with
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, int grid, hipStream_t s, int threads = 256, int unroll = 4, int lds = 0);
+// Compute units a launch takes beside a copy of kLinkUnits workgroups: those workgroups' own units are left out, but no more than a
+// sixteenth of the device (256 units: 16), which may be a small partition of the GPU
+constexpr int kLinkUnits = 16;
+int units_beside_link(int n_cu);
 // a one-wavefront kernel that lasts about `microseconds` (at most 1 s): stand-in for a task that
 // runs on other hardware
 hipError_t launch_busy(double microseconds, hipStream_t s);

@@ -62,14 +62,17 @@ constexpr int kNarrowVariant = -2;
 constexpr int kLoaderVariant = -9, kAlongRows = 14336, kAlongK = 512;
 
 // Chunks that arrive while others are multiplied (moe_ep_forward): kLinkUnits copy workgroups of four wavefronts (128 KB over the link, as
-// 64 of one), and a projection's launch that runs beside them leaves them as many compute units.  They ask for LDS they do not
-// use, more than a workgroup of loader_gemm.hip leaves: on one compute unit the projection's loads would queue behind
-// reads that take microseconds, and the launch lasts as long as its slowest workgroup.  Qwen3-235B-A22B-shaped share, 4096 tokens
+// 64 of one), and a tiled projection's launch that runs beside them leaves them as many compute units (units_beside_link).  They ask
+// for LDS they do not use, more than a workgroup of loader_gemm.hip leaves: on one compute unit the projection's loads would queue
+// behind reads that take microseconds, and the launch lasts as long as its slowest workgroup.  Qwen3-235B-A22B-shaped share, 4096 tokens
 // in two chunks: gate/up beside the second chunk's transfer 155 -> 84 us, gate 28 -> 9, forward 1362 -> 1334; four chunks 1494 ->
-// 1379, 2000 tokens in two 805 -> 740.  (Not in moe_ep_forward_dep, whose other launches fill every compute unit.)  The same
+// 1379, 2000 tokens in two 805 -> 740.  Chunks in narrow tiles, whose launches leave nothing free, 64 copy workgroups of one wavefront / these:
+// Qwen3-235B-A22B-shaped share, 300 / 512 tokens in two chunks 307 / 304, 368 / 363, 512 / 1024 in four 584 / 587, 716 / 693;
+// DeepSeek-V2-Lite-shaped layer, 512 tokens in two 492 / 492, in four 872 / 879; Qwen3-30B-A3B-shaped layer, 512 in four 920 / 926.
+// (Not in moe_ep_forward_dep, whose other launches fill every compute unit.)  The same
 // forwards with a chunk's outbound rows on a stream of their own beside the next chunk's projections, in one to eight pieces, on
 // 2 to 128 workgroups: 1320 - 1400 us and more, the two directions slow each other and the projections down.
-constexpr int kLinkUnits = 16, kLinkLds = 24 * 1024;
+constexpr int kLinkLds = 24 * 1024;
 
 struct ProfSpan { hipEvent_t a, b; int stage; int forward; };
 
@@ -976,7 +979,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
 
         const long long a_max = (long long)Tn * k;  // the most rows the routing can keep
         // the next chunk is on the link (shared experts that come first have waited for every chunk)
-        const int cus = units_apart && !shared_first && cidx + 1 < r ? n_cu - kLinkUnits : n_cu;
+        const int cus = units_apart && !ctx->memcpy_in && !shared_first && cidx + 1 < r ? units_beside_link(n_cu) : n_cu;
 
         GemmArgs g1{};
         routed_up_w(g1);

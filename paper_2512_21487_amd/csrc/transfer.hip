@@ -45,6 +45,8 @@ hipError_t launch_copy(void* dst, const void* src, size_t bytes, int grid, hipSt
     return hipGetLastError();
 }
 
+int units_beside_link(int n_cu) { return n_cu - (n_cu / 16 < kLinkUnits ? n_cu / 16 : kLinkUnits); }
+
 // Stand-in for an attention-group task of a given duration (Sec. 2.3: the attention of a
 // micro-batch runs on other GPUs; here only its place in the schedule matters): one wavefront that
 // sleeps until the constant 100 MHz wall clock has advanced by `ticks`, or until `max_polls` polls

@@ -41,3 +41,9 @@ def test_a_gate_inside_a_launch_without_one_is_refused(max_tokens, dense_rows):
     rc = launch(ctypes.byref(routed), ctypes.byref(shared), ctypes.c_bool(True), 256, ctypes.c_double(max_tokens * k / 64), max_tokens,
                 ctypes.c_longlong(max_tokens * k), None, ctypes.byref(kind), ctypes.byref(gate))
     assert rc == INVALID_VALUE
+
+
+def test_compute_units_left_to_the_link():
+    """A sixteenth of the device at most, whatever its size: a launch beside a copy always has some."""
+    beside = pkg.load_library()._ZN6moe_ep17units_beside_linkEi
+    assert [beside(n) for n in (256, 304, 64, 32, 16, 8, 1)] == [240, 288, 60, 30, 15, 8, 1]
