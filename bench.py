@@ -108,8 +108,9 @@ def fit_pipeline(ctx, tokens, logits, routed, shared, out, T, k, order, stream, 
     point, the protocol of Sec. 5.2), give them to the context, let it choose r_2, and measure the sweep.
 
     First set (tasks alone): forwards of ONE chunk of m tokens, where nothing overlaps; the copy times
-    are the measured stage times, the compute time is the rest of the forward's wall time, so the three
-    add up to what a one-chunk forward takes.  Second set (tasks beside other tasks): on one GPU the
+    are the measured stage times, the compute time is the rest of an untimed forward's wall time, so the
+    three add up to what a one-chunk forward takes (there the gate's launch brings the rows in: what that
+    saves against a copy of its own lessens "compute").  Second set (tasks beside other tasks): on one GPU the
     copies and the kernels slow each other down and kernel boundaries wait for host-bound writes, so
     isolated task times under-price a pipeline; instead the closed form S(r, m) = t_in + t_e + t_out +
     (r - 1) Y of Sec. 4.2 is fitted to forwards of 2 and of 4 chunks of m tokens each:
@@ -123,16 +124,18 @@ def fit_pipeline(ctx, tokens, logits, routed, shared, out, T, k, order, stream, 
         for _ in range(10):
             ctx.forward(tokens, logits, routed, shared, k, r, order, n_tokens=n_tokens, out=out, stream=stream)
         torch.cuda.synchronize()
-        if stages:
-            ctx.set_profiling_stages(["copy_in", "copy_out"])
-            ctx.set_profiling(20)
         t1 = time.perf_counter()
         for _ in range(20):
             ctx.forward(tokens, logits, routed, shared, k, r, order, n_tokens=n_tokens, out=out, stream=stream)
         torch.cuda.synchronize()
         wall = (time.perf_counter() - t1) / 20 * 1e3
         st = None
-        if stages:
+        if stages:   # forwards of their own: timed inbound copies are launches of their own (moe_ep_set_profiling)
+            ctx.set_profiling_stages(["copy_in", "copy_out"])
+            ctx.set_profiling(20)
+            for _ in range(20):
+                ctx.forward(tokens, logits, routed, shared, k, r, order, n_tokens=n_tokens, out=out, stream=stream)
+            torch.cuda.synchronize()
             st = ctx.get_stage_ms()
             ctx.set_profiling(0)
             ctx.set_profiling_stages(None)

@@ -79,3 +79,33 @@ def test_overlap_models_match_oracle_brute_force():
         if got != want:
             assert makespan_overlap(got, T, alone, beside) == pytest.approx(makespan_overlap(want, T, alone, beside), rel=1e-12)
         assert 1 <= got <= r_max
+
+
+def test_fit_prices_one_chunk_as_an_untimed_forward(monkeypatch):
+    """bench.fit_pipeline against a context whose forwards last longer while stages are timed (timed inbound copies are
+    launches of their own): the fitted task models must add up to the untimed forward."""
+    import types
+
+    import torch
+
+    import bench
+
+    class Context:
+        cfg = types.SimpleNamespace(max_chunks=8)
+        now, timed, models = 0.0, False, []
+
+        def forward(self, *args, n_tokens, **kw):
+            r = args[5] or 1
+            self.now += 1e-3 * (0.1 * r + 1e-3 * n_tokens + 0.05 * self.timed)
+        def set_profiling_stages(self, names): pass
+        def set_profiling(self, depth): self.timed = depth > 0
+        def get_stage_ms(self): return {"copy_in": 0.02, "copy_out": 0.0}
+        def set_pipeline_model(self, model): self.models.append(model)
+        def last_chunks(self): return 1
+
+    ctx = Context()
+    monkeypatch.setattr(bench, "time", types.SimpleNamespace(perf_counter=lambda: ctx.now))
+    monkeypatch.setattr(torch.cuda, "synchronize", lambda: None)
+    res = bench.fit_pipeline(ctx, None, None, None, None, None, 4096, 8, 0, None)
+    assert res["measured_ms"]["1"] == pytest.approx(0.1 + 4.096)
+    assert res["predicted_ms"]["1"] == pytest.approx(res["measured_ms"]["1"])
