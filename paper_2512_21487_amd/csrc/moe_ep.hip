@@ -883,7 +883,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
             return Plan{true, false, beside && !shared_timed, kNarrowVariant, kNarrowVariant};
         // loader_gemm.hip addresses the activation rows of its tallest tile with 32-bit byte offsets (token rows it gathers: `fits`)
         const auto addressed = [](long long row) { return kLoaderRows * row * 2 < (1ll << 32); };
-        if (ctx->by_rule && Tn > 0 && addressed(H) && (fits || addressed(M))) {
+        if (ctx->by_rule && addressed(H) && (fits || addressed(M))) {
             const bool pays = rows <= kAlongRows && M >= kAlongK && H >= kAlongK && Hs >= kAlongK, reach = addressed(M) && addressed((long long)Ns * Hs);
             return Plan{false, true, rows > 0 && !shared_timed && reach && (ctx->merge == 1 || (ctx->merge != 0 && pays)), kLoaderVariant, kLoaderVariant};
         }

@@ -91,6 +91,21 @@ def test_more_tiles_than_are_decoded_ahead(monkeypatch):
     assert outs[0].any() and torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
 
 
+def test_tile_shape_of_a_chunk_without_a_token(monkeypatch):
+    """Five tokens in four chunks of two: the last chunk launches nothing and is answered as the others."""
+    import gpu_util as g
+    wl = tiny_workload(name="loader_empty", n_tokens=5, hidden=128, inter=192, n_experts=4, n_local=4, top_k=2, n_shared=1, shared_inter=64)
+    with monkeypatch.context() as m:
+        m.setenv("MOE_EP_NARROW_ROWS", "0")
+        ctx = g.make_ctx(wl)
+    g.run_forward(ctx, wl, g.DeviceInputs(wl, make_inputs(wl, seed=75)), r=4, order=1)
+    for stage in ("routed_gate_up_gemm", "routed_down_gemm"):
+        shapes = [ctx.last_tile_shape(stage, chunk) for chunk in range(4)]
+        assert shapes[0]["rows"] == 192 and all(shape == shapes[0] for shape in shapes)
+    assert not ctx.last_shared_beside(3)
+    ctx.destroy()
+
+
 # 192 rows of 11184832 elements and more are 2^32 bytes: past what a lane of these kernels addresses in one tile
 @pytest.mark.parametrize("hidden,inter,env", [
     (64, 11184832, {}),                                    # the down projection's rows
