@@ -91,6 +91,37 @@ def test_more_tiles_than_are_decoded_ahead(monkeypatch):
     assert outs[0].any() and torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
 
 
+@pytest.mark.parametrize("prepared", [False, True])
+def test_more_mixed_tiles_than_are_decoded_ahead(monkeypatch, prepared):
+    """The same with shared experts in the launch and experts of one row tile, every second workgroup going through its tiles
+    backwards: the list of decoded tiles (32 entries) is written over more than once, in either direction."""
+    import paper_2512_21487_amd as pkg
+    M, H, E, T, k, Ns, Hs = 8704, 64, 512, 2048, 8, 2, 64
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    assert E * (M // 256) > 2 * 32 * n_cu, "tiles of a workgroup"
+    gen = torch.Generator(device="cuda").manual_seed(76)
+    normal = lambda n, std: torch.empty(n, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    tokens, routed, shared = normal(T * M, 1.0), normal(E * 3 * H * M, 0.02), normal(Ns * 3 * Hs * M, 0.02)
+    logits = torch.empty((T, E), dtype=torch.float32, device="cuda").normal_(generator=gen)
+    outs = []
+    for env in ({"MOE_EP_GEMM_VARIANT": "21"}, {"MOE_EP_NARROW_ROWS": "0", "MOE_EP_MERGE": "1"}):
+        with monkeypatch.context() as m:
+            for name, value in env.items():
+                m.setenv(name, value)
+            ctx = pkg.MoeEp(hidden=M, inter=H, n_experts=E, n_local=E, n_shared=Ns, shared_inter=Hs, max_tokens=T, max_top_k=k, max_chunks=1)
+        if prepared:
+            ctx.prepare_weights(routed, shared)
+        out = torch.zeros(T * M, dtype=torch.bfloat16, device="cuda")
+        ctx.forward(tokens, logits, routed, shared, k, 1, 0, n_tokens=T, out=out)
+        torch.cuda.synchronize()
+        own = "MOE_EP_MERGE" in env
+        assert (ctx.last_tile_shape("routed_down_gemm")["rows"] == 192) == own and ctx.last_shared_beside() == own, "the launches under test"
+        assert ctx.get_routing()["count"].max() <= 192, "one row tile each"
+        outs.append(out)
+        ctx.destroy()
+    assert outs[0].any() and torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+
+
 def test_tile_shape_of_a_chunk_without_a_token(monkeypatch):
     """Five tokens in four chunks of two: the last chunk launches nothing and is answered as the others."""
     import gpu_util as g
