@@ -135,7 +135,8 @@ inline int narrow_sum_cols(int N, int n_cu) { return N / 16 < n_cu ? 8 : 16; }
 // Whether it is the faster one: where a compute unit has one workgroup up to kSumRows tokens; where some have two, which all read the
 // token rows, up to kSumWideRows.  Separate launches / one, DeepSeek-V2-shaped share (5120 columns): 1 / 4 / 6 / 8 / 16 tokens 49.4 /
 // 45.2, 59.4 / 57.1, 67.6 / 66.5, 76.6 / 76.9, 110.9 / 113.7 us, all of 16 tokens on eight experts 94 / 104 (Qwen3-235B-A22B-shaped
-// share 65 / 64, with row-major weights 77 / 79).
+// share 65 / 64).  With weights in the caller's layout, Qwen3-235B-A22B-shaped share, 16 tokens balanced 96 / 89, Zipf 1.1 57 / 49, all on 16 / 8 of
+// its experts 125 / 123, 77 / 79, 14 tokens on 8 77 / 77.
 // Reductions of less than kSumK were not compared.
 constexpr int kSumWideRows = 4, kSumK = 512;
 inline bool narrow_sum_pays(int Tn, int N, int K, int n_cu) { return K >= kSumK && Tn <= (N / 16 <= n_cu ? kSumRows : kSumWideRows); }

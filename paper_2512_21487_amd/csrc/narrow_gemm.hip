@@ -127,7 +127,7 @@ __device__ __forceinline__ void narrow_tile(const NarrowTile<Cfg>& t, int nrows,
         wk += t.w_step;
         if (--seg == 0) { seg = t.seg_steps; wk += t.seg_jump; }
     };
-    // token rows: thread -> row tid / ROW_CHUNKS + PASS_ROWS * i (passes of 8 rows with four wavefronts, of 4 with two),
+    // token rows: thread -> row tid / ROW_CHUNKS + PASS_ROWS * i (passes of 8 rows with four wavefronts, of 4 with two, of 2 with one),
     // 16-byte chunk tid % ROW_CHUNKS of the row's staged ROW_BYTES (32 chunks, 512 bytes).  In LDS chunk c of row r
     // lies at c ^ (r mod 16), so that both the writes (one row) and the fragment reads (16 rows, one
     // chunk column) touch all banks evenly.  Chunks past the end of a row re-read its last one, unused.
@@ -135,14 +135,12 @@ __device__ __forceinline__ void narrow_tile(const NarrowTile<Cfg>& t, int nrows,
     auto load_x = [&](int ch) __attribute__((always_inline)) {
         const uint32_t k_off = min((uint32_t)(ch * Cfg::ROW_BYTES + st_chunk * 16), (uint32_t)t.KT * (kPackK * 2) - 16u);
 #pragma unroll
-        for (int i = 0; i < PASSES; ++i)
-            if (Cfg::PASS_ROWS > 1 || i < nrows) st[i] = load16(t.x, t.x_off[i] + k_off, 0);   // a row a load: none for rows that are not there
+        for (int i = 0; i < PASSES; ++i) st[i] = load16(t.x, t.x_off[i] + k_off, 0);
     };
     auto stage_x = [&](int ch) __attribute__((always_inline)) {
         char* buf = lds + (ch & 1) * Cfg::BUFFER_BYTES;
 #pragma unroll
         for (int i = 0; i < PASSES; ++i) {
-            if (Cfg::PASS_ROWS == 1 && i >= nrows) continue;
             const int r = st_row + Cfg::PASS_ROWS * i;
             *reinterpret_cast<uint4*>(buf + r * Cfg::ROW_BYTES + (st_chunk ^ (r & 15)) * 16) = st[i];
         }
@@ -299,9 +297,6 @@ constexpr int narrow_cols() { return Cfg::WAVES * (SWIGLU ? 16 : 32); }
 
 }  // namespace
 
-// Tile ids: first those of the shared experts s (s.G == 0: none), then those of the routed groups r; each XCD
-// (workgroup id mod 8) takes a contiguous run of both, in which the row tiles of one column tile are neighbours,
-// so that a group with several of them finds its weights in that XCD's L2 after the first.
 // The gate's LDS in a launch that routes by itself: where token rows are staged later.
 struct GateLds {
     uint32_t mask[kNarrowMaxGroups];   // tokens of a local expert, a bit each
@@ -365,6 +360,9 @@ __device__ __forceinline__ void route_here(const GateArgs& t, int G, int lane, b
     }
 }
 
+// Tile ids: first those of the shared experts s (s.G == 0: none), then those of the routed groups r; each XCD
+// (workgroup id mod 8) takes a contiguous run of both, in which the row tiles of one column tile are neighbours,
+// so that a group with several of them finds its weights in that XCD's L2 after the first.
 // GATE: the launch routes by itself, every workgroup with a routed tile for its own use, about 1 us where the gate's own launch and
 // the boundary behind it are 5; shared experts' tiles do not wait for it.
 template <class Cfg, bool SWIGLU, bool PACKED, bool GATE = false>
@@ -655,7 +653,10 @@ hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bo
         // 82.1, 127 / 120; DeepSeek-V2-shaped share, 1 / 4 / 16 tokens 58.0 / 49.2, 65.5 / 60.3, 130 / 111; Qwen3-235B-A22B-shaped share, 1 / 2
         // tokens 25.2 / 21.6, 31.8 / 26.8; with 8 K steps in flight instead of 4 44.4, 61.6, 90.7, 134; 52.5, 62.2, 118; 23.2, 30.0.
         // Four / two wavefronts, 32 rows: DeepSeek-V2-shaped share, 20 / 33 tokens 135 / 120, 145 / 135, Qwen3-235B-A22B-shaped share, 24 / 32
-        // tokens 103 / 95, 104 / 100 (all on eight experts, 20 tokens: 69 / 72).  Beyond 32 tokens an expert can have a second
+        // tokens 103 / 95, 104 / 100; with its load skewed, 20 / 32 tokens: Zipf 1.1 52 / 42, 58 / 54, all on 16 of its experts 115 / 113, 118 /
+        // 116, on 12 105 / 97, 108 / 103.  The mean alone decides, though where all tokens choose the same eight experts, 128-column
+        // tiles are one per compute unit, 64-column ones stage every token row twice: 66 / 69, 70 / 75 (weights in the caller's layout
+        // 78 / 75, 79 / 75; DeepSeek-V2-shaped share 103 / 103, 102 / 97).  Beyond 32 tokens an expert can have a second
         // tile: balanced loads of 33 to 64 tokens still gain 1 - 4 %, all tokens on eight experts lose 25 %.
         const double worth = shared ? (double)sh.K / routed.K : 0.0, touched = routed.G * (1.0 - std::exp(-expected_rows));
         const auto busiest = [&](int w) {
