@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cmath>
+
 namespace moe_ep {
 
 // tokens per router / permute workgroup: one bit each in a 64-bit mask per expert
@@ -132,14 +134,30 @@ constexpr int kSumKind = sizeof(kNarrowTiles) / sizeof(kNarrowTiles[0]);   // be
 // Qwen3-30B-A3B-shaped layer (2048), 1 / 16 tokens 33.1 / 30.7 / 29.9, 146.7 / 149.4 / 141.3; Qwen3-235B-A22B-shaped share (4096), 4 / 16
 // tokens 49.9 / 45.8 / 46.5, 81.5 / 78.2 / 79.7.
 inline int narrow_sum_cols(int N, int n_cu) { return N / 16 < n_cu ? 8 : 16; }
-// Whether it is the faster one: where a compute unit has one workgroup up to kSumRows tokens; where some have two, which all read the
+// Where a compute unit has one workgroup it serves up to kSumRows tokens; where some have two, which all read the
 // token rows, up to kSumWideRows.  Separate launches / one, DeepSeek-V2-shaped share (5120 columns): 1 / 4 / 6 / 8 / 16 tokens 49.4 /
 // 45.2, 59.4 / 57.1, 67.6 / 66.5, 76.6 / 76.9, 110.9 / 113.7 us, all of 16 tokens on eight experts 94 / 104 (Qwen3-235B-A22B-shaped
 // share 65 / 64).  With weights in the caller's layout, Qwen3-235B-A22B-shaped share, 16 tokens balanced 96 / 89, Zipf 1.1 57 / 49, all on 16 / 8 of
 // its experts 125 / 123, 77 / 79, 14 tokens on 8 77 / 77.
 // Reductions of less than kSumK were not compared.
 constexpr int kSumWideRows = 4, kSumK = 512;
-inline bool narrow_sum_pays(int Tn, int N, int K, int n_cu) { return K >= kSumK && Tn <= (N / 16 <= n_cu ? kSumRows : kSumWideRows); }
+inline bool narrow_sum_fits(int Tn, int N, int K, int n_cu) { return K >= kSumK && Tn <= (N / 16 <= n_cu ? kSumRows : kSumWideRows); }
+// And whether it is the faster one.  A workgroup draws its columns of every expert that has a row, and 8 or 16 token rows beside them,
+// at 46 GB/s; of few columns there are few workgroups.  Separate launches spread the same weights over all compute units, up to
+// the 6.2 TB/s of HBM (0.53 of the units' rate), a tile of 64 columns at least, and last about 4 us longer: kSumWorth columns
+// times K of one compute unit.  Separate / one, us, 2 of 8, 8 of 64, 64 of 64 experts per token: 64 columns, K 1408, 4 tokens 20 / 14,
+// 26 / 34, 78 / 109; 512 columns, K 1024, 4 tokens 20 / 16, 29 / 34, 92 / 109; 2048 columns, K 1408, 9 tokens 42 / 37, 136 / 130,
+// 204 / 212.  Over 2156 layers of 64 to 2560 columns, 512 to 5120 deep, 2 to 256 experts, 1 to 16 tokens, of the 3.9 ms that the
+// better one of both saves 3.4 are kept and the worst choice costs 5 % (2 us); always one launch: up to four times as long.
+constexpr double kSumWorth = 1e5;
+inline bool narrow_sum_pays(int Tn, int k, int E, int El, int N, int K, int shared_K, int n_cu)
+{
+    const double rows = (double)Tn * k / E, routed = El * (1.0 - std::exp(-rows)) * K;
+    const int cols = narrow_sum_cols(N, n_cu), turns = (N / cols + n_cu - 1) / n_cu;
+    const auto width = [&](double r) { return cols + (r <= 8.0 ? 8 : 16); };
+    const double here = turns * (routed * width(rows) + (double)shared_K * width(Tn));
+    return here - std::fmax(64.0 * (K > shared_K ? K : shared_K), (routed + shared_K) * N / (0.53 * n_cu)) <= kSumWorth;
+}
 // Tiled projections of prefill with loading wavefronts (loader_gemm.hip): the routed groups `routed` (ragged) and, when
 // `shared` is not NULL, the shared experts (dense) in one launch; no other epilogue than epi == 0, no max_units, both
 // or neither with weights in tile order.

@@ -1015,7 +1015,8 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         uint16_t* sum_rows = fused_out ? reinterpret_cast<uint16_t*>(h_out) + (size_t)t0 * M : out_rows;
         // a few tokens: the down projection's launch aggregates, unless one of the two is timed, the shared experts' rows are elsewhere or
         // `out` begins in the middle of a 4-byte word, of which that launch stores whole ones
-        const bool sums = narrow && !(reinterpret_cast<uintptr_t>(sum_rows) & 3) && narrow_sum_pays(Tn, M, along && Ns * Hs < H ? Ns * Hs : H, n_cu) && !dep && (along ? s2.dense_rows == Tn : Ns == 0) &&
+        const bool sums = narrow && !(reinterpret_cast<uintptr_t>(sum_rows) & 3) && narrow_sum_fits(Tn, M, along && Ns * Hs < H ? Ns * Hs : H, n_cu) &&
+                          (ctx->narrow_named || narrow_sum_pays(Tn, k, E, El, M, H, along ? Ns * Hs : 0, n_cu)) && !dep && (along ? s2.dense_rows == Tn : Ns == 0) &&
                           !(prof && (ctx->prof_mask & ((1u << ST_GEMM2) | (1u << ST_COMBINE))));
         sp = prof_begin(ctx, prof, ST_GEMM2, s_comp);
         if (sums) { HIP_TRY(ctx, launch_narrow_sum(g2, along ? &s2 : nullptr, pos, w, Tn, k, !fused_out, sum_rows, n_cu, s_comp)); kind_down = kSumKind; }

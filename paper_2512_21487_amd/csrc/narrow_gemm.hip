@@ -442,7 +442,7 @@ __global__ __launch_bounds__(Cfg::THREADS, 2) void narrow_gemm_kernel(GemmArgs r
 // expert outputs in memory would be, and add them up in the order of combine.hip.  As two launches the second one, its gap and
 // the first one's last tiles are 8 us or more of one token's forward: the weights of every column are drawn from the start here, by
 // eight wavefronts per workgroup, and the expert outputs never leave the compute unit.  The token rows are read as operands,
-// by every workgroup again (out of L2): at 16 rows per expert as many bytes as the weights, which is where it ends (narrow_sum_pays).
+// by every workgroup again (out of L2): at 16 rows per expert as many bytes as the weights, which is where it ends (narrow_sum_fits, narrow_sum_pays).
 struct SumArgs { const int32_t* pos; const float* w; int Tn, k; bool shared_alone; uint16_t* out; };
 
 // 16 bytes of the lane eight further on in its row of 16 lanes

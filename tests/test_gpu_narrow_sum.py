@@ -84,3 +84,25 @@ def test_output_that_begins_anywhere(offset, pinned):
         rest = flat.cpu().numpy()
         assert (rest[:offset] == 7).all() and (rest[offset + n * wl.hidden:] == 7).all()
     ctx.destroy()
+
+
+@pytest.mark.parametrize("hidden,inter,n_experts,top_k,n_tokens,one", [
+    (64, 1408, 8, 2, 4, True),
+    (64, 1408, 128, 33, 2, False),         # eight workgroups would draw the weights of 58 experts
+    (512, 1024, 64, 64, 4, False),
+    (512, 1024, 8, 2, 9, True),
+    (1024, 2880, 64, 64, 9, False),
+    (2048, 1024, 64, 6, 16, True),         # a workgroup per compute unit
+])
+def test_few_columns_of_many_experts_take_launches_of_their_own(hidden, inter, n_experts, top_k, n_tokens, one):
+    import paper_2512_21487_amd as pkg
+    gen = torch.Generator(device="cuda").manual_seed(93)
+    normal = lambda n, std: torch.empty(n, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    tokens, routed = normal(n_tokens * hidden, 1.0), normal(n_experts * 3 * inter * hidden, 0.02)
+    scores = torch.empty((n_tokens, n_experts), dtype=torch.float32, device="cuda").normal_(generator=gen)
+    out = torch.zeros(n_tokens * hidden, dtype=torch.bfloat16, device="cuda")
+    ctx = pkg.MoeEp(hidden=hidden, inter=inter, n_experts=n_experts, n_local=n_experts, max_tokens=n_tokens, max_top_k=top_k, max_chunks=1)
+    ctx.forward(tokens, scores, routed, None, top_k, n_tokens=n_tokens, out=out)
+    torch.cuda.synchronize()
+    assert (ctx.last_tile_shape("routed_down_gemm")["waves_n"] == 8) == one and out.any()
+    ctx.destroy()
