@@ -599,6 +599,12 @@ static bool narrow_args_fit(const GemmArgs& a)
     return !(a.ldc % 4 || a.c_group_col_stride % 4 || (reinterpret_cast<uintptr_t>(a.C) & 7));
 }
 
+bool narrow_gate_pays(int Tn, int k, int E, int El, int H, int n_cu)
+{
+    const double tiles = El * (1.0 - std::exp(-(double)Tn * k / E)) * ((H + 63) / 64) / n_cu;   // of a compute unit, as far as the host can foresee
+    return k * (tiles - 1.0) <= kGateWorth;
+}
+
 hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bool swiglu, int n_cu, double expected_rows,
                               int max_tokens, long long max_rows, hipStream_t s, int* kind, const GateArgs* gate)
 {

@@ -47,3 +47,18 @@ def test_compute_units_left_to_the_link():
     """A sixteenth of the device at most, whatever its size: a launch beside a copy always has some."""
     beside = pkg.load_library()._ZN6moe_ep17units_beside_linkEi
     assert [beside(n) for n in (256, 304, 64, 32, 16, 8, 1)] == [240, 288, 60, 30, 15, 8, 1]
+
+
+@pytest.mark.parametrize("tokens,top_k,experts,local,inter,inside", [
+    (1, 6, 64, 64, 1408, True), (4, 6, 64, 64, 1408, True), (4, 6, 160, 20, 1536, True), (4, 8, 128, 16, 1536, True), (4, 8, 128, 128, 768, True),
+    (4, 64, 64, 64, 64, True),         # many rounds, a tile in four compute units
+    (1, 64, 64, 64, 1536, False),      # many rounds, six tiles on every compute unit
+    (4, 33, 128, 128, 1536, False),
+    (4, 33, 128, 16, 1536, True),      # a share of them
+    (4, 16, 256, 256, 7168, False),
+    (1, 8, 8, 8, 7168, True),
+])
+def test_gate_of_many_rounds_takes_a_launch_of_its_own(tokens, top_k, experts, local, inter, inside):
+    pays = pkg.load_library()._ZN6moe_ep16narrow_gate_paysEiiiiii
+    pays.restype = ctypes.c_bool
+    assert pays(tokens, top_k, experts, local, inter, 256) == inside
