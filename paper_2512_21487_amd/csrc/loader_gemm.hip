@@ -36,6 +36,7 @@ namespace {
 
 constexpr int kLdGroups = 512;
 constexpr int kLdBlocks = kLoaderRows / 16;                 // 16-row blocks of the tallest tile
+constexpr int kLdLowBlocks = 8;                             // of one where a launch is a single round
 constexpr int kLdWSlots = 3, kLdXSlots = 2;                 // ring slots, a K step of 64 each
 constexpr int kLdWBytes = kPackRows * kPackK * 2;           // weights of a slot, 128 bytes a row
 constexpr int kLdXBytes = kLoaderRows * kPackK * 2;         // token rows of a slot
@@ -48,11 +49,11 @@ constexpr int kLdWRegions = kPackRows / 8 / kLdLoad;        // 1 KB regions (8 r
 constexpr int kLdXRegions = kLoaderRows / 8 / kLdLoad;      // and of token rows, at most
 
 struct Cut { int tiles, base, rem; };   // row tiles of base blocks, the first rem of them one more
-__host__ __device__ __forceinline__ Cut cut_rows(int rows)
+__device__ __forceinline__ Cut cut_rows(int rows, int most)   // most: blocks of the tallest, kLdLowBlocks or kLdBlocks
 {
     Cut c;
     const int u = (rows + 15) / 16;
-    c.tiles = (u + kLdBlocks - 1) / kLdBlocks;
+    c.tiles = most == kLdLowBlocks ? (u + kLdLowBlocks - 1) / kLdLowBlocks : (u + kLdBlocks - 1) / kLdBlocks;
     c.base = c.tiles ? u / c.tiles : 0;
     c.rem = c.tiles ? u - c.base * c.tiles : 0;
     return c;
@@ -204,36 +205,58 @@ __global__ __launch_bounds__(kLdThreads) void loader_gemm_kernel(GemmArgs a, Gem
     char* const lds = reinterpret_cast<char*>(lds4);
     int4* const s_tile = reinterpret_cast<int4*>(lds + kLdRing);
     int* const s_filled = reinterpret_cast<int*>(s_tile + kLdCache);
-    int* const s_pref = s_filled + 1;
+    int* const s_most = s_filled + 1;
+    int* const s_pref = s_most + 1;
     constexpr int COLS = SWIGLU ? kPackRows / 2 : kPackRows;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // row tiles before every ragged group
+    const int NT = (a.N + COLS - 1) / COLS;
+    // the dense groups' column tiles, and how many ragged tiles one of theirs is worth (its K may be longer)
+    const int d_nt = d.G > 0 ? (d.N + COLS - 1) / COLS : 0, d_worth = d.G > 0 ? max(1, (d.K + a.K / 2) / a.K) : 1;
+
+    // Row tiles before every ragged group.  Where tiles of at most kLdLowBlocks blocks are one round all the same, that is what they
+    // are: the round lasts as long as its tallest tile.  Forwards, tiles of up to 12 / 8 blocks, us: one expert of 146 rows, 1536 x 1536, 63 / 57,
+    // two of 174, 1408 x 7168, 153 / 127, 16 of about 160, 1024 x 2880, 83 / 63 (in grouped_gemm.hip, 128 rows, 55, 125, 77).
     if (wave == 0) {
-        int before = 0, filled = 0;
-        for (int g0 = 0; g0 < a.G; g0 += 64) {
-            const int g = g0 + lane;
-            const int n = g < a.G ? cut_rows(a.offset[g + 1] - a.offset[g]).tiles : 0;
-            int incl = n;
+        int before = 0, filled = 0, low = 0;   // low: how many more there would be of kLdLowBlocks, this lane's groups
+        const auto count_tiles = [&](int most) {
+            before = filled = low = 0;
+            for (int g0 = 0; g0 < a.G; g0 += 64) {
+                const int g = g0 + lane, rows = g < a.G ? a.offset[g + 1] - a.offset[g] : 0;
+                const int n = cut_rows(rows, most).tiles;
+                low += cut_rows(rows, kLdLowBlocks).tiles - n;
+                int incl = n;
 #pragma unroll
-            for (int s = 1; s < 64; s <<= 1) {
-                const int up = __shfl_up(incl, s, 64);
-                if (lane >= s) incl += up;
+                for (int s = 1; s < 64; s <<= 1) {
+                    const int up = __shfl_up(incl, s, 64);
+                    if (lane >= s) incl += up;
+                }
+                if (g < a.G) s_pref[g] = before + incl - n;
+                before += __shfl(incl, 63, 64);
+                filled += __builtin_popcountll(__ballot(n > 0));
             }
-            if (g < a.G) s_pref[g] = before + incl - n;
-            before += __shfl(incl, 63, 64);
-            filled += __builtin_popcountll(__ballot(n > 0));
+            if (lane == 0) { s_pref[a.G] = before; *s_filled = filled; }
+        };
+        count_tiles(kLdBlocks);
+        int most = kLdBlocks;
+        if (before * NT <= (int)gridDim.x) {
+            const bool lower = __ballot(low > 0) != 0;   // a group has more tiles of kLdLowBlocks
+            if (lower)
+#pragma unroll
+                for (int s = 1; s < 64; s <<= 1) low += __shfl_xor(low, s, 64);
+            const int d_low = d.G > 0 ? d.G * cut_rows(d.dense_rows, kLdLowBlocks).tiles * d_nt * d_worth : 0;
+            if ((before + low) * NT + d_low <= (int)gridDim.x) {
+                most = kLdLowBlocks;
+                if (lower) count_tiles(most);
+            }
         }
-        if (lane == 0) { s_pref[a.G] = before; *s_filled = filled; }
+        if (lane == 0) *s_most = most;
     }
     __syncthreads();
-    const int NT = (a.N + COLS - 1) / COLS;
-    const int total = __builtin_amdgcn_readfirstlane(s_pref[a.G]) * NT;
-    // the dense groups' tiles, and how many ragged ones a tile of them is worth (its K may be longer)
-    const int d_nt = d.G > 0 ? (d.N + COLS - 1) / COLS : 0;
-    const int d_mt = d.G > 0 ? cut_rows(d.dense_rows).tiles : 0;
-    const int d_total = d.G * d_mt * d_nt, d_worth = d.G > 0 ? max(1, (d.K + a.K / 2) / a.K) : 1;
+    const int total = __builtin_amdgcn_readfirstlane(s_pref[a.G]) * NT, most = __builtin_amdgcn_readfirstlane(*s_most);
+    const int d_mt = d.G > 0 ? cut_rows(d.dense_rows, most).tiles : 0;
+    const int d_total = d.G * d_mt * d_nt;
     const int worth = total + d_total * d_worth;
     const int rounds = (worth + (int)gridDim.x - 1) / (int)gridDim.x;
     const int active = rounds > 0 ? min((int)gridDim.x, (((worth + rounds - 1) / rounds) + 7) & ~7) : 0;
@@ -283,7 +306,7 @@ __global__ __launch_bounds__(kLdThreads) void loader_gemm_kernel(GemmArgs a, Gem
         const int band = l / (kBand * nt), band_h = min(kBand, mt - band * kBand), lb = l - band * kBand * nt;
         const int ni = lb / band_h, mi = band * kBand + (lb - ni * band_h);
         const int g_row0 = dense ? 0 : a.offset[g], g_end = dense ? d.dense_rows : a.offset[g + 1];
-        const Cut c = cut_rows(g_end - g_row0);
+        const Cut c = cut_rows(g_end - g_row0, most);
         const int blocks = c.base + (mi < c.rem ? 1 : 0), row0 = g_row0 + (mi * c.base + min(mi, c.rem)) * 16;
         return make_int4(dense ? a.G + g : g, row0, min(blocks * 16, g_end - row0) | blocks << 16 | (mt == 1 ? 1 << 24 : 0), ni * COLS);
     };
@@ -469,7 +492,7 @@ hipError_t launch_loader_gemm(const GemmArgs& routed, const GemmArgs* shared, bo
     const GemmArgs& sh = shared ? *shared : none;
     if (routed.offset == nullptr || !loader_args_fit(routed, swiglu, true)) return hipErrorInvalidValue;
     if (shared && (sh.offset || sh.dense_rows < 1 || (sh.Wp != nullptr) != (routed.Wp != nullptr) || !loader_args_fit(sh, swiglu, false))) return hipErrorInvalidValue;
-    const int lds = kLdRing + kLdCache * 16 + (routed.G + 2) * 4;
+    const int lds = kLdRing + kLdCache * 16 + (routed.G + 3) * 4;
     const auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((n_cu + 7) / 8 * 8), dim3(kLdThreads), lds, s, routed, sh); };
     if (routed.Wp) swiglu ? go(loader_gemm_kernel<true, true>) : go(loader_gemm_kernel<false, true>);
     else swiglu ? go(loader_gemm_kernel<true, false>) : go(loader_gemm_kernel<false, false>);
@@ -478,8 +501,8 @@ hipError_t launch_loader_gemm(const GemmArgs& routed, const GemmArgs* shared, bo
 
 hipError_t loader_gemm_init()
 {
-    const int most = kLdRing + kLdCache * 16 + (kLdGroups + 2) * 4;
-    static_assert(kLdRing + kLdCache * 16 + (kLdGroups + 2) * 4 <= 160 * 1024, "a workgroup's LDS");
+    const int most = kLdRing + kLdCache * 16 + (kLdGroups + 3) * 4;
+    static_assert(kLdRing + kLdCache * 16 + (kLdGroups + 3) * 4 <= 160 * 1024, "a workgroup's LDS");
     for (const void* f : {reinterpret_cast<const void*>(&loader_gemm_kernel<true, true>), reinterpret_cast<const void*>(&loader_gemm_kernel<false, true>),
                           reinterpret_cast<const void*>(&loader_gemm_kernel<true, false>), reinterpret_cast<const void*>(&loader_gemm_kernel<false, false>)}) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, most);

@@ -165,3 +165,32 @@ def test_rows_longer_than_a_tile_can_address(monkeypatch, hidden, inter, env):
     # bf16 rounding of the activation, of the expert's output and of the result: 2^-9 / sqrt(3) each at most, relative to the norm;
     # sums of 1.1e7 products in 3.5e5 steps of fp32: under 2^-24 sqrt(3.5e5) = 3.5e-5
     assert float((out.float().view(T, hidden) - want).norm() / want.norm()) < 5e-3
+
+
+@pytest.mark.parametrize("n_shared", [0, 1])
+@pytest.mark.parametrize("past", [0, 1])
+def test_low_tiles_fill_one_round_or_miss_it(monkeypatch, n_shared, past):
+    """Two experts that every token chooses: 128-row tiles, those of a shared expert among them, that are as many as there are workgroups
+    (or one less); with one row more in each expert they would be a second round and are 192 rows high."""
+    import paper_2512_21487_amd as pkg
+    n_cu = (torch.cuda.get_device_properties(0).multi_processor_count + 7) // 8 * 8
+    tiles = n_cu // (2 + n_shared)
+    M, H, T = 64, 64, tiles * 128 + past
+    gen = torch.Generator(device="cuda").manual_seed(77)
+    normal = lambda n, std: torch.empty(n, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    tokens, routed, shared = normal(T * M, 1.0), normal(2 * 3 * H * M, 0.1), normal(3 * H * M, 0.1) if n_shared else None
+    logits = torch.empty((T, 2), dtype=torch.float32, device="cuda").normal_(generator=gen)
+    outs = []
+    for env in ({"MOE_EP_GEMM_VARIANT": "21"}, {"MOE_EP_MERGE": "1"}):
+        with monkeypatch.context() as m:
+            for name, value in env.items():
+                m.setenv(name, value)
+            ctx = pkg.MoeEp(hidden=M, inter=H, n_experts=2, n_local=2, n_shared=n_shared, shared_inter=H if n_shared else 0, max_tokens=T,
+                            max_top_k=2, max_chunks=1)
+        out = torch.zeros(T * M, dtype=torch.bfloat16, device="cuda")
+        ctx.forward(tokens, logits, routed, shared, 2, 1, 0, n_tokens=T, out=out)
+        torch.cuda.synchronize()
+        assert (ctx.last_tile_shape("routed_down_gemm")["rows"] == 192) == ("MOE_EP_MERGE" in env)
+        outs.append(out)
+        ctx.destroy()
+    assert outs[0].any() and torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
