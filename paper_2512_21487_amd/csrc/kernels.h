@@ -13,6 +13,14 @@ constexpr int kTokPerBlock = 64;
 // Token rows that a launch of the gate brings in beside its own work (16-byte aligned; first: set by the launcher)
 struct RowCopy { void* dst; const void* src; size_t bytes; int first; };
 
+// Whether the first of r chunks is brought in that way.  Not where the shared experts come first: they wait for every chunk, and the
+// others start on the link one hand-over between streams later.  Nor with more scores than a lane's 16 (E > 256), which the gate
+// then reads one by one over the link.  Pinned host I/O, the first chunk on the copies' stream / with the gate, us: 1024 hidden, 32 of 256
+// experts and one shared, 64 tokens, interleaved in one / two / four chunks 75 / 59, 101 / 95, 153 / 146, shared first in two / four 107 / 120,
+// 174 / 199, 512 tokens 158 / 168, 272 / 284 (DeepSeek-V2-Lite-shaped layer, 64 / 4096 tokens in two 406 / 404, 1387 / 1387); 384 hidden, 512
+// experts, 64 / 160 tokens in two 104 / 115, 119 / 130, 4096 in one 339 / 364, but 16 / 512 in one 71 / 56, 108 / 97.
+bool rows_come_with_gate(int E, int r, bool shared_first);
+
 // ---- gate: softmax + top-k (Sec. 2.1) and per-workgroup expert bit masks for the partition
 hipError_t launch_router(const float* logits, int Tn, int E, int k, int e0, int El, int32_t* idx,
                          float* w, unsigned long long* blk_mask, hipStream_t s, const RowCopy* copy = nullptr);

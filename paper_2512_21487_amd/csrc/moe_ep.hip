@@ -725,10 +725,11 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         }
     }
     // The first chunk: the gate's launch reads the scores where the caller has them and brings the token rows in, on the
-    // caller's stream.  The others come in on a stream of their own, as does the first one where that is timed.  Qwen3-235B-A22B-shaped
+    // caller's stream.  The others come in on a stream of their own, as does the first one where that is timed or the slower way (rows_come_with_gate).  Qwen3-235B-A22B-shaped
     // share in 2 chunks, its first one on the copies' stream / here: 500 / 1024 / 2000 / 4096 tokens 373 / 362, 512 / 502, 750 / 732,
     // 1343 / 1343 us (there the next chunk's rows are the longer wait); in 4 chunks 300 / 4096 tokens 565 / 545, 1379 / 1368.
-    const bool in_place = pinned && !dep && !ctx->memcpy_in && !(reinterpret_cast<uintptr_t>(h_tokens) & 15) &&
+    const bool shared_first = !dep && Ns > 0 && order == MOE_EP_ORDER_SHARED_FIRST;
+    const bool in_place = pinned && !dep && rows_come_with_gate(E, r, shared_first) && !ctx->memcpy_in && !(reinterpret_cast<uintptr_t>(h_tokens) & 15) &&
                           !(prof && (ctx->prof_mask & (1u << ST_COPY_IN)));
     const auto comes_in = [&](int cidx) { return pinned && !(in_place && cidx == 0); };
     const bool inbound = comes_in(r - 1);
@@ -897,7 +898,6 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
     };
     // The shared experts may run beside routed ones -- every token's with the first chunk where they come first -- unless
     // only one side's weights are in tile order.
-    const bool shared_first = !dep && Ns > 0 && order == MOE_EP_ORDER_SHARED_FIRST;
     const bool shared_beside = !dep && Ns > 0 && (prep_r != nullptr) == (prep_s != nullptr);
     const auto rows_beside = [&](int cidx, int Tn) { return !shared_beside ? 0 : !shared_first ? Tn : cidx == 0 ? T : 0; };
     int c0_t0, c0_Tn;

@@ -20,6 +20,8 @@
 
 namespace moe_ep {
 
+bool rows_come_with_gate(int E, int r, bool shared_first) { return E <= 256 && (r == 1 || !shared_first); }
+
 constexpr int kRouterTokens = 16;   // of a workgroup: 16 lanes each
 constexpr int kLinkBytes = 128 * 1024;   // in flight over the host link while rows come in
 

@@ -62,3 +62,11 @@ def test_gate_of_many_rounds_takes_a_launch_of_its_own(tokens, top_k, experts, l
     pays = pkg.load_library()._ZN6moe_ep16narrow_gate_paysEiiiiii
     pays.restype = ctypes.c_bool
     assert pays(tokens, top_k, experts, local, inter, 256) == inside
+
+
+@pytest.mark.parametrize("experts,chunks,shared_first,with_gate", [
+    (256, 1, False, True), (256, 1, True, True), (256, 2, False, True), (256, 2, True, False), (257, 1, False, False), (512, 4, True, False)])
+def test_first_chunk_comes_in_with_the_gate(experts, chunks, shared_first, with_gate):
+    rule = pkg.load_library()._ZN6moe_ep19rows_come_with_gateEiib
+    rule.restype = ctypes.c_bool
+    assert rule(experts, chunks, ctypes.c_bool(shared_first)) == with_gate
