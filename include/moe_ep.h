@@ -224,7 +224,9 @@ int moe_ep_get_routing(moe_ep_ctx *ctx, int32_t chunk, int32_t *idx, float *w, i
  * may run in the routed experts' launches (moe_ep_last_shared_beside); a forward that times stage 4 or 5 gives them
  * launches of their own, since stages that share a launch have no times of their own: the same bits, and possibly a
  * longer forward than the same call untimed (moe_ep_set_profiling_stages leaves the two out).  The same holds for stages 3 and 6
- * of up to 16 tokens, and for stages 0, 1 and 2 of up to 4.
+ * of up to 16 tokens, and for stages 0, 1 and 2 of up to 4.  In pinned-host mode it holds for stage 8: a forward that times it brings
+ * the first chunk's rows in with copies of their own; in one that does not, the gate's launch may do so, and ms[0] then has
+ * their time.
  * moe_ep_get_stage_ms synchronises, returns the per-forward AVERAGE over the forwards recorded
  * since the last call, and opens a new window of `depth` forwards:
  *   ms[0] gate  ms[1] partition (permute + row gather)  ms[2] routed gate/up GEMM
@@ -238,7 +240,7 @@ int moe_ep_get_routing(moe_ep_ctx *ctx, int32_t chunk, int32_t *idx, float *w, i
 int moe_ep_set_profiling(moe_ep_ctx *ctx, int32_t depth);
 /* Restricts the events to the stages whose bit (1 << index into ms[]) is set in `mask`; the default
  * is every stage.  Events between all stages cost a few percent of a forward (more for small
- * calls).  Without the bits of stages 4 and 5 a forward makes the launches it makes untimed; where the shared experts
+ * calls).  Without the bits of the stages named above a forward makes the launches it makes untimed; where the shared experts
  * run in the routed experts' launches, ms[2] and ms[3] are then the times of both together. */
 int moe_ep_set_profiling_stages(moe_ep_ctx *ctx, uint32_t mask);
 int moe_ep_get_stage_ms(moe_ep_ctx *ctx, float *ms, int32_t n);

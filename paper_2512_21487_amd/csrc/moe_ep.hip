@@ -29,6 +29,8 @@ enum Stage { ST_ROUTER = 0, ST_PARTITION, ST_GEMM1, ST_GEMM2, ST_SGEMM1, ST_SGEM
 // 48 rows 174 / 180, 210 / 198, 215 / 213, 249 / 243; DeepSeek-V2-shaped share, 11 / 19 / 24 / 28 rows 230 / 220, 256 / 247, 255 / 258,
 // 260 / 285; Qwen3-235B-A22B-shaped share, 8 / 16 / 32 rows 119 / 117, 115 / 117, 121 / 121; Qwen3-30B-A3B-shaped layer, 16 / 24 rows
 // 210 / 208, 217 / 219, and with its load skewed (Zipf 1.1) 24 rows 173 / 180.
+// At 8 to 19 rows the narrow ones win by up to 6 % (Qwen3-235B-A22B-shaped share, 16 rows: lose 2), at 24 both are within 2 % (4 under that skew), at
+// 28 and more they lose up to 10 (DeepSeek-V2-Lite-shaped layer: win 2).  Three rows, 32 tokens, lose 3: no line in rows per expert alone parts the two.
 constexpr double kNarrowMeanRows = 24.0;
 // The shared experts go along up to this many rows; beyond, launches of their own with tall tiles.  Apart / along, the routed
 // experts in narrow tiles both times: DeepSeek-V2-Lite-shaped layer, 256 / 512 tokens 251 / 212, 269 / 229 us; DeepSeek-V2-shaped share,
@@ -57,8 +59,12 @@ constexpr int kNarrowVariant = -2;
 // The tiled launches of the kernels with loading wavefronts (loader_gemm.hip), as a variant.  Shared experts run beside the
 // routed ones up to kAlongRows rows -- apart (256-row tiles of their own) / along, us: DeepSeek-V2-shaped share, 1600 / 5000 /
 // 10000 / 12000 tokens 349 / 289, 691 / 622, 1146 / 1120, 1330 / 1287, 16384 tokens 1709 / 1711 and on another box 1688 / 1705;
-// DeepSeek-V2-Lite-shaped layer, 1531 / 2700 / 4096 tokens 351 / 304, 462 / 428, 592 / 568 -- and where every reduction has at
-// least kAlongK steps: shorter launches are mostly start-up and epilogue, and were not compared.
+// DeepSeek-V2-Lite-shaped layer, 1531 / 2700 / 4096 tokens 351 / 304, 462 / 428, 592 / 568 -- and where hidden and both
+// intermediate sizes are at least kAlongK elements (8 K steps of the up and routed down reductions, as many of each shared expert's part of its
+// own): shorter launches are mostly start-up and epilogue, and were not compared.  Routed experts alone were, against the kernels without loading
+// wavefronts: hidden and intermediate 64 to 1024, 2 to 64 experts, 128 to 16384 tokens 0.72 - 1.04 of their time (128 x 64, 8 experts, 128 / 16384
+// tokens 25.6 / 21.8, 51 / 37 us; 512 x 256, 16 experts, 4096 tokens 38.8 / 40.3), 512 experts of 2048 x 512 and one shared, 2048 / 16384 tokens
+// 664 / 634, 2603 / 1440; moe_ep_forward_dep, the four layers in 2 and 4 chunks, 0.89 - 1.00.
 constexpr int kLoaderVariant = -9, kAlongRows = 14336, kAlongK = 512;
 
 // Chunks that arrive while others are multiplied (moe_ep_forward): kLinkUnits copy workgroups of four wavefronts (128 KB over the link, as

@@ -13,8 +13,8 @@
 // both (narrow_gemm.hip).
 // Where a call's token rows have to cross the host link first, more workgroups of the same launch fetch them (RowCopy):
 // scores and rows are read in place, and the call stays on one stream.  Qwen3-235B-A22B-shaped share, pinned host I/O, copies on a stream of
-// their own, scores first / now: 1 / 64 / 256 / 1024 tokens 63 / 34, 155 / 135,
-// 210 / 191, 447 / 430 us (256 KB over the link instead of 128: 34, 138, 193, 431).
+// their own, scores first / now: 1 / 64 / 256 / 1024 tokens 63 / 34, 146 / 130, 207 / 188, 449 / 425 us (256 KB over the
+// link instead of 128: 1 - 2 % slower).
 #include "gate.h"
 #include "partition.h"
 

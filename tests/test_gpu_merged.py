@@ -1,4 +1,4 @@
-"""Routed and shared experts in one launch per projection (launch_merged_gemm) against the same tiles in launches of
+"""Routed and shared experts in one launch per projection (loader_gemm.hip) against the tiled kernels in launches of
 their own, which the oracle tests pin: the same bits whatever the two sides' tile counts, K and columns are."""
 import numpy as np
 import pytest
