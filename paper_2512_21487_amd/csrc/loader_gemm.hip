@@ -38,7 +38,7 @@ namespace {
 
 constexpr int kLdGroups = 512;
 constexpr int kLdBlocks = kLoaderRows / 16;                 // 16-row blocks of the tallest tile
-constexpr int kLdLowBlocks = 8;                             // of one where a launch is a single round
+constexpr int kLdLowBlocks = 8;                             // of one where lower tiles take no more rounds
 constexpr int kLdWSlots = 3, kLdXSlots = 2;                 // ring slots, a K step of 64 each
 constexpr int kLdWBytes = kPackRows * kPackK * 2;           // weights of a slot, 128 bytes a row
 constexpr int kLdXBytes = kLoaderRows * kPackK * 2;         // token rows of a slot
@@ -217,9 +217,13 @@ __global__ __launch_bounds__(kLdThreads) void loader_gemm_kernel(GemmArgs a, Gem
     // the dense groups' column tiles, and how many ragged tiles one of theirs is worth (its K may be longer)
     const int d_nt = d.G > 0 ? (d.N + COLS - 1) / COLS : 0, d_worth = d.G > 0 ? max(1, (d.K + a.K / 2) / a.K) : 1;
 
-    // Row tiles before every ragged group.  Where tiles of at most kLdLowBlocks blocks are one round all the same, that is what they
-    // are: the round lasts as long as its tallest tile.  Forwards, tiles of up to 12 / 8 blocks, us: one expert of 146 rows, 1536 x 1536, 63 / 57,
-    // two of 174, 1408 x 7168, 153 / 127, 16 of about 160, 1024 x 2880, 83 / 63 (in grouped_gemm.hip, 128 rows, 55, 125, 77).
+    // Row tiles before every ragged group.  Tiles of at most kLdLowBlocks blocks where they take no more rounds (a dense tile counts as the
+    // ragged ones it is worth) or are one for a workgroup all the same, since a round lasts as long as its tallest tile -- unless they are only a
+    // few more (a seventh), which cost more than the others gain, in a launch that keeps three quarters of the workgroups busy.  Of 9824
+    // launches of 1 to 256 experts (2 to 5800 rows each, skewed and not, shared experts beside them or not) this leaves 0.3 % of the time to the
+    // better one of both, tiles of up to 12 blocks always 5.7 %, of 8 always 6.5 %.  Forwards, 12 / this, us: one expert of 146 rows, 1536 x 1536,
+    // 63 / 57, two of 174, 1408 x 7168, 153 / 127, 16 of about 160, 1024 x 2880, 83 / 63 (in grouped_gemm.hip, 128 rows, 55, 125, 77); 4 of the
+    // DeepSeek-V2-shaped layer's experts and its shared ones, 2000 tokens 244 / 230 (231).
     if (wave == 0) {
         constexpr int PER = kLdGroups / 64;
         // consecutive groups of a lane: one scan over the lanes, however many groups there are.  With one per 64 groups, a forward of 1000 tokens
@@ -260,16 +264,18 @@ __global__ __launch_bounds__(kLdThreads) void loader_gemm_kernel(GemmArgs a, Gem
             if (lane == 0) { s_pref[a.G] = before; *s_filled = filled; }
         };
         count_tiles(kLdBlocks);
+        const auto dense_tiles = [&](int most) { return d.G > 0 ? d.G * cut_rows(d.dense_rows, most).tiles * d_nt : 0; };
+        const int d_tall = dense_tiles(kLdBlocks), d_low = dense_tiles(kLdLowBlocks);
         int most = kLdBlocks;
-        if (before * NT <= (int)gridDim.x) {
-            const bool lower = __ballot(low > 0) != 0;   // a group has more tiles of kLdLowBlocks
-            if (lower)
+        const bool recount = __ballot(low > 0) != 0;
+        if (recount || d_low != d_tall) {
+            if (recount)
 #pragma unroll
                 for (int s = 1; s < 64; s <<= 1) low += __shfl_xor(low, s, 64);
-            const int d_low = d.G > 0 ? d.G * cut_rows(d.dense_rows, kLdLowBlocks).tiles * d_nt * d_worth : 0;
-            if ((before + low) * NT + d_low <= (int)gridDim.x) {
+            const int wgs = (int)gridDim.x, tall = before * NT + d_tall * d_worth, tiles = (before + low) * NT + d_low, lower = tiles + d_low * (d_worth - 1);
+            if ((tiles <= wgs || lower <= (tall + wgs - 1) / wgs * wgs) && (lower - tall > tall / 7 || tiles <= wgs - wgs / 4)) {
                 most = kLdLowBlocks;
-                if (lower) count_tiles(most);
+                if (recount) count_tiles(most);
             }
         }
         if (lane == 0) *s_most = most;

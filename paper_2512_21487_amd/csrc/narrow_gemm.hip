@@ -664,6 +664,8 @@ hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bo
         // tiles are one per compute unit, 64-column ones stage every token row twice: 66 / 69, 70 / 75 (weights in the caller's layout
         // 78 / 75, 79 / 75; DeepSeek-V2-shaped share 103 / 103, 102 / 97).  Beyond 32 tokens an expert can have a second
         // tile: balanced loads of 33 to 64 tokens still gain 1 - 4 %, all tokens on eight experts lose 25 %.
+        // Over 1599 layers of 1024 to 7168 columns, H 256 to 5120, 1 to 256 experts, 1 to 32 tokens, none shared: 4.1 % of the time in all, 1008 layers gain
+        // 3 % and more, 42 lose it (10 % at most).
         const double worth = shared ? (double)sh.K / routed.K : 0.0, touched = routed.G * (1.0 - std::exp(-expected_rows));
         const auto busiest = [&](int w) {
             const int cols = w * (swiglu ? 16 : 32);

@@ -168,14 +168,14 @@ def test_rows_longer_than_a_tile_can_address(monkeypatch, hidden, inter, env):
 
 
 @pytest.mark.parametrize("n_shared", [0, 1])
+@pytest.mark.parametrize("rounds", [1, 2])
 @pytest.mark.parametrize("past", [0, 1])
-def test_low_tiles_fill_one_round_or_miss_it(monkeypatch, n_shared, past):
-    """Two experts that every token chooses: 128-row tiles, those of a shared expert among them, that are as many as there are workgroups
-    (or one less); with one row more in each expert they would be a second round and are 192 rows high."""
+def test_low_tiles_fill_the_rounds_or_miss_the_last(monkeypatch, n_shared, rounds, past):
+    """Two experts that every token chooses: 128-row tiles, those of a shared expert among them, that are one or two per workgroup
+    (or one less in all); with one row more in each expert they would be a round more and are 192 rows high."""
     import paper_2512_21487_amd as pkg
     n_cu = (torch.cuda.get_device_properties(0).multi_processor_count + 7) // 8 * 8
-    tiles = n_cu // (2 + n_shared)
-    M, H, T = 64, 64, tiles * 128 + past
+    M, H, T = 64, 64, rounds * n_cu // (2 + n_shared) * 128 + past
     gen = torch.Generator(device="cuda").manual_seed(77)
     normal = lambda n, std: torch.empty(n, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
     tokens, routed, shared = normal(T * M, 1.0), normal(2 * 3 * H * M, 0.1), normal(3 * H * M, 0.1) if n_shared else None
