@@ -121,12 +121,14 @@ hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bo
 // round, 5 / 9 / 16 tokens 89 / 87, 125 / 129, 154 / 165; 67 / 62, -, 111 / 115; 47 / 46, -, 78 / 74; 71 / 74, -, 140 / 143: every
 // workgroup that follows another one on its compute unit routes again.
 constexpr int kGateTokens = 4, kGateExperts = 256;
-// And with many experts per token, or many tiles, the same is true of up to four: a round of the gate per expert chosen, for every 64-column
-// tile that a compute unit has beyond its first.  Apart / in the launch, 64-column layers, 8 of 256, 16 of 256, 33 of 128, 64 of 64 experts: H 1536,
-// 4 tokens 35 / 33, 48 / 51, 60 / 112, 59 / 90 us, 1 token 26 / 20, 34 / 30, 43 / 46, 58 / 74; H 7168, 4 tokens 91 / 98, 134 / 193, 164 / 405, 138 / 292.  Over
-// 921 layers of 64 to 4096 columns, H 64 to 7168, the rule keeps 3.33 of the 3.34 ms that the better one of both saves; the worst choice costs 4 us.
-constexpr double kGateWorth = 40.0;
-bool narrow_gate_pays(int Tn, int k, int E, int El, int H, int n_cu);
+// And with many experts per token, or many tiles, the same is true of up to four: a round of the gate per expert chosen, in every workgroup
+// launched -- one per 64 columns of every expert that could be chosen, whether it is or not -- that a compute unit has beyond one or two.  Apart /
+// in the launch, 64-column layers, 8 of 256, 16 of 256, 33 of 128, 64 of 64 experts: H 1536, 4 tokens 35 / 33, 48 / 51, 60 / 112, 59 / 90 us, 1 token 26 / 20,
+// 34 / 30, 43 / 46, 58 / 74; H 7168, 4 tokens 91 / 98, 134 / 193, 164 / 405, 138 / 292; 33 of 256 with 32 of them here, 128 columns, H 7168, 1 token 46 / 116.
+// Over 5648 layers of 128 to 4096 columns, H 256 to 7168, 8 to 256 experts here, the rule keeps 17.4 of the 18.5 ms that the better one of both
+// saves, and none that it takes in is slower by more than 3 %.
+constexpr double kGateWorth = 15.0, kGateFree = 1.5;
+bool narrow_gate_pays(int Tn, int k, int El, int H, int n_cu);
 constexpr int kNarrowRows = 64, kNarrowWaves = 4;         // tallest row tile, wavefronts
 constexpr int kNarrowFewRows = 16, kNarrowFewWaves = 2;   // the same of the tiles for a few tokens; also of one wavefront
 constexpr int kNarrowPairRows = 32;                       // and of two wavefronts for some more

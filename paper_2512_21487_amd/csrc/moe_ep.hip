@@ -961,7 +961,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         int32_t* perm = ctx->perm + (size_t)t0 * k;
 
         // a few tokens that are on the GPU: the gate/up projection's launch routes, unless one of the two is timed
-        const bool routes = narrow && Tn > 0 && Tn <= kGateTokens && E <= kGateExperts && k <= E && (ctx->narrow_named || narrow_gate_pays(Tn, k, E, El, H, n_cu)) && !dep && !pinned && !(along && takes_all && T != Tn) &&
+        const bool routes = narrow && Tn > 0 && Tn <= kGateTokens && E <= kGateExperts && k <= E && (ctx->narrow_named || narrow_gate_pays(Tn, k, El, H, n_cu)) && !dep && !pinned && !(along && takes_all && T != Tn) &&
                             !(prof && (ctx->prof_mask & ((1u << ST_ROUTER) | (1u << ST_PARTITION) | (1u << ST_GEMM1))));
         const GateArgs route{log_dev + (size_t)t0 * E, Tn, E, k, e0, idx, w, count, offset, pos, perm};
         if (!routes && !(in_place && cidx == 0)) { const int rc = gate(cidx); if (rc != MOE_EP_OK) return rc; }

@@ -599,10 +599,10 @@ static bool narrow_args_fit(const GemmArgs& a)
     return !(a.ldc % 4 || a.c_group_col_stride % 4 || (reinterpret_cast<uintptr_t>(a.C) & 7));
 }
 
-bool narrow_gate_pays(int Tn, int k, int E, int El, int H, int n_cu)
+bool narrow_gate_pays(int Tn, int k, int El, int H, int n_cu)
 {
-    const double tiles = El * (1.0 - std::exp(-(double)Tn * k / E)) * ((H + 63) / 64) / n_cu;   // of a compute unit, as far as the host can foresee
-    return k * (tiles - 1.0) <= kGateWorth;
+    const double wgs = (double)(Tn * k < El ? Tn * k : El) * ((H + 63) / 64) / n_cu;   // of a compute unit
+    return k * (wgs - kGateFree) <= kGateWorth;
 }
 
 hipError_t launch_narrow_gemm(const GemmArgs& routed, const GemmArgs* shared, bool swiglu, int n_cu, double expected_rows,

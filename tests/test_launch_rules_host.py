@@ -49,19 +49,20 @@ def test_compute_units_left_to_the_link():
     assert [beside(n) for n in (256, 304, 64, 32, 16, 8, 1)] == [240, 288, 60, 30, 15, 8, 1]
 
 
-@pytest.mark.parametrize("tokens,top_k,experts,local,inter,inside", [
-    (1, 6, 64, 64, 1408, True), (4, 6, 64, 64, 1408, True), (4, 6, 160, 20, 1536, True), (4, 8, 128, 16, 1536, True), (4, 8, 128, 128, 768, True),
-    (4, 64, 64, 64, 64, True),         # many rounds, a tile in four compute units
-    (1, 64, 64, 64, 1536, False),      # many rounds, six tiles on every compute unit
-    (4, 33, 128, 128, 1536, False),
-    (4, 33, 128, 16, 1536, True),      # a share of them
-    (4, 16, 256, 256, 7168, False),
-    (1, 8, 8, 8, 7168, True),
+@pytest.mark.parametrize("tokens,top_k,local,inter,inside", [
+    (1, 6, 64, 1408, True), (4, 6, 64, 1408, True), (4, 6, 20, 1536, True), (4, 8, 16, 1536, True), (4, 8, 128, 768, True),
+    (4, 64, 64, 64, True),         # many rounds, a tile in four compute units
+    (1, 64, 64, 1536, False),      # many rounds, six tiles on every compute unit
+    (4, 33, 128, 1536, False),
+    (4, 33, 16, 1536, True),       # few experts here
+    (1, 33, 32, 7168, False),      # few, but many columns
+    (4, 16, 256, 7168, False),
+    (1, 8, 8, 4096, True),
 ])
-def test_gate_of_many_rounds_takes_a_launch_of_its_own(tokens, top_k, experts, local, inter, inside):
-    pays = pkg.load_library()._ZN6moe_ep16narrow_gate_paysEiiiiii
+def test_gate_of_many_rounds_takes_a_launch_of_its_own(tokens, top_k, local, inter, inside):
+    pays = pkg.load_library()._ZN6moe_ep16narrow_gate_paysEiiiii
     pays.restype = ctypes.c_bool
-    assert pays(tokens, top_k, experts, local, inter, 256) == inside
+    assert pays(tokens, top_k, local, inter, 256) == inside
 
 
 @pytest.mark.parametrize("experts,chunks,shared_first,with_gate", [
