@@ -6,7 +6,7 @@
 // out, the loads alone were three quarters of a launch (Qwen3-30B-A3B-shaped layer, 8192 tokens, gate/up 345 of 437 us).  In
 // grouped_gemm.hip a wavefront loads and multiplies, and a load that finds the path full holds back the MFMAs behind it.  A launch is
 // also bound by how its tiles are dealt, by number: of several rounds 6 to 16 % of the units' time has no workgroup, of one row tile per
-// expert up to 31 (profiles/loader_gemm_counters.txt, where the matrix pipes are busy 54 - 60 % of a gate/up launch that fills the chip).
+// expert up to 30 (profiles/loader_gemm_counters.txt, where the matrix pipes are busy 54 - 59 % of a gate/up launch that fills the chip).
 // Here four wavefronts only load and eight only multiply, so that the two overlap whatever each waits for:
 //  - Loading: global_load_lds into two rings, the weights (three slots of 32 KB, two K steps ahead) and the token rows
 //    (two slots, one K step ahead).  Each wavefront counts its own loads; one barrier of the workgroup per K step hands a
