@@ -162,19 +162,21 @@ __device__ __forceinline__ void run_tile(const char* lds, uint32_t xa, uint32_t 
     asm volatile("s_nop 15");
     asm volatile("s_nop 15");
     SB();
-    // a lane holds token row (lane & 15) of each block and output columns 4 * (lane >> 4) + {0..3} of it; two
-    // neighbouring column blocks exchange halves so that it stores 8 consecutive columns of one of them
+    // A lane holds token row (lane & 15) of each block and output columns 4 * (lane >> 4) + {0..3} of it.  Two neighbouring column
+    // blocks exchange halves, so that it has 8 consecutive columns of one of them, and the lanes trade places: four neighbours then
+    // store 64 consecutive bytes of a row, which leave a compute unit four at a time; 16 bytes of 16 rows in turn kept a down
+    // launch waiting (DeepSeek-V2-Lite-shaped layer, 4096 tokens, down launch 196 / 191 us, the launch without its epilogue 160).
     int lane;   // asked for here: kept over the K loop it would cost a register
     asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
-    const int fr = lane & 15, kh = lane >> 4, col = (kh & 1) * 16 + (kh >> 1) * 8;
-    const uint32_t at = (uint32_t)(fr * out.ldc + col) * 2u;
+    const int row = lane >> 2, col = (lane & 3) * 8;
+    const int from = (((lane & 1) * 2 + (lane >> 1 & 1)) * 16 + row) * 4;   // the lane that computed them, as ds_bpermute counts
+    const uint32_t at = (uint32_t)(row * out.ldc + col) * 2u;
     const auto store = [&](auto guard) __attribute__((always_inline)) {
 #pragma unroll
         for (int mb = 0; mb < N; ++mb) {
             // a row of blocks is pinned in its registers right before its turn
             asm volatile("; accumulator row" : "+v"(acc[mb][0]), "+v"(acc[mb][1]), "+v"(acc[mb][2]), "+v"(acc[mb][3]));
-            const int m = mb * 16 + fr;
-            if (m >= out.nrows) continue;   // the same for the lanes of an exchange (they share lane & 15)
+            if (mb * 16 >= out.nrows) break;
 #pragma unroll
             for (int nb = 0; nb < (SWIGLU ? 2 : 4); nb += 2) {
                 uint32_t pk[2][2];
@@ -188,10 +190,11 @@ __device__ __forceinline__ void run_tile(const char* lds, uint32_t xa, uint32_t 
                 }
                 const auto s0 = __builtin_amdgcn_permlane16_swap(pk[0][0], pk[1][0], false, false);
                 const auto s1 = __builtin_amdgcn_permlane16_swap(pk[0][1], pk[1][1], false, false);
-                if (decltype(guard)::value && nb * 16 + col >= out.n_left) continue;
-                uint4 o;
-                o.x = s0[0]; o.y = s1[0]; o.z = s0[1]; o.w = s1[1];
-                *reinterpret_cast<uint4*>(reinterpret_cast<char*>(out.c + (size_t)(mb * 16) * out.ldc + nb * 16) + at) = o;
+                uint4 o;   // every lane takes part, also for rows and columns that are not there
+                o.x = __builtin_amdgcn_ds_bpermute(from, s0[0]); o.y = __builtin_amdgcn_ds_bpermute(from, s1[0]);
+                o.z = __builtin_amdgcn_ds_bpermute(from, s0[1]); o.w = __builtin_amdgcn_ds_bpermute(from, s1[1]);
+                if (mb * 16 + row < out.nrows && !(decltype(guard)::value && nb * 16 + col >= out.n_left))
+                    *reinterpret_cast<uint4*>(reinterpret_cast<char*>(out.c + (size_t)(mb * 16) * out.ldc + nb * 16) + at) = o;
             }
         }
     };
