@@ -48,7 +48,8 @@ def kernel_name(ctx, stage):
     if (sh["rows"], sh["waves_n"]) == (16, 8):   # the launch that aggregates as well
         return f"narrow_sum_kernel<{tile_order}, {sh['cols']}>"
     if (sh["rows"], sh["cols"], sh["waves_m"], sh["waves_n"]) == (192, 256, 2, 4):   # loading wavefronts beside the multiplying ones
-        return f"loader_gemm_kernel<{swiglu}, {tile_order}>"
+        # (a launch that is timed is of one projection: 1 gate/up, 2 down)
+        return f"loader_gemm_kernel<{1 if swiglu == 'true' else 2}, {tile_order}>"
     # last argument: what the epilogue writes (MOE_EP_EXPERT_OUT, the routed down projection only)
     epi = {"f": 1, "s": 2}.get(os.environ.get("MOE_EP_EXPERT_OUT", " ")[0], 0) if stage == "routed_down_gemm" else 0
     # and whether the weights are read from a tile-order copy (moe_ep_prepare_weights)

@@ -224,7 +224,8 @@ int moe_ep_get_routing(moe_ep_ctx *ctx, int32_t chunk, int32_t *idx, float *w, i
  * may run in the routed experts' launches (moe_ep_last_shared_beside); a forward that times stage 4 or 5 gives them
  * launches of their own, since stages that share a launch have no times of their own: the same bits, and possibly a
  * longer forward than the same call untimed (moe_ep_set_profiling_stages leaves the two out).  The same holds for stages 3 and 6
- * of up to 16 tokens, and for stages 0, 1 and 2 of up to 4.  In pinned-host mode it holds for stage 8: a forward that times it brings
+ * of up to 16 tokens, for stages 0, 1 and 2 of up to 4, and for stages 2 and 3 of larger calls, whose projections may
+ * be one launch.  In pinned-host mode it holds for stage 8: a forward that times it brings
  * the first chunk's rows in with copies of their own; in one that does not, the gate's launch may do so, and ms[0] then has
  * their time.
  * moe_ep_get_stage_ms synchronises, returns the per-forward AVERAGE over the forwards recorded

@@ -22,8 +22,9 @@ constexpr int kPermuteThreads = 1024;
 __global__ __launch_bounds__(kPermuteThreads) void dispatch_permute_kernel(
     const int32_t* __restrict__ idx, const unsigned long long* __restrict__ blk_mask, int nblk, int Tn, int k,
     int e0, int El, int32_t* __restrict__ count, int32_t* __restrict__ offset, int32_t* __restrict__ pos,
-    int32_t* __restrict__ perm)
+    int32_t* __restrict__ perm, Clear clear)
 {
+    for (int i = blockIdx.x * kPermuteThreads + threadIdx.x; i < clear.n; i += gridDim.x * kPermuteThreads) clear.p[i] = 0;
     extern __shared__ unsigned long long smem[];
     unsigned long long* smask = smem;
     int* sbase = reinterpret_cast<int*>(smem + El);   // rows of this workgroup's tokens before it, then the row base
@@ -89,7 +90,7 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(
 }
 
 hipError_t launch_dispatch(const int32_t* idx, const unsigned long long* blk_mask, int Tn, int k, int e0, int El,
-                           int32_t* count, int32_t* offset, int32_t* pos, int32_t* perm, hipStream_t s)
+                           int32_t* count, int32_t* offset, int32_t* pos, int32_t* perm, hipStream_t s, const Clear& clear)
 {
     if (Tn <= 0) {
         hipLaunchKernelGGL(dispatch_empty_kernel, dim3(1), dim3(256), 0, s, El, count, offset);
@@ -98,7 +99,7 @@ hipError_t launch_dispatch(const int32_t* idx, const unsigned long long* blk_mas
     const int nblk = (Tn + kTokPerBlock - 1) / kTokPerBlock;
     hipLaunchKernelGGL(dispatch_permute_kernel, dim3(nblk), dim3(kPermuteThreads),
                        El * (sizeof(unsigned long long) + 2 * sizeof(int)), s, idx, blk_mask, nblk, Tn, k, e0, El,
-                       count, offset, pos, perm);
+                       count, offset, pos, perm, clear);
     return hipGetLastError();
 }
 

@@ -13,6 +13,9 @@ constexpr int kTokPerBlock = 64;
 // Token rows that a launch of the gate brings in beside its own work (16-byte aligned; first: set by the launcher)
 struct RowCopy { void* dst; const void* src; size_t bytes; int first; };
 
+// integers that a launch of the partition sets to zero for the launches behind it
+struct Clear { int32_t* p; int n; };
+
 // Whether the first of r chunks is brought in that way.  Not where the shared experts come first: they wait for every chunk, and the
 // others start on the link one hand-over between streams later.  Nor with more scores than a lane's 16 (E > 256), which the gate
 // then reads one by one over the link.  Pinned host I/O, the first chunk on the copies' stream / with the gate, us: 1024 hidden, 32 of 256
@@ -27,12 +30,13 @@ hipError_t launch_router(const float* logits, int Tn, int E, int k, int e0, int 
 
 // gate and partition of at most kTokPerBlock tokens in one launch; outputs as launch_router and launch_dispatch
 hipError_t launch_route_and_partition(const float* logits, int Tn, int E, int k, int e0, int El, int32_t* idx, float* w,
-                                      int32_t* count, int32_t* offset, int32_t* pos, int32_t* perm, hipStream_t s, const RowCopy* copy = nullptr);
+                                      int32_t* count, int32_t* offset, int32_t* pos, int32_t* perm, hipStream_t s, const RowCopy* copy = nullptr,
+                                      const Clear& clear = Clear{nullptr, 0});
 
 // ---- partition by expert (Sec. 2.1; Sec. 3.1 "The MoE Part")
 // count [El], offset [El + 1], pos [Tn * k] (row of an assignment or -1), perm [rows] (row -> assignment)
 hipError_t launch_dispatch(const int32_t* idx, const unsigned long long* blk_mask, int Tn, int k, int e0, int El,
-                           int32_t* count, int32_t* offset, int32_t* pos, int32_t* perm, hipStream_t s);
+                           int32_t* count, int32_t* offset, int32_t* pos, int32_t* perm, hipStream_t s, const Clear& clear = Clear{nullptr, 0});
 hipError_t launch_gather_rows(const void* tokens, const int32_t* perm, const int32_t* n_rows_ptr,
                               int k, int M, void* xp, int grid, hipStream_t s);
 
@@ -174,11 +178,28 @@ inline bool narrow_sum_pays(int Tn, int k, int E, int El, int N, int K, int shar
     const double here = turns * (routed * width(rows) + (double)shared_K * width(Tn));
     return here - std::fmax(64.0 * (K > shared_K ? K : shared_K), (routed + shared_K) * N / (0.53 * n_cu)) <= kSumWorth;
 }
-// Tiled projections of prefill with loading wavefronts (loader_gemm.hip): the routed groups `routed` (ragged) and, when
-// `shared` is not NULL, the shared experts (dense) in one launch; no other epilogue than epi == 0, no max_units, both
-// or neither with weights in tile order.
-hipError_t launch_loader_gemm(const GemmArgs& routed, const GemmArgs* shared, bool swiglu, int n_cu, hipStream_t s);
+// Tiled projections of prefill with loading wavefronts (loader_gemm.hip): the routed groups `up` (gate/up), `down` or both (ragged)
+// and, when up_shared / down_shared are not NULL, the shared experts (dense) in one launch; no other epilogue than epi == 0, no
+// max_units, all or none with weights in tile order.  Of both, the down projection reads what the same launch's gate/up projection writes, for the
+// same offset and dense rows.  sync: kLdCounters zeros, and of both projections kRowTileInts more for every row tile (loader_row_tiles).
+hipError_t launch_loader_gemm(const GemmArgs* up, const GemmArgs* up_shared, const GemmArgs* down, const GemmArgs* down_shared, int n_cu, int32_t* sync, hipStream_t s);
+constexpr int kLdCounters = 1024, kRowTileInts = 32;      // a counter has a line of its own
+// the most row tiles of Tn tokens, k experts each, El of them here, and of dense_rows rows beside them: of 128 rows, the last of an expert lower
+inline long long loader_row_tiles(long long Tn, int k, int El, long long dense_rows) { return Tn * (k < El ? k : El) / 128 + El + (dense_rows + 127) / 128; }
 constexpr int kLoaderRows = 192;                          // tallest row tile
+// Both projections in one launch where the gate/up projection has kPairRounds tiles for a compute unit, of `rows` rows per expert expected.  With
+// fewer, nearly every workgroup has one tile of each projection, and what was a launch's end is a wait for the last of them.  Forwards, us, launches
+// of their own / one: 0.75 rounds Qwen3-235B-A22B-shaped share, 1024 / 2500 / 4096 tokens 119 / 129, 149 / 150, 222 / 233; 1.3 and 1.6 rounds
+// DeepSeek-V2-shaped share, 900 / 1700 tokens 253 / 259, 291 / 313; 2.2 and 2.6 rounds 2502 in a chunk 738 / 729 (two chunks), 4096 tokens 475 / 470; more:
+// 9000 / 16384 tokens 971 / 934, 1631 / 1636; DeepSeek-V2-Lite-shaped layer, 500 / 1531 / 2500 / 4096 tokens 242 / 216, 302 / 276, 408 / 404, 555 / 546, weights in the
+// caller's layout, 800 tokens 268 / 237; Qwen3-30B-A3B-shaped layer, 1000 / 2000 tokens 237 / 239, 275 / 268, skewed, 2000 / 4000 / 8192 tokens 308 / 282,
+// 422 / 404, 687 / 677.
+constexpr double kPairRounds = 2.0;
+inline double loader_up_tiles(double rows, int El, int H, int dense_rows, int Ns, int Hs)
+{
+    const double tiles = rows / kLoaderRows + 0.5;
+    return El * (tiles > 1.0 ? tiles : 1.0) * ((H + 127) / 128) + (double)Ns * ((dense_rows + kLoaderRows - 1) / kLoaderRows) * ((Hs + 127) / 128);
+}
 hipError_t loader_gemm_init();    // raises the dynamic-LDS limit of its kernels once
 hipError_t grouped_gemm_init();   // raises the dynamic-LDS limit of every instantiation once
 // the shape a launch of `variant` really runs (after the fall-backs for a short K or many groups):

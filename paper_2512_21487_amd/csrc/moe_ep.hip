@@ -100,6 +100,7 @@ struct moe_ep_ctx {
     bool narrow_named = false;   // the number came from the environment: it alone decides
     bool by_rule = true;     // no tile shape, instruction or form of the expert outputs was asked for by name
     int merge = -1;          // shared and routed experts in one tiled launch: -1 by rule (plan_chunk), 0 never, 1 always
+    int pair = -1;           // both projections in one tiled launch: -1 by rule (plan_chunk), 0 never, 1 always
     int last_shared_up = -1, last_shared_down = -1;   // tile variants of the shared experts' last launches; before any, shared_variant
     bool fused_gather = true;  // the gate/up projection gathers the token rows itself (no grouped copy)
     int y_mode = 0;            // expert outputs: 0 bf16, 1 fp32, 2 bf16 scaled by the routing weight (expert_out_mode)
@@ -131,6 +132,7 @@ struct moe_ep_ctx {
     int32_t* count = nullptr; int32_t* offset = nullptr;
     uint16_t* xp = nullptr; uint16_t* h = nullptr; uint16_t* y = nullptr;
     uint16_t* hs = nullptr;
+    int32_t* sync = nullptr; long long sync_tiles = 0;   // launch_loader_gemm's, and the row tiles there is room for
     // streams and events
     hipStream_t s_in = nullptr, s_out = nullptr;  // the two link directions (pinned-host mode)
     hipEvent_t ev_start = nullptr, ev_done = nullptr, ev_comp_done = nullptr;
@@ -230,6 +232,16 @@ void bind_workspaces(moe_ep_ctx* ctx, char* slab, const WsLayout& L)
     ctx->hs = reinterpret_cast<uint16_t*>(slab + L.hs);
 }
 
+// Row tiles of launches of both projections that a context has counters for: a line for 128 rows and one for an expert, up to 2 MB.
+// Beyond, the projections are launches of their own.
+constexpr long long kSyncTiles = 1 << 14, kNoallocSyncTiles = 1 << 13;
+size_t sync_ints(long long row_tiles) { return (size_t)kLdCounters + (size_t)row_tiles * kRowTileInts; }
+long long sync_tiles(const moe_ep_config& c)
+{
+    const long long n = loader_row_tiles(c.max_tokens, c.max_top_k, c.n_local, c.n_shared > 0 ? c.max_tokens : 0);
+    return n <= kSyncTiles ? n : 0;
+}
+
 // the environment knobs of a context (tuning and comparison aids; none changes a result bit)
 void read_knobs(moe_ep_ctx* ctx)
 {
@@ -243,6 +255,7 @@ void read_knobs(moe_ep_ctx* ctx)
     if (const char* v = getenv("MOE_EP_UP_UNITS")) ctx->up_units = atoi(v);
     if (const char* v = getenv("MOE_EP_DOWN_UNITS")) ctx->down_units = atoi(v);
     if (const char* v = getenv("MOE_EP_MERGE")) ctx->merge = atoi(v) != 0;
+    if (const char* v = getenv("MOE_EP_PAIR")) ctx->pair = atoi(v) != 0;
     if (const char* v = getenv("MOE_EP_NARROW_ROWS")) { ctx->narrow_rows = atof(v); ctx->narrow_named = true; }
     // workgroups of a copy kernel: ~128 KB in flight fills the host link; more only queues up in the
     // memory fabric in front of the compute kernels
@@ -511,7 +524,9 @@ int moe_ep_create(const moe_ep_config* cfg, moe_ep_ctx** out_ctx)
 
     const WsLayout L = ws_layout(*cfg);
     char* slab = nullptr;
-    if (hipMalloc(reinterpret_cast<void**>(&slab), L.total) != hipSuccess) { delete ctx; return MOE_EP_ENOMEM; }
+    ctx->sync_tiles = sync_tiles(*cfg);
+    if (hipMalloc(reinterpret_cast<void**>(&slab), L.total + sync_ints(ctx->sync_tiles) * 4) != hipSuccess) { delete ctx; return MOE_EP_ENOMEM; }
+    ctx->sync = reinterpret_cast<int32_t*>(slab + L.total);
     bind_workspaces(ctx, slab, L);  // L.tokens == 0: d_tokens is the slab base, freed in destroy
     ctx->last_variants.assign((size_t)cfg->max_chunks, {-1, -1, false});
 
@@ -877,9 +892,11 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
     }
     // How a chunk of Tn tokens runs, and whether `rows` rows of the shared experts run in the same launches (rows = 0:
     // there are none, or they may not).
-    struct Plan { bool narrow, loader, along; int up, down; };
+    // pair: both projections in one launch of loader_gemm.hip.
+    struct Plan { bool narrow, loader, along; int up, down; bool pair = false; };
     // timing the shared experts' stages takes launches of their own
     const bool shared_timed = prof && (ctx->prof_mask & ((1u << ST_SGEMM1) | (1u << ST_SGEMM2)));
+    const bool projection_timed = prof && (ctx->prof_mask & ((1u << ST_GEMM1) | (1u << ST_GEMM2)));
     const int ct_up = (H + 127) / 128, ct_down = (M + 255) / 256;
     const auto plan_chunk = [&](int Tn, int rows) -> Plan {
         Plan p{false, false, false, -1, -1};
@@ -892,7 +909,11 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         const auto addressed = [](long long row) { return kLoaderRows * row * 2 < (1ll << 32); };
         if (ctx->by_rule && addressed(H) && (fits || addressed(M))) {
             const bool pays = rows <= kAlongRows && M >= kAlongK && H >= kAlongK && Hs >= kAlongK, reach = addressed(M) && addressed((long long)Ns * Hs);
-            return Plan{false, true, rows > 0 && !shared_timed && reach && (ctx->merge == 1 || (ctx->merge != 0 && pays)), kLoaderVariant, kLoaderVariant};
+            p = Plan{false, true, rows > 0 && !shared_timed && reach && (ctx->merge == 1 || (ctx->merge != 0 && pays)), kLoaderVariant, kLoaderVariant};
+            // a projection that is timed is a launch of its own
+            p.pair = !projection_timed && ctx->pair != 0 && loader_row_tiles(Tn, k, El, p.along ? rows : 0) <= ctx->sync_tiles &&
+                     (ctx->pair == 1 || loader_up_tiles((double)Tn * k / E, El, H, p.along ? rows : 0, Ns, Hs) >= kPairRounds * n_cu);
+            return p;
         }
         // a shape, an instruction or a form of the expert outputs was asked for by name, or rows are too long for the above:
         // grouped_gemm.hip.  Tile shapes of the two routed projections: N = H in tiles of 128 activation columns, N = M in tiles of 256 columns
@@ -909,6 +930,13 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
     int c0_t0, c0_Tn;
     chunk_range(T, r_1, r_2, 0, &c0_t0, &c0_Tn);
     const bool first_takes_all = shared_first && plan_chunk(c0_Tn, rows_beside(0, c0_Tn)).along;
+    // what the launch of the partition clears for a chunk's projections
+    const auto to_clear = [&](int cidx, int Tn) -> Clear {
+        const int rows = rows_beside(cidx, Tn);
+        const Plan p = plan_chunk(Tn, rows);
+        if (!p.loader) return Clear{nullptr, 0};
+        return Clear{ctx->sync, (int)sync_ints(p.pair ? loader_row_tiles(Tn, k, El, p.along ? rows : 0) : 0)};
+    };
     const auto gate = [&](int cidx) -> int {
         int t0, Tn;
         chunk_range(T, r_1, r_2, cidx, &t0, &Tn);
@@ -924,7 +952,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         if (Tn > 0 && Tn <= kTokPerBlock)   // one workgroup's tokens: partitioned in the same launch
             HIP_TRY(ctx, launch_route_and_partition(scores, Tn, E, k, e0, El, idx, w, ctx->count + (size_t)cidx * El,
                                                     ctx->offset + (size_t)cidx * (El + 1), ctx->pos + (size_t)t0 * k, ctx->perm + (size_t)t0 * k,
-                                                    s_comp, here ? &rows : nullptr));
+                                                    s_comp, here ? &rows : nullptr, to_clear(cidx, Tn)));
         else HIP_TRY(ctx, launch_router(scores, Tn, E, k, e0, El, idx, w, ctx->blk_mask, s_comp, here ? &rows : nullptr));
         prof_end(ctx, sp, s_comp);
         return MOE_EP_OK;
@@ -970,7 +998,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         // the fused gather addresses a chunk's token rows with 32-bit byte offsets
         const bool fused = ctx->fused_gather && (unsigned long long)Tn * M * 2 < (1ull << 32);
         int sp = prof_begin(ctx, prof, ST_PARTITION, s_comp);
-        if (!one_block) HIP_TRY(ctx, launch_dispatch(idx, ctx->blk_mask, Tn, k, e0, El, count, offset, pos, perm, s_comp));
+        if (!one_block) HIP_TRY(ctx, launch_dispatch(idx, ctx->blk_mask, Tn, k, e0, El, count, offset, pos, perm, s_comp, to_clear(cidx, Tn)));
         if (Tn > 0 && !fused) {   // the grouped copy reads the token rows
             if (comes_in(cidx)) HIP_TRY(ctx, hipStreamWaitEvent(s_comp, ctx->ev_in[cidx], 0));
             HIP_TRY(ctx, launch_gather_rows(tok_dev + (size_t)t0 * M, perm, offset + El, k, M, ctx->xp, bw_grid, s_comp));
@@ -1004,7 +1032,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         int kind_up = 0, kind_down = 0;   // of the narrow launches that follow
         sp = prof_begin(ctx, prof, ST_GEMM1, s_comp);
         if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g1, along ? &s1 : nullptr, true, n_cu, (double)Tn * k / E, Tn, a_max, s_comp, &kind_up, routes ? &route : nullptr));
-        else if (loader) HIP_TRY(ctx, launch_loader_gemm(g1, along ? &s1 : nullptr, true, cus, s_comp));
+        else if (loader) { if (!plan.pair) HIP_TRY(ctx, launch_loader_gemm(&g1, along ? &s1 : nullptr, nullptr, nullptr, cus, ctx->sync, s_comp)); }
         else HIP_TRY(ctx, launch_grouped_gemm(g1, true, v_up, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);
 
@@ -1027,7 +1055,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         sp = prof_begin(ctx, prof, ST_GEMM2, s_comp);
         if (sums) { HIP_TRY(ctx, launch_narrow_sum(g2, along ? &s2 : nullptr, pos, w, Tn, k, !fused_out, sum_rows, n_cu, s_comp)); kind_down = kSumKind; }
         else if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g2, along ? &s2 : nullptr, false, n_cu, (double)Tn * k / E, Tn, a_max, s_comp, &kind_down));
-        else if (loader) HIP_TRY(ctx, launch_loader_gemm(g2, along ? &s2 : nullptr, false, cus, s_comp));
+        else if (loader) HIP_TRY(ctx, launch_loader_gemm(plan.pair ? &g1 : nullptr, plan.pair && along ? &s1 : nullptr, &g2, along ? &s2 : nullptr, cus, ctx->sync, s_comp));
         else HIP_TRY(ctx, launch_grouped_gemm(g2, false, v_down, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);
         if (narrow) {
@@ -1303,6 +1331,7 @@ int moe_ep_get_routing(moe_ep_ctx* ctx, int32_t chunk, int32_t* idx, float* w, i
 // the moment the code object is loaded until the process ends.  In host code the name is only a handle
 // for hipGetSymbolAddress; kernels and copies get the address that call returns on each device.
 __device__ __align__(256) static unsigned char scratch[MOE_EP_NOALLOC_SCRATCH_BYTES];
+__device__ __align__(256) static int32_t scratch_sync[kLdCounters + kNoallocSyncTiles * kRowTileInts];   // beside what moe_ep_workspace_bytes counts
 
 namespace {
 
@@ -1349,6 +1378,13 @@ extern "C" int moe_ep_forward_noalloc(const moe_ep_config* cfg, const void* toke
             if (hipGetDeviceProperties(&prop, cfg->device) != hipSuccess) { set_why(why, "hipGetDeviceProperties failed"); return MOE_EP_EHIP; }
             if (grouped_gemm_init() != hipSuccess || loader_gemm_init() != hipSuccess) { set_why(why, "raising the kernels' LDS limit failed"); return MOE_EP_EHIP; }
             slot.base = static_cast<char*>(p);
+            if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch_sync)) != hipSuccess || p == nullptr) {
+                (void)hipGetLastError();
+                set_why(why, "hipGetSymbolAddress(scratch_sync) failed");
+                return MOE_EP_EHIP;
+            }
+            ctx->sync = static_cast<int32_t*>(p);
+            ctx->sync_tiles = kNoallocSyncTiles;
             ctx->n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
             read_knobs(ctx);
             slot.ready = true;

@@ -5,7 +5,7 @@
 
 namespace moe_ep {
 
-struct PartitionOut { int32_t *count, *offset, *pos, *perm; };   // as launch_dispatch writes them
+struct PartitionOut { int32_t *count, *offset, *pos, *perm; Clear clear; };   // as launch_dispatch writes them
 
 // One wavefront: exclusive prefix of the rows of all experts, added to base[e] (rows of this workgroup's
 // tokens' predecessors); count != NULL: rows and prefix are also written out.  El <= 512: a lane owns 8

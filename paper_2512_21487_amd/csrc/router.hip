@@ -64,6 +64,7 @@ __global__ __launch_bounds__((PARTITION ? kTokPerBlock : kRouterTokens) * 16) vo
     }
     __syncthreads();
     if (PARTITION) {
+        for (int i = tid; i < part.clear.n; i += THREADS) part.clear.p[i] = 0;
         for (int e = tid; e < El; e += THREADS) { s_total[e] = __popcll(smask[e]); s_base[e] = 0; }
         __syncthreads();
         if (wave == 0) scan_experts(lane, El, s_total, s_base, part.count, part.offset);
@@ -119,10 +120,10 @@ hipError_t launch_router(const float* logits, int Tn, int E, int k, int e0, int 
 }
 
 hipError_t launch_route_and_partition(const float* logits, int Tn, int E, int k, int e0, int El, int32_t* idx, float* w,
-                                      int32_t* count, int32_t* offset, int32_t* pos, int32_t* perm, hipStream_t s, const RowCopy* copy)
+                                      int32_t* count, int32_t* offset, int32_t* pos, int32_t* perm, hipStream_t s, const RowCopy* copy, const Clear& clear)
 {
     if (Tn < 1 || Tn > kTokPerBlock) return hipErrorInvalidValue;
-    return launch<true>(logits, Tn, E, k, e0, El, idx, w, nullptr, PartitionOut{count, offset, pos, perm}, copy, s);
+    return launch<true>(logits, Tn, E, k, e0, El, idx, w, nullptr, PartitionOut{count, offset, pos, perm, clear}, copy, s);
 }
 
 }  // namespace moe_ep

@@ -1,0 +1,148 @@
+"""Both projections in one launch (loader_gemm.hip) against a launch of each, which test_gpu_loader.py pins: the same bits on every
+row count, K extent and column remainder, however many tiles are drawn at a time and whoever draws them."""
+import numpy as np
+import pytest
+
+from workloads import make_inputs, tiny_workload
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# as in test_gpu_loader.py: none, one, around blocks of 16 and row tiles of 128 and 192
+LOADS = [0, 1, 15, 16, 17, 0, 33, 95, 96, 97, 191, 192, 193, 210, 385, 600]
+
+
+def _ctx(monkeypatch, make, pair, **env):
+    with monkeypatch.context() as m:
+        m.setenv("MOE_EP_NARROW_ROWS", "0")
+        m.setenv("MOE_EP_PAIR", str(pair))
+        for name, value in env.items():
+            m.setenv(name, value)
+        return make()
+
+
+@pytest.mark.parametrize("prepared", [False, True])
+@pytest.mark.parametrize("merge", ["0", "1"])
+@pytest.mark.parametrize("hidden,inter,shared_inter", [
+    (64, 64, 64),        # one K step everywhere: eight tiles at a time
+    (128, 192, 64),      # 2, 3, and a shared down projection of 2
+    (576, 256, 704),     # 9, 4 and 22; columns that end inside a tile
+    (64, 1088, 64),      # 17 column tiles of gate/up, one of down
+])
+def test_same_bits_as_a_launch_of_each(monkeypatch, hidden, inter, shared_inter, merge, prepared):
+    import gpu_util as g
+    wl = tiny_workload(name=f"pair_M{hidden}_H{inter}", n_tokens=sum(LOADS), hidden=hidden, inter=inter, n_experts=16,
+                       n_local=16, top_k=1, n_shared=2, shared_inter=shared_inter)
+    inp = make_inputs(wl, seed=81)
+    logits = np.full((wl.n_tokens, wl.n_experts), -30.0, dtype=np.float32)
+    logits[np.arange(wl.n_tokens), np.repeat(np.arange(16), LOADS)] = 5.0
+    inp["gate_logits"][:] = logits[np.random.default_rng(8).permutation(wl.n_tokens)]
+    outs = []
+    for pair in (0, 1):
+        ctx = _ctx(monkeypatch, lambda: g.make_ctx(wl), pair, MOE_EP_MERGE=merge)
+        d = g.DeviceInputs(wl, inp)
+        if prepared:
+            ctx.prepare_weights(d.routed, d.shared)
+        outs.append([g.run_forward(ctx, wl, d, r=r, order=order) for r, order in ((1, 0), (3, 0), (3, 1))])
+        assert ctx.last_tile_shape("routed_gate_up_gemm")["rows"] == 192, "the launches under test"
+        ctx.destroy()
+    assert outs[0][0].any() and all(np.array_equal(a, b) for a, b in zip(*outs))
+
+
+@pytest.mark.parametrize("n_tokens,n_local,shared_inter", [
+    (40, 7, 64),        # one row tile each: some workgroups begin with the routed tiles
+    (700, 1, 64),       # one expert
+    (700, 300, 192),    # most experts one short tile, some none
+    (1, 3, 64),         # one row
+])
+def test_few_and_many_experts(monkeypatch, n_tokens, n_local, shared_inter):
+    import gpu_util as g
+    wl = tiny_workload(name=f"pair_{n_local}", n_tokens=n_tokens, hidden=320, inter=192, n_experts=n_local + 3, local_begin=2,
+                       n_local=n_local, top_k=2 if n_local > 1 else 1, n_shared=2, shared_inter=shared_inter)
+    inp = make_inputs(wl, seed=82)
+    outs = []
+    for pair in (0, 1):
+        ctx = _ctx(monkeypatch, lambda: g.make_ctx(wl), pair, MOE_EP_MERGE="1")
+        d = g.DeviceInputs(wl, inp)
+        ctx.prepare_weights(d.routed, d.shared)
+        outs.append([g.run_forward(ctx, wl, d, r=r, order=r - 1) for r in (1, 2)])
+        ctx.destroy()
+    assert outs[0][0].any() and all(np.array_equal(a, b) for a, b in zip(*outs))
+
+
+def _layer(monkeypatch, pair, M=4352, H=64, E=512, T=2048, k=8, seed=83):
+    """Experts of one row tile and 17 column tiles of a single K step in the down projection."""
+    import paper_2512_21487_amd as pkg
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    normal = lambda n, std: torch.empty(n, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    tokens, routed = normal(T * M, 1.0), normal(E * 3 * H * M, 0.02)
+    logits = torch.empty((T, E), dtype=torch.float32, device="cuda").normal_(generator=gen)
+    ctx = _ctx(monkeypatch, lambda: pkg.MoeEp(hidden=M, inter=H, n_experts=E, n_local=E, n_shared=0, shared_inter=0, max_tokens=T,
+                                              max_top_k=k, max_chunks=1), pair)
+    out = torch.zeros(T * M, dtype=torch.bfloat16, device="cuda")
+    return ctx, lambda: ctx.forward(tokens, logits, routed, None, k, 1, 0, n_tokens=T, out=out), out, logits
+
+
+def test_more_tiles_than_are_kept_and_two_streams(monkeypatch):
+    """The list of drawn tiles is written over many times; two contexts on two streams share the compute units."""
+    want = []
+    for seed in (83, 84):
+        ctx, run, out, _ = _layer(monkeypatch, 0, seed=seed)
+        run()
+        torch.cuda.synchronize()
+        want.append(out.clone())
+        ctx.destroy()
+    sides = [_layer(monkeypatch, 1, seed=seed) for seed in (83, 84)]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    for _ in range(4):
+        for (ctx, run, out, _), s in zip(sides, streams):
+            with torch.cuda.stream(s):
+                out.zero_()
+                run()
+    torch.cuda.synchronize()
+    for (ctx, _, out, _), w in zip(sides, want):
+        assert w.any() and torch.equal(out.view(torch.int16), w.view(torch.int16))
+        ctx.destroy()
+
+
+def test_replayed_graph(monkeypatch):
+    """The counters are cleared inside the captured launches: every replay gives the eager bits, also for other scores."""
+    ctx, run, out, logits = _layer(monkeypatch, 1, T=512)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        run()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        run()
+    for i in range(4):
+        logits.copy_(torch.roll(logits, 7, 1))
+        run()
+        torch.cuda.synchronize()
+        want = out.clone()
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert want.any() and torch.equal(out.view(torch.int16), want.view(torch.int16)), f"replay {i}"
+    ctx.destroy()
+
+
+def test_without_a_context(monkeypatch):
+    """moe_ep_forward_noalloc, at a size that makes one launch of both projections by rule."""
+    import paper_2512_21487_amd as pkg
+    M, H, E, T, k = 1024, 512, 128, 1500, 4
+    gen = torch.Generator(device="cuda").manual_seed(85)
+    normal = lambda n, std: torch.empty(n, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    tokens, routed = normal(T * M, 1.0), normal(E * 3 * H * M, 0.02)
+    logits = torch.empty((T, E), dtype=torch.float32, device="cuda").normal_(generator=gen)
+    layer = dict(hidden=M, inter=H, n_experts=E, n_local=E, n_shared=0, shared_inter=0, max_tokens=T, max_top_k=k, max_chunks=2)
+    ctx = _ctx(monkeypatch, lambda: pkg.MoeEp(**layer), 0)
+    cfg = pkg.MoeEpConfig(local_begin=0, io_mode=pkg.IO_DEVICE, device=0, **layer)
+    want, got = (torch.zeros(T * M, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    for r in (1, 2):
+        ctx.forward(tokens, logits, routed, None, k, r, 0, n_tokens=T, out=want)
+        pkg.forward_noalloc(cfg, tokens, logits, routed, None, k, r, 0, n_tokens=T, out=got)
+        torch.cuda.synchronize()
+        assert want.any() and torch.equal(got.view(torch.int16), want.view(torch.int16)), f"r = {r}"
+    ctx.destroy()
