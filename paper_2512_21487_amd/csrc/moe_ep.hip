@@ -32,6 +32,11 @@ enum Stage { ST_ROUTER = 0, ST_PARTITION, ST_GEMM1, ST_GEMM2, ST_SGEMM1, ST_SGEM
 // At 8 to 19 rows the narrow ones win by up to 6 % (Qwen3-235B-A22B-shaped share, 16 rows: lose 2), at 24 both are within 2 % (4 under that skew), at
 // 28 and more they lose up to 10 (DeepSeek-V2-Lite-shaped layer: win 2).  Three rows, 32 tokens, lose 3: no line in rows per expert alone parts the two.
 constexpr double kNarrowMeanRows = 24.0;
+// And where the tiled kernels would be one launch of both projections, with shared experts or weights in tile order.  Narrow / that:
+// DeepSeek-V2-Lite-shaped layer, 6 / 12 / 15 / 19 / 23 rows 190 / 194, 197 / 198, 204 / 201, 205 / 198, 209 / 201, weights in the caller's layout 12 / 19 rows
+// 206 / 203, 219 / 202; Qwen3-30B-A3B-shaped layer, 8 / 15 / 19 / 23 rows 204 / 207, 211 / 211, 213 / 215, 216 / 218, skewed 15 / 16 / 23 rows 156 / 151, 159 / 152,
+// 182 / 166, with weights in the caller's layout, which the tiled kernels draw at 4.9 TB/s, and balanced load 19 rows 218 / 228.
+constexpr double kNarrowPairMeanRows = 14.0;
 // The shared experts go along up to this many rows; beyond, launches of their own with tall tiles.  Apart / along, the routed
 // experts in narrow tiles both times: DeepSeek-V2-Lite-shaped layer, 256 / 512 tokens 251 / 212, 269 / 229 us; DeepSeek-V2-shaped share,
 // 300 / 640 / 800 / 1200 tokens 278 / 220, 289 / 254, 282 / 292, 300 / 336.
@@ -901,20 +906,25 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
     const auto plan_chunk = [&](int Tn, int rows) -> Plan {
         Plan p{false, false, false, -1, -1};
         const bool fits = ctx->by_rule && ctx->fused_gather && (unsigned long long)Tn * M * 2 < (1ull << 32);
-        // few rows per routed expert: the narrow kernels, bound by the weight stream alone
-        const bool beside = rows > 0 && rows <= kNarrowSharedRows;
-        if (fits && Tn > 0 && (double)Tn * k / E <= ctx->narrow_rows && (beside || ctx->narrow_named || narrow_under_any_load(Tn, k, El)))
-            return Plan{true, false, beside && !shared_timed, kNarrowVariant, kNarrowVariant};
         // loader_gemm.hip addresses the activation rows of its tallest tile with 32-bit byte offsets (token rows it gathers: `fits`)
         const auto addressed = [](long long row) { return kLoaderRows * row * 2 < (1ll << 32); };
-        if (ctx->by_rule && addressed(H) && (fits || addressed(M))) {
+        const bool loader = ctx->by_rule && addressed(H) && (fits || addressed(M));
+        bool pair = false;   // but for timing
+        if (loader) {
             const bool pays = rows <= kAlongRows && M >= kAlongK && H >= kAlongK && Hs >= kAlongK, reach = addressed(M) && addressed((long long)Ns * Hs);
             p = Plan{false, true, rows > 0 && !shared_timed && reach && (ctx->merge == 1 || (ctx->merge != 0 && pays)), kLoaderVariant, kLoaderVariant};
+            const int beside = rows > 0 && reach && pays ? rows : 0;
+            pair = ctx->pair != 0 && loader_row_tiles(Tn, k, El, beside) <= ctx->sync_tiles &&
+                   (ctx->pair == 1 || loader_up_tiles((double)Tn * k / E, El, H, beside, Ns, Hs) >= kPairRounds * n_cu);
             // a projection that is timed is a launch of its own
-            p.pair = !projection_timed && ctx->pair != 0 && loader_row_tiles(Tn, k, El, p.along ? rows : 0) <= ctx->sync_tiles &&
-                     (ctx->pair == 1 || loader_up_tiles((double)Tn * k / E, El, H, p.along ? rows : 0, Ns, Hs) >= kPairRounds * n_cu);
-            return p;
+            p.pair = pair && !projection_timed && loader_row_tiles(Tn, k, El, p.along ? rows : 0) <= ctx->sync_tiles;
         }
+        // few rows per routed expert: the narrow kernels, bound by the weight stream alone
+        const bool beside = rows > 0 && rows <= kNarrowSharedRows;
+        const double few = pair && !ctx->narrow_named && (rows > 0 || prep_r) ? kNarrowPairMeanRows : ctx->narrow_rows;
+        if (fits && Tn > 0 && (double)Tn * k / E <= few && (beside || ctx->narrow_named || narrow_under_any_load(Tn, k, El)))
+            return Plan{true, false, beside && !shared_timed, kNarrowVariant, kNarrowVariant};
+        if (loader) return p;
         // a shape, an instruction or a form of the expert outputs was asked for by name, or rows are too long for the above:
         // grouped_gemm.hip.  Tile shapes of the two routed projections: N = H in tiles of 128 activation columns, N = M in tiles of 256 columns
         p.up = ctx->gemm_variant >= 0 ? ctx->gemm_variant : picked(routed_variant(Tn, k, E, El, ct_up, M, n_cu));
