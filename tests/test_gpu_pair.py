@@ -146,3 +146,33 @@ def test_without_a_context(monkeypatch):
         torch.cuda.synchronize()
         assert want.any() and torch.equal(got.view(torch.int16), want.view(torch.int16)), f"r = {r}"
     ctx.destroy()
+
+
+@pytest.mark.parametrize("n_tokens,prepared,tile_rows", [(224, True, 64), (240, True, 192), (240, False, 64), (384, True, 192), (400, False, 192)])
+def test_narrow_or_one_tiled_launch(monkeypatch, n_tokens, prepared, tile_rows):
+    """On both sides of the line between the narrow kernels and one tiled launch: 14 and 15 rows per expert, 24 and 25 with weights as the
+    caller holds them.  The bits do not depend on it."""
+    import paper_2512_21487_amd as pkg
+    if torch.cuda.get_device_properties(0).multi_processor_count > 320:
+        pytest.skip("640 tiles are not two rounds here")
+    M, H, E, k = 512, 576, 128, 8
+    gen = torch.Generator(device="cuda").manual_seed(86)
+    normal = lambda n, std: torch.empty(n, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    tokens, routed = normal(n_tokens * M, 1.0), normal(E * 3 * H * M, 0.02)
+    logits = torch.empty((n_tokens, E), dtype=torch.float32, device="cuda").normal_(generator=gen)
+    outs = []
+    for env in ({}, {"MOE_EP_GEMM_VARIANT": "21"}):
+        with monkeypatch.context() as m:
+            for name, value in env.items():
+                m.setenv(name, value)
+            ctx = pkg.MoeEp(hidden=M, inter=H, n_experts=E, n_local=E, n_shared=0, shared_inter=0, max_tokens=n_tokens, max_top_k=k, max_chunks=1)
+        if prepared:
+            ctx.prepare_weights(routed, None)
+        out = torch.zeros(n_tokens * M, dtype=torch.bfloat16, device="cuda")
+        ctx.forward(tokens, logits, routed, None, k, 1, 0, n_tokens=n_tokens, out=out)
+        torch.cuda.synchronize()
+        if not env:
+            assert ctx.last_tile_shape("routed_gate_up_gemm")["rows"] == tile_rows, "the launches under test"
+        outs.append(out)
+        ctx.destroy()
+    assert outs[0].any() and torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
