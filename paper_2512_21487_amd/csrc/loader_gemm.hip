@@ -1,9 +1,10 @@
 // Expert projections out of workgroups whose loads and multiplications are different wavefronts (Sec. 3.1): the tiled
 // form of prefill, routed experts (ragged groups) with or without the shared ones (dense groups) in the same launch.
 //
-// What bounds a tile is the compute unit's vector memory path: it keeps about 32 KB of requests in flight, so it
-// draws 80 GB/s from L2 and 46 GB/s from HBM, and a K step of a 160 x 256 tile is 52 KB.  With the multiplications taken
-// out, the loads alone were three quarters of a launch (Qwen3-30B-A3B-shaped layer, 8192 tokens, gate/up 345 of 437 us).  In
+// What bounds a tile is loads that a K step has to wait for: they draw 80 GB/s from L2 and 46 GB/s from HBM for a compute unit (nothing but
+// loads, never waited for together, 140 GB/s from L2, 64 bytes a cycle), and a K step of a 160 x 256 tile is 52 KB.  With the multiplications taken
+// out, the loads alone were three quarters of a launch (Qwen3-30B-A3B-shaped layer, 8192 tokens, gate/up 345 of 437 us); with the loads taken out,
+// the multiplications alone were 87 / 82 % of a gate/up / down launch, and either without its epilogue 93 / 82 % (DeepSeek-V2-Lite-shaped layer, 4096).  In
 // grouped_gemm.hip a wavefront loads and multiplies, and a load that finds the path full holds back the MFMAs behind it.  A launch is
 // also bound by how its tiles are dealt, by number: of several rounds 6 to 16 % of the units' time has no workgroup, of one row tile per
 // expert up to 30 (profiles/loader_gemm_counters.txt, where the matrix pipes are busy 54 - 59 % of a gate/up launch that fills the chip).
