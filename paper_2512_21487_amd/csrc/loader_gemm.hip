@@ -61,7 +61,8 @@ constexpr int kLdXRegions = kLoaderRows / 8 / kLdLoad;      // and of token rows
 constexpr int kLdDrawAhead = 6, kLdDrawSteps = 8;           // K steps of weights left when the next tiles are drawn; K steps drawn at a time, at least
 constexpr int kXcds = 8, kLdLine = 32, kLdListBytes = 88;                     // integers of a line: a counter of its own
 static_assert(kLdCounters == 4 * kXcds * kLdLine, "two lists of each projection, a share per XCD");
-constexpr int loader_lds(int groups) { return kLdRing + kLdCache * (16 + 4 + 4) + 4 * kLdListBytes + (4 + 2 * (groups + 1)) * 4; }
+constexpr int kLdTold = 3;                                  // tiles whose multiplying wavefronts may be counted at a time (Told)
+constexpr int loader_lds(int groups) { return kLdRing + kLdCache * (16 + 4 + 4) + 4 * kLdListBytes + (2 + kLdTold + 2 * (groups + 1)) * 4; }
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) u32x4_t global_u32x4;   // an address that comes from LDS is not known to be global: a flat store would hold up LDS reads
@@ -141,7 +142,8 @@ __device__ __forceinline__ bool goes_on(const int4* next)
 }
 
 // A gate/up tile whose rows a down tile of the launch will read: its row tile's count, and in LDS how many of the multiplying wavefronts have their
-// share in memory.  Nobody is two tiles ahead of anybody, so two such numbers in turn do.
+// share in memory.  A tile is told of behind the next one's K loop, the last gate/up tile behind its own.  With one K step a wavefront meets
+// no hand-over in that one and tells of three tiles in a row, the first of which others may still have to tell of: kLdTold such numbers in turn.
 struct Told { int32_t* done; int* waves; };
 __device__ __forceinline__ void tell(const Told& t)
 {
@@ -309,13 +311,13 @@ __global__ __launch_bounds__(kLdThreads) void loader_gemm_kernel(GemmArgs a1, Ge
     int* const s_filled = s_ready + kLdCache;
     int* const s_most = s_filled + 1;
     int* const s_waves = s_most + 1;
-    int* const s_pref = s_waves + 2;
+    int* const s_pref = s_waves + kLdTold;
     int* const s_row = s_pref + G + 1;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const auto columns_to_tiles = [&](int n, bool down) { return !UP || (DOWN && down) ? (n + kPackRows - 1) / kPackRows : (n + kPackRows / 2 - 1) / (kPackRows / 2); };
 
-    if (tid < 2) s_waves[tid] = 0;
+    if (tid < kLdTold) s_waves[tid] = 0;
     if (tid < 4) {
         const bool dense = tid & 1, down = tid >> 1;
         List l;
@@ -752,7 +754,7 @@ __global__ __launch_bounds__(kLdThreads) void loader_gemm_kernel(GemmArgs a1, Ge
             }
         }
         if (BOTH) {
-            told = Told{t.down ? nullptr : done + (size_t)t.dep * kRowTileInts, s_waves + (it & 1)};
+            told = Told{t.down ? nullptr : done + (size_t)t.dep * kRowTileInts, s_waves + it % kLdTold};
             if (!more && told.done) { tell(told); told.done = nullptr; }   // the loading wavefronts may be waiting for these rows
         }
         if (!tile_at(it + 1, t)) break;
