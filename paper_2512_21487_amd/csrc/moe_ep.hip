@@ -903,6 +903,8 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
     const bool shared_timed = prof && (ctx->prof_mask & ((1u << ST_SGEMM1) | (1u << ST_SGEMM2)));
     const bool projection_timed = prof && (ctx->prof_mask & ((1u << ST_GEMM1) | (1u << ST_GEMM2)));
     const int ct_up = (H + 127) / 128, ct_down = (M + 255) / 256;
+    // what the narrow kernels refuse elsewhere than on 16 bytes is still theirs to refuse
+    const bool sources_16 = !((reinterpret_cast<uintptr_t>(tok_dev) | reinterpret_cast<uintptr_t>(routed_w) | reinterpret_cast<uintptr_t>(shared_w)) & 15);
     const auto plan_chunk = [&](int Tn, int rows) -> Plan {
         Plan p{false, false, false, -1, -1};
         const bool fits = ctx->by_rule && ctx->fused_gather && (unsigned long long)Tn * M * 2 < (1ull << 32);
@@ -921,7 +923,9 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         }
         // few rows per routed expert: the narrow kernels, bound by the weight stream alone
         const bool beside = rows > 0 && rows <= kNarrowSharedRows;
-        const double few = pair && !ctx->narrow_named && (rows > 0 || prep_r) ? kNarrowPairMeanRows : ctx->narrow_rows;
+        // (they write the shared experts' rows 8 bytes at a time, the tiled ones 16: an `out` that begins on 8 is theirs up to the line without a pair)
+        const bool takes_out = rows == 0 || !(reinterpret_cast<uintptr_t>(out_dev) & 15);
+        const double few = pair && takes_out && sources_16 && !ctx->narrow_named && (rows > 0 || prep_r) ? kNarrowPairMeanRows : ctx->narrow_rows;
         if (fits && Tn > 0 && (double)Tn * k / E <= few && (beside || ctx->narrow_named || narrow_under_any_load(Tn, k, El)))
             return Plan{true, false, beside && !shared_timed, kNarrowVariant, kNarrowVariant};
         if (loader) return p;

@@ -176,3 +176,37 @@ def test_narrow_or_one_tiled_launch(monkeypatch, n_tokens, prepared, tile_rows):
         outs.append(out)
         ctx.destroy()
     assert outs[0].any() and torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+
+
+@pytest.mark.parametrize("prepared", [False, True])
+@pytest.mark.parametrize("r,order", [(1, 0), (1, 1), (2, 0), (2, 1)])
+def test_output_that_begins_on_8_bytes(r, order, prepared):
+    """The shared experts write into `out` itself, the narrow kernels 8 bytes at a time, the tiled ones 16: between the two lines an `out`
+    that begins on 8 bytes stays with the narrow ones, and what neither takes is refused."""
+    import paper_2512_21487_amd as pkg
+    if torch.cuda.get_device_properties(0).multi_processor_count > 288:
+        pytest.skip("576 tiles are not two rounds here")
+    M, H, E, k, T = 512, 1088, 64, 6, 200 * r       # 18.75 rows per expert and chunk, nine column tiles
+    gen = torch.Generator(device="cuda").manual_seed(87)
+    normal = lambda n, std: torch.empty(n, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    tokens, routed, shared = normal(T * M, 1.0), normal(E * 3 * H * M, 0.02), normal(2 * 3 * 512 * M, 0.02)
+    logits = torch.empty((T, E), dtype=torch.float32, device="cuda").normal_(generator=gen)
+    ctx = pkg.MoeEp(hidden=M, inter=H, n_experts=E, n_local=E, n_shared=2, shared_inter=512, max_tokens=T, max_top_k=k, max_chunks=r)
+    if prepared:
+        ctx.prepare_weights(routed, shared)
+    outs = {}
+    for offset, rows in ((0, 192), (4, 64), (8, 192), (12, 64)):
+        flat = torch.full((T * M + 16,), 7.0, dtype=torch.bfloat16, device="cuda")
+        out = flat[offset:offset + T * M]
+        ctx.forward(tokens, logits, routed, shared, k, r, order, n_tokens=T, out=out)
+        torch.cuda.synchronize()
+        assert ctx.last_tile_shape("routed_gate_up_gemm")["rows"] == rows, f"the launches under test, offset {offset}"
+        outs[offset] = out.view(torch.int16).cpu()
+        assert bool((flat[:offset] == 7.0).all()) and bool((flat[offset + T * M:] == 7.0).all())
+    assert outs[0].any() and all(torch.equal(o, outs[0]) for o in outs.values())
+    flat = torch.zeros(T * M + 8, dtype=torch.bfloat16, device="cuda")
+    for args, out in (((tokens, logits), flat[2:2 + T * M]), ((flat[4:4 + T * M], logits), torch.zeros_like(tokens))):
+        with pytest.raises(pkg.MoeEpError):
+            ctx.forward(*args, routed, shared, k, r, order, n_tokens=T, out=out)
+    torch.cuda.synchronize()
+    ctx.destroy()
