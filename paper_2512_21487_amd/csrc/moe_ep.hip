@@ -20,6 +20,8 @@
 
 using namespace moe_ep;
 
+namespace moe_ep { long long context_row_tiles(const moe_ep_config& c); }
+
 namespace {
 
 enum Stage { ST_ROUTER = 0, ST_PARTITION, ST_GEMM1, ST_GEMM2, ST_SGEMM1, ST_SGEMM2, ST_COMBINE, ST_TOTAL, ST_COPY_IN, ST_COPY_OUT, ST_ATTN, ST_COUNT };
@@ -237,15 +239,21 @@ void bind_workspaces(moe_ep_ctx* ctx, char* slab, const WsLayout& L)
     ctx->hs = reinterpret_cast<uint16_t*>(slab + L.hs);
 }
 
-// Row tiles of launches of both projections that a context has counters for: a line for 128 rows and one for an expert, up to 2 MB.
-// Beyond, the projections are launches of their own.
+// Counters for launches of both projections: a line for 128 rows and one for an expert, up to 2 MB.  A call of more row tiles than a
+// context has counters for runs its projections in launches of their own.
 constexpr long long kSyncTiles = 1 << 14, kNoallocSyncTiles = 1 << 13;
 size_t sync_ints(long long row_tiles) { return (size_t)kLdCounters + (size_t)row_tiles * kRowTileInts; }
-long long sync_tiles(const moe_ep_config& c)
+
+}  // namespace
+
+// row tiles that a context of this configuration has counters for
+long long moe_ep::context_row_tiles(const moe_ep_config& c)
 {
     const long long n = loader_row_tiles(c.max_tokens, c.max_top_k, c.n_local, c.n_shared > 0 ? c.max_tokens : 0);
-    return n <= kSyncTiles ? n : 0;
+    return n < kSyncTiles ? n : kSyncTiles;
 }
+
+namespace {
 
 // the environment knobs of a context (tuning and comparison aids; none changes a result bit)
 void read_knobs(moe_ep_ctx* ctx)
@@ -529,7 +537,7 @@ int moe_ep_create(const moe_ep_config* cfg, moe_ep_ctx** out_ctx)
 
     const WsLayout L = ws_layout(*cfg);
     char* slab = nullptr;
-    ctx->sync_tiles = sync_tiles(*cfg);
+    ctx->sync_tiles = context_row_tiles(*cfg);
     if (hipMalloc(reinterpret_cast<void**>(&slab), L.total + sync_ints(ctx->sync_tiles) * 4) != hipSuccess) { delete ctx; return MOE_EP_ENOMEM; }
     ctx->sync = reinterpret_cast<int32_t*>(slab + L.total);
     bind_workspaces(ctx, slab, L);  // L.tokens == 0: d_tokens is the slab base, freed in destroy

@@ -210,3 +210,26 @@ def test_output_that_begins_on_8_bytes(r, order, prepared):
             ctx.forward(*args, routed, shared, k, r, order, n_tokens=T, out=out)
     torch.cuda.synchronize()
     ctx.destroy()
+
+
+def test_a_small_call_of_a_context_for_large_ones():
+    """A context whose largest call has more row tiles than there are counters for still runs a small one as any other context does."""
+    import paper_2512_21487_amd as pkg
+    if torch.cuda.get_device_properties(0).multi_processor_count > 320:
+        pytest.skip("640 tiles are not two rounds here")
+    M, H, E, k, T = 128, 576, 128, 8, 240      # 15 rows per expert: past the line only where both projections are one launch
+    gen = torch.Generator(device="cuda").manual_seed(88)
+    normal = lambda n, std: torch.empty(n, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    tokens, routed = normal(T * M, 1.0), normal(E * 3 * H * M, 0.02)
+    logits = torch.empty((T, E), dtype=torch.float32, device="cuda").normal_(generator=gen)
+    outs = []
+    for most in (T, 1 << 18):
+        ctx = pkg.MoeEp(hidden=M, inter=H, n_experts=E, n_local=E, n_shared=0, shared_inter=0, max_tokens=most, max_top_k=k, max_chunks=1)
+        ctx.prepare_weights(routed, None)
+        out = torch.zeros(T * M, dtype=torch.bfloat16, device="cuda")
+        ctx.forward(tokens, logits, routed, None, k, 1, 0, n_tokens=T, out=out)
+        torch.cuda.synchronize()
+        assert ctx.last_tile_shape("routed_gate_up_gemm")["rows"] == 192, "the launches under test"
+        outs.append(out.view(torch.int16))
+        ctx.destroy()
+    assert outs[0].any() and torch.equal(*outs)

@@ -1,5 +1,7 @@
-"""The order in which the multiplying wavefronts of loader_gemm.hip tell that a gate/up tile's activation is in memory, as a model on the
-CPU: in every interleaving a tile is counted once, behind its last wavefront."""
+"""The counters of launches of both projections, on the CPU: how many a context has, and a model of the order in which the multiplying
+wavefronts of loader_gemm.hip tell that a gate/up tile's activation is in memory: in every interleaving a tile is counted once, behind its
+last wavefront."""
+import ctypes
 import os
 import re
 
@@ -63,3 +65,15 @@ def test_every_tile_is_counted_once_behind_its_last_wavefront(tiles, steps):
 
 def test_two_numbers_in_turn_are_too_few_for_one_step():
     assert faults(3, 1, 2) and not faults(3, 2, 2)
+
+
+@pytest.mark.parametrize("max_tokens,top_k,n_local,n_shared,row_tiles", [
+    (1, 1, 1, 0, 1), (4096, 6, 64, 2, 192 + 64 + 32), (16384, 8, 4, 0, 512 + 4), (260096, 8, 128, 0, 1 << 14),
+    (262144, 8, 128, 0, 1 << 14),      # its largest call has more, its small ones do not
+    (1 << 22, 64, 512, 2, 1 << 14)])
+def test_a_context_of_any_size_has_counters(max_tokens, top_k, n_local, n_shared, row_tiles):
+    count = pkg.load_library()._ZN6moe_ep17context_row_tilesERK13moe_ep_config
+    count.restype = ctypes.c_longlong
+    cfg = pkg.MoeEpConfig(hidden=64, inter=64, n_experts=512, local_begin=0, n_local=n_local, n_shared=n_shared, shared_inter=64 if n_shared else 0,
+                          max_tokens=max_tokens, max_top_k=top_k, max_chunks=1, io_mode=pkg.IO_DEVICE, device=0)
+    assert count(ctypes.byref(cfg)) == row_tiles
