@@ -181,7 +181,7 @@ inline bool narrow_sum_pays(int Tn, int k, int E, int El, int N, int K, int shar
 // Tiled projections of prefill with loading wavefronts (loader_gemm.hip): the routed groups `up` (gate/up), `down` or both (ragged)
 // and, when up_shared / down_shared are not NULL, the shared experts (dense) in one launch; no other epilogue than epi == 0, no
 // max_units, all or none with weights in tile order.  Of both, the down projection reads what the same launch's gate/up projection writes, for the
-// same offset and dense rows.  sync: kLdCounters zeros, and of both projections kRowTileInts more for every row tile (loader_row_tiles).
+// same offset and dense rows.  sync, of both only: kLdCounters zeros, and kRowTileInts more for every row tile (loader_row_tiles).
 hipError_t launch_loader_gemm(const GemmArgs* up, const GemmArgs* up_shared, const GemmArgs* down, const GemmArgs* down_shared, int n_cu, int32_t* sync, hipStream_t s);
 constexpr int kLdCounters = 1024, kRowTileInts = 32;      // a counter has a line of its own
 // the most row tiles of Tn tokens, k experts each, El of them here, and of dense_rows rows beside them: of 128 rows, the last of an expert lower

@@ -293,7 +293,7 @@ __device__ __forceinline__ T pick(bool dense, bool down, T a1, T d1, T a2, T d2)
 }
 
 // PROJ: 1 gate/up (a1, d1), 2 down (a2, d2), 3 both, the down projection reading what this launch's gate/up projection wrote.
-// sync: kLdCounters zeros where tiles are drawn from; of both projections, kRowTileInts zeros per row tile behind them.
+// sync, of both: kLdCounters zeros where tiles are drawn from, and kRowTileInts zeros per row tile behind them.
 template <int PROJ, bool PACKED>
 __global__ __launch_bounds__(kLdThreads) void loader_gemm_kernel(GemmArgs a1, GemmArgs d1, GemmArgs a2, GemmArgs d2, int32_t* sync)
 {
@@ -500,7 +500,7 @@ __global__ __launch_bounds__(kLdThreads) void loader_gemm_kernel(GemmArgs a1, Ge
         return slot >= n - (int)(n * fminf(0.5f, r / (d + r)));
     };
     const bool ragged_up = BOTH && few_rows && begins_ragged(false), ragged_down = BOTH && few_rows && begins_ragged(true);
-    bool drawing_down = !UP, second = false, elsewhere = false, drawn_all = false, asked = false;
+    bool drawing_down = false, second = false, elsewhere = false, drawn_all = false, asked = false;
     int drawn = 0, ahead = 0, ticket = 0;   // ahead: K steps of weights drawn and not yet asked for
     int peeked = 0, peek_from = 0, peek_need = 0, peek = 0;   // down tiles whose rows' counts have been asked for: how many, from which, the count they need
     int32_t* const done = sync + kLdCounters;
@@ -521,9 +521,9 @@ __global__ __launch_bounds__(kLdThreads) void loader_gemm_kernel(GemmArgs a1, Ge
         if (k <= 0) return false;
         if (lane < k) {
             const int dep = decode(dense, drawing_down, n / kXcds * x + min(x, n % kXcds) + t + lane, (drawn + lane) % kLdCache);
-            if (BOTH && drawing_down) { peek_need = needed(dep); peek = count_of(dep); }
+            if (drawing_down) { peek_need = needed(dep); peek = count_of(dep); }
         }
-        peeked = BOTH && drawing_down ? k : 0;
+        peeked = drawing_down ? k : 0;
         peek_from = drawn;
         drawn += k;
         ahead += k * steps_of(dense, drawing_down);
@@ -549,7 +549,7 @@ __global__ __launch_bounds__(kLdThreads) void loader_gemm_kernel(GemmArgs a1, Ge
             if (most_left >= 0) {
                 const int i = most_left % (2 * kXcds);
                 if (take(i >= kXcds, i % kXcds, ask(i >= kXcds, i % kXcds))) return;
-            } else if (BOTH && !drawing_down) {
+            } else if (!drawing_down) {
                 drawing_down = true;
                 second = elsewhere = false;
             } else {
@@ -782,7 +782,7 @@ hipError_t launch_loader_gemm(const GemmArgs* up, const GemmArgs* up_shared, con
     const GemmArgs none{};
     const GemmArgs* const routed[2] = {up, down};
     const GemmArgs* const dense[2] = {up_shared, down_shared};
-    if ((!up && !down) || (up_shared && !up) || (down_shared && !down) || sync == nullptr) return hipErrorInvalidValue;
+    if ((!up && !down) || (up_shared && !up) || (down_shared && !down) || (up && down && sync == nullptr)) return hipErrorInvalidValue;
     const GemmArgs& first = up ? *up : *down;
     for (int i = 0; i < 2; ++i) {
         const GemmArgs* r = routed[i];

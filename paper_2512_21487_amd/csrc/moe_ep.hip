@@ -956,8 +956,8 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
     const auto to_clear = [&](int cidx, int Tn) -> Clear {
         const int rows = rows_beside(cidx, Tn);
         const Plan p = plan_chunk(Tn, rows);
-        if (!p.loader) return Clear{nullptr, 0};
-        return Clear{ctx->sync, (int)sync_ints(p.pair ? loader_row_tiles(Tn, k, El, p.along ? rows : 0) : 0)};
+        if (!p.pair) return Clear{nullptr, 0};
+        return Clear{ctx->sync, (int)sync_ints(loader_row_tiles(Tn, k, El, p.along ? rows : 0))};
     };
     const auto gate = [&](int cidx) -> int {
         int t0, Tn;
@@ -1054,7 +1054,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         int kind_up = 0, kind_down = 0;   // of the narrow launches that follow
         sp = prof_begin(ctx, prof, ST_GEMM1, s_comp);
         if (narrow) HIP_TRY(ctx, launch_narrow_gemm(g1, along ? &s1 : nullptr, true, n_cu, (double)Tn * k / E, Tn, a_max, s_comp, &kind_up, routes ? &route : nullptr));
-        else if (loader) { if (!plan.pair) HIP_TRY(ctx, launch_loader_gemm(&g1, along ? &s1 : nullptr, nullptr, nullptr, cus, ctx->sync, s_comp)); }
+        else if (loader) { if (!plan.pair) HIP_TRY(ctx, launch_loader_gemm(&g1, along ? &s1 : nullptr, nullptr, nullptr, cus, nullptr, s_comp)); }
         else HIP_TRY(ctx, launch_grouped_gemm(g1, true, v_up, n_cu, a_max, s_comp));
         prof_end(ctx, sp, s_comp);
 

@@ -71,3 +71,15 @@ def test_first_chunk_comes_in_with_the_gate(experts, chunks, shared_first, with_
     rule = pkg.load_library()._ZN6moe_ep19rows_come_with_gateEiib
     rule.restype = ctypes.c_bool
     assert rule(experts, chunks, ctypes.c_bool(shared_first)) == with_gate
+
+
+@pytest.mark.parametrize("up,down,counters,refused", [
+    (True, False, False, False), (False, True, False, False),   # a launch of one projection deals its tiles
+    (True, True, False, True), (True, True, True, False)])
+def test_counters_are_for_launches_of_both_projections(up, down, counters, refused):
+    launch = pkg.load_library()._ZN6moe_ep18launch_loader_gemmEPKNS_8GemmArgsES2_S2_S2_iPiP12ihipStream_t
+    M, H, A = 1024, 512, 0x1000
+    gate_up = GemmArgs(A=A, W=A, C=A, offset=A, G=8, K=M, N=H, lda=M, ldc=H, ldw=M, w_group_stride=3 * H * M, w_up_offset=H * M, kseg_len=M)
+    out = GemmArgs(A=A, W=A, C=A, offset=A, G=8, K=H, N=M, lda=H, ldc=M, ldw=H, w_group_stride=3 * H * M, kseg_len=H)
+    rc = launch(ctypes.byref(gate_up) if up else None, None, ctypes.byref(out) if down else None, None, 256, ctypes.c_void_p(A if counters else None), None)
+    assert rc != 0 and (rc == INVALID_VALUE) == refused
