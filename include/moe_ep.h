@@ -225,7 +225,7 @@ int moe_ep_get_routing(moe_ep_ctx *ctx, int32_t chunk, int32_t *idx, float *w, i
  * launches of their own, since stages that share a launch have no times of their own: the same bits, and possibly a
  * longer forward than the same call untimed (moe_ep_set_profiling_stages leaves the two out).  The same holds for stages 3 and 6
  * of up to 16 tokens, for stages 0, 1 and 2 of up to 4, and for stages 2 and 3 of larger calls, whose projections may
- * be one launch.  In pinned-host mode it holds for stage 8: a forward that times it brings
+ * be one launch (moe_ep_last_projections_joint).  In pinned-host mode it holds for stage 8: a forward that times it brings
  * the first chunk's rows in with copies of their own; in one that does not, the gate's launch may do so, and ms[0] then has
  * their time.
  * moe_ep_get_stage_ms synchronises, returns the per-forward AVERAGE over the forwards recorded
@@ -392,6 +392,12 @@ int moe_ep_last_tile_shape(const moe_ep_ctx *ctx, int32_t chunk, int32_t stage, 
  * MOE_EP_ESTATE before any forward, MOE_EP_EINVAL for a chunk it did not have.
  */
 int moe_ep_last_shared_beside(const moe_ep_ctx *ctx, int32_t chunk);
+
+/*
+ * 1 if the last forward ran the gate/up and the down projection of this chunk's routed experts in one launch (with the shared
+ * experts' projections where moe_ep_last_shared_beside says so), else 0.  Errors as for moe_ep_last_shared_beside.
+ */
+int moe_ep_last_projections_joint(const moe_ep_ctx *ctx, int32_t chunk);
 
 int moe_ep_forward_dep(moe_ep_ctx *ctx, const void *tokens, const float *gate_logits,
                        const void *routed_w, const void *shared_w, int32_t top_k, int32_t r_1,

@@ -132,6 +132,8 @@ def load_library() -> ctypes.CDLL:
     lib.moe_ep_get_routing.argtypes = [vp, i32, vp, vp, vp, vp, vp, vp]
     lib.moe_ep_last_shared_beside.restype = ctypes.c_int
     lib.moe_ep_last_shared_beside.argtypes = [vp, i32]
+    lib.moe_ep_last_projections_joint.restype = ctypes.c_int
+    lib.moe_ep_last_projections_joint.argtypes = [vp, i32]
     lib.moe_ep_set_profiling.restype = ctypes.c_int
     lib.moe_ep_set_profiling.argtypes = [vp, i32]
     lib.moe_ep_set_profiling_stages.restype = ctypes.c_int
@@ -490,6 +492,13 @@ class MoeEp:
         rc = self._lib.moe_ep_last_shared_beside(self._ctx, chunk)
         if rc < 0:
             raise MoeEpError(rc, "moe_ep_last_shared_beside: no forward, or no such chunk")
+        return rc == 1
+
+    def last_projections_joint(self, chunk: int = 0) -> bool:
+        """Whether the last forward ran both projections of this chunk's routed experts in one launch."""
+        rc = self._lib.moe_ep_last_projections_joint(self._ctx, chunk)
+        if rc < 0:
+            raise MoeEpError(rc, "moe_ep_last_projections_joint: no forward, or no such chunk")
         return rc == 1
 
     # -- timing model ---------------------------------------------------------------------

@@ -155,7 +155,7 @@ struct moe_ep_ctx {
     // last forward (for moe_ep_get_routing): tokens, top_k, chunks = micro-batches x chunks of each
     int last_T = -1, last_k = 0, last_r = 0, last_r1 = 1;
     bool last_prepared_routed = false, last_prepared_shared = false;  // it read tile-order copies of the weights
-    struct ChunkVariants { int up, down; bool beside; };   // beside: the shared experts ran in the same launches
+    struct ChunkVariants { int up, down; bool beside, joint; };   // beside: the shared experts ran in the same launches; joint: both projections in one
     std::vector<ChunkVariants> last_variants;  // per chunk of the last forward: tile variants of the routed projections
     // stage profiling
     int prof_depth = 0, prof_recorded = 0;
@@ -541,7 +541,7 @@ int moe_ep_create(const moe_ep_config* cfg, moe_ep_ctx** out_ctx)
     if (hipMalloc(reinterpret_cast<void**>(&slab), L.total + sync_ints(ctx->sync_tiles) * 4) != hipSuccess) { delete ctx; return MOE_EP_ENOMEM; }
     ctx->sync = reinterpret_cast<int32_t*>(slab + L.total);
     bind_workspaces(ctx, slab, L);  // L.tokens == 0: d_tokens is the slab base, freed in destroy
-    ctx->last_variants.assign((size_t)cfg->max_chunks, {-1, -1, false});
+    ctx->last_variants.assign((size_t)cfg->max_chunks, {-1, -1, false, false});
 
     // the chunk events order GPU work against GPU work only, so they skip the system-scope cache
     // write-back a default event record implies (it stalled the other streams' kernels)
@@ -1004,7 +1004,7 @@ int forward_impl(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits, 
         const Plan plan = plan_chunk(Tn, rows_beside(cidx, Tn));
         const bool narrow = plan.narrow, loader = plan.loader, along = plan.along;
         const int v_up = plan.up, v_down = plan.down;
-        if (cidx < (int)ctx->last_variants.size()) ctx->last_variants[cidx] = {v_up, v_down, along};
+        if (cidx < (int)ctx->last_variants.size()) ctx->last_variants[cidx] = {v_up, v_down, along, plan.pair && Tn > 0};
         int32_t* idx = ctx->idx + (size_t)t0 * k;
         float* w = ctx->w + (size_t)t0 * k;
         int32_t* pos = ctx->pos + (size_t)t0 * k;
@@ -1185,6 +1185,14 @@ int moe_ep_last_shared_beside(const moe_ep_ctx* ctx, int32_t chunk)
     if (ctx->last_T < 0) return MOE_EP_ESTATE;
     if (chunk < 0 || chunk >= ctx->last_r || chunk >= (int)ctx->last_variants.size()) return MOE_EP_EINVAL;
     return ctx->last_T > 0 && ctx->last_variants[chunk].beside;
+}
+
+int moe_ep_last_projections_joint(const moe_ep_ctx* ctx, int32_t chunk)
+{
+    if (!ctx) return MOE_EP_EINVAL;
+    if (ctx->last_T < 0) return MOE_EP_ESTATE;
+    if (chunk < 0 || chunk >= ctx->last_r || chunk >= (int)ctx->last_variants.size()) return MOE_EP_EINVAL;
+    return ctx->last_T > 0 && ctx->last_variants[chunk].joint;
 }
 
 int moe_ep_forward(moe_ep_ctx* ctx, const void* tokens, const float* gate_logits,
