@@ -58,6 +58,11 @@ def kernel_name(ctx, stage):
             f"{sh['mfma_rows']}>")
 
 
+def joint_kernel_name(ctx):
+    """The kernel of a launch of both projections."""
+    return f"loader_gemm_kernel<3, {'true' if ctx.last_tile_shape('routed_gate_up_gemm')['tile_order'] else 'false'}>"
+
+
 def measured_traffic(workload, r_chunks, stage, kernel):
     """HBM-side bytes of one launch from the committed counter summary profiles/hbm_traffic_<workload>.txt
     (lines "traffic <r_chunks> <stage> <kernel> <read bytes> <written bytes>"): returned only when
@@ -353,6 +358,8 @@ def main() -> int:
     dt = time.perf_counter() - t0
     # did the shared experts run in the routed experts' launches?
     beside = wl.n_shared > 0 and all(ctx.last_shared_beside(c) for c in range(ctx.last_chunks() if args.order == 1 else 1))
+    # and both projections of the routed experts in one launch?
+    pair = all(ctx.last_projections_joint(c) for c in range(ctx.last_chunks()))
     joint = None   # those launches' times
 
     def timed_pass(names):
@@ -369,10 +376,16 @@ def main() -> int:
         per_forward_ms = [e - b for n, _, b, e in ctx.get_timeline() if n == "forward"]
         ctx.get_stage_ms()
         # Outside the timed region, the same forwards again.  If the shared experts ran beside the routed ones: once with
-        # events around those launches.  Then with events around the dominant kernel and the routed projections only (events
-        # between all stages cost 2 % of a dsv2_eg forward and 20 % of a 256-token one; the shared experts in launches of
-        # their own), and with events around every stage.
-        if beside:
+        # events around those launches; if both projections were one launch, whose stages a timed forward runs apart, with
+        # events around everything else instead (not where transfers run beside it).  Then with events around the dominant
+        # kernel and the routed projections only (events between all stages cost 2 % of a dsv2_eg forward and 20 % of a
+        # 256-token one; the shared experts in launches of their own), and with events around every stage.
+        if pair and not pinned:
+            others = ["router", "partition", "aggregation"] + (["shared_gate_up_gemm", "shared_down_gemm"] if wl.n_shared and not beside else [])
+            rest = timed_pass(others + ["forward"])
+            joint = {"routed_projections": rest["forward"] - sum(rest[n] for n in others)}   # with the gaps between launches
+            joint_kernels = {"routed_projections": joint_kernel_name(ctx)}
+        elif beside:
             joint = timed_pass(["routed_gate_up_gemm", "routed_down_gemm"])
             joint_kernels = {n: kernel_name(ctx, n) for n in ("routed_gate_up_gemm", "routed_down_gemm")}
         few_events = timed_pass(timed_stages)
@@ -445,11 +458,17 @@ def main() -> int:
         if line_ is not None and st in names:
             line_["kernel"] = names[st]
 
-    if joint:   # routed and shared experts of a projection together
+    if joint:   # routed and shared experts of a projection together, or both projections (and the shared experts where they run beside)
         up, down = "routed_gate_up_gemm", "routed_down_gemm"
         w_bytes = r * wl.n_local * 2.0 * H * M + Ns * 2.0 * Hs * M   # of one weight matrix per expert
-        both = {up: gemm_line(4.0 * M * (kept * H + T * Ns * Hs), 2 * w_bytes + 2.0 * (kept * (M + H) + T * (M + Ns * Hs)), joint[up]),
-                down: gemm_line(2.0 * M * (kept * H + T * Ns * Hs), w_bytes + 2.0 * (kept * (M + H) + T * (M + Ns * Hs)), joint[down])}
+        if "routed_projections" in joint:
+            s_rows = T * Ns if beside else 0
+            w_bytes = r * wl.n_local * 2.0 * H * M + (Ns * 2.0 * Hs * M if beside else 0.0)
+            both = {"routed_projections": gemm_line(6.0 * M * (kept * H + s_rows * Hs), 3 * w_bytes + 4.0 * (kept * (M + H) + (T * M if beside else 0) + s_rows * Hs),
+                                                    joint["routed_projections"])}
+        else:
+            both = {up: gemm_line(4.0 * M * (kept * H + T * Ns * Hs), 2 * w_bytes + 2.0 * (kept * (M + H) + T * (M + Ns * Hs)), joint[up]),
+                    down: gemm_line(2.0 * M * (kept * H + T * Ns * Hs), w_bytes + 2.0 * (kept * (M + H) + T * (M + Ns * Hs)), joint[down])}
         joint = {n: dict(l, kernel=joint_kernels[n]) for n, l in both.items() if l}
 
     line = {
@@ -473,7 +492,9 @@ def main() -> int:
                           + ("" if args.no_stage_timing else
                              " (there: " + ", ".join(f"{n} {all_events[n]:.4f}" for n in timed_stages) + " ms)")
                           + ("; shared experts in launches of their own, in the timed region they ran in the routed "
-                             "experts' (joint_launches)" if beside else "")),
+                             "experts' (joint_launches)" if beside else "")
+                          + ("; the routed experts' two projections in launches of their own, with their kernels, in the "
+                             "timed region they were one launch" + (" (joint_launches)" if joint else "") if pair else "")),
         "host_enqueue_ms_per_step": t_enq / args.steps * 1e3,
     }
     if not args.no_stage_timing and per_forward_ms:
