@@ -89,7 +89,9 @@ int moe_ep_validate_forward(const moe_ep_config *cfg, const void *tokens,
                             int32_t order, int32_t n_tokens, const void *out,
                             const char **why);
 
-/* Device bytes moe_ep_create will allocate for this configuration (0 if invalid). */
+/* Device bytes of this configuration's workspaces (0 if invalid).  moe_ep_create allocates these and, in the same block, 4096 bytes and
+ * 128 for each of max_tokens * min(max_top_k, n_local) / 128 + n_local row tiles (with shared experts (max_tokens + 127) / 128 more),
+ * at most 16384 of them: the counters of launches of both projections. */
 size_t moe_ep_workspace_bytes(const moe_ep_config *cfg);
 
 /* Create a context: selects cfg->device, allocates all workspaces, streams and
@@ -176,7 +178,8 @@ size_t moe_ep_prepared_weight_bytes(const moe_ep_config *cfg, int32_t routed, in
  * workspaces a context would own (routing arrays, activation, expert outputs; the layout
  * moe_ep_workspace_bytes(cfg) describes) live in one array of MOE_EP_NOALLOC_SCRATCH_BYTES bytes that
  * is part of the library's device image, so every GPU the library runs on holds it from the first
- * use until the process ends.  The call allocates and frees nothing, on the host or on the device,
+ * use until the process ends; a second one, of 1 MiB and 4 KiB, has the counters of launches of both projections and
+ * does not count against that size.  The call allocates and frees nothing, on the host or on the device,
  * creates no stream or event, sets no memory and never waits on the host; it runs the same kernels
  * as moe_ep_forward and produces the same bits.
  *
@@ -189,11 +192,12 @@ size_t moe_ep_prepared_weight_bytes(const moe_ep_config *cfg, int32_t routed, in
  *             (valid until the next call for the same device)
  *   all other arguments, layouts, ownership and determinism as for moe_ep_forward.
  *
- * Every call on a GPU uses that GPU's one array, which keeps the previous call's contents (nothing
- * in it has to start at zero: each forward overwrites what it reads).  Two calls that overlap on one
- * GPU -- from two host threads, or on two streams without an order between them -- race; calls
- * on one stream, or ordered by events, are safe.  The first call on a device looks up the array's
- * address on that device and raises the kernels' LDS limit.
+ * Every call on a GPU uses that GPU's two arrays, which keep the previous call's contents (nothing
+ * in them has to start at zero: each forward overwrites what it reads, and clears the counters it uses).  Two calls that overlap on one
+ * GPU -- from two host threads, or on two streams without an order between them -- race, and may then give wrong results or wait
+ * for a count that never comes; calls
+ * on one stream, or ordered by events, are safe.  The first call on a device looks up the arrays'
+ * addresses on that device and raises the kernels' LDS limit.
  */
 #define MOE_EP_NOALLOC_SCRATCH_BYTES (32u << 20)
 int moe_ep_forward_noalloc(const moe_ep_config *cfg, const void *tokens, const float *gate_logits,

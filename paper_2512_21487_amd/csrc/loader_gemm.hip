@@ -4,7 +4,8 @@
 // What bounds a tile is loads that a K step has to wait for: they draw 80 GB/s from L2 and 46 GB/s from HBM for a compute unit (nothing but
 // loads, never waited for together, 140 GB/s from L2, 64 bytes a cycle), and a K step of a 160 x 256 tile is 52 KB.  With the multiplications taken
 // out, the loads alone were three quarters of a launch (Qwen3-30B-A3B-shaped layer, 8192 tokens, gate/up 345 of 437 us); with the loads taken out,
-// the multiplications alone were 87 / 82 % of a gate/up / down launch, and either without its epilogue 93 / 82 % (DeepSeek-V2-Lite-shaped layer, 4096).  In
+// the multiplications alone were 87 / 82 % of a gate/up / down launch (DeepSeek-V2-Lite-shaped layer, 4096 tokens).  The results' way out is the rest: with and
+// without its stores that layer's forward takes 553 / 513 us, the Qwen3-30B-A3B-shaped one's, 8192 skewed tokens, 689 / 627.  In
 // grouped_gemm.hip a wavefront loads and multiplies, and a load that finds the path full holds back the MFMAs behind it.  A launch is
 // also bound by how its tiles are dealt, by number: of several rounds 6 to 16 % of the units' time has no workgroup, of one row tile per
 // expert up to 30 (profiles/loader_gemm_counters.txt, where the matrix pipes are busy 54 - 59 % of a gate/up launch that fills the chip).
@@ -580,7 +581,8 @@ __global__ __launch_bounds__(kLdThreads) void loader_gemm_kernel(GemmArgs a1, Ge
         long long w_step = 0, seg_jump = 0;
         bool once = false;
         // Until the activation rows of tile `it` are in memory: the drawing wavefront asks, the others look in LDS.  No line of them was in a
-        // cache of this launch before, so there is nothing to drop: a launch begins with none, lines belong to one row, and rows are not read earlier.
+        // cache of this launch before, so there is nothing to drop: a launch begins with none, lines belong to one row, and rows are not read earlier
+        // (load_x, behind this wait, is the only place that may read them).
         const auto wait_for = [&](int it, int dep) {
             int* const ready = s_ready + it % kLdCache;
             const auto is_ready = [&]() { return __builtin_amdgcn_readfirstlane(__hip_atomic_load(ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)); };

@@ -36,8 +36,9 @@ enum Stage { ST_ROUTER = 0, ST_PARTITION, ST_GEMM1, ST_GEMM2, ST_SGEMM1, ST_SGEM
 constexpr double kNarrowMeanRows = 24.0;
 // And where the tiled kernels would be one launch of both projections, with shared experts or weights in tile order.  Narrow / that:
 // DeepSeek-V2-Lite-shaped layer, 6 / 12 / 15 / 19 / 23 rows 190 / 194, 197 / 198, 204 / 201, 205 / 198, 209 / 201, weights in the caller's layout 12 / 19 rows
-// 206 / 203, 219 / 202; Qwen3-30B-A3B-shaped layer, 8 / 15 / 19 / 23 rows 204 / 207, 211 / 211, 213 / 215, 216 / 218, skewed 15 / 16 / 23 rows 156 / 151, 159 / 152,
-// 182 / 166, with weights in the caller's layout, which the tiled kernels draw at 4.9 TB/s, and balanced load 19 rows 218 / 228.
+// 206 / 203, 219 / 202; Qwen3-30B-A3B-shaped layer, 8 rows 204 / 207, 14 / 16 / 19 / 21 / 24 rows under perfectly balanced load 210 / 212, 212 / 212, 214 / 216,
+// 215 / 216, 218 / 218, with its load skewed 155 / 150, 160 / 153, 171 / 158, 178 / 161, 183 / 166: the host knows the mean only, and gives up to 1.3 % of
+// the one for 3 to 10 % of the other.  With weights in the caller's layout, which the tiled kernels draw at 4.9 TB/s, and balanced load 19 rows 218 / 228.
 constexpr double kNarrowPairMeanRows = 14.0;
 // The shared experts go along up to this many rows; beyond, launches of their own with tall tiles.  Apart / along, the routed
 // experts in narrow tiles both times: DeepSeek-V2-Lite-shaped layer, 256 / 512 tokens 251 / 212, 269 / 229 us; DeepSeek-V2-shaped share,
