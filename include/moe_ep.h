@@ -127,6 +127,8 @@ int moe_ep_create(const moe_ep_config *cfg, moe_ep_ctx **out_ctx);
  *               kernel runs on `stream`, after what is already there; in pinned-host mode the
  *               chunk copies run on streams of the context and `stream` is made to wait
  *               for the last of them.  Buffers must stay valid until `stream` reaches that point.
+ *               Forwards of one context share its workspaces: two that overlap, on streams without an
+ *               order between them, race as two of moe_ep_forward_noalloc do.
  *               In device mode the call allocates nothing, sets no memory and never waits on the
  *               host, so it may be recorded into a HIP graph (stream capture) and replayed.
  *
